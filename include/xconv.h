@@ -168,6 +168,16 @@ xconv_status xconv_dw_exact(const xconv_desc *desc, const void *dY_dev, const vo
 xconv_status xconv_conv_fwd(const xconv_desc *desc, const void *X_dev, const void *W_dev, void *Y_dev, void *stream);
 xconv_status xconv_dx_exact(const xconv_desc *desc, const void *dY_dev, const void *W_dev, void *dX_dev, void *stream);
 
+/* The same two operations with scratch: the weights are first brought into the order in which the matrix instructions
+ * read them (a copy of W, at most 2 us), which the entry points above do without at the price of gathering them in
+ * every workgroup.  bias_dev: [C_out] in desc->dtype, added in fp32 to the rounded product and the sum rounded again (as a separate addition would), or NULL.  ws_dev:
+ * xconv_conv_workspace_bytes() bytes, 16-byte aligned (too few: XCONV_EWORKSPACE), or NULL for the entry points' own way. */
+size_t xconv_conv_workspace_bytes(const xconv_desc *desc, int input_gradient);
+xconv_status xconv_conv_fwd_ws(const xconv_desc *desc, const void *X_dev, const void *W_dev, const void *bias_dev, void *Y_dev,
+                               void *ws_dev, size_t ws_bytes, void *stream);
+xconv_status xconv_dx_exact_ws(const xconv_desc *desc, const void *dY_dev, const void *W_dev, void *dX_dev,
+                               void *ws_dev, size_t ws_bytes, void *stream);
+
 /* Launch plan of the correlation kernel for op XCONV_OP_ESTIMATE or
  * XCONV_OP_EXACT, for reports and tests (host only).  Fills out[0..15] with
  * K-splits S, steps NS, rows per step RB, columns per step CW, waves along

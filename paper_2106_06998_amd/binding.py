@@ -75,6 +75,12 @@ def lib():
         L.xconv_conv_fwd.argtypes = [P, vp, vp, vp, vp]
         L.xconv_dx_exact.restype = i32
         L.xconv_dx_exact.argtypes = [P, vp, vp, vp, vp]
+        L.xconv_conv_workspace_bytes.restype = sz
+        L.xconv_conv_workspace_bytes.argtypes = [P, i32]
+        L.xconv_conv_fwd_ws.restype = i32
+        L.xconv_conv_fwd_ws.argtypes = [P, vp, vp, vp, vp, vp, sz, vp]
+        L.xconv_dx_exact_ws.restype = i32
+        L.xconv_dx_exact_ws.argtypes = [P, vp, vp, vp, vp, sz, vp]
         L.xconv_dw_estimate_static.restype = i32
         L.xconv_dw_estimate_static.argtypes = [P, vp, vp, vp, vp, vp]
         L.xconv_static_scratch_bytes.restype = sz
@@ -218,6 +224,20 @@ def xconv_conv_fwd(desc, X_dev, W_dev, Y_dev, stream=None):
 
 def xconv_dx_exact(desc, dY_dev, W_dev, dX_dev, stream=None):
     _check(lib().xconv_dx_exact(ctypes.byref(desc), _ptr(dY_dev), _ptr(W_dev), _ptr(dX_dev), _stream(stream)), "xconv_dx_exact")
+
+
+def xconv_conv_workspace_bytes(desc, input_gradient):
+    return int(lib().xconv_conv_workspace_bytes(ctypes.byref(desc), int(input_gradient)))
+
+
+def xconv_conv_fwd_ws(desc, X_dev, W_dev, bias_dev, Y_dev, ws_dev, stream=None):
+    _check(lib().xconv_conv_fwd_ws(ctypes.byref(desc), _ptr(X_dev), _ptr(W_dev), _ptr(bias_dev), _ptr(Y_dev), _ptr(ws_dev),
+                                   _nbytes(ws_dev), _stream(stream)), "xconv_conv_fwd_ws")
+
+
+def xconv_dx_exact_ws(desc, dY_dev, W_dev, dX_dev, ws_dev, stream=None):
+    _check(lib().xconv_dx_exact_ws(ctypes.byref(desc), _ptr(dY_dev), _ptr(W_dev), _ptr(dX_dev), _ptr(ws_dev), _nbytes(ws_dev),
+                                   _stream(stream)), "xconv_dx_exact_ws")
 
 
 def xconv_dw_estimate_static(desc, dY_dev, Xt_dev, Z_dev, dW_dev, stream=None):

@@ -287,20 +287,46 @@ __device__ inline int xcd_block(int b, int grid)
     return (grid & 7) == 0 ? (b & 7) * (grid >> 3) + (b >> 3) : b;
 }
 
-// ---- forward convolution / exact input gradient as one implicit GEMM (conv_kernels.hip) ----
-struct ConvGemmParams {
+// ---- forward convolution / exact input gradient as implicit GEMMs (conv_core.h, conv_kernels.hip) ----
+constexpr int kConvUnits = 4;   // 16-byte units of channels per staged chunk
+constexpr int kConvGatherM = 128;   // most output channels of a tile whose weights are gathered (no workspace)
+constexpr int kConvResident = 128;   // most contraction channels whose whole patch is kept in LDS
+constexpr int kConvSubs = 4;    // classes of output positions per launch
+
+// One class of output positions: an ordinary convolution with its own taps.  The forward convolution is one class; the
+// input gradient of a strided layer is sh*sw of them (output positions by their remainder modulo the stride).
+struct ConvSub {
+    int kH, kW, ph, pw;        // taps and padding in front (negative: the first source row lies inside); no taps: zeros
+    int Ho, Wo;                // output positions of the class
+    int oy0, ox0;              // its first output row and column (the steps are ConvParams::osy, osx)
+    int ky0, kx0, kys, kxs;    // kernel offset of tap (i, j): (ky0 + i*kys, kx0 + j*kxs), in the order they are summed
+    int SW, TPS, TU;           // columns per strip, tiles per strip, positions per tile
+    int sth, stw;              // staged rows (columns) per output row (column): min(stride, taps)
+    int PWv, PH, PWs, NPOS, NPPmax;   // staging tasks per patch row, columns per remainder class, LDS positions per row and in all, tasks per unit
+    int wg0;                   // first workgroup of the class
+    long long w0;              // first 16-byte unit of its packed weights
+};
+struct ConvParams {
     const void *in;    // activation-like tensor the contraction runs over (X, or dY for the input gradient)
     const void *w;     // weights [C_out, C_in, kH, kW] in the storage type
+    const void *wp;    // the same in fragment order (conv_pack_kernel), or null: fragments are gathered from w
+    const void *bias;  // per output channel in the storage type, or null
     void *out;         // Y, or dX
-    int Cin, Cout;     // contraction channels and output channels of this product
+    int B, Cin, Cout;  // images, contraction channels and output channels of this product
     int Hi, Wi;        // extent of `in`
-    int Ho, Wo;        // extent of `out`
-    int kH, kW, sh, sw, ph, pw;
-    int transposed;    // 0: src = (y*sh + ky - ph, x*sw + kx - pw); 1: src = ((y + ph - ky) / sh, ...) where that divides
-    long long npix;    // B * Ho * Wo
+    int sh, sw;        // stride of the source position (1 for the input gradient)
+    int osy, osx;      // output step between the positions of a class
+    int kWfull;        // kernel width of w
     long long in_sb, out_sb;                              // element strides: image,
     int in_sc, in_sy, in_sx, out_sc, out_sy, out_sx;      // channel, row, column
     int w_sco, w_sci;                                     // weights: output channel of the product, contraction channel
+    int MT, NT, WM;    // 32-row tiles and 32-column tiles per wave, waves along the output channels
+    int NMT, NMB;      // tiles of output channels, blocks of 32 packed output channels
+    int vec, swap, big;   // how the input is read, which side of the accumulator the channels are on, 64-bit addresses
+    int rev;              // taps reach back: tap (i, j) reads patch position (kH-1-i, kW-1-j) (input gradient)
+    int res, SPC;         // all channels of a patch resident; steps of kConvUnits units per chunk (1 unless resident)
+    int nsub, nwg, lds_bytes;
+    ConvSub sub[kConvSubs];
 };
 
 }  // namespace xc

@@ -1,0 +1,550 @@
+// Forward convolution and exact input gradient of the layer (Sec. 2: XConv leaves the forward pass and
+// the backpropagation through the layer exact; Algorithm 1 forward step 1 and the gradient with respect
+// to the input):
+//
+//   forward      Y[b,m,oy,ox]  = sum_{n,ky,kx} W[m,n,ky,kx] X[b,n, oy*sh+ky-ph, ox*sw+kx-pw]
+//   input grad   dX[b,n,iy,ix] = sum_{m,ky,kx} W[m,n,ky,kx] dY[b,m,oy,ox],  oy*sh+ky-ph = iy, ox*sw+kx-pw = ix
+//
+// Both are implicit GEMMs out[co, p] = sum_{tap, ci} W[co, ci, tap] * in[ci, src(p, tap)].  The input gradient of a
+// strided layer is split by the remainder of the output position modulo the stride: each class is an ordinary
+// unit-stride convolution with the taps that reach it (ConvSub), so no product with a structural zero is formed.
+//
+// Work split.  A workgroup of 4 waves owns TM = 32*MT*WM output channels x TN = 32*NT*(4/WM) output positions; a wave
+// 32*MT x 32*NT of them as 32x32 accumulator tiles.  Positions are counted along strips of SW columns, row after row and
+// image after image, so that small images fill a tile and wide ones give tiles of several short rows (a small halo).
+// The input patch of a tile (its rows and columns with the halo, zero outside the image) is staged into LDS as
+// [unit][position] (a unit = 16 bytes of channels: 8 at 16-bit storage, 4 at fp32) and serves all kernel taps from there:
+// a tap only shifts the position a lane reads, so the input is read from memory about once instead of once per tap.
+//   RES   all channels of the patch are resident: one staging phase, one barrier, then taps and channels without another
+//         (up to kConvResident channels; the workgroups that share a compute unit cover each other's staging).  The
+//         products of an output are summed tap by tap and, within a tap, by ascending channel.
+//   !RES  chunks of 4 units: the next chunk's patch is on its way through registers while the current one is multiplied
+//         (two LDS buffers, one barrier per chunk).
+// Strided layers keep the patch columns split by their remainder modulo the stride, so that the lanes' reads stay consecutive.
+// Weights come packed in fragment order (conv_pack_kernel, one coalesced kilobyte per fragment, read through the L1 by
+// every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, tap by tap.
+#pragma once
+#include <algorithm>
+
+#include "common.h"
+#include "launch.h"
+
+namespace xc {
+
+namespace {
+
+typedef float f32x16c __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4c __attribute__((ext_vector_type(4)));
+
+// one 16-byte fragment pair: 32x32x16 at 16-bit storage, four 32x32x2 at fp32 (lanes 0-31 hold the first unit of a k-step,
+// lanes 32-63 the second)
+template <int DT> __device__ inline f32x16c conv_mma(const u32x4c &a, const u32x4c &b, f32x16c c)
+{
+    if constexpr (DT == XCONV_F32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), c, 0, 0, 0);
+        return c;
+    } else if constexpr (DT == XCONV_BF16) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    } else {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
+}
+
+template <int DT> struct ConvElem { typedef uint16_t t; static constexpr int UE = 8, ES = 2; };
+template <> struct ConvElem<XCONV_F32> { typedef float t; static constexpr int UE = 4, ES = 4; };
+
+// channel (within a step) of element e of unit u.  fp32 products run two channels at a time, one from each unit of a k-step:
+// with the even channels in one unit and the odd ones in the other they come in ascending order.  Channels-last tensors are
+// read as whole units of four consecutive channels instead.
+template <int UE, bool IL> __device__ inline int conv_unit_channel(int u, int e) { return IL ? (u >> 1) * 2 * UE + 2 * e + (u & 1) : u * UE + e; }
+
+constexpr uint32_t kConvOob = 0x80000000u;   // byte offset past every buffer descriptor: the load returns zero
+
+}  // namespace
+
+// VEC: how a staging task reads `in`: 0 element by element (any strides), 1 pairs of columns (16-bit planes of even width),
+//      2 whole units (channels-last, channels a multiple of the unit).
+// SWAP: output positions in the rows of the accumulator tile (channels-last output: lanes along the channels), else in its columns.
+// PACKED: weights in fragment order.  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES>
+__global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvParams P)
+{
+    typedef typename ConvElem<DT>::t elem_t;
+    constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
+    constexpr int NU = kConvUnits, KS = NU / 2, CK = NU * UE;   // units, k-steps and channels of a step
+    constexpr bool IL = DT == XCONV_F32 && VEC != 2;             // units of a pair hold the even and the odd channels (conv_unit_channel)
+    constexpr int VW = VEC == 1 ? 2 : 1;                         // columns per staging task
+    constexpr int RW = VEC == 2 ? 4 : UE;                        // registers per staging task
+    constexpr int G = (RES ? 64 : 32) / RW;                      // staging tasks of a thread in flight
+
+    extern __shared__ uint4 conv_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    int id = xcd_block(blockIdx.x, gridDim.x);
+    if (id >= P.nwg) return;
+    int cls = 0;
+    while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
+    const ConvSub &S = P.sub[cls];
+    id -= S.wg0;
+    const int mtile = id % P.NMT;
+    id /= P.NMT;
+    const int strip = id / S.TPS, tile = id - strip * S.TPS;
+
+    const int WN = 4 / P.WM, wm = wave % P.WM, wn = wave / P.WM;
+    const int TN = 32 * NT * WN;
+    const int npp_max = S.NPPmax;
+    const int SPC = RES ? P.SPC : 1;                                            // steps of NU units per chunk
+    uint4 *patch = conv_lds;                                                    // [RES ? 1 : 2][NU * SPC][NPOS]
+    const int patch_units = (RES ? NU * SPC : 2 * NU) * S.NPOS;
+    uint2 *ptab = reinterpret_cast<uint2 *>(conv_lds + patch_units);             // [NPPmax] {source byte offset, LDS positions}
+    uint2 *otab = ptab + npp_max;                                               // [TN] {output offset, LDS position of tap (0, 0)}
+    uint4 *alds = conv_lds + patch_units + (npp_max + TN + 1) / 2;           // !PACKED: [2][KS][MT * WM][64] weight fragments of a tap
+
+    // ---- the tile: positions q0 .. q0 + TU - 1 of this strip (TU < TN where the patch of TN would not fit into LDS), rows R0 .. R1 counted over the batch
+    const int TU = S.TU;
+    const long long q0 = (long long)tile * TU;
+    const int NR = P.B * S.Ho;
+    const int R0 = (int)(q0 / S.SW);
+    const int x0 = (int)(q0 - (long long)R0 * S.SW);
+    int R1 = (int)((q0 + TU - 1) / S.SW);
+    R1 = R1 < NR - 1 ? R1 : NR - 1;
+    const int b0 = R0 / S.Ho, oyA = R0 - b0 * S.Ho;
+    const int b1 = R1 / S.Ho;
+    const int HV = (S.Ho - 1) * S.sth + S.kH;                                   // staged rows of a whole image
+    const int NPR = (R1 - R0) * S.sth + (b1 - b0) * (S.kH - S.sth) + S.kH;      // staged rows of this tile
+    const int xs = strip * S.SW * P.sw - S.pw;                                  // source column of patch column `xa`
+    const int xa = VW == 2 ? (xs & 1) : 0;
+    const int npp = S.kH > 0 ? NPR * S.PWv : 0;   // a class without taps stages nothing
+
+    {
+        const float rp = frcp(S.PWv);
+        for (int pp = tid; pp < npp; pp += kThreads) {
+            int prow, pc, bi, l;
+            fast_divmod(pp, S.PWv, rp, prow, pc);
+            bi = (oyA * S.sth + prow) / HV;
+            l = oyA * S.sth + prow - bi * HV;
+            const int c = pc * VW;
+            const int iy = (S.kH >= P.sh ? l : (l / S.kH) * P.sh + l % S.kH) - S.ph;
+            const int ix = xs - xa + (S.kW >= P.sw ? c : (c / S.kW) * P.sw + c % S.kW);
+            const bool ok = b0 + bi < P.B && (unsigned)iy < (unsigned)P.Hi && (unsigned)ix < (unsigned)P.Wi;
+            const uint32_t off = (uint32_t)bi * (uint32_t)P.in_sb + (uint32_t)iy * (uint32_t)P.in_sy + (uint32_t)ix * (uint32_t)P.in_sx;
+            const int p0 = prow * S.PWs + (c % S.stw) * S.PH + c / S.stw;
+            const int p1 = prow * S.PWs + ((c + 1) % S.stw) * S.PH + (c + 1) / S.stw;
+            ptab[pp] = uint2{ok ? (BIG ? off : off * ES) : (BIG ? 0xffffffffu : kConvOob), (uint32_t)p0 | ((uint32_t)p1 << 16)};
+        }
+        const float rs = frcp(S.SW);
+        for (int n = tid; n < TN; n += kThreads) {
+            int dr, x, bi, oy;
+            fast_divmod(x0 + n, S.SW, rs, dr, x);
+            const int row = R0 + dr, ox = strip * S.SW + x;
+            bi = (oyA + dr) / S.Ho;
+            oy = oyA + dr - bi * S.Ho;
+            const bool in_batch = row < NR && n < TU, ok = in_batch && ox < S.Wo;
+            const uint32_t off = (uint32_t)bi * (uint32_t)P.out_sb + (uint32_t)(S.oy0 + oy * P.osy) * (uint32_t)P.out_sy +
+                                 (uint32_t)(S.ox0 + ox * P.osx) * (uint32_t)P.out_sx;
+            const int pr = dr * S.sth + bi * (S.kH - S.sth);
+            otab[n] = uint2{ok ? off : 0xffffffffu, (uint32_t)(in_batch ? pr * S.PWs + x : 0)};
+        }
+    }
+    __syncthreads();
+
+    const int taps = S.kH * S.kW;
+    const int nck = taps == 0 ? 0 : (P.Cin + CK * SPC - 1) / (CK * SPC);
+    const elem_t *in_b = static_cast<const elem_t *>(P.in) + (size_t)b0 * P.in_sb;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(in_b), 0, (int)kConvOob, 0x00020000);
+
+    // ---- staging: task t = (unit, position); a phase of a chunk is G tasks of every thread
+    const int ntask = npp * NU * SPC;
+    const float rnpp = frcp(npp);
+    uint32_t sr[G][RW];
+    auto split = [&](int t, int &u, int &pp) {
+        if constexpr (VEC == 2) { u = t % NU; pp = t / NU; if constexpr (RES) { const int b = pp / npp; u += NU * b; pp -= npp * b; } }
+        else fast_divmod(t, npp, rnpp, u, pp);
+    };
+    auto stage_load = [&](int c0, int phase) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int t = tid + kThreads * (phase * G + i);
+            if (t < ntask) {
+                int u, pp;
+                split(t, u, pp);
+                const uint32_t off = ptab[pp].x;
+                if constexpr (BIG) {
+                    const elem_t *src = in_b + (size_t)off;
+#pragma unroll
+                    for (int e = 0; e < UE; ++e) {
+                        const int c = c0 + conv_unit_channel<UE, IL>(u, e);
+                        elem_t v = elem_t(0);
+                        if (off != 0xffffffffu && c < P.Cin) v = src[(size_t)c * (size_t)P.in_sc];
+                        sr[i][e] = ES == 4 ? __builtin_bit_cast(uint32_t, (float)v) : (uint32_t)v;
+                    }
+                } else if constexpr (VEC == 2) {
+                    const uint32_t vo = c0 + u * UE < P.Cin ? off + (uint32_t)u * 16u : kConvOob;
+                    const u32x4c v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)vo, c0 * ES, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sr[i][e] = v[e];
+                } else {
+                    const uint32_t cs = (uint32_t)P.in_sc * ES;             // bytes from a channel to the next
+                    const int cu = conv_unit_channel<UE, IL>(u, 0), left = P.Cin - c0 - cu;
+                    const uint32_t vo = off + (uint32_t)cu * cs;
+#pragma unroll
+                    for (int e = 0; e < UE; ++e) {
+                        constexpr int step = IL ? 2 : 1;
+                        const int v = (int)(e * step < left ? vo : kConvOob), so = (int)((uint32_t)(c0 + e * step) * cs);
+                        if constexpr (VEC == 1 || ES == 4) sr[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, so, 0);
+                        else sr[i][e] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, v, so, 0);
+                    }
+                }
+            }
+        }
+    };
+    auto stage_write = [&](int buf, int phase) {
+        uint4 *dst = patch + (size_t)buf * NU * S.NPOS;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int t = tid + kThreads * (phase * G + i);
+            if (t < ntask) {
+                int u, pp;
+                split(t, u, pp);
+                const uint32_t pos = ptab[pp].y;
+                uint4 *d = dst + (size_t)u * S.NPOS;
+                if constexpr (VEC == 1) {
+                    uint32_t rows[8][1];
+                    uint4 cols[2];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) rows[e][0] = sr[i][e];
+                    transpose_rows8<1>(rows, cols);
+                    d[pos & 0xffffu] = cols[0];
+                    d[pos >> 16] = cols[1];
+                } else if constexpr (VEC == 2 || ES == 4) {
+                    d[pos & 0xffffu] = uint4{sr[i][0], sr[i][1], sr[i][2], sr[i][3]};
+                } else {
+                    d[pos & 0xffffu] = uint4{sr[i][0] | (sr[i][1] << 16), sr[i][2] | (sr[i][3] << 16), sr[i][4] | (sr[i][5] << 16),
+                                             sr[i][6] | (sr[i][7] << 16)};
+                }
+            }
+        }
+    };
+    const int nphase = (ntask + kThreads * G - 1) / (kThreads * G);
+
+    f32x16c acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[mt][nt][e] = 0.f;
+
+    const int co_w = (mtile * P.WM + wm) * (32 * MT);    // first output channel of this wave
+    int pos[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) pos[nt] = (int)otab[(wn * NT + nt) * 32 + l32].y + h * S.NPOS;
+
+    // ---- weight fragments of one tap: k-steps 0 .. KS-1, one kilobyte each for 32 output channels
+    const int nk = nck * taps * SPC * KS;
+    const u32x4c *apk[MT];
+    if constexpr (PACKED) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            int mb = co_w / 32 + mt;
+            mb = mb < P.NMB ? mb : P.NMB - 1;
+            apk[mt] = reinterpret_cast<const u32x4c *>(P.wp) + S.w0 + (size_t)mb * nk * 64 + lane;
+        }
+    }
+    // without packed weights the workgroup gathers a tap's fragments (32*MT*WM output channels x CK channels) through LDS, the
+    // elements of the next tap on their way in registers; the lanes run along whichever channel index has the smaller stride
+    constexpr int NEL = PACKED ? 1 : kConvGatherM * CK / kThreads;
+    elem_t wg[NEL];
+    const elem_t *wraw = static_cast<const elem_t *>(P.w);
+    const int TMW = 32 * MT * P.WM, co_t = mtile * TMW;
+    auto gather_at = [&](int i, int &cl, int &col) {
+        const int idx = tid + kThreads * i;
+        if (P.w_sci < P.w_sco) { cl = idx % CK; col = idx / CK; }
+        else { col = idx & (TMW - 1); cl = idx / TMW; }
+        return cl < CK && col < TMW;
+    };
+    auto gather_load = [&](int c0, int tap) {
+        const int ky = tap / S.kW, kx = tap - ky * S.kW;
+        const int o = (S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs;
+#pragma unroll
+        for (int i = 0; i < NEL; ++i) {
+            int cl, col;
+            wg[i] = elem_t(0);
+            if (gather_at(i, cl, col) && co_t + col < P.Cout && c0 + cl < P.Cin)
+                wg[i] = wraw[(size_t)(co_t + col) * P.w_sco + (size_t)(c0 + cl) * P.w_sci + o];
+        }
+    };
+    auto gather_write = [&](int buf) {
+        elem_t *d = reinterpret_cast<elem_t *>(alds + (size_t)buf * KS * MT * P.WM * 64);
+#pragma unroll
+        for (int i = 0; i < NEL; ++i) {
+            int cl, col;
+            if (gather_at(i, cl, col)) {
+                const int hh = IL ? cl & 1 : cl / UE & 1, e = IL ? cl % (2 * UE) / 2 : cl % UE;
+                d[(((cl / (2 * UE)) * MT * P.WM + col / 32) * 64 + hh * 32 + col % 32) * UE + e] = wg[i];
+            }
+        }
+    };
+    auto load_a = [&](u32x4c (&a)[KS][MT], int buf) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                if constexpr (PACKED) a[s][mt] = apk[mt][s * 64];
+                else a[s][mt] = reinterpret_cast<const u32x4c *>(alds)[((buf * KS + s) * MT * P.WM + wm * MT + mt) * 64 + lane];
+            }
+            if constexpr (PACKED) apk[mt] += KS * 64;
+        }
+    };
+
+    // one step: KS k-steps of the tap whose patch positions are shifted by toff
+    u32x4c a[KS][MT], an[KS][MT];
+    auto multiply = [&](const u32x4c *pb, int toff, bool two) {
+        u32x4c b[KS][NT];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) b[s][nt] = pb[pos[nt] + toff + 2 * s * S.NPOS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            if (s == 0 || two) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[mt][nt] = SWAP ? conv_mma<DT>(b[s][nt], a[s][mt], acc[mt][nt]) : conv_mma<DT>(a[s][mt], b[s][nt], acc[mt][nt]);
+            }
+    };
+    auto next_a = [&](bool next) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) a[s][mt] = an[s][mt];
+        if (next) load_a(an, 0);
+    };
+    auto tap_offset = [&](int ky, int kx) {
+        const int cy = P.rev ? S.kH - 1 - ky : ky, cx = (P.rev ? S.kW - 1 - kx : kx) + xa;
+        return cy * S.PWs + (S.stw == 1 ? cx : (cx % S.stw) * S.PH + cx / S.stw);
+    };
+
+    if constexpr (RES) {
+        if (nck > 0) {
+            load_a(an, 0);
+            for (int ph = 0; ph < nphase; ++ph) {
+                stage_load(0, ph);
+                stage_write(0, ph);
+            }
+            __syncthreads();
+            const bool two_last = P.Cin - (SPC - 1) * CK > CK / 2;      // channels in the second k-step of the last step
+            int ky = 0, kx = 0;
+            for (int tap = 0; tap < taps; ++tap) {
+                const int toff = tap_offset(ky, kx);
+                const u32x4c *pb = reinterpret_cast<const u32x4c *>(patch);
+                for (int sp = 0; sp < SPC; ++sp, pb += NU * S.NPOS) {
+                    next_a(tap + 1 < taps || sp + 1 < SPC);
+                    multiply(pb, toff, sp + 1 < SPC || two_last);
+                }
+                if (++kx == S.kW) { kx = 0; ++ky; }
+            }
+        }
+    } else if (nck > 0) {
+        int abuf = 0;
+        if constexpr (PACKED) load_a(an, 0);
+        else { gather_load(0, 0); gather_write(0); }
+        for (int ph = 0; ph < nphase; ++ph) {
+            stage_load(0, ph);
+            stage_write(0, ph);
+        }
+        __syncthreads();
+        for (int ck = 0; ck < nck; ++ck) {
+            const int c0 = ck * CK;
+            const bool more = ck + 1 < nck;
+            const bool two = P.Cin - c0 > CK / 2;
+            const u32x4c *pb = reinterpret_cast<const u32x4c *>(patch + (size_t)(ck & 1) * NU * S.NPOS);
+            int tap = 0, ky = 0, kx = 0;
+            for (int ph = 0; ph < nphase; ++ph) {
+                if (more) stage_load(c0 + CK, ph);
+                const int tend = taps * (ph + 1) / nphase;
+                for (; tap < tend; ++tap) {
+                    const bool next = tap + 1 < taps || more;
+                    if constexpr (PACKED) next_a(next);
+                    else {
+                        load_a(a, abuf);
+                        if (tap + 1 < taps) gather_load(c0, tap + 1);
+                        else if (more) gather_load(c0 + CK, 0);
+                    }
+                    multiply(pb, tap_offset(ky, kx), two);
+                    if constexpr (!PACKED) {
+                        abuf ^= 1;
+                        if (next) gather_write(abuf);
+                        __syncthreads();
+                    }
+                    if (++kx == S.kW) { kx = 0; ++ky; }
+                }
+                if (more) stage_write((ck + 1) & 1, ph);
+            }
+            __syncthreads();
+        }
+    }
+
+    // ---- accumulator tile: lane l holds column l % 32 and rows 8*(i/4) + 4*(l/32) + i%4; one rounding to the storage type
+    elem_t *out_b = static_cast<elem_t *>(P.out) + (size_t)b0 * P.out_sb;
+    const elem_t *bias = static_cast<const elem_t *>(P.bias);
+    auto to_f32 = [](elem_t v) {
+        if constexpr (ES == 4) return v;
+        else return st16_to_f32<DT>(v);
+    };
+    // the bias is added to the rounded product, in fp32, and the sum rounded again: what a separate addition gives, bit for
+    // bit (a sum rounded once falls on the other side of zero now and then, which a ReLU behind the layer would show)
+    auto put = [&](uint32_t off, int co, float v, float bv) {
+        elem_t *d = out_b + (size_t)off + (size_t)co * (size_t)P.out_sc;
+        if constexpr (ES == 4) *d = v + bv;
+        else {
+            const uint16_t q = f32_to_st16<DT>(v);
+            *d = bias ? f32_to_st16<DT>(st16_to_f32<DT>(q) + bv) : q;
+        }
+    };
+    if constexpr (SWAP) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int co = co_w + mt * 32 + l32;
+            const float bv = bias && co < P.Cout ? to_f32(bias[co]) : 0.f;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const uint32_t off = otab[(wn * NT + nt) * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
+                    if (off != 0xffffffffu && co < P.Cout) put(off, co, acc[mt][nt][i], bv);
+                }
+        }
+    } else {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            float bv[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int co = co_w + mt * 32 + 8 * (i / 4) + 4 * h + i % 4;
+                bv[i] = bias && co < P.Cout ? to_f32(bias[co]) : 0.f;
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const uint32_t off = otab[(wn * NT + nt) * 32 + l32].x;
+                if (off != 0xffffffffu) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int co = co_w + mt * 32 + 8 * (i / 4) + 4 * h + i % 4;
+                        if (co < P.Cout) put(off, co, acc[mt][nt][i], bv[i]);
+                    }
+                }
+            }
+        }
+    }
+}
+
+// Weights in fragment order: [block of 32 output channels][chunk of P.SPC steps][tap][k-step][lane] of 16 bytes, per class of taps; zero beyond
+// the channels.  One thread per 16-byte unit, lanes along the output channels.
+template <int DT, bool IL>
+__global__ __launch_bounds__(kThreads) void conv_pack_kernel(const ConvParams P, uint4 *out)
+{
+    typedef typename ConvElem<DT>::t elem_t;
+    constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
+    const int KS = kConvUnits / 2 * P.SPC, CK = kConvUnits * UE * P.SPC;
+    const ConvSub &S = P.sub[blockIdx.y];
+    const int taps = S.kH * S.kW, nck = (P.Cin + CK - 1) / CK;
+    const long long n = (long long)P.NMB * nck * taps * KS * 64;
+    const elem_t *w = static_cast<const elem_t *>(P.w);
+    for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
+        const int lane = (int)(i & 63);
+        long long k = i >> 6;
+        const int s = (int)(k % KS);
+        k /= KS;
+        const int tap = (int)(k % taps);
+        k /= taps;
+        const int ck = (int)(k % nck), mb = (int)(k / nck);
+        const int ky = tap / S.kW, kx = tap - ky * S.kW;
+        const int o = (S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs;
+        const int co = mb * 32 + (lane & 31), u = 2 * s + (lane >> 5);
+        const elem_t *src = w + (size_t)co * P.w_sco + o;
+        uint32_t v[UE];
+#pragma unroll
+        for (int e = 0; e < UE; ++e) {
+            const int c = ck * CK + conv_unit_channel<UE, IL>(u, e);
+            elem_t x = elem_t(0);
+            if (co < P.Cout && c < P.Cin) x = src[(size_t)c * P.w_sci];
+            v[e] = ES == 4 ? __builtin_bit_cast(uint32_t, (float)x) : (uint32_t)x;
+        }
+        if constexpr (ES == 4) out[S.w0 + i] = uint4{v[0], v[1], v[2], v[3]};
+        else out[S.w0 + i] = uint4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+    }
+}
+
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false>
+static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
+{
+    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES>);
+    if (P.lds_bytes > 64 * 1024) {
+        static bool attr_set[64] = {};   // per device; a repeated call only sets it again
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
+        if (dev < 0 || dev >= 64 || !attr_set[dev]) {
+            hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+            if (dev >= 0 && dev < 64) attr_set[dev] = true;
+        }
+    }
+    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
+                       (unsigned)P.lds_bytes, st, P);
+    return hipGetLastError();
+}
+
+template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const ConvParams &P, hipStream_t st)
+{
+    if (P.big) {
+        if constexpr (VEC == 0) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, true>(P, st);
+        else return hipErrorInvalidValue;
+    }
+    const int shape = P.MT * 10 + P.NT;
+    if (P.res) {
+        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false, true>(P, st);
+        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false, true>(P, st);
+        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false, true>(P, st);
+        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false, true>(P, st);
+    }
+    if (P.wp) {
+        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false>(P, st);
+        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false>(P, st);
+        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false>(P, st);
+        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false>(P, st);
+    }
+    if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, false>(P, st);
+    if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, false, false>(P, st);
+    return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false>(P, st);
+}
+
+template <int DT> static hipError_t launch_conv_dt(const ConvParams &P, hipStream_t st)
+{
+    if (P.vec == 1) {
+        if constexpr (DT == XCONV_F32) return hipErrorInvalidValue;
+        else return launch_conv_shape<DT, 1, false>(P, st);
+    }
+    if (P.vec == 2) return launch_conv_shape<DT, 2, true>(P, st);
+    return P.swap ? launch_conv_shape<DT, 0, true>(P, st) : launch_conv_shape<DT, 0, false>(P, st);
+}
+
+template <int DT> static hipError_t launch_conv_pack_dt(const ConvParams &P, void *out, hipStream_t st)
+{
+    const int KS = kConvUnits / 2 * P.SPC, CK = kConvUnits * ConvElem<DT>::UE * P.SPC;
+    long long n = 0;
+    for (int i = 0; i < P.nsub; ++i) n = std::max(n, (long long)P.NMB * ceil_div(P.Cin, CK) * P.sub[i].kH * P.sub[i].kW * KS * 64);
+    if (n == 0) return hipSuccess;
+    const unsigned wgs = (unsigned)std::min<long long>((n + kThreads - 1) / kThreads, 4096);
+    if (DT == XCONV_F32 && P.vec != 2)
+        hipLaunchKernelGGL((conv_pack_kernel<DT, DT == XCONV_F32>), dim3(wgs, (unsigned)P.nsub), dim3(kThreads), 0, st, P, static_cast<uint4 *>(out));
+    else
+        hipLaunchKernelGGL((conv_pack_kernel<DT, false>), dim3(wgs, (unsigned)P.nsub), dim3(kThreads), 0, st, P, static_cast<uint4 *>(out));
+    return hipGetLastError();
+}
+
+}  // namespace xc

@@ -1,218 +1,314 @@
-// Forward convolution and exact input gradient of the layer (Sec. 2: XConv leaves the forward pass and
-// the backpropagation through the layer exact; Algorithm 1 forward step 1 and the gradient with respect
-// to the input):
-//
-//   forward      Y[b,m,oy,ox]  = sum_{n,ky,kx} W[m,n,ky,kx] X[b,n, oy*sh+ky-ph, ox*sw+kx-pw]
-//   input grad   dX[b,n,iy,ix] = sum_{m,ky,kx} W[m,n,ky,kx] dY[b,m,oy,ox],  oy*sh+ky-ph = iy, ox*sw+kx-pw = ix
-//
-// Both are the implicit GEMM  out[co, p] = sum_{(o, ci)} Wv[co, ci, o] * in[ci, src(p, o)]  over output
-// pixels p = (b, y, x), kernel offsets o and contraction channels ci, with zero for a source pixel outside
-// the tensor (or, for the input gradient, between the strides).  One kernel does both: the host hands it
-// the strides of the three tensors and the rule for src.  A workgroup owns TM output channels x 64 output
-// pixels; for every offset it walks the contraction channels in chunks that are staged through LDS in the
-// operand form of the matrix instruction (16x16x16 with four consecutive channels per lane for 16-bit
-// storage, 16x16x4 for fp32), sums in fp32 and rounds once to the storage type.  LDS use is small (a few KB)
-// so that several workgroups share a compute unit and hide each other's staging.
+// Host side of the forward convolution and the exact input gradient: classes of output positions, tiles, launches
+// (the kernels are in conv_core.h).
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <memory>
+#include <mutex>
+#include <vector>
+
 #include "common.h"
 #include "launch.h"
 
 namespace xc {
 
+hipError_t launch_conv_f32(const ConvParams &P, hipStream_t st);
+hipError_t launch_conv_bf16(const ConvParams &P, hipStream_t st);
+hipError_t launch_conv_f16(const ConvParams &P, hipStream_t st);
+hipError_t launch_conv_pack_f32(const ConvParams &P, void *out, hipStream_t st);
+hipError_t launch_conv_pack_bf16(const ConvParams &P, void *out, hipStream_t st);
+hipError_t launch_conv_pack_f16(const ConvParams &P, void *out, hipStream_t st);
+
 namespace {
 
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
+constexpr int kLdsMax = 160 * 1024;
+constexpr long long kMaxRows = 1LL << 24;      // rows over the batch in one launch (32-bit tile arithmetic)
 
-template <int DT> struct ConvTraits;
-template <> struct ConvTraits<XCONV_F32> {
-    typedef float elem_t;
-    typedef float unit_t;                // one channel per lane
-    static constexpr int KP = 1, KC = 16;
-};
-template <> struct ConvTraits<XCONV_F16> {
-    typedef uint16_t elem_t;
-    typedef uint2 unit_t;                // four consecutive channels per lane
-    static constexpr int KP = 4, KC = 32;
-};
-template <> struct ConvTraits<XCONV_BF16> {
-    typedef uint16_t elem_t;
-    typedef uint2 unit_t;
-    static constexpr int KP = 4, KC = 32;
-};
+int units_elems(int dtype) { return dtype == XCONV_F32 ? 4 : 8; }
+int elem_size(int dtype) { return dtype == XCONV_F32 ? 4 : 2; }
 
-template <int DT> __device__ inline f32x4 conv_mfma(const typename ConvTraits<DT>::unit_t &a, const typename ConvTraits<DT>::unit_t &b, f32x4 c)
+void image_strides(int layout, int C, int H, int W, long long &sb, int &sc, int &sy, int &sx)
 {
-    if constexpr (DT == XCONV_F32) return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    else if constexpr (DT == XCONV_F16)
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, a), __builtin_bit_cast(f16x4, b), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+    if (layout == XCONV_NHWC) { sb = (long long)H * W * C; sc = 1; sy = W * C; sx = C; }
+    else { sb = (long long)C * H * W; sc = H * W; sy = W; sx = 1; }
 }
 
-template <int DT> __device__ inline typename ConvTraits<DT>::unit_t conv_pack(const typename ConvTraits<DT>::elem_t (&v)[ConvTraits<DT>::KP])
+// classes of output positions of the product
+std::vector<ConvSub> make_subs(const xconv_desc *d, int transposed, int Ho, int Wo)
 {
-    if constexpr (DT == XCONV_F32) return v[0];
-    else return uint2{(uint32_t)v[0] | ((uint32_t)v[1] << 16), (uint32_t)v[2] | ((uint32_t)v[3] << 16)};
+    std::vector<ConvSub> v;
+    if (!transposed) {
+        ConvSub s{};
+        s.kH = d->kH; s.kW = d->kW; s.ph = d->pad_h; s.pw = d->pad_w;
+        s.Ho = Ho; s.Wo = Wo;
+        s.kys = s.kxs = 1;
+        v.push_back(s);
+        return v;
+    }
+    // input row iy = a + sh*t takes dY row (iy + ph - ky)/sh where that divides: taps ky = ky0 + sh*i, row t + (a+ph-ky0)/sh - i,
+    // i.e. a unit-stride convolution whose taps reach back (ConvParams::rev)
+    auto axis = [](int a, int k, int s, int p, int &n, int &first, int &pad) {
+        first = (a + p) % s;
+        n = first < k ? (k - 1 - first) / s + 1 : 0;
+        pad = (n - 1) - (a + p - first) / s;
+    };
+    for (int a = 0; a < std::min(d->stride_h, d->H); ++a)
+        for (int b = 0; b < std::min(d->stride_w, d->W); ++b) {
+            ConvSub s{};
+            axis(a, d->kH, d->stride_h, d->pad_h, s.kH, s.ky0, s.ph);
+            axis(b, d->kW, d->stride_w, d->pad_w, s.kW, s.kx0, s.pw);
+            if (s.kH == 0 || s.kW == 0) s.kH = s.kW = s.ph = s.pw = 0;
+            s.kys = d->stride_h; s.kxs = d->stride_w;
+            s.oy0 = a; s.ox0 = b;
+            s.Ho = (d->H - a + d->stride_h - 1) / d->stride_h;
+            s.Wo = (d->W - b + d->stride_w - 1) / d->stride_w;
+            v.push_back(s);
+        }
+    return v;
+}
+
+int chunks(int dtype, int C) { return ceil_div(C, kConvUnits * units_elems(dtype)); }
+long long packed_units(const ConvSub &s, int dtype, int Cin, int Cout)
+{
+    return (long long)ceil_div(Cout, 32) * chunks(dtype, Cin) * s.kH * s.kW * (kConvUnits / 2) * 64;
+}
+
+// Strips and LDS extents of a class for tiles of TN positions: the strip width with the least work in all (products for
+// positions of ragged tiles and strips, staging of the halo).  Returns the cost per launch in cycles of one compute unit.
+double plan_sub(ConvSub &s, const ConvParams &P, int TN, double mma_clk, int nck, int lds_max)
+{
+    const int VW = P.vec == 1 ? 2 : 1;
+    const int taps = s.kH * s.kW;
+    double best = -1;
+    // fewer positions per tile only where the patch of a full tile does not fit (large strides or kernels on narrow images)
+    for (int TU = TN; TU >= 1 && best < 0; TU /= 2) {
+        ConvSub bs = s;
+        for (int nst = 1; nst <= s.Wo; ++nst) {
+            const int SW = ceil_div(s.Wo, nst);
+            if (nst > 1 && SW < 8 && TU == TN) break;
+            if (nst > 1 && ceil_div(s.Wo, SW) != nst) continue;
+            ConvSub c = s;
+            c.SW = SW;
+            c.TU = TU;
+            c.sth = std::max(1, std::min(P.sh, s.kH));
+            c.stw = std::max(1, std::min(P.sw, s.kW));
+            const long long NR = (long long)P.B * s.Ho;
+            const int nr = (int)std::min<long long>((SW + TU - 2) / SW + 1, NR);
+            const int nb = std::min(nr >= 2 ? (nr - 2) / s.Ho + 1 : 0, P.B - 1);
+            const int NPR = std::max(1, (nr - 1) * c.sth + nb * std::max(0, s.kH - c.sth) + s.kH);
+            const int PWl = (SW - 1) * c.stw + s.kW + (VW - 1);
+            c.PWv = std::max(1, ceil_div(PWl, VW));
+            c.PH = ceil_div(c.PWv * VW, c.stw);
+            c.PWs = c.stw * c.PH;
+            c.NPOS = round_up(NPR * c.PWs, 16);
+            c.NPPmax = NPR * c.PWv;
+            c.TPS = (int)((NR * SW + TU - 1) / TU);
+            if ((P.res ? P.SPC : 2LL) * kConvUnits * c.NPOS * 16 + (c.NPPmax + TN + 1) / 2 * 16LL > lds_max || c.NPOS > 65535) continue;
+            const double ntask = (double)c.NPPmax * kConvUnits * P.SPC / kThreads;
+            const double cost = (double)nst * c.TPS * (nck * (taps * P.SPC * mma_clk + ntask * 120.0) + 2500.0);
+            if (best < 0 || cost < best) { best = cost; bs = c; }
+        }
+        s = bs;
+    }
+    return best;
+}
+
+struct Shape { int MT, NT; double eff; };
+// wave tiles of the kernel, with the share of the matrix rate each was measured at on large layers (16-bit storage)
+const Shape kShapes[] = {{2, 4, 0.60}, {2, 2, 0.45}, {1, 2, 0.33}, {1, 1, 0.22}};
+
+bool plan(ConvParams &P, int dtype, int ncu)
+{
+    int force = 0, force_wm = 0;
+    if (const char *e = getenv("XCONV_CONV_SHAPE")) force = atoi(e);
+    if (const char *e = getenv("XCONV_CONV_WM")) force_wm = atoi(e);
+    P.SPC = P.res ? chunks(dtype, P.Cin) : 1;
+    const int nck = P.res ? 1 : chunks(dtype, P.Cin);
+    double best = -1;
+    ConvParams bp = P;
+    for (const Shape &sh : kShapes)
+        for (int WM = 1; WM <= 4; WM *= 2) {
+            if (force && !P.big && (P.wp || force != 24) && sh.MT * 10 + sh.NT != force) continue;
+            if (force_wm && WM != force_wm) continue;
+            if (!P.wp && (sh.NT > 2 || 32 * sh.MT * WM > kConvGatherM)) continue;
+            if (P.big && sh.MT * sh.NT != 4) continue;
+            if (WM > 1 && 32 * sh.MT * (WM / 2) >= P.Cout) continue;         // half of the waves would have no channels
+            ConvParams C = P;
+            C.MT = sh.MT; C.NT = sh.NT; C.WM = WM;
+            const int extra = P.wp ? 0 : 2 * (kConvUnits / 2) * sh.MT * WM * 1024;   // LDS of the gathered weights
+            const int TM = 32 * sh.MT * WM, TN = 32 * sh.NT * (4 / WM);
+            C.NMT = ceil_div(P.Cout, TM);
+            // cycles of the four waves' products of one tap of a chunk (one wave per SIMD)
+            const double per = sh.MT * sh.NT * (kConvUnits / 2) * (dtype == XCONV_F32 ? 256.0 / 0.85 : 32.0 / sh.eff);
+            double cost = 0;
+            long long nwg = 0;
+            int lds = 0;
+            bool ok = true;
+            for (int i = 0; i < P.nsub && ok; ++i) {
+                const double c = plan_sub(C.sub[i], C, TN, per, nck, kLdsMax - extra);
+                if (c < 0) { ok = false; break; }
+                cost += c * C.NMT;
+                C.sub[i].wg0 = (int)nwg;
+                nwg += (long long)ceil_div(C.sub[i].Wo, C.sub[i].SW) * C.sub[i].TPS * C.NMT;
+                lds = std::max(lds, (P.res ? P.SPC : 2) * kConvUnits * C.sub[i].NPOS * 16 + (C.sub[i].NPPmax + TN + 1) / 2 * 16 + extra);
+            }
+            if (!ok || nwg > 0x3fffffff) continue;
+            C.nwg = (int)nwg;
+            C.lds_bytes = lds;
+            // average workgroup times the workgroups of the busiest compute unit
+            const double rounds = (double)((nwg + ncu - 1) / ncu);
+            double t = cost / nwg * rounds;
+            if (rounds < 2 || lds > kLdsMax / 2) t *= 1.3;               // one wave per SIMD: its latencies are not covered
+            if (best < 0 || t < best) { best = t; bp = C; }
+        }
+    if (best < 0) return false;
+    P = bp;
+    return true;
 }
 
 }  // namespace
 
-// MT: 16-row tiles of output channels per wave (TM = 32 * MT output channels per workgroup)
-template <int DT, int MT>
-__global__ __launch_bounds__(kThreads) void conv_gemm_kernel(const ConvGemmParams P)
+size_t conv_ws_bytes(const xconv_desc *d, int transposed)
 {
-    typedef ConvTraits<DT> T;
-    typedef typename T::elem_t elem_t;
-    typedef typename T::unit_t unit_t;
-    constexpr int KP = T::KP, KC = T::KC, NU = KC / KP;   // units (lane operands) per chunk along the contraction
-    constexpr int TM = 32 * MT, TP = 64;
-    constexpr int UPT = NU / 4;                           // units per staging thread and tile row
-    constexpr int NAW = TM * KC / kThreads;               // weight elements per staging thread and chunk
-    __shared__ unit_t As[NU][TM];
-    __shared__ unit_t Bs[NU][TP];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l16 = lane & 15, g = lane >> 4;
-    const int wm = wave & 1, wp = wave >> 1;
-    const int co0 = blockIdx.y * TM;
-    const long long p0 = (long long)blockIdx.x * TP;
-    const elem_t *in = static_cast<const elem_t *>(P.in);
-    const elem_t *wv = static_cast<const elem_t *>(P.w);
-    const int HoWo = P.Ho * P.Wo;
-    const int K2 = P.kH * P.kW;
-    const bool w_along_ci = P.w_sci < P.w_sco;
-
-    // staging roles for `in`: pixel tid % 64, units kg, kg + 4, ...
-    const int sl = tid & 63, kg = tid >> 6;
-    const long long sp = p0 + sl;
-    const bool p_ok = sp < P.npix;
-    const long long spc = p_ok ? sp : 0;
-    const int sb = (int)(spc / HoWo);
-    const int srem = (int)(spc - (long long)sb * HoWo);
-    const int soy = srem / P.Wo, sox = srem - soy * P.Wo;
-    const elem_t *in_b = in + (size_t)sb * P.in_sb;
-
-    f32x4 acc[MT][2];
-#pragma unroll
-    for (int tm = 0; tm < MT; ++tm)
-#pragma unroll
-        for (int tp = 0; tp < 2; ++tp) acc[tm][tp] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // ---- in[ci, src(p, o)] and Wv[co, ci, o] of step (o, c0) -> registers (zero beyond the tensors).  The lanes of a weight
-    // load run along whichever of the two channel indices has the smaller stride in [C_out, C_in, kH, kW] (values 18 or 36
-    // bytes apart for a 3x3 kernel: a few cache lines per instruction; along the other index it would be one line per lane).
-    unit_t bu[UPT];
-    elem_t aw[NAW];
-    auto load_step = [&](int o, int c0) {
-        const int ky = o / P.kW, kx = o - ky * P.kW;
-        // source pixel of my staging pixel for this offset
-        int sy, sx;
-        bool ok = p_ok;
-        if (P.transposed) {
-            const int ty = soy + P.ph - ky, tx = sox + P.pw - kx;
-            ok = ok && ty >= 0 && tx >= 0 && ty % P.sh == 0 && tx % P.sw == 0;
-            sy = ty / P.sh;
-            sx = tx / P.sw;
-        } else {
-            sy = soy * P.sh + ky - P.ph;
-            sx = sox * P.sw + kx - P.pw;
-        }
-        ok = ok && (unsigned)sy < (unsigned)P.Hi && (unsigned)sx < (unsigned)P.Wi;
-        const elem_t *src = in_b + (size_t)(ok ? sy : 0) * P.in_sy + (size_t)(ok ? sx : 0) * P.in_sx;
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) {
-            const int u = kg + 4 * i;
-            elem_t v[KP];
-#pragma unroll
-            for (int e = 0; e < KP; ++e) {
-                const int c = c0 + u * KP + e;
-                v[e] = (ok && c < P.Cin) ? src[(size_t)c * P.in_sc] : elem_t(0);
-            }
-            bu[i] = conv_pack<DT>(v);
-        }
-#pragma unroll
-        for (int i = 0; i < NAW; ++i) {
-            const int idx = tid + kThreads * i;
-            const int cl = w_along_ci ? idx % KC : idx / TM, col = w_along_ci ? idx / KC : idx % TM;
-            const int c = c0 + cl, co = co0 + col;
-            aw[i] = (co < P.Cout && c < P.Cin) ? wv[(size_t)co * P.w_sco + (size_t)c * P.w_sci + o] : elem_t(0);
-        }
-    };
-
-    // Steps (offset, chunk of contraction channels) in turn: the loads of the next step are issued before the matrix
-    // instructions of the current one, whose operands are in LDS by then.
-    int o = 0, c0 = 0;
-    load_step(0, 0);
-    while (o < K2) {
-        __syncthreads();   // the previous step's fragments have been read
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) Bs[kg + 4 * i][sl] = bu[i];
-#pragma unroll
-        for (int i = 0; i < NAW; ++i) {
-            const int idx = tid + kThreads * i;
-            const int cl = w_along_ci ? idx % KC : idx / TM, col = w_along_ci ? idx / KC : idx % TM;
-            reinterpret_cast<elem_t *>(&As[0][0])[((cl / KP) * TM + col) * KP + cl % KP] = aw[i];
-        }
-        __syncthreads();
-        c0 += KC;
-        if (c0 >= P.Cin) { c0 = 0; ++o; }
-        if (o < K2) load_step(o, c0);
-#pragma unroll
-        for (int kk = 0; kk < NU / 4; ++kk) {
-            unit_t a[MT], b[2];
-#pragma unroll
-            for (int tm = 0; tm < MT; ++tm) a[tm] = As[kk * 4 + g][wm * (16 * MT) + tm * 16 + l16];
-#pragma unroll
-            for (int tp = 0; tp < 2; ++tp) b[tp] = Bs[kk * 4 + g][wp * 32 + tp * 16 + l16];
-#pragma unroll
-            for (int tm = 0; tm < MT; ++tm)
-#pragma unroll
-                for (int tp = 0; tp < 2; ++tp) acc[tm][tp] = conv_mfma<DT>(a[tm], b[tp], acc[tm][tp]);
-        }
-    }
-
-    // ---- D tile: lane (l16, g) holds output channels 4g .. 4g+3 of pixel l16; one rounding to the storage type
-    elem_t *out = static_cast<elem_t *>(P.out);
-#pragma unroll
-    for (int tp = 0; tp < 2; ++tp) {
-        const long long p = p0 + wp * 32 + tp * 16 + l16;
-        if (p >= P.npix) continue;
-        const int b = (int)(p / HoWo);
-        const int rem = (int)(p - (long long)b * HoWo);
-        const int oy = rem / P.Wo, ox = rem - oy * P.Wo;
-        elem_t *dst = out + (size_t)b * P.out_sb + (size_t)oy * P.out_sy + (size_t)ox * P.out_sx;
-#pragma unroll
-        for (int tm = 0; tm < MT; ++tm)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int co = co0 + wm * (16 * MT) + tm * 16 + 4 * g + v;
-                if (co < P.Cout) {
-                    if constexpr (DT == XCONV_F32) dst[(size_t)co * P.out_sc] = acc[tm][tp][v];
-                    else dst[(size_t)co * P.out_sc] = f32_to_st16<DT>(acc[tm][tp][v]);
-                }
-            }
-    }
+    const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
+    long long n = 0;
+    for (const ConvSub &s : make_subs(d, transposed, Ho, Wo))
+        n += packed_units(s, d->dtype, transposed ? d->C_out : d->C_in, transposed ? d->C_in : d->C_out);
+    return (size_t)n * 16 + 16;
 }
 
-template <int DT> static hipError_t launch_conv_dt(const ConvGemmParams &P, hipStream_t st)
+namespace {
+
+// One launch of a product: a class group of a run of images.  The pointers of P are filled in per call.
+struct ConvLaunch {
+    ConvParams P;
+    size_t in_off, out_off;   // bytes of the run's first image
+    bool pack;                // the weights of these classes are packed in front of it
+};
+struct ConvPlan {
+    int key[20];
+    std::vector<ConvLaunch> launches;
+};
+std::mutex g_conv_mu;
+std::vector<std::shared_ptr<const ConvPlan>> g_conv_plans;   // the last 64 products, handed out by reference
+constexpr size_t kConvPlans = 64;
+
+int device_cus()
 {
-    const long long tiles = (P.npix + 63) / 64;
-    // tiles of 128, 64 or 32 output channels: the smallest that covers the channels with the fewest empty rows
-    if (P.Cout > 64 && (P.Cout % 128 == 0 || P.Cout % 128 > 64)) {
-        hipLaunchKernelGGL((conv_gemm_kernel<DT, 4>), dim3((unsigned)tiles, (unsigned)ceil_div(P.Cout, 128)), dim3(kThreads), 0, st, P);
-    } else if (P.Cout > 32) {
-        hipLaunchKernelGGL((conv_gemm_kernel<DT, 2>), dim3((unsigned)tiles, (unsigned)ceil_div(P.Cout, 64)), dim3(kThreads), 0, st, P);
-    } else {
-        hipLaunchKernelGGL((conv_gemm_kernel<DT, 1>), dim3((unsigned)tiles, (unsigned)ceil_div(P.Cout, 32)), dim3(kThreads), 0, st, P);
-    }
-    return hipGetLastError();
+    static int cus[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (!cus[dev] && (hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus[dev] <= 0)) cus[dev] = 256;
+    return cus[dev];
 }
 
-hipError_t launch_conv_gemm(int dtype, const ConvGemmParams &P, hipStream_t st)
+// align: alignment of the input pointer in bytes, up to 16
+bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, int align, int ncu)
 {
-    if (dtype == XCONV_F32) return launch_conv_dt<XCONV_F32>(P, st);
-    if (dtype == XCONV_BF16) return launch_conv_dt<XCONV_BF16>(P, st);
-    return launch_conv_dt<XCONV_F16>(P, st);
+    const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
+    const int es = elem_size(d->dtype), ue = units_elems(d->dtype);
+    ConvParams P{};
+    P.Cin = transposed ? d->C_out : d->C_in;
+    P.Cout = transposed ? d->C_in : d->C_out;
+    P.Hi = transposed ? Ho : d->H;
+    P.Wi = transposed ? Wo : d->W;
+    const int Hout = transposed ? d->H : Ho, Wout = transposed ? d->W : Wo;
+    P.sh = transposed ? 1 : d->stride_h;
+    P.sw = transposed ? 1 : d->stride_w;
+    P.osy = transposed ? d->stride_h : 1;
+    P.osx = transposed ? d->stride_w : 1;
+    P.kWfull = d->kW;
+    P.rev = transposed;
+    image_strides(d->layout, P.Cin, P.Hi, P.Wi, P.in_sb, P.in_sc, P.in_sy, P.in_sx);
+    image_strides(d->layout, P.Cout, Hout, Wout, P.out_sb, P.out_sc, P.out_sy, P.out_sx);
+    P.w_sco = transposed ? d->kH * d->kW : d->C_in * d->kH * d->kW;
+    P.w_sci = transposed ? d->C_in * d->kH * d->kW : d->kH * d->kW;
+    P.NMB = ceil_div(P.Cout, 32);
+    const bool nhwc = d->layout == XCONV_NHWC;
+    P.swap = nhwc;
+    std::vector<ConvSub> subs = make_subs(d, transposed, Ho, Wo);
+    long long w0 = 0;
+    for (ConvSub &s : subs) {
+        s.w0 = w0;
+        w0 += packed_units(s, d->dtype, P.Cin, P.Cout);
+    }
+    // images per launch: 32-bit row and tile arithmetic
+    const int bstep = (int)std::max<long long>(1, std::min<long long>(d->B, kMaxRows / std::max(1, std::max(Hout, P.Hi))));
+    for (size_t s0 = 0; s0 < subs.size(); s0 += kConvSubs) {
+        P.nsub = (int)std::min<size_t>(kConvSubs, subs.size() - s0);
+        for (int i = 0; i < P.nsub; ++i) P.sub[i] = subs[s0 + i];
+        for (int bb = 0; bb < d->B; bb += bstep) {
+            P.B = std::min(bstep, d->B - bb);
+            // a tile reads the images of at most 512 positions: offsets from its first image fit a 2 GiB buffer descriptor
+            // unless a few images exceed that
+            const long long span = (512 / std::max(1, (Hout / P.osy) * (Wout / P.osx)) + 2) * P.in_sb * es;
+            P.big = span >= 0x7f000000LL;
+            P.vec = 0;
+            if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
+            bool pairs = !P.big && !nhwc && es == 2 && P.Wi % 2 == 0 && align % 4 == 0;
+            for (int i = 0; i < P.nsub; ++i) pairs = pairs && P.sub[i].kW >= P.sw;
+            if (pairs) P.vec = 1;
+            ConvLaunch L{};
+            L.P = P;
+            L.P.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
+            L.P.res = L.P.wp && P.Cin <= kConvResident;
+            if (!plan(L.P, d->dtype, ncu)) {
+                L.P.res = 0;
+                if (!plan(L.P, d->dtype, ncu)) return false;
+            }
+            L.in_off = (size_t)bb * P.in_sb * es;
+            L.out_off = (size_t)bb * P.out_sb * es;
+            L.pack = L.P.wp && bb == 0;
+            out.launches.push_back(L);
+        }
+    }
+    return true;
+}
+
+std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, bool packed, int align)
+{
+    const char *fs = getenv("XCONV_CONV_SHAPE"), *fw = getenv("XCONV_CONV_WM");   // overrides of tests and sweeps
+    const int ncu = device_cus();
+    const int key[20] = {d->B, d->C_in, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dtype, d->layout,
+                         transposed, packed, align, ncu, fs ? atoi(fs) : 0, fw ? atoi(fw) : 0, 0};
+    {
+        std::lock_guard<std::mutex> lk(g_conv_mu);
+        for (const auto &p : g_conv_plans)
+            if (memcmp(p->key, key, sizeof(key)) == 0) return p;
+    }
+    auto p = std::make_shared<ConvPlan>();
+    memcpy(p->key, key, sizeof(key));
+    if (!make_plan(*p, d, transposed, packed, align, ncu)) return nullptr;
+    std::lock_guard<std::mutex> lk(g_conv_mu);
+    if (g_conv_plans.size() >= kConvPlans) g_conv_plans.erase(g_conv_plans.begin());
+    g_conv_plans.push_back(p);
+    return p;
+}
+
+}  // namespace
+
+hipError_t launch_conv(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out, void *ws,
+                       hipStream_t st)
+{
+    const uintptr_t ia = reinterpret_cast<uintptr_t>(in);
+    const auto plan = conv_plan(d, transposed, ws != nullptr, ia % 16 == 0 ? 16 : ia % 4 == 0 ? 4 : 2);
+    if (!plan) return hipErrorInvalidConfiguration;
+    for (const ConvLaunch &L : plan->launches) {
+        ConvParams P = L.P;
+        P.in = static_cast<const char *>(in) + L.in_off;
+        P.out = static_cast<char *>(out) + L.out_off;
+        P.w = w;
+        P.bias = bias;
+        P.wp = P.wp ? ws : nullptr;
+        hipError_t e = hipSuccess;
+        if (L.pack) {
+            e = d->dtype == XCONV_F32 ? launch_conv_pack_f32(P, ws, st) : d->dtype == XCONV_BF16 ? launch_conv_pack_bf16(P, ws, st) : launch_conv_pack_f16(P, ws, st);
+            if (e != hipSuccess) return e;
+        }
+        e = d->dtype == XCONV_F32 ? launch_conv_f32(P, st) : d->dtype == XCONV_BF16 ? launch_conv_bf16(P, st) : launch_conv_f16(P, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace xc

@@ -74,9 +74,8 @@ class _XConvFunction(torch.autograd.Function):
             Wo = (W + 2 * padding[1] - weight.shape[3]) // stride[1] + 1
             y = _empty_like_layout((B, weight.shape[0], Ho, Wo), x.dtype, x.device, lay)
             with torch.cuda.device(x.device):
-                xb.xconv_conv_fwd(d0, xs0, weight.detach().contiguous(), y)
-            if bias is not None:
-                y += bias.detach().view(1, -1, 1, 1)
+                xb.xconv_conv_fwd_ws(d0, xs0, weight.detach().contiguous(), None if bias is None else bias.detach().contiguous(), y,
+                                     xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d0, 0), x.device))
         else:
             y = F.conv2d(x, weight, bias, stride, padding)
         ctx.has_state = False
@@ -126,7 +125,8 @@ class _XConvFunction(torch.autograd.Function):
                                   _DTYPE[dy.dtype], "rademacher", 0, lay)
                 dx = _empty_like_layout(tuple(ctx.x_shape), dy.dtype, dy.device, lay)
                 with torch.cuda.device(dy.device):
-                    xb.xconv_dx_exact(d0, dys0, weight.detach().contiguous(), dx)
+                    xb.xconv_dx_exact_ws(d0, dys0, weight.detach().contiguous(), dx,
+                                         xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d0, 1), dy.device))
             else:
                 dx = torch.nn.grad.conv2d_input(ctx.x_shape, weight, dy, stride=ctx.stride, padding=ctx.padding)
         if ctx.has_state and ctx.needs_input_grad[1]:
