@@ -288,10 +288,14 @@ __device__ inline int xcd_block(int b, int grid)
 }
 
 // ---- forward convolution / exact input gradient as implicit GEMMs (conv_core.h, conv_kernels.hip) ----
-constexpr int kConvUnits = 4;   // 16-byte units of channels per staged chunk
-constexpr int kConvGatherM = 128;   // most output channels of a tile whose weights are gathered (no workspace)
+constexpr int kConvUnits = 8;   // 16-byte units of channels per staged chunk
+constexpr int kConvGatherM = 64;   // most output channels of a tile whose weights are gathered (no workspace)
 constexpr int kConvResident = 128;   // most contraction channels whose whole patch is kept in LDS
+constexpr int kConvOverread = 4096; // bytes behind the packed weights that the last requests may touch
 constexpr int kConvSubs = 4;    // classes of output positions per launch
+
+// 16-byte entries of a list of k-steps (four steps each, one more that only prefetches touch)
+__host__ __device__ inline int conv_step_list(int taps, int steps_per_tap) { return (taps * steps_per_tap + 3) / 4 + 1; }
 
 // One class of output positions: an ordinary convolution with its own taps.  The forward convolution is one class; the
 // input gradient of a strided layer is sh*sw of them (output positions by their remainder modulo the stride).
@@ -323,8 +327,9 @@ struct ConvParams {
     int MT, NT, WM;    // 32-row tiles and 32-column tiles per wave, waves along the output channels
     int NMT, NMB;      // tiles of output channels, blocks of 32 packed output channels
     int vec, swap, big;   // how the input is read, which side of the accumulator the channels are on, 64-bit addresses
+    int pair;             // 16-bit outputs: neighbouring positions (channels-last: channels) share an aligned 4-byte word
     int rev;              // taps reach back: tap (i, j) reads patch position (kH-1-i, kW-1-j) (input gradient)
-    int res, SPC;         // all channels of a patch resident; steps of kConvUnits units per chunk (1 unless resident)
+    int res;              // all channels of a patch resident
     int nsub, nwg, lds_bytes;
     ConvSub sub[kConvSubs];
 };

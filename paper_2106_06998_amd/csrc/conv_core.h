@@ -18,13 +18,14 @@
 //   RES   all channels of the patch are resident: one staging phase, one barrier, then taps and channels without another
 //         (up to kConvResident channels; the workgroups that share a compute unit cover each other's staging).  The
 //         products of an output are summed tap by tap and, within a tap, by ascending channel.
-//   !RES  chunks of 4 units: the next chunk's patch is on its way through registers while the current one is multiplied
+//   !RES  chunks of kConvUnits units: the next chunk's patch is on its way through registers while the current one is multiplied
 //         (two LDS buffers, one barrier per chunk).
 // Strided layers keep the patch columns split by their remainder modulo the stride, so that the lanes' reads stay consecutive.
 // Weights come packed in fragment order (conv_pack_kernel, one coalesced kilobyte per fragment, read through the L1 by
 // every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, tap by tap.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -51,6 +52,13 @@ template <int DT> __device__ inline f32x16c conv_mma(const u32x4c &a, const u32x
     }
 }
 
+// round to nearest even on the conversion instructions of the chip
+template <int DT> __device__ inline uint16_t conv_round(float f)
+{
+    if constexpr (DT == XCONV_BF16) return __builtin_bit_cast(uint16_t, (__bf16)f);
+    else return f32_to_f16_rne(f);
+}
+
 template <int DT> struct ConvElem { typedef uint16_t t; static constexpr int UE = 8, ES = 2; };
 template <> struct ConvElem<XCONV_F32> { typedef float t; static constexpr int UE = 4, ES = 4; };
 
@@ -72,7 +80,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
 {
     typedef typename ConvElem<DT>::t elem_t;
     constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
-    constexpr int NU = kConvUnits, KS = NU / 2, CK = NU * UE;   // units, k-steps and channels of a step
+    constexpr int KS = kConvUnits / 2, CK = kConvUnits * UE;     // k-steps and channels of a chunk (!RES)
     constexpr bool IL = DT == XCONV_F32 && VEC != 2;             // units of a pair hold the even and the odd channels (conv_unit_channel)
     constexpr int VW = VEC == 1 ? 2 : 1;                         // columns per staging task
     constexpr int RW = VEC == 2 ? 4 : UE;                        // registers per staging task
@@ -95,20 +103,22 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int WN = 4 / P.WM, wm = wave % P.WM, wn = wave / P.WM;
     const int TN = 32 * NT * WN;
     const int npp_max = S.NPPmax;
-    const int SPC = RES ? P.SPC : 1;                                            // steps of NU units per chunk
-    uint4 *patch = conv_lds;                                                    // [RES ? 1 : 2][NU * SPC][NPOS]
-    const int patch_units = (RES ? NU * SPC : 2 * NU) * S.NPOS;
+    const int nks = (P.Cin + 2 * UE - 1) / (2 * UE);                            // k-steps of all channels
+    const int NU = RES ? 2 * nks : kConvUnits;                                  // units of a staged patch
+    uint4 *patch = conv_lds;                                                    // [RES ? 1 : 2][NU][NPOS]
+    const int patch_units = (RES ? 1 : 2) * NU * S.NPOS;
     uint2 *ptab = reinterpret_cast<uint2 *>(conv_lds + patch_units);             // [NPPmax] {source byte offset, LDS positions}
     uint2 *otab = ptab + npp_max;                                               // [TN] {output offset, LDS position of tap (0, 0)}
-    uint4 *alds = conv_lds + patch_units + (npp_max + TN + 1) / 2;           // !PACKED: [2][KS][MT * WM][64] weight fragments of a tap
+    uint4 *stab = conv_lds + patch_units + (npp_max + TN + 1) / 2;           // PACKED: LDS offsets of the k-steps' fragments, two lists
+    uint4 *alds = stab;                                                         // !PACKED: [2][KS][MT * WM][64] weight fragments of a tap
 
     // ---- the tile: positions q0 .. q0 + TU - 1 of this strip (TU < TN where the patch of TN would not fit into LDS), rows R0 .. R1 counted over the batch
     const int TU = S.TU;
-    const long long q0 = (long long)tile * TU;
+    const uint32_t q0 = (uint32_t)tile * (uint32_t)TU;       // below 2^31 (host)
     const int NR = P.B * S.Ho;
-    const int R0 = (int)(q0 / S.SW);
-    const int x0 = (int)(q0 - (long long)R0 * S.SW);
-    int R1 = (int)((q0 + TU - 1) / S.SW);
+    const int R0 = (int)(q0 / (uint32_t)S.SW);
+    const int x0 = (int)(q0 - (uint32_t)R0 * (uint32_t)S.SW);
+    int R1 = R0 + (x0 + TU - 1) / S.SW;
     R1 = R1 < NR - 1 ? R1 : NR - 1;
     const int b0 = R0 / S.Ho, oyA = R0 - b0 * S.Ho;
     const int b1 = R1 / S.Ho;
@@ -119,48 +129,69 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int npp = S.kH > 0 ? NPR * S.PWv : 0;   // a class without taps stages nothing
 
     {
-        const float rp = frcp(S.PWv);
+        const float rp = frcp(S.PWv), rh = frcp(HV), rs = frcp(S.SW), ro = frcp(S.Ho);
+        // image and row of row n of a stack of images of d rows (n < d + the rows of a tile)
+        auto image_row = [](int n, int d, float rd, int &img, int &row) {
+            if (d < (1 << 21)) fast_divmod(n, d, rd, img, row);
+            else { img = n >= d ? 1 : 0; row = n - img * d; }
+        };
         for (int pp = tid; pp < npp; pp += kThreads) {
             int prow, pc, bi, l;
             fast_divmod(pp, S.PWv, rp, prow, pc);
-            bi = (oyA * S.sth + prow) / HV;
-            l = oyA * S.sth + prow - bi * HV;
+            image_row(oyA * S.sth + prow, HV, rh, bi, l);
             const int c = pc * VW;
             const int iy = (S.kH >= P.sh ? l : (l / S.kH) * P.sh + l % S.kH) - S.ph;
             const int ix = xs - xa + (S.kW >= P.sw ? c : (c / S.kW) * P.sw + c % S.kW);
             const bool ok = b0 + bi < P.B && (unsigned)iy < (unsigned)P.Hi && (unsigned)ix < (unsigned)P.Wi;
             const uint32_t off = (uint32_t)bi * (uint32_t)P.in_sb + (uint32_t)iy * (uint32_t)P.in_sy + (uint32_t)ix * (uint32_t)P.in_sx;
-            const int p0 = prow * S.PWs + (c % S.stw) * S.PH + c / S.stw;
-            const int p1 = prow * S.PWs + ((c + 1) % S.stw) * S.PH + (c + 1) / S.stw;
+            int p0 = prow * S.PWs + c, p1 = p0 + 1;
+            if (S.stw != 1) {
+                p0 = prow * S.PWs + (c % S.stw) * S.PH + c / S.stw;
+                p1 = prow * S.PWs + ((c + 1) % S.stw) * S.PH + (c + 1) / S.stw;
+            }
             ptab[pp] = uint2{ok ? (BIG ? off : off * ES) : (BIG ? 0xffffffffu : kConvOob), (uint32_t)p0 | ((uint32_t)p1 << 16)};
         }
-        const float rs = frcp(S.SW);
         for (int n = tid; n < TN; n += kThreads) {
             int dr, x, bi, oy;
             fast_divmod(x0 + n, S.SW, rs, dr, x);
             const int row = R0 + dr, ox = strip * S.SW + x;
-            bi = (oyA + dr) / S.Ho;
-            oy = oyA + dr - bi * S.Ho;
+            image_row(oyA + dr, S.Ho, ro, bi, oy);
             const bool in_batch = row < NR && n < TU, ok = in_batch && ox < S.Wo;
             const uint32_t off = (uint32_t)bi * (uint32_t)P.out_sb + (uint32_t)(S.oy0 + oy * P.osy) * (uint32_t)P.out_sy +
                                  (uint32_t)(S.ox0 + ox * P.osx) * (uint32_t)P.out_sx;
             const int pr = dr * S.sth + bi * (S.kH - S.sth);
-            otab[n] = uint2{ok ? off : 0xffffffffu, (uint32_t)(in_batch ? pr * S.PWs + x : 0)};
+            otab[n] = uint2{ok ? (BIG ? off : off * ES) : (BIG ? 0xffffffffu : kConvOob), (uint32_t)(in_batch ? pr * S.PWs + x : 0)};
+        }
+    }
+    const int taps = S.kH * S.kW;
+    const int nck = taps == 0 ? 0 : RES ? 1 : (P.Cin + CK - 1) / CK;
+    auto tap_offset = [&](int ky, int kx) {
+        const int cy = P.rev ? S.kH - 1 - ky : ky, cx = (P.rev ? S.kW - 1 - kx : kx) + xa;
+        return cy * S.PWs + (S.stw == 1 ? cx : (cx % S.stw) * S.PH + cx / S.stw);
+    };
+    // Byte offset of k-step i's fragment from that of the first tap's first: list 0 for a resident patch or a full chunk, list 1
+    // for the last chunk.  One 16-byte read serves four steps, so the loop over the steps has no index arithmetic of its own.
+    const int nks_last = RES ? nks : nks - (nck - 1) * KS;
+    const int n_full = taps * (RES ? nks : KS), n_last = taps * nks_last;
+    if constexpr (PACKED) {
+        int *t = reinterpret_cast<int *>(stab);
+        const int cap = conv_step_list(taps, RES ? nks : KS) * 4;
+        for (int i = tid; i < (RES ? cap : 2 * cap); i += kThreads) {
+            const int list = i >= cap ? 1 : 0, k = i - list * cap, per = list ? nks_last : RES ? nks : KS, tap = k / per, ky = tap / S.kW;
+            t[i] = k < taps * per ? (tap_offset(ky, tap - ky * S.kW) + 2 * (k - tap * per) * S.NPOS) * 16 : 0;
         }
     }
     __syncthreads();
 
-    const int taps = S.kH * S.kW;
-    const int nck = taps == 0 ? 0 : (P.Cin + CK * SPC - 1) / (CK * SPC);
     const elem_t *in_b = static_cast<const elem_t *>(P.in) + (size_t)b0 * P.in_sb;
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(in_b), 0, (int)kConvOob, 0x00020000);
 
     // ---- staging: task t = (unit, position); a phase of a chunk is G tasks of every thread
-    const int ntask = npp * NU * SPC;
-    const float rnpp = frcp(npp);
+    const int ntask = npp * NU;
+    const float rnpp = frcp(VEC == 2 ? NU : npp);
     uint32_t sr[G][RW];
     auto split = [&](int t, int &u, int &pp) {
-        if constexpr (VEC == 2) { u = t % NU; pp = t / NU; if constexpr (RES) { const int b = pp / npp; u += NU * b; pp -= npp * b; } }
+        if constexpr (VEC == 2) fast_divmod(t, NU, rnpp, pp, u);
         else fast_divmod(t, npp, rnpp, u, pp);
     };
     auto stage_load = [&](int c0, int phase) {
@@ -189,13 +220,17 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                     const uint32_t cs = (uint32_t)P.in_sc * ES;             // bytes from a channel to the next
                     const int cu = conv_unit_channel<UE, IL>(u, 0), left = P.Cin - c0 - cu;
                     const uint32_t vo = off + (uint32_t)cu * cs;
+                    constexpr int step = IL ? 2 : 1;
+                    auto load = [&](auto part) {
 #pragma unroll
-                    for (int e = 0; e < UE; ++e) {
-                        constexpr int step = IL ? 2 : 1;
-                        const int v = (int)(e * step < left ? vo : kConvOob), so = (int)((uint32_t)(c0 + e * step) * cs);
-                        if constexpr (VEC == 1 || ES == 4) sr[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, so, 0);
-                        else sr[i][e] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, v, so, 0);
-                    }
+                        for (int e = 0; e < UE; ++e) {
+                            const int v = (int)(!decltype(part)::value || e * step < left ? vo : kConvOob), so = (int)((uint32_t)(c0 + e * step) * cs);
+                            if constexpr (VEC == 1 || ES == 4) sr[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, so, 0);
+                            else sr[i][e] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, v, so, 0);
+                        }
+                    };
+                    if (c0 + NU * UE <= P.Cin) load(std::false_type{});
+                    else load(std::true_type{});
                 }
             }
         }
@@ -240,19 +275,20 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int co_w = (mtile * P.WM + wm) * (32 * MT);    // first output channel of this wave
     int pos[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) pos[nt] = (int)otab[(wn * NT + nt) * 32 + l32].y + h * S.NPOS;
+    for (int nt = 0; nt < NT; ++nt) pos[nt] = ((int)otab[(wn * NT + nt) * 32 + l32].y + h * S.NPOS) * 16;   // bytes
 
-    // ---- weight fragments of one tap: k-steps 0 .. KS-1, one kilobyte each for 32 output channels
-    const int nk = nck * taps * SPC * KS;
-    const u32x4c *apk[MT];
+    // ---- packed weight fragments: one kilobyte per k-step and 32 output channels, in the order of the k-steps
+    const int nk = taps * nks;
+    const char *apk[MT];
     if constexpr (PACKED) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             int mb = co_w / 32 + mt;
             mb = mb < P.NMB ? mb : P.NMB - 1;
-            apk[mt] = reinterpret_cast<const u32x4c *>(P.wp) + S.w0 + (size_t)mb * nk * 64 + lane;
+            apk[mt] = static_cast<const char *>(P.wp) + ((size_t)S.w0 + (size_t)mb * nk * 64) * 16;
         }
     }
+    const uint32_t lane16 = (uint32_t)lane * 16u;
     // without packed weights the workgroup gathers a tap's fragments (32*MT*WM output channels x CK channels) through LDS, the
     // elements of the next tap on their way in registers; the lanes run along whichever channel index has the smaller stride
     constexpr int NEL = PACKED ? 1 : kConvGatherM * CK / kThreads;
@@ -261,7 +297,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int TMW = 32 * MT * P.WM, co_t = mtile * TMW;
     auto gather_at = [&](int i, int &cl, int &col) {
         const int idx = tid + kThreads * i;
-        if (P.w_sci < P.w_sco) { cl = idx % CK; col = idx / CK; }
+        if (P.w_sci < P.w_sco) { cl = idx & (CK - 1); col = idx / CK; }
         else { col = idx & (TMW - 1); cl = idx / TMW; }
         return cl < CK && col < TMW;
     };
@@ -287,196 +323,254 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             }
         }
     };
-    auto load_a = [&](u32x4c (&a)[KS][MT], int buf) {
+    // ---- k-steps.  Weights are requested kAhead k-steps ahead (they come from the L2), patch fragments one step ahead, both in
+    // front of the step's matrix instructions (sched_barrier: left alone, the compiler reads each fragment right before its
+    // use and waits).  Four steps make a block, so that the rings are indexed by constants.
+    constexpr int kRing = 4, kAhead = kRing - 1;
+    static_assert(KS == kRing, "a full chunk is whole blocks");
+    u32x4c a[kRing][MT], b[2][NT];
+    auto load_a = [&](auto slot) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                if constexpr (PACKED) a[s][mt] = apk[mt][s * 64];
-                else a[s][mt] = reinterpret_cast<const u32x4c *>(alds)[((buf * KS + s) * MT * P.WM + wm * MT + mt) * 64 + lane];
-            }
-            if constexpr (PACKED) apk[mt] += KS * 64;
+            a[decltype(slot)::value][mt] = *reinterpret_cast<const u32x4c *>(apk[mt] + lane16);
+            apk[mt] += 1024;
         }
     };
-
-    // one step: KS k-steps of the tap whose patch positions are shifted by toff
-    u32x4c a[KS][MT], an[KS][MT];
-    auto multiply = [&](const u32x4c *pb, int toff, bool two) {
-        u32x4c b[KS][NT];
+    const char *patch_b = reinterpret_cast<const char *>(patch);
+    auto load_b = [&](auto slot, int off) {
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
+        for (int nt = 0; nt < NT; ++nt) b[decltype(slot)::value][nt] = *reinterpret_cast<const u32x4c *>(patch_b + (pos[nt] + off));
+    };
+    auto multiply = [&](auto as, auto bs) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) b[s][nt] = pb[pos[nt] + toff + 2 * s * S.NPOS];
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
-            if (s == 0 || two) {
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        acc[mt][nt] = SWAP ? conv_mma<DT>(b[s][nt], a[s][mt], acc[mt][nt]) : conv_mma<DT>(a[s][mt], b[s][nt], acc[mt][nt]);
+            for (int mt = 0; mt < MT; ++mt) {
+                const u32x4c &av = a[decltype(as)::value][mt], &bv = b[decltype(bs)::value][nt];
+                acc[mt][nt] = SWAP ? conv_mma<DT>(bv, av, acc[mt][nt]) : conv_mma<DT>(av, bv, acc[mt][nt]);
             }
     };
-    auto next_a = [&](bool next) {
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) a[s][mt] = an[s][mt];
-        if (next) load_a(an, 0);
+    auto step = [&](auto jc, int next_off) {
+        constexpr int j = decltype(jc)::value;
+        load_b(std::integral_constant<int, (j + 1) & 1>{}, next_off);
+        load_a(std::integral_constant<int, (j + kAhead) % kRing>{});
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(std::integral_constant<int, j>{}, std::integral_constant<int, j & 1>{});
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto tap_offset = [&](int ky, int kx) {
-        const int cy = P.rev ? S.kH - 1 - ky : ky, cx = (P.rev ? S.kW - 1 - kx : kx) + xa;
-        return cy * S.PWs + (S.stw == 1 ? cx : (cx % S.stw) * S.PH + cx / S.stw);
+    // blocks b0 .. b1-1 of a list, and the rest of n steps behind the last whole block when `tail`
+    int4 so;
+    auto first_block = [&](const uint4 *list, int base) {
+        so = reinterpret_cast<const int4 *>(list)[0];
+        load_b(std::integral_constant<int, 0>{}, base + so.x);
     };
-
-    if constexpr (RES) {
-        if (nck > 0) {
-            load_a(an, 0);
-            for (int ph = 0; ph < nphase; ++ph) {
-                stage_load(0, ph);
-                stage_write(0, ph);
-            }
-            __syncthreads();
-            const bool two_last = P.Cin - (SPC - 1) * CK > CK / 2;      // channels in the second k-step of the last step
-            int ky = 0, kx = 0;
-            for (int tap = 0; tap < taps; ++tap) {
-                const int toff = tap_offset(ky, kx);
-                const u32x4c *pb = reinterpret_cast<const u32x4c *>(patch);
-                for (int sp = 0; sp < SPC; ++sp, pb += NU * S.NPOS) {
-                    next_a(tap + 1 < taps || sp + 1 < SPC);
-                    multiply(pb, toff, sp + 1 < SPC || two_last);
-                }
-                if (++kx == S.kW) { kx = 0; ++ky; }
-            }
+    auto run_blocks = [&](const uint4 *list, int base, int blk0, int blk1) {
+        for (int i = blk0; i < blk1; ++i) {
+            const int4 sn = reinterpret_cast<const int4 *>(list)[i + 1];
+            step(std::integral_constant<int, 0>{}, base + so.y);
+            step(std::integral_constant<int, 1>{}, base + so.z);
+            step(std::integral_constant<int, 2>{}, base + so.w);
+            step(std::integral_constant<int, 3>{}, base + sn.x);
+            so = sn;
         }
-    } else if (nck > 0) {
-        int abuf = 0;
-        if constexpr (PACKED) load_a(an, 0);
-        else { gather_load(0, 0); gather_write(0); }
+    };
+    auto run_tail = [&](int base, int left) {
+        if (left > 0) step(std::integral_constant<int, 0>{}, base + so.y);
+        if (left > 1) step(std::integral_constant<int, 1>{}, base + so.z);
+        if (left > 2) step(std::integral_constant<int, 2>{}, base + so.w);
+    };
+
+    if (nck > 0) {
+        if constexpr (PACKED) {
+            load_a(std::integral_constant<int, 0>{});
+            load_a(std::integral_constant<int, 1>{});
+            load_a(std::integral_constant<int, 2>{});
+        } else {
+            gather_load(0, 0);
+            gather_write(0);
+        }
         for (int ph = 0; ph < nphase; ++ph) {
             stage_load(0, ph);
             stage_write(0, ph);
         }
         __syncthreads();
-        for (int ck = 0; ck < nck; ++ck) {
-            const int c0 = ck * CK;
-            const bool more = ck + 1 < nck;
-            const bool two = P.Cin - c0 > CK / 2;
-            const u32x4c *pb = reinterpret_cast<const u32x4c *>(patch + (size_t)(ck & 1) * NU * S.NPOS);
-            int tap = 0, ky = 0, kx = 0;
-            for (int ph = 0; ph < nphase; ++ph) {
-                if (more) stage_load(c0 + CK, ph);
-                const int tend = taps * (ph + 1) / nphase;
-                for (; tap < tend; ++tap) {
-                    const bool next = tap + 1 < taps || more;
-                    if constexpr (PACKED) next_a(next);
-                    else {
-                        load_a(a, abuf);
-                        if (tap + 1 < taps) gather_load(c0, tap + 1);
-                        else if (more) gather_load(c0 + CK, 0);
-                    }
-                    multiply(pb, tap_offset(ky, kx), two);
-                    if constexpr (!PACKED) {
+        if constexpr (RES) {
+            first_block(stab, 0);
+            run_blocks(stab, 0, 0, n_full / 4);
+            run_tail(0, n_full & 3);
+        } else if constexpr (PACKED) {
+            const uint4 *list1 = stab + conv_step_list(taps, KS);
+            for (int ck = 0; ck < nck; ++ck) {
+                const bool more = ck + 1 < nck;
+                const uint4 *list = more ? stab : list1;
+                const int nblk = (more ? n_full : n_last) / 4, base = (ck & 1) * NU * S.NPOS * 16;
+                first_block(list, base);
+                for (int ph = 0; ph < nphase; ++ph) {
+                    if (more) stage_load((ck + 1) * CK, ph);
+                    run_blocks(list, base, nblk * ph / nphase, nblk * (ph + 1) / nphase);
+                    if (more) stage_write((ck + 1) & 1, ph);
+                }
+                if (!more) run_tail(base, n_last & 3);
+                __syncthreads();
+            }
+        } else {
+            int abuf = 0;
+            for (int ck = 0; ck < nck; ++ck) {
+                const int c0 = ck * CK;
+                const bool more = ck + 1 < nck;
+                const int base = (ck & 1) * NU * S.NPOS * 16;
+                int tap = 0, ky = 0, kx = 0;
+                for (int ph = 0; ph < nphase; ++ph) {
+                    if (more) stage_load(c0 + CK, ph);
+                    const int tend = taps * (ph + 1) / nphase;
+                    for (; tap < tend; ++tap) {
+                        const bool next = tap + 1 < taps || more;
+                        if (next) gather_load(tap + 1 < taps ? c0 : c0 + CK, tap + 1 < taps ? tap + 1 : 0);
+                        const int toff = tap_offset(ky, kx);
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                            for (int mt = 0; mt < MT; ++mt)
+                                a[s][mt] = reinterpret_cast<const u32x4c *>(alds)[((abuf * KS + s) * MT * P.WM + wm * MT + mt) * 64 + lane];
+                            load_b(std::integral_constant<int, 0>{}, base + (toff + 2 * s * S.NPOS) * 16);
+                            if (s == 0) multiply(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+                            if (s == 1) multiply(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
+                            if (s == 2) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
+                            if (s == 3) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, 0>{});
+                        }
                         abuf ^= 1;
                         if (next) gather_write(abuf);
                         __syncthreads();
+                        if (++kx == S.kW) { kx = 0; ++ky; }
                     }
-                    if (++kx == S.kW) { kx = 0; ++ky; }
+                    if (more) stage_write((ck + 1) & 1, ph);
                 }
-                if (more) stage_write((ck + 1) & 1, ph);
+                __syncthreads();
             }
-            __syncthreads();
         }
     }
 
-    // ---- accumulator tile: lane l holds column l % 32 and rows 8*(i/4) + 4*(l/32) + i%4; one rounding to the storage type
+    // ---- accumulator tile: lane l holds column l % 32 and rows 8*(i/4) + 4*(l/32) + i%4, rounded once to the storage type.
+    // The bias is added to the rounded product, in fp32, and the sum rounded again: what a separate addition gives, bit for
+    // bit (a sum rounded once falls on the other side of zero now and then, which a ReLU behind the layer would show).
     elem_t *out_b = static_cast<elem_t *>(P.out) + (size_t)b0 * P.out_sb;
     const elem_t *bias = static_cast<const elem_t *>(P.bias);
-    auto to_f32 = [](elem_t v) {
+    auto bias_of = [&](int co) {
+        if (co >= P.Cout) return 0.f;
+        if constexpr (ES == 4) return bias[co];
+        else return st16_to_f32<DT>(bias[co]);
+    };
+    auto add_bias = [](float v, float bv) {
+        if constexpr (ES == 4) return v + bv;
+        else return st16_to_f32<DT>(conv_round<DT>(v)) + bv;
+    };
+    auto stored = [](float v) -> elem_t {
         if constexpr (ES == 4) return v;
-        else return st16_to_f32<DT>(v);
+        else return conv_round<DT>(v);
     };
-    // the bias is added to the rounded product, in fp32, and the sum rounded again: what a separate addition gives, bit for
-    // bit (a sum rounded once falls on the other side of zero now and then, which a ReLU behind the layer would show)
-    auto put = [&](uint32_t off, int co, float v, float bv) {
-        elem_t *d = out_b + (size_t)off + (size_t)co * (size_t)P.out_sc;
-        if constexpr (ES == 4) *d = v + bv;
-        else {
-            const uint16_t q = f32_to_st16<DT>(v);
-            *d = bias ? f32_to_st16<DT>(st16_to_f32<DT>(q) + bv) : q;
-        }
-    };
-    if constexpr (SWAP) {
+    // byte offsets in a 2 GiB descriptor: per lane the position and its first channel, per register a scalar
+    const auto orsrc = __builtin_amdgcn_make_buffer_rsrc(out_b, 0, (int)kConvOob, 0x00020000);
+    const uint32_t cs = (uint32_t)P.out_sc * ES;
+    const uint32_t odd = (uint32_t)lane & 1u;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int co = co_w + mt * 32 + l32;
-            const float bv = bias && co < P.Cout ? to_f32(bias[co]) : 0.f;
+    for (int mt = 0; mt < MT; ++mt) {
+        const int cb = co_w + mt * 32;          // channels cb .. cb + 31
+        if (cb >= P.Cout) break;
+        const bool full = cb + 32 <= P.Cout;
+        if (bias) {
+            float bv[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bv[i] = bias_of(SWAP ? cb + l32 : cb + 8 * (i / 4) + 4 * h + i % 4);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const uint32_t off = otab[(wn * NT + nt) * 32 + 8 * (i / 4) + 4 * h + i % 4].x;
-                    if (off != 0xffffffffu && co < P.Cout) put(off, co, acc[mt][nt][i], bv);
-                }
+                for (int i = 0; i < 16; ++i) acc[mt][nt][i] = add_bias(acc[mt][nt][i], bv[i]);
         }
-    } else {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            float bv[16];
+        for (int nt = 0; nt < NT; ++nt) {
+            if constexpr (BIG) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int co = co_w + mt * 32 + 8 * (i / 4) + 4 * h + i % 4;
-                bv[i] = bias && co < P.Cout ? to_f32(bias[co]) : 0.f;
-            }
+                for (int i = 0; i < 16; ++i) {
+                    const int r = 8 * (i / 4) + 4 * h + i % 4, co = cb + (SWAP ? l32 : r);
+                    const uint32_t off = otab[(wn * NT + nt) * 32 + (SWAP ? r : l32)].x;
+                    if (off != 0xffffffffu && co < P.Cout) out_b[(size_t)off + (size_t)co * (size_t)P.out_sc] = stored(acc[mt][nt][i]);
+                }
+            } else if (ES == 2 && P.pair) {
+                // neighbouring lanes exchange halves: the even one stores two neighbours of register i, the odd one of register i + 1
+                const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+                auto both = [&](int i) {
+                    const uint32_t p = (uint32_t)stored(acc[mt][nt][i]) | ((uint32_t)stored(acc[mt][nt][i + 1]) << 16);
+                    const uint32_t q = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+                    return __builtin_amdgcn_perm(q, p, sel);
+                };
+                if constexpr (SWAP) {
+                    const uint32_t lo = (uint32_t)(l32 & ~1) * 2u;
+                    const bool on = cb + l32 < P.Cout;
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const uint32_t off = otab[(wn * NT + nt) * 32 + l32].x;
-                if (off != 0xffffffffu) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int co = co_w + mt * 32 + 8 * (i / 4) + 4 * h + i % 4;
-                        if (co < P.Cout) put(off, co, acc[mt][nt][i], bv[i]);
+                    for (int i = 0; i < 16; i += 2) {
+                        const uint2 *e = otab + (wn * NT + nt) * 32 + 8 * (i / 4) + 4 * h + i % 4;
+                        const uint32_t off = e[odd].x;
+                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)(on ? off + lo : kConvOob), cb * 2, 0);
                     }
+                } else {
+                    const uint32_t off = otab[(wn * NT + nt) * 32 + l32].x;
+                    const uint32_t vo = off == kConvOob ? off : off + (4u * h + odd) * cs - odd * 2u;
+#pragma unroll
+                    for (int i = 0; i < 16; i += 2) {
+                        const int r = 8 * (i / 4) + i % 4;      // + 4 * h + odd
+                        const uint32_t v = full || cb + r + 4 * h + (int)odd < P.Cout ? vo : kConvOob;
+                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)v, (int)((uint32_t)(cb + r) * cs), 0);
+                    }
+                }
+            } else {
+                const uint32_t lo = SWAP ? (uint32_t)l32 * cs : (uint32_t)(4 * h) * cs;
+                const uint32_t offl = otab[(wn * NT + nt) * 32 + l32].x;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int r = 8 * (i / 4) + i % 4;          // + 4 * h
+                    const uint32_t off = SWAP ? otab[(wn * NT + nt) * 32 + r + 4 * h].x : offl;
+                    const bool on = full || cb + (SWAP ? l32 : r + 4 * h) < P.Cout;
+                    const int vo = (int)(on && off != kConvOob ? off + lo : kConvOob), so = (int)((uint32_t)(SWAP ? cb : cb + r) * cs);
+                    const elem_t v = stored(acc[mt][nt][i]);
+                    if constexpr (ES == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, vo, so, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b16((short)v, orsrc, vo, so, 0);
                 }
             }
         }
     }
 }
 
-// Weights in fragment order: [block of 32 output channels][chunk of P.SPC steps][tap][k-step][lane] of 16 bytes, per class of taps; zero beyond
-// the channels.  One thread per 16-byte unit, lanes along the output channels.
+// Weights in fragment order, [block of 32 output channels][chunk][tap][k-step][lane] of 16 bytes per class of taps (a chunk =
+// kConvUnits / 2 k-steps of channels, or all of them for resident patches); zero beyond the channels.  One thread per 16 bytes.
 template <int DT, bool IL>
 __global__ __launch_bounds__(kThreads) void conv_pack_kernel(const ConvParams P, uint4 *out)
 {
     typedef typename ConvElem<DT>::t elem_t;
     constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
-    const int KS = kConvUnits / 2 * P.SPC, CK = kConvUnits * UE * P.SPC;
     const ConvSub &S = P.sub[blockIdx.y];
-    const int taps = S.kH * S.kW, nck = (P.Cin + CK - 1) / CK;
-    const long long n = (long long)P.NMB * nck * taps * KS * 64;
+    const int taps = S.kH * S.kW, nks = (P.Cin + 2 * UE - 1) / (2 * UE), nk = taps * nks;
+    const int cks = P.res ? nks : kConvUnits / 2;             // k-steps of a full chunk
     const elem_t *w = static_cast<const elem_t *>(P.w);
-    for (long long i = (long long)blockIdx.x * kThreads + threadIdx.x; i < n; i += (long long)gridDim.x * kThreads) {
-        const int lane = (int)(i & 63);
-        long long k = i >> 6;
-        const int s = (int)(k % KS);
-        k /= KS;
-        const int tap = (int)(k % taps);
-        k /= taps;
-        const int ck = (int)(k % nck), mb = (int)(k / nck);
+    const int lane = threadIdx.x & 63;
+    const long long n = (long long)P.NMB * nk;
+    for (long long i = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); i < n; i += (long long)gridDim.x * (kThreads / 64)) {
+        const int mb = (int)(i / nk), k = (int)(i - (long long)mb * nk);
+        const int ck = k / (taps * cks), r = k - ck * taps * cks;
+        const int per = min(cks, nks - ck * cks), tap = r / per, s = r - tap * per;
         const int ky = tap / S.kW, kx = tap - ky * S.kW;
         const int o = (S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs;
-        const int co = mb * 32 + (lane & 31), u = 2 * s + (lane >> 5);
+        const int co = mb * 32 + (lane & 31), u = 2 * (ck * cks + s) + (lane >> 5);
         const elem_t *src = w + (size_t)co * P.w_sco + o;
         uint32_t v[UE];
 #pragma unroll
         for (int e = 0; e < UE; ++e) {
-            const int c = ck * CK + conv_unit_channel<UE, IL>(u, e);
+            const int c = conv_unit_channel<UE, IL>(u, e);
             elem_t x = elem_t(0);
             if (co < P.Cout && c < P.Cin) x = src[(size_t)c * P.w_sci];
             v[e] = ES == 4 ? __builtin_bit_cast(uint32_t, (float)x) : (uint32_t)x;
         }
-        if constexpr (ES == 4) out[S.w0 + i] = uint4{v[0], v[1], v[2], v[3]};
-        else out[S.w0 + i] = uint4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
+        if constexpr (ES == 4) out[S.w0 + i * 64 + lane] = uint4{v[0], v[1], v[2], v[3]};
+        else out[S.w0 + i * 64 + lane] = uint4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
     }
 }
 
@@ -535,11 +629,11 @@ template <int DT> static hipError_t launch_conv_dt(const ConvParams &P, hipStrea
 
 template <int DT> static hipError_t launch_conv_pack_dt(const ConvParams &P, void *out, hipStream_t st)
 {
-    const int KS = kConvUnits / 2 * P.SPC, CK = kConvUnits * ConvElem<DT>::UE * P.SPC;
+    const int nks = ceil_div(P.Cin, 2 * ConvElem<DT>::UE);
     long long n = 0;
-    for (int i = 0; i < P.nsub; ++i) n = std::max(n, (long long)P.NMB * ceil_div(P.Cin, CK) * P.sub[i].kH * P.sub[i].kW * KS * 64);
+    for (int i = 0; i < P.nsub; ++i) n = std::max(n, (long long)P.NMB * nks * P.sub[i].kH * P.sub[i].kW);
     if (n == 0) return hipSuccess;
-    const unsigned wgs = (unsigned)std::min<long long>((n + kThreads - 1) / kThreads, 4096);
+    const unsigned wgs = (unsigned)std::min<long long>((n + kThreads / 64 - 1) / (kThreads / 64), 8192);
     if (DT == XCONV_F32 && P.vec != 2)
         hipLaunchKernelGGL((conv_pack_kernel<DT, DT == XCONV_F32>), dim3(wgs, (unsigned)P.nsub), dim3(kThreads), 0, st, P, static_cast<uint4 *>(out));
     else

@@ -22,7 +22,7 @@ hipError_t launch_conv_pack_f16(const ConvParams &P, void *out, hipStream_t st);
 namespace {
 
 constexpr int kLdsMax = 160 * 1024;
-constexpr long long kMaxRows = 1LL << 24;      // rows over the batch in one launch (32-bit tile arithmetic)
+constexpr long long kMaxPos = 1LL << 30;       // positions over the batch in one launch (32-bit tile arithmetic)
 
 int units_elems(int dtype) { return dtype == XCONV_F32 ? 4 : 8; }
 int elem_size(int dtype) { return dtype == XCONV_F32 ? 4 : 2; }
@@ -67,15 +67,23 @@ std::vector<ConvSub> make_subs(const xconv_desc *d, int transposed, int Ho, int 
     return v;
 }
 
-int chunks(int dtype, int C) { return ceil_div(C, kConvUnits * units_elems(dtype)); }
+int ksteps(int dtype, int C) { return ceil_div(C, 2 * units_elems(dtype)); }
 long long packed_units(const ConvSub &s, int dtype, int Cin, int Cout)
 {
-    return (long long)ceil_div(Cout, 32) * chunks(dtype, Cin) * s.kH * s.kW * (kConvUnits / 2) * 64;
+    return (long long)ceil_div(Cout, 32) * ksteps(dtype, Cin) * s.kH * s.kW * 64;
+}
+
+// LDS of a workgroup: patch, tables, step lists (conv_kernel's layout; gathered weights come on top)
+long long conv_lds(const ConvParams &P, const ConvSub &c, int TN, int nks)
+{
+    const int taps = c.kH * c.kW;
+    return (P.res ? 2LL * nks : 2LL * kConvUnits) * c.NPOS * 16 + (c.NPPmax + TN + 1) / 2 * 16 +
+           (P.res ? conv_step_list(taps, nks) : 2 * conv_step_list(taps, kConvUnits / 2)) * 16;
 }
 
 // Strips and LDS extents of a class for tiles of TN positions: the strip width with the least work in all (products for
 // positions of ragged tiles and strips, staging of the halo).  Returns the cost per launch in cycles of one compute unit.
-double plan_sub(ConvSub &s, const ConvParams &P, int TN, double mma_clk, int nck, int lds_max)
+double plan_sub(ConvSub &s, const ConvParams &P, int TN, double mma_clk, int nks, int lds_max)
 {
     const int VW = P.vec == 1 ? 2 : 1;
     const int taps = s.kH * s.kW;
@@ -103,9 +111,9 @@ double plan_sub(ConvSub &s, const ConvParams &P, int TN, double mma_clk, int nck
             c.NPOS = round_up(NPR * c.PWs, 16);
             c.NPPmax = NPR * c.PWv;
             c.TPS = (int)((NR * SW + TU - 1) / TU);
-            if ((P.res ? P.SPC : 2LL) * kConvUnits * c.NPOS * 16 + (c.NPPmax + TN + 1) / 2 * 16LL > lds_max || c.NPOS > 65535) continue;
-            const double ntask = (double)c.NPPmax * kConvUnits * P.SPC / kThreads;
-            const double cost = (double)nst * c.TPS * (nck * (taps * P.SPC * mma_clk + ntask * 120.0) + 2500.0);
+            if (conv_lds(P, c, TN, nks) > lds_max || c.NPOS > 65535) continue;
+            const double ntask = (double)c.NPPmax * 2 * nks / kThreads;
+            const double cost = (double)nst * c.TPS * (taps * nks * mma_clk + ntask * 120.0 + 2500.0);
             if (best < 0 || cost < best) { best = cost; bs = c; }
         }
         s = bs;
@@ -122,8 +130,7 @@ bool plan(ConvParams &P, int dtype, int ncu)
     int force = 0, force_wm = 0;
     if (const char *e = getenv("XCONV_CONV_SHAPE")) force = atoi(e);
     if (const char *e = getenv("XCONV_CONV_WM")) force_wm = atoi(e);
-    P.SPC = P.res ? chunks(dtype, P.Cin) : 1;
-    const int nck = P.res ? 1 : chunks(dtype, P.Cin);
+    const int nks = ksteps(dtype, P.Cin);
     double best = -1;
     ConvParams bp = P;
     for (const Shape &sh : kShapes)
@@ -138,19 +145,19 @@ bool plan(ConvParams &P, int dtype, int ncu)
             const int extra = P.wp ? 0 : 2 * (kConvUnits / 2) * sh.MT * WM * 1024;   // LDS of the gathered weights
             const int TM = 32 * sh.MT * WM, TN = 32 * sh.NT * (4 / WM);
             C.NMT = ceil_div(P.Cout, TM);
-            // cycles of the four waves' products of one tap of a chunk (one wave per SIMD)
-            const double per = sh.MT * sh.NT * (kConvUnits / 2) * (dtype == XCONV_F32 ? 256.0 / 0.85 : 32.0 / sh.eff);
+            // cycles of a wave's products of one k-step
+            const double per = sh.MT * sh.NT * (dtype == XCONV_F32 ? 256.0 / 0.85 : 32.0 / sh.eff);
             double cost = 0;
             long long nwg = 0;
             int lds = 0;
             bool ok = true;
             for (int i = 0; i < P.nsub && ok; ++i) {
-                const double c = plan_sub(C.sub[i], C, TN, per, nck, kLdsMax - extra);
+                const double c = plan_sub(C.sub[i], C, TN, per, nks, kLdsMax - extra);
                 if (c < 0) { ok = false; break; }
                 cost += c * C.NMT;
                 C.sub[i].wg0 = (int)nwg;
                 nwg += (long long)ceil_div(C.sub[i].Wo, C.sub[i].SW) * C.sub[i].TPS * C.NMT;
-                lds = std::max(lds, (P.res ? P.SPC : 2) * kConvUnits * C.sub[i].NPOS * 16 + (C.sub[i].NPPmax + TN + 1) / 2 * 16 + extra);
+                lds = std::max(lds, (int)conv_lds(P, C.sub[i], TN, nks) + extra);
             }
             if (!ok || nwg > 0x3fffffff) continue;
             C.nwg = (int)nwg;
@@ -174,7 +181,7 @@ size_t conv_ws_bytes(const xconv_desc *d, int transposed)
     long long n = 0;
     for (const ConvSub &s : make_subs(d, transposed, Ho, Wo))
         n += packed_units(s, d->dtype, transposed ? d->C_out : d->C_in, transposed ? d->C_in : d->C_out);
-    return (size_t)n * 16 + 16;
+    return (size_t)n * 16 + kConvOverread;
 }
 
 namespace {
@@ -202,8 +209,8 @@ int device_cus()
     return cus[dev];
 }
 
-// align: alignment of the input pointer in bytes, up to 16
-bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, int align, int ncu)
+// align, oalign: alignment of the input and the output pointer in bytes, up to 16
+bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, int align, int oalign, int ncu)
 {
     const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
     const int es = elem_size(d->dtype), ue = units_elems(d->dtype);
@@ -233,7 +240,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
         w0 += packed_units(s, d->dtype, P.Cin, P.Cout);
     }
     // images per launch: 32-bit row and tile arithmetic
-    const int bstep = (int)std::max<long long>(1, std::min<long long>(d->B, kMaxRows / std::max(1, std::max(Hout, P.Hi))));
+    const int bstep = (int)std::max<long long>(1, std::min<long long>(d->B, kMaxPos / ((long long)Hout * Wout)));
     for (size_t s0 = 0; s0 < subs.size(); s0 += kConvSubs) {
         P.nsub = (int)std::min<size_t>(kConvSubs, subs.size() - s0);
         for (int i = 0; i < P.nsub; ++i) P.sub[i] = subs[s0 + i];
@@ -241,7 +248,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
             P.B = std::min(bstep, d->B - bb);
             // a tile reads the images of at most 512 positions: offsets from its first image fit a 2 GiB buffer descriptor
             // unless a few images exceed that
-            const long long span = (512 / std::max(1, (Hout / P.osy) * (Wout / P.osx)) + 2) * P.in_sb * es;
+            const long long span = (512 / std::max(1, (Hout / P.osy) * (Wout / P.osx)) + 2) * std::max(P.in_sb, P.out_sb) * es;
             P.big = span >= 0x7f000000LL;
             P.vec = 0;
             if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
@@ -256,6 +263,9 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
                 L.P.res = 0;
                 if (!plan(L.P, d->dtype, ncu)) return false;
             }
+            // words of two outputs: channels-last, neighbouring channels; planes, neighbouring columns of an even strip of a unit-step class
+            L.P.pair = es == 2 && !P.big && oalign % 4 == 0 && (nhwc ? P.Cout % 2 == 0 : P.osx == 1 && Wout % 2 == 0);
+            for (int i = 0; i < P.nsub && !nhwc; ++i) L.P.pair = L.P.pair && L.P.sub[i].SW % 2 == 0 && L.P.sub[i].TU % 2 == 0;
             L.in_off = (size_t)bb * P.in_sb * es;
             L.out_off = (size_t)bb * P.out_sb * es;
             L.pack = L.P.wp && bb == 0;
@@ -265,12 +275,12 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
     return true;
 }
 
-std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, bool packed, int align)
+std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, bool packed, int align, int oalign)
 {
     const char *fs = getenv("XCONV_CONV_SHAPE"), *fw = getenv("XCONV_CONV_WM");   // overrides of tests and sweeps
     const int ncu = device_cus();
     const int key[20] = {d->B, d->C_in, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dtype, d->layout,
-                         transposed, packed, align, ncu, fs ? atoi(fs) : 0, fw ? atoi(fw) : 0, 0};
+                         transposed, packed, align, ncu, fs ? atoi(fs) : 0, fw ? atoi(fw) : 0, oalign};
     {
         std::lock_guard<std::mutex> lk(g_conv_mu);
         for (const auto &p : g_conv_plans)
@@ -278,7 +288,7 @@ std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, b
     }
     auto p = std::make_shared<ConvPlan>();
     memcpy(p->key, key, sizeof(key));
-    if (!make_plan(*p, d, transposed, packed, align, ncu)) return nullptr;
+    if (!make_plan(*p, d, transposed, packed, align, oalign, ncu)) return nullptr;
     std::lock_guard<std::mutex> lk(g_conv_mu);
     if (g_conv_plans.size() >= kConvPlans) g_conv_plans.erase(g_conv_plans.begin());
     g_conv_plans.push_back(p);
@@ -291,7 +301,7 @@ hipError_t launch_conv(const xconv_desc *d, int transposed, const void *in, cons
                        hipStream_t st)
 {
     const uintptr_t ia = reinterpret_cast<uintptr_t>(in);
-    const auto plan = conv_plan(d, transposed, ws != nullptr, ia % 16 == 0 ? 16 : ia % 4 == 0 ? 4 : 2);
+    const auto plan = conv_plan(d, transposed, ws != nullptr, ia % 16 == 0 ? 16 : ia % 4 == 0 ? 4 : 2, reinterpret_cast<uintptr_t>(out) % 4 == 0 ? 4 : 2);
     if (!plan) return hipErrorInvalidConfiguration;
     for (const ConvLaunch &L : plan->launches) {
         ConvParams P = L.P;
