@@ -130,6 +130,18 @@ xconv_status xconv_dw_estimate(const xconv_desc *desc, const void *dY_dev, const
                                const float *Z_dev, float *dW_dev,
                                void *ws_dev, size_t ws_bytes, void *stream);
 
+/* xconv_dw_estimate with dW in the type the caller keeps its weights in: dw_dtype is an xconv_dtype, dW_dev is
+ * [C_out,C_in,kH,kW] of it, every value the fp32 result rounded once (nearest even). */
+xconv_status xconv_dw_estimate_as(const xconv_desc *desc, const void *dY_dev, const void *Xt_dev,
+                                  const float *Z_dev, void *dW_dev, int dw_dtype,
+                                  void *ws_dev, size_t ws_bytes, void *stream);
+
+/* Bias gradient of the layer, db[m] = sum over images and positions of dY[b,m,oy,ox]: fp32 sums, rounded once to
+ * desc->dtype; deterministic.  dY_dev as in xconv_dw_estimate (aligned to the element size), db_dev: [C_out] in
+ * desc->dtype, ws_dev: xconv_bias_workspace_bytes() bytes, 16-byte aligned. */
+size_t xconv_bias_workspace_bytes(const xconv_desc *desc);
+xconv_status xconv_bias_grad(const xconv_desc *desc, const void *dY_dev, void *db_dev, void *ws_dev, size_t ws_bytes, void *stream);
+
 /* xconv_dw_estimate for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): no workspace argument.
  * The scratch is a device array inside the library, XCONV_STATIC_SCRATCH_BYTES per GPU the
@@ -280,6 +292,9 @@ xconv_status xconv_pixel_probe_fwd(const xconv_desc *desc, const void *X_dev, fl
                                    void *ws_dev, size_t ws_bytes, void *stream);
 xconv_status xconv_pixel_dw_estimate(const xconv_desc *desc, const void *dY_dev, const float *Xbar_dev,
                                      float *dW_dev, void *ws_dev, size_t ws_bytes, void *stream);
+/* The gradient rounded to dw_dtype as in xconv_dw_estimate_as; XCONV_EUNSUPPORTED for a 16-bit type with keep_q15 != 0. */
+xconv_status xconv_pixel_dw_estimate_as(const xconv_desc *desc, const void *dY_dev, const float *Xbar_dev,
+                                        void *dW_dev, int dw_dtype, void *ws_dev, size_t ws_bytes, void *stream);
 
 /* Independent probing (Sec. 3: trace estimation applied to every input/output channel
  * pair on its own, the alternative that the multi-channel case of Eq. (6) is set

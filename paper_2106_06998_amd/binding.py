@@ -81,6 +81,14 @@ def lib():
         L.xconv_conv_fwd_ws.argtypes = [P, vp, vp, vp, vp, vp, sz, vp]
         L.xconv_dx_exact_ws.restype = i32
         L.xconv_dx_exact_ws.argtypes = [P, vp, vp, vp, vp, sz, vp]
+        L.xconv_dw_estimate_as.restype = i32
+        L.xconv_dw_estimate_as.argtypes = [P, vp, vp, vp, vp, i32, vp, sz, vp]
+        L.xconv_pixel_dw_estimate_as.restype = i32
+        L.xconv_pixel_dw_estimate_as.argtypes = [P, vp, vp, vp, i32, vp, sz, vp]
+        L.xconv_bias_workspace_bytes.restype = sz
+        L.xconv_bias_workspace_bytes.argtypes = [P]
+        L.xconv_bias_grad.restype = i32
+        L.xconv_bias_grad.argtypes = [P, vp, vp, vp, sz, vp]
         L.xconv_dw_estimate_static.restype = i32
         L.xconv_dw_estimate_static.argtypes = [P, vp, vp, vp, vp, vp]
         L.xconv_static_scratch_bytes.restype = sz
@@ -167,7 +175,8 @@ def _ptr(t):
 def _stream(stream):
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the raw handle of the current stream of the current device (torch.cuda.current_stream() builds a Stream object for it)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     if isinstance(stream, int):
         return ctypes.c_void_p(stream)
     return ctypes.c_void_p(stream.cuda_stream)
@@ -216,6 +225,20 @@ def xconv_probe_fwd(desc, X_dev, Xt_dev, Z_dev=None, ws_dev=None, stream=None):
 def xconv_dw_estimate(desc, dY_dev, Xt_dev, Z_dev, dW_dev, ws_dev, stream=None):
     _check(lib().xconv_dw_estimate(ctypes.byref(desc), _ptr(dY_dev), _ptr(Xt_dev), _ptr(Z_dev), _ptr(dW_dev),
                                    _ptr(ws_dev), _nbytes(ws_dev), _stream(stream)), "xconv_dw_estimate")
+
+
+def xconv_dw_estimate_as(desc, dY_dev, Xt_dev, Z_dev, dW_dev, dw_dtype, ws_dev, stream=None):
+    _check(lib().xconv_dw_estimate_as(ctypes.byref(desc), _ptr(dY_dev), _ptr(Xt_dev), _ptr(Z_dev), _ptr(dW_dev), int(dw_dtype),
+                                      _ptr(ws_dev), _nbytes(ws_dev), _stream(stream)), "xconv_dw_estimate_as")
+
+
+def xconv_bias_workspace_bytes(desc):
+    return int(lib().xconv_bias_workspace_bytes(ctypes.byref(desc)))
+
+
+def xconv_bias_grad(desc, dY_dev, db_dev, ws_dev, stream=None):
+    _check(lib().xconv_bias_grad(ctypes.byref(desc), _ptr(dY_dev), _ptr(db_dev), _ptr(ws_dev), _nbytes(ws_dev), _stream(stream)),
+           "xconv_bias_grad")
 
 
 def xconv_conv_fwd(desc, X_dev, W_dev, Y_dev, stream=None):
@@ -327,6 +350,11 @@ def xconv_pixel_probe_fwd(desc, X_dev, Xbar_dev, ws_dev, stream=None):
 def xconv_pixel_dw_estimate(desc, dY_dev, Xbar_dev, dW_dev, ws_dev, stream=None):
     _check(lib().xconv_pixel_dw_estimate(ctypes.byref(desc), _ptr(dY_dev), _ptr(Xbar_dev), _ptr(dW_dev), _ptr(ws_dev),
                                          _nbytes(ws_dev), _stream(stream)), "xconv_pixel_dw_estimate")
+
+
+def xconv_pixel_dw_estimate_as(desc, dY_dev, Xbar_dev, dW_dev, dw_dtype, ws_dev, stream=None):
+    _check(lib().xconv_pixel_dw_estimate_as(ctypes.byref(desc), _ptr(dY_dev), _ptr(Xbar_dev), _ptr(dW_dev), int(dw_dtype), _ptr(ws_dev),
+                                            _nbytes(ws_dev), _stream(stream)), "xconv_pixel_dw_estimate_as")
 
 
 XCONV_DIAG_OUT_BYTES = 8192

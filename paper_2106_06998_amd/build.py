@@ -10,8 +10,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxconv.so")
+GLUE = os.path.join(HERE, "_torch_glue.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["xconv_api.hip", "probe_kernels.hip", "corr_kernels.hip", "corr_ws_kernels.hip", "corr_row_kernels.hip", "corr_ws32_kernels.hip", "pixel_kernels.hip", "relu_kernels.hip", "conv_kernels.hip", "conv_f32.hip", "conv_bf16.hip", "conv_f16.hip", "diag_kernels.hip"]
+SOURCES = ["xconv_api.hip", "probe_kernels.hip", "corr_kernels.hip", "corr_ws_kernels.hip", "corr_row_kernels.hip", "corr_ws32_kernels.hip", "pixel_kernels.hip", "relu_kernels.hip", "bias_kernels.hip", "conv_kernels.hip", "conv_f32.hip", "conv_bf16.hip", "conv_f16.hip", "diag_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # XCONV_SANITIZE_HOST=1: a second library whose host code (descriptor checks, plans, size arithmetic) is built under
@@ -40,16 +41,34 @@ def _compile(src):
     return obj
 
 
+def _compile_glue():
+    """The layers' host path, a Python extension module over torch's C++ interface (no device code)."""
+    import sysconfig
+
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-sign-compare", "-DPY_SSIZE_T_CLEAN",
+           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "torch_glue.cpp"), "-o", GLUE, "-L" + tlib, "-Wl,-rpath," + tlib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("%s failed for torch_glue.cpp:\n%s" % (cmd[0], p.stdout))
+
+
 def build(verbose=True):
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        glue = None if SANITIZE_HOST else ex.submit(_compile_glue)
         objs = list(ex.map(_compile, SOURCES))
+        if glue:
+            glue.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     if SANITIZE_HOST:
         cmd += ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined"]
     subprocess.run(cmd, check=True)
     if verbose:
-        print("built", LIB)
+        print("built", LIB, "" if SANITIZE_HOST else GLUE)
     return LIB
 
 

@@ -34,7 +34,8 @@ enum KernelId {
     K_CONV = 15,
     K_PASS2 = 16,
     K_DIAG = 17,
-    K_COUNT = 18
+    K_BIAS = 18,
+    K_COUNT = 19
 };
 
 // Where the probe output of a voxel goes in Xt.  sd == 0: plain order, pixel `first` of the

@@ -694,10 +694,17 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const f32x4 *
 // ---------------------------------------------------------------------------
 // nnz_norm: rows are scaled by 1 / nnz(Z_n), the number of non-zero entries of row n of Z (Eq. (8),
 // block-sparse probing vectors), instead of 1 / r; a row without any gives zeros.
+// one value of dW in the type the caller keeps its weights in (dt: an xconv_dtype, the same for the whole launch)
+__device__ inline void store_dw(void *dW, size_t i, float v, int dt)
+{
+    if (dt == XCONV_F32) static_cast<float *>(dW)[i] = v;
+    else static_cast<uint16_t *>(dW)[i] = dt == XCONV_BF16 ? f32_to_bf16_rne(v) : f32_to_f16_rne(v);
+}
+
 template <int OG>
 __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T, const float *__restrict__ Z,
-                                                    float *__restrict__ dW, int K2, int JP, int MP, int C_out, int C_in, int r,
-                                                    int NTN, int nnz_norm)
+                                                    void *__restrict__ dW, int K2, int JP, int MP, int C_out, int C_in, int r,
+                                                    int NTN, int nnz_norm, int dt)
 {
     const int lane = threadIdx.x, l16 = lane & 15, g = lane >> 4;
     const int nt = blockIdx.x % NTN, mt = blockIdx.x / NTN;
@@ -744,10 +751,10 @@ __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T,
         for (int v = 0; v < 4; ++v) {
             const int m = mt * 16 + 4 * g + v;
             if (m < C_out) {
-                float *dst = dW + ((size_t)m * C_in + ncol) * K2 + o0;
+                const size_t dst = ((size_t)m * C_in + ncol) * K2 + o0;
 #pragma unroll
                 for (int o = 0; o < OG; ++o)
-                    if (o0 + o < K2) dst[o] = acc[o][v] * inv_r;
+                    if (o0 + o < K2) store_dw(dW, dst + o, acc[o][v] * inv_r, dt);
             }
         }
     }
@@ -810,8 +817,8 @@ template <int NC> __device__ inline f32x4 once_sum(const f32x4 *p, int first, in
 // kernel-depth offset), og = set * K2 + o, K2T = nsets * K2.  The grid's first extent is a multiple of 8, so
 // the workgroups that write the K2T offsets of one (m, n) run of dW share an L2, which merges their 4-byte stores.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__restrict__ part, float *__restrict__ dW, int S, int K2,
-                                                               int K2T, int JP, int MQ, int JC, int C_out, int C_in)
+__global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__restrict__ part, void *__restrict__ dW, int S, int K2,
+                                                               int K2T, int JP, int MQ, int JC, int C_out, int C_in, int dt)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [JC], then the thread groups' sums [NG][NE] (few-element slabs only)
     const int tid = threadIdx.x;
@@ -842,7 +849,7 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
     for (int e = tid; e < JC * 4; e += kThreads) {
         const int mi = e & 3, j = e >> 2;
         const int m = 4 * mq + mi, n = j0 + j;
-        if (m < C_out && n < C_in) dW[((size_t)m * C_in + n) * K2T + og] = slab[e];
+        if (m < C_out && n < C_in) store_dw(dW, ((size_t)m * C_in + n) * K2T + og, slab[e], dt);
     }
 }
 
@@ -865,8 +872,8 @@ constexpr int kP2Threads = 1024;
 
 template <int QW>
 __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__restrict__ part, const float *__restrict__ Z,
-                                                                float *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
-                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS)
+                                                                void *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
+                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, int dt)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [QW][JP], then the thread groups' sums [NG][NE] (few-element slabs only) and, after them, rows of Z [NR][ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -974,7 +981,7 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int m = 4 * (mg * QW + q4) + v;
-                    if (m < C_out) dW[((size_t)m * C_in + n) * K2T + og] = acc[v] * inv_r;
+                    if (m < C_out) store_dw(dW, ((size_t)m * C_in + n) * K2T + og, acc[v] * inv_r, dt);
                 }
             }
         }
@@ -982,8 +989,8 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 }
 
 // Exact path: dW[m,n,o] = T[o,n,m] (a transpose of the reduced tile).
-__global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restrict__ T, float *__restrict__ dW, int K2, int JP,
-                                                          int MP, int C_out, int C_in)
+__global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restrict__ T, void *__restrict__ dW, int K2, int JP,
+                                                          int MP, int C_out, int C_in, int dt)
 {
     const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
     const long long total = (long long)C_out * C_in * K2;
@@ -991,7 +998,7 @@ __global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restric
     const int o = (int)(i % K2);
     const long long mn = i / K2;
     const int n = (int)(mn % C_in), m = (int)(mn / C_in);
-    dW[i] = T[tile_index(o, n, m, JP, MP)];
+    store_dw(dW, (size_t)i, T[tile_index(o, n, m, JP, MP)], dt);
 }
 
 // dY planes whose size is not a whole number of 16-byte vectors are copied once into planes
@@ -1299,8 +1306,8 @@ bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in,
     return (long long)K2T * (MQ / (exact ? 1 : pass2_quads(MQ, K2T))) <= 256;
 }
 
-hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, float *dW, int C_in, int r, bool nnz_norm, int dist,
-                                uint64_t seed, int nsets, hipStream_t st)
+hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
+                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype)
 {
     const int MQ = P.MP / 4;
     const int K2T = nsets * P.K2;
@@ -1314,7 +1321,7 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
         const int NG = NE >= kThreads ? 1 : kThreads / NE;
         const size_t lds = (size_t)NE * 16 + (NG > 1 ? (size_t)NG * NE * 16 : 0);
         const dim3 grid((unsigned)round_up(MQ, 8), (unsigned)K2T, (unsigned)(P.JP / JC));
-        hipLaunchKernelGGL(pass2_exact_kernel, grid, dim3(kThreads), lds, st, part, dW, P.S, P.K2, K2T, P.JP, MQ, JC, P.C_out, C_in);
+        hipLaunchKernelGGL(pass2_exact_kernel, grid, dim3(kThreads), lds, st, part, dW, P.S, P.K2, K2T, P.JP, MQ, JC, P.C_out, C_in, dw_dtype);
     } else {
         int QW = env_int("XCONV_PASS2_QW", pass2_quads(MQ, K2T));
         if ((QW != 1 && QW != 2 && QW != 4) || MQ % QW != 0) QW = 1;
@@ -1338,7 +1345,7 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
             done = true;                                                                                                 \
         }                                                                                                                \
         hipLaunchKernelGGL(pass2_mfma_kernel<Q>, grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
-                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS);                                           \
+                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, dw_dtype);                                 \
     }
         if (QW == 4) XC_P2M(4) else if (QW == 2) XC_P2M(2) else XC_P2M(1)
 #undef XC_P2M
@@ -1346,8 +1353,8 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
     return hipGetLastError();
 }
 
-hipError_t launch_expand(const CorrParams &P, const float *Z, float *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
-                         const float *Tin, int K2in)
+hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
+                         const float *Tin, int K2in, int dw_dtype)
 {
     const int nn = nnz_norm ? 1 : 0;
     const int K2 = K2in > 0 ? K2in : P.K2;
@@ -1360,16 +1367,16 @@ hipError_t launch_expand(const CorrParams &P, const float *Z, float *dW, int C_i
         og = env_int("XCONV_EXPAND_OG", og);
         const dim3 grid((unsigned)tiles, (unsigned)ceil_div(K2, og));
         if (og == 9)
-            hipLaunchKernelGGL(expand_kernel<9>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn);
+            hipLaunchKernelGGL(expand_kernel<9>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn, dw_dtype);
         else if (og == 3)
-            hipLaunchKernelGGL(expand_kernel<3>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn);
+            hipLaunchKernelGGL(expand_kernel<3>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn, dw_dtype);
         else
             hipLaunchKernelGGL(expand_kernel<1>, dim3((unsigned)tiles, (unsigned)K2), dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP,
-                               P.C_out, C_in, r, NTN, nn);
+                               P.C_out, C_in, r, NTN, nn, dw_dtype);
     } else {
         const long long total = (long long)P.C_out * C_in * K2;
         hipLaunchKernelGGL(untile_kernel, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, T, dW, K2,
-                           P.JP, P.MP, P.C_out, C_in);
+                           P.JP, P.MP, P.C_out, C_in, dw_dtype);
     }
     return hipGetLastError();
 }

@@ -73,13 +73,14 @@ hipError_t launch_reduce_raw(const float *part, float *T, int S, int E4, hipStre
 // gradient, the transposed store, straight into dW [C_out, C_in, nsets*K2].  reduce_expand_fused says whether this launch applies (otherwise launch_reduce
 // followed by launch_expand do the same in two).
 bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in, int r, int dist, int nsets = 1);
-hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, float *dW, int C_in, int r, bool nnz_norm, int dist,
-                                uint64_t seed, int nsets, hipStream_t st);
+// dw_dtype: storage type dW is rounded to (XCONV_F32: stored as it is)
+hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
+                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype = XCONV_F32);
 // dW[m,n,o] = (1/r) * sum_j Z[n,j] * T[o,j,m]   (Z != nullptr)
 // dW[m,n,o] = T[o,n,m]                          (Z == nullptr, exact path)
 // T != nullptr: K2 tiles [K2, JP, MP] are read from there (volumetric layers: kD * kH * kW offsets).
-hipError_t launch_expand(const CorrParams &P, const float *Z, float *dW, int C_in, int r, hipStream_t st, bool nnz_norm = false,
-                         const float *T = nullptr, int K2 = 0);
+hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm = false,
+                         const float *T = nullptr, int K2 = 0, int dw_dtype = XCONV_F32);
 
 
 // corr_ws_kernels.hip: producer/consumer variant for 16-bit storage.  plan_corr_ws returns
@@ -104,6 +105,10 @@ hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st);
 size_t conv_ws_bytes(const xconv_desc *d, int transposed);
 hipError_t launch_conv(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out, void *ws,
                        hipStream_t st);
+
+// bias_kernels.hip: db[m] = sum of dY over images and positions, rounded to the storage type; part: bias_ws_bytes(C) bytes
+size_t bias_ws_bytes(int C);
+hipError_t launch_bias_grad(int dtype, const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st);
 
 // pixel_kernels.hip: Xbar[b, j] = sum_k X[b, k] Zimg[j, k] (forward product of the pixel x channel probes)
 bool pixel_fwd_ok(int dtype, long long K, const void *X);

@@ -373,13 +373,15 @@ xconv_status xconv_probe_fwd(const xconv_desc *d, const void *X_dev, void *Xt_de
     return probe_impl(d, d->H * d->W, d->H * d->W, SliceMap{}, X_dev, Xt_dev, Z_dev, ws_dev, ws_bytes, static_cast<hipStream_t>(stream));
 }
 
-xconv_status xconv_dw_estimate(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, float *dW_dev,
-                               void *ws_dev, size_t ws_bytes, void *stream)
+// dw_dtype: the type dW is rounded to
+static xconv_status estimate_impl(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, void *dW_dev, int dw_dtype,
+                                  void *ws_dev, size_t ws_bytes, void *stream)
 {
     xconv_status s = xconv_check_desc(d);
     if (s != XCONV_OK) return s;
     if (!dY_dev || !Xt_dev || !dW_dev || !ws_dev) return XCONV_EINVAL;
-    if (!aligned16(Xt_dev) || !aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_dev) & 3u) != 0) return XCONV_EINVAL;
+    if (dw_dtype < XCONV_F32 || dw_dtype > XCONV_F16) return XCONV_EINVAL;
+    if (!aligned16(Xt_dev) || !aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_dev) & (elem_bytes(dw_dtype) - 1)) != 0) return XCONV_EINVAL;
     if (!aligned16(dY_dev)) return XCONV_EINVAL;
     if (!Z_dev && d->probe == XCONV_USER_Z) return XCONV_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -428,11 +430,43 @@ xconv_status xconv_dw_estimate(const xconv_desc *d, const void *dY_dev, const vo
         XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
     }
     if (fused) {
-        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, Z, false, dW_dev, d->C_in, d->r, d->keep_q15 != 0, probe_code(d), d->seed, 1, st));
+        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, Z, false, dW_dev, d->C_in, d->r, d->keep_q15 != 0, probe_code(d), d->seed, 1, st, dw_dtype));
         return XCONV_OK;
     }
     XC_LAUNCH(K_REDUCE, st, launch_reduce(P, st, zw, d->C_in * d->r, probe_code(d), d->seed));
-    XC_LAUNCH(K_EXPAND, st, launch_expand(P, Z, dW_dev, d->C_in, d->r, st, d->keep_q15 != 0));
+    XC_LAUNCH(K_EXPAND, st, launch_expand(P, Z, dW_dev, d->C_in, d->r, st, d->keep_q15 != 0, nullptr, 0, dw_dtype));
+    return XCONV_OK;
+}
+
+xconv_status xconv_dw_estimate(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, float *dW_dev,
+                               void *ws_dev, size_t ws_bytes, void *stream)
+{
+    return estimate_impl(d, dY_dev, Xt_dev, Z_dev, dW_dev, XCONV_F32, ws_dev, ws_bytes, stream);
+}
+
+xconv_status xconv_dw_estimate_as(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, void *dW_dev, int dw_dtype,
+                                  void *ws_dev, size_t ws_bytes, void *stream)
+{
+    return estimate_impl(d, dY_dev, Xt_dev, Z_dev, dW_dev, dw_dtype, ws_dev, ws_bytes, stream);
+}
+
+size_t xconv_bias_workspace_bytes(const xconv_desc *d)
+{
+    if (xconv_check_desc(d) != XCONV_OK) return 0;
+    return bias_ws_bytes(d->C_out);
+}
+
+xconv_status xconv_bias_grad(const xconv_desc *d, const void *dY_dev, void *db_dev, void *ws_dev, size_t ws_bytes, void *stream)
+{
+    xconv_status s = xconv_check_desc(d);
+    if (s != XCONV_OK) return s;
+    if (!dY_dev || !db_dev || !ws_dev) return XCONV_EINVAL;
+    const uintptr_t em = elem_bytes(d->dtype) - 1;
+    if ((reinterpret_cast<uintptr_t>(dY_dev) & em) || (reinterpret_cast<uintptr_t>(db_dev) & em) || !aligned16(ws_dev)) return XCONV_EINVAL;
+    if (ws_bytes < bias_ws_bytes(d->C_out)) return XCONV_EWORKSPACE;
+    const int Ho = out_extent(d->H, d->kH, d->stride_h, d->pad_h), Wo = out_extent(d->W, d->kW, d->stride_w, d->pad_w);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    XC_LAUNCH(K_BIAS, st, launch_bias_grad(d->dtype, dY_dev, static_cast<float *>(ws_dev), db_dev, d->B, d->C_out, Ho * Wo, d->layout == XCONV_NHWC, st));
     return XCONV_OK;
 }
 
@@ -490,14 +524,14 @@ namespace {
 
 // Exact-gradient path.  A_ready != nullptr: the activation is already channels-last [B, H, W, C_in rounded up
 // to 16] with zero pad columns (X_dev is then ignored and may be null).
-xconv_status exact_impl(const xconv_desc *d, const void *dY_dev, const void *X_dev, const void *A_ready, float *dW_dev, void *ws_dev,
-                        size_t ws_bytes, void *stream)
+xconv_status exact_impl(const xconv_desc *d, const void *dY_dev, const void *X_dev, const void *A_ready, void *dW_dev, void *ws_dev,
+                        size_t ws_bytes, void *stream, int dw_dtype = XCONV_F32)
 {
     xconv_status s = xconv_check_desc(d);
     if (s != XCONV_OK) return s;
     if (A_ready) X_dev = A_ready;
     if (!dY_dev || !X_dev || !dW_dev || !ws_dev) return XCONV_EINVAL;
-    if (!aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_dev) & 3u) != 0) return XCONV_EINVAL;
+    if (!aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_dev) & (elem_bytes(dw_dtype) - 1)) != 0) return XCONV_EINVAL;
     const size_t eb = elem_bytes(d->dtype);
     if (!aligned16(dY_dev) || (reinterpret_cast<uintptr_t>(X_dev) & (eb - 1)) != 0) return XCONV_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -541,11 +575,11 @@ xconv_status exact_impl(const xconv_desc *d, const void *dY_dev, const void *X_d
         XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
     }
     if (reduce_expand_fused(P, false, true, d->C_in, d->r, 0)) {
-        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, nullptr, true, dW_dev, d->C_in, d->r, false, 0, 0, 1, st));
+        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, nullptr, true, dW_dev, d->C_in, d->r, false, 0, 0, 1, st, dw_dtype));
         return XCONV_OK;
     }
     XC_LAUNCH(K_REDUCE, st, launch_reduce(P, st));
-    XC_LAUNCH(K_EXPAND, st, launch_expand(P, nullptr, dW_dev, d->C_in, d->r, st));
+    XC_LAUNCH(K_EXPAND, st, launch_expand(P, nullptr, dW_dev, d->C_in, d->r, st, false, nullptr, 0, dw_dtype));
     return XCONV_OK;
 }
 
@@ -1001,14 +1035,17 @@ xconv_status pixel_probe_fwd(const xconv_desc *d, bool indep, const void *X_dev,
     return xconv_dw_exact(&g.fwd, X_dev, ws, Xbar_dev, ws + g.zimg_f, ws_bytes - g.zimg_f, stream);
 }
 
-xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_dev, const float *Xbar_dev, float *dW_dev,
-                               void *ws_dev, size_t ws_bytes, void *stream)
+// dw_dtype other than fp32: multi-channel probing with dense vectors only (the other modes work on dW after it is written)
+xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_dev, const float *Xbar_dev, void *dW_out,
+                               void *ws_dev, size_t ws_bytes, void *stream, int dw_dtype = XCONV_F32)
 {
     PixelGeom g;
     xconv_status s = pixel_geom(d, indep, g);
     if (s != XCONV_OK) return s;
-    if (!dY_dev || !Xbar_dev || !dW_dev || !ws_dev) return XCONV_EINVAL;
-    if (!aligned16(dY_dev) || !aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_dev) & 3u) != 0 ||
+    if (!dY_dev || !Xbar_dev || !dW_out || !ws_dev || dw_dtype < XCONV_F32 || dw_dtype > XCONV_F16) return XCONV_EINVAL;
+    if (dw_dtype != XCONV_F32 && (indep || d->keep_q15 != 0)) return XCONV_EUNSUPPORTED;
+    float *dW_dev = static_cast<float *>(dW_out);
+    if (!aligned16(dY_dev) || !aligned16(ws_dev) || (reinterpret_cast<uintptr_t>(dW_out) & (elem_bytes(dw_dtype) - 1)) != 0 ||
         (reinterpret_cast<uintptr_t>(Xbar_dev) & 3u) != 0)
         return XCONV_EINVAL;
     const size_t need = pixel_workspace_bytes(d, indep, XCONV_OP_ESTIMATE);
@@ -1061,7 +1098,7 @@ xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_d
     if (s != XCONV_OK) return s;
     XC_LAUNCH(K_REPACK, st, launch_to_nchw(d->dtype, lt, l, 1, g.CS, (int)g.P, (int)g.P, st));
     // dw_i = tr(L T_{-k(i)} Z) (Alg. 1 backward step 4; the factor 1/r is already in L)
-    s = exact_impl(&g.bwd, l, nullptr, zimg, dW_dev, xws, xws_bytes, stream);
+    s = exact_impl(&g.bwd, l, nullptr, zimg, dW_out, xws, xws_bytes, stream, dw_dtype);
     if (s != XCONV_OK || d->keep_q15 == 0) return s;
     // block-sparse probes: 1/nnz(Z_n) per input channel in place of the 1/r that L carries (Eq. (8))
     XC_LAUNCH(K_SCALE, st, launch_nnz_rescale(dW_dev, d->C_out, d->C_in, d->kH * d->kW, d->r, probe_code(d), d->seed, st));
@@ -1081,6 +1118,11 @@ xconv_status xconv_pixel_dw_estimate(const xconv_desc *d, const void *dY_dev, co
                                      size_t ws_bytes, void *stream)
 {
     return pixel_dw_estimate(d, false, dY_dev, Xbar_dev, dW_dev, ws_dev, ws_bytes, stream);
+}
+xconv_status xconv_pixel_dw_estimate_as(const xconv_desc *d, const void *dY_dev, const float *Xbar_dev, void *dW_dev, int dw_dtype,
+                                        void *ws_dev, size_t ws_bytes, void *stream)
+{
+    return pixel_dw_estimate(d, false, dY_dev, Xbar_dev, dW_dev, ws_dev, ws_bytes, stream, dw_dtype);
 }
 
 size_t xconv_pixel_indep_xbar_bytes(const xconv_desc *d) { return pixel_xbar_bytes(d, true); }
@@ -1173,7 +1215,8 @@ const char *xconv_prof_kernel_name(int id)
     case K_UNPACK: return "unpack_kernel";
     case K_REPACK: return "repack_planes_kernel";
     case K_PACK_Z: return "pack_z_kernel";
-    case K_CONV: return "conv_gemm_kernel";
+    case K_CONV: return "conv_kernel";
+    case K_BIAS: return "bias_grad_kernel";
     case K_ZERO_GAPS: return "zero_gap_slices_kernel";
     case K_GEN_ZIMG: return "gen_zimg_kernel";
     case K_SCALE: return "scale_kernel";

@@ -7,9 +7,9 @@ instead of the input X it stores the probe output, r/C_in of X for probes over t
 (mode "channel"), B*r numbers for probes over pixels and channels (mode "multi", Eq. (6)), B*C_in*r
 for independent probing (mode "independent"); the weight gradient then comes from the matching
 estimate entry point of the library.  For 2-D layers the forward convolution and the input gradient
-are exact and run on the library's own kernels as well (xconv_conv_fwd, xconv_dx_exact;
-engine="library", the default), or on the framework's operators (engine="framework"); the bias is
-added, and its gradient summed, by the framework.  Volumetric layers use the framework's forward
+are exact and run on the library's own kernels as well (xconv_conv_fwd_ws with the bias, xconv_dx_exact_ws,
+xconv_bias_grad; engine="library", the default), or on the framework's operators (engine="framework").  The
+steps of a 2-D layer or a SignReLU are one native call each per pass (csrc/torch_glue.cpp).  Volumetric layers use the framework's forward
 convolution and input gradient.
 
 Z is drawn from a seed that changes with every forward call (Algorithm 1: seed and probing matrix
@@ -23,6 +23,7 @@ import torch.nn.functional as F
 from . import binding as xb
 
 MODES = ("channel", "multi", "independent")
+_MODE_CODE = {m: i for i, m in enumerate(MODES)}
 _DTYPE = {torch.float32: "f32", torch.bfloat16: "bf16", torch.float16: "f16"}
 _calls = itertools.count(1)
 
@@ -36,115 +37,72 @@ def _aligned(t):
     return t if t.data_ptr() % 16 == 0 else t.clone(memory_format=torch.preserve_format)
 
 
-def _layout_of(x):
-    """(layout code, tensor whose memory is in that layout)."""
-    if x.is_contiguous():
-        return xb.XCONV_NCHW, _aligned(x)
-    if x.is_contiguous(memory_format=torch.channels_last):
-        return xb.XCONV_NHWC, _aligned(x)
-    return xb.XCONV_NCHW, x.contiguous()
-
-
-def _as_layout(t, layout):
-    if layout == xb.XCONV_NHWC:
-        return _aligned(t.contiguous(memory_format=torch.channels_last))
-    return _aligned(t.contiguous())
-
-
 def _library_conv_ok(x, weight):
     return x.is_cuda and x.dtype in _DTYPE and weight.dtype == x.dtype and weight.device == x.device
 
 
-def _empty_like_layout(shape, dtype, device, layout):
-    return torch.empty(shape, dtype=dtype, device=device,
-                       memory_format=torch.channels_last if layout == xb.XCONV_NHWC else torch.contiguous_format)
+_glue_module = None
+
+
+def _glue():
+    """The layers' native host path (csrc/torch_glue.cpp), bound to the library that binding.py has loaded."""
+    global _glue_module
+    if _glue_module is None:
+        xb.lib()
+        try:
+            from . import _torch_glue
+        except ImportError as e:
+            raise RuntimeError("_torch_glue.so is not built or does not match this torch (%s). Run `python -m paper_2106_06998_amd.build`; "
+                               "there is no fallback path." % e)
+        _torch_glue.init(xb.LIB_PATH, xb.XConvError)
+        _glue_module = _torch_glue
+    return _glue_module
+
+
+def _raw_stream(t):
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 class _XConvFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, bias, stride, padding, r, probe, mode, seed, engine):
-        ctx.own = engine == "library" and _library_conv_ok(x, weight)
-        if ctx.own:
-            # forward convolution on the library's kernel (Alg. 1 forward step 1)
-            lay, xs0 = _layout_of(x.detach())
-            B, C_in, H, W = x.shape
-            d0 = xb.make_desc(B, C_in, weight.shape[0], H, W, tuple(weight.shape[2:]), stride, padding, 1, _DTYPE[x.dtype],
-                              "rademacher", 0, lay)
-            Ho = (H + 2 * padding[0] - weight.shape[2]) // stride[0] + 1
-            Wo = (W + 2 * padding[1] - weight.shape[3]) // stride[1] + 1
-            y = _empty_like_layout((B, weight.shape[0], Ho, Wo), x.dtype, x.device, lay)
-            with torch.cuda.device(x.device):
-                xb.xconv_conv_fwd_ws(d0, xs0, weight.detach().contiguous(), None if bias is None else bias.detach().contiguous(), y,
-                                     xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d0, 0), x.device))
+        own = engine == "library" and _library_conv_ok(x, weight)
+        estimate = weight.requires_grad
+        # forward convolution on the library's kernel (Alg. 1 forward step 1), or the framework's
+        y = None if own else F.conv2d(x, weight, bias, stride, padding)
+        if estimate:
+            if not x.is_cuda:
+                raise RuntimeError("XConv2d: the estimator runs on the GPU only (input on %s)" % x.device)
+            if x.dtype not in _DTYPE:
+                raise RuntimeError("XConv2d: storage type %s is not supported (float32, bfloat16, float16)" % x.dtype)
+        ctx.own, ctx.has_state, ctx.has_bias = own, estimate, bias is not None
+        ctx.stride, ctx.padding, ctx.x_shape, ctx.x_dtype, ctx.mode = stride, padding, x.shape, x.dtype, _MODE_CODE[mode]
+        if own or estimate:
+            yl, state, ctx.desc = _glue().forward(x, weight, bias, stride[0], stride[1], padding[0], padding[1], r, xb.PROBES[probe],
+                                                  ctx.mode, seed, own, estimate, _raw_stream(x))
+            if own:
+                y = yl
+        if estimate:
+            ctx.save_for_backward(weight, state)
         else:
-            y = F.conv2d(x, weight, bias, stride, padding)
-        ctx.has_state = False
-        ctx.stride, ctx.padding, ctx.x_shape = stride, padding, x.shape
-        ctx.has_bias = bias is not None
-        if not weight.requires_grad:
             ctx.save_for_backward(weight)
-            return y
-        if not x.is_cuda:
-            raise RuntimeError("XConv2d: the estimator runs on the GPU only (input on %s)" % x.device)
-        if x.dtype not in _DTYPE:
-            raise RuntimeError("XConv2d: storage type %s is not supported (float32, bfloat16, float16)" % x.dtype)
-        layout, xs = _layout_of(x.detach())
-        B, C_in, H, W = x.shape
-        d = xb.make_desc(B, C_in, weight.shape[0], H, W, tuple(weight.shape[2:]), stride, padding, r, _DTYPE[x.dtype], probe,
-                         seed, layout)
-        dev = x.device
-        with torch.cuda.device(dev):
-            if mode == "channel":
-                if xb.xconv_xt_bytes(d) == 0 or xb.xconv_workspace_bytes(d, xb.XCONV_OP_ESTIMATE) == 0:
-                    raise RuntimeError("XConv2d: layer not supported by the library (%s, r=%d)" % (tuple(x.shape), r))
-                state = xb.alloc_bytes(xb.xconv_xt_bytes(d), dev)
-                xb.xconv_probe_fwd(d, xs, state, None, xb.alloc_bytes(xb.xconv_workspace_bytes(d, xb.XCONV_OP_PROBE), dev))
-            else:
-                indep = mode == "independent"
-                nbytes = (xb.xconv_pixel_indep_xbar_bytes if indep else xb.xconv_pixel_xbar_bytes)(d)
-                wbytes = (xb.xconv_pixel_indep_workspace_bytes if indep else xb.xconv_pixel_workspace_bytes)(d, xb.XCONV_OP_PROBE)
-                if nbytes == 0 or wbytes == 0:
-                    raise RuntimeError("XConv2d: layer not supported in mode %r (%s, r=%d)" % (mode, tuple(x.shape), r))
-                state = torch.empty(nbytes // 4, dtype=torch.float32, device=dev)
-                (xb.xconv_pixel_indep_probe_fwd if indep else xb.xconv_pixel_probe_fwd)(d, xs, state, xb.alloc_bytes(wbytes, dev))
-        ctx.save_for_backward(weight, state)
-        ctx.has_state, ctx.desc, ctx.mode, ctx.layout, ctx.x_dtype = True, d, mode, layout, x.dtype
         return y
 
     @staticmethod
     def backward(ctx, dy):
         saved = ctx.saved_tensors
         weight = saved[0]
+        want_dx, want_dw, want_db = ctx.needs_input_grad[0], ctx.has_state and ctx.needs_input_grad[1], ctx.has_bias and ctx.needs_input_grad[2]
+        native = dy.is_cuda and dy.dtype in _DTYPE
+        # exact input gradient (Sec. 2: backpropagation through the layer stays exact) and bias gradient on the library's kernels
+        own_dx, own_db = want_dx and ctx.own and dy.dtype == weight.dtype, want_db and native and (ctx.own or ctx.has_state)
         dx = dw = db = None
-        if ctx.needs_input_grad[0]:
-            if ctx.own and dy.dtype == weight.dtype:
-                # exact input gradient on the library's kernel (Sec. 2: backpropagation through the layer stays exact)
-                lay, dys0 = _layout_of(dy.detach())
-                B, C_in, H, W = ctx.x_shape
-                d0 = xb.make_desc(B, C_in, weight.shape[0], H, W, tuple(weight.shape[2:]), ctx.stride, ctx.padding, 1,
-                                  _DTYPE[dy.dtype], "rademacher", 0, lay)
-                dx = _empty_like_layout(tuple(ctx.x_shape), dy.dtype, dy.device, lay)
-                with torch.cuda.device(dy.device):
-                    xb.xconv_dx_exact_ws(d0, dys0, weight.detach().contiguous(), dx,
-                                         xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d0, 1), dy.device))
-            else:
-                dx = torch.nn.grad.conv2d_input(ctx.x_shape, weight, dy, stride=ctx.stride, padding=ctx.padding)
-        if ctx.has_state and ctx.needs_input_grad[1]:
-            state, d, dev = saved[1], ctx.desc, dy.device
-            dys = _as_layout(dy.to(ctx.x_dtype), ctx.layout)
-            dw32 = torch.empty(weight.shape, dtype=torch.float32, device=dev)
-            with torch.cuda.device(dev):
-                if ctx.mode == "channel":
-                    ws = xb.alloc_bytes(xb.xconv_workspace_bytes(d, xb.XCONV_OP_ESTIMATE), dev)
-                    xb.xconv_dw_estimate(d, dys, state, None, dw32, ws)
-                elif ctx.mode == "multi":
-                    ws = xb.alloc_bytes(xb.xconv_pixel_workspace_bytes(d, xb.XCONV_OP_ESTIMATE), dev)
-                    xb.xconv_pixel_dw_estimate(d, dys, state, dw32, ws)
-                else:
-                    ws = xb.alloc_bytes(xb.xconv_pixel_indep_workspace_bytes(d, xb.XCONV_OP_ESTIMATE), dev)
-                    xb.xconv_pixel_indep_dw_estimate(d, dys, state, dw32, ws)
-            dw = dw32.to(weight.dtype)
-        if ctx.has_bias and ctx.needs_input_grad[2]:
+        if own_dx or want_dw or own_db:
+            dx, dw, db = _glue().backward(dy, weight, saved[1] if want_dw else None, ctx.desc, ctx.mode, own_dx, want_dw, own_db,
+                                          _raw_stream(dy))
+        if want_dx and not own_dx:
+            dx = torch.nn.grad.conv2d_input(ctx.x_shape, weight, dy, stride=ctx.stride, padding=ctx.padding)
+        if want_db and not own_db:
             db = dy.sum(dim=(0, 2, 3))
         return dx, dw, db, None, None, None, None, None, None, None
 
@@ -193,31 +151,16 @@ class _SignReLUFunction(torch.autograd.Function):
             raise RuntimeError("SignReLU: runs on the GPU only (input on %s)" % x.device)
         if x.dtype not in _DTYPE:
             raise RuntimeError("SignReLU: storage type %s is not supported (float32, bfloat16, float16)" % x.dtype)
-        # values in memory order: the mask is per element, whatever the layout
-        xs = x.detach()
-        if not (xs.is_contiguous() or xs.is_contiguous(memory_format=torch.channels_last)
-                or (xs.dim() == 5 and xs.is_contiguous(memory_format=torch.channels_last_3d))):
-            xs = xs.contiguous()
-        xs = _aligned(xs)
-        y = torch.empty_like(xs)          # same strides as xs
-        n = xs.numel()
-        mask = torch.empty(max(xb.xconv_relu_mask_bytes(n) // 8, 1), dtype=torch.int64, device=x.device)
-        with torch.cuda.device(x.device):
-            xb.xconv_relu_fwd(_DTYPE[x.dtype], xs, y, mask, n)
+        y, mask = _glue().relu_forward(x, _raw_stream(x))
         ctx.save_for_backward(mask)
-        ctx.meta = (tuple(y.shape), tuple(y.stride()), y.dtype)     # not y itself: nothing but the mask is kept
+        ctx.meta = (tuple(y.shape), y.stride(), xb.DTYPES[_DTYPE[y.dtype]])     # not y itself: nothing but the mask is kept
         return y
 
     @staticmethod
     def backward(ctx, dy):
         (mask,) = ctx.saved_tensors
         shape, strides, dtype = ctx.meta
-        # the gradient in the memory order of the output
-        g = torch.empty_strided(shape, strides, dtype=dtype, device=dy.device)
-        g.copy_(dy)
-        with torch.cuda.device(g.device):
-            xb.xconv_relu_bwd(_DTYPE[g.dtype], g, mask, g, g.numel())
-        return g
+        return _glue().relu_backward(dy, mask, shape, strides, dtype, _raw_stream(dy))
 
 
 class SignReLU(torch.nn.Module):
