@@ -298,6 +298,38 @@ constexpr int kConvSubs = 4;    // classes of output positions per launch
 // 16-byte entries of a list of k-steps (four steps each, one more that only prefetches touch)
 __host__ __device__ inline int conv_step_list(int taps, int steps_per_tap) { return (taps * steps_per_tap + 3) / 4 + 1; }
 
+// Quotients by a number the host knows: one multiplication and a shift (n < 2^31).  For d >= 2 and l = ceil(log2 d),
+// m = floor(2^(31+l) / d) + 1 < 2^32 gives floor(n / d) = floor(n m / 2^(31+l)); d = 1 passes n through.
+struct FastDiv {
+    uint32_t m, pass;
+    int sh, d;
+    __host__ __device__ int div(int n) const
+    {
+#ifdef __HIP_DEVICE_COMPILE__
+        return (int)((__umulhi((uint32_t)n, m) + ((uint32_t)n & pass)) >> sh);
+#else
+        return n / d;
+#endif
+    }
+    __host__ __device__ void divmod(int n, int &q, int &r) const
+    {
+        q = div(n);
+        r = n - q * d;
+    }
+};
+inline FastDiv fast_div(int d)
+{
+    FastDiv f{0, ~0u, 0, d < 1 ? 1 : d};
+    if (f.d > 1) {
+        int l = 1;
+        while ((1LL << l) < f.d) ++l;
+        f.m = (uint32_t)((1ull << (31 + l)) / (unsigned)f.d + 1);
+        f.pass = 0;
+        f.sh = l - 1;
+    }
+    return f;
+}
+
 // One class of output positions: an ordinary convolution with its own taps.  The forward convolution is one class; the
 // input gradient of a strided layer is sh*sw of them (output positions by their remainder modulo the stride).
 struct ConvSub {
@@ -308,6 +340,7 @@ struct ConvSub {
     int SW, TPS, TU;           // columns per strip, tiles per strip, positions per tile
     int sth, stw;              // staged rows (columns) per output row (column): min(stride, taps)
     int PWv, PH, PWs, NPOS, NPPmax;   // staging tasks per patch row, columns per remainder class, LDS positions per row and in all, tasks per unit
+    FastDiv dSW, dHo, dHV, dPWv, dTPS, dkW;   // quotients by SW, Ho, staged rows of a whole image, PWv, TPS, kW
     int wg0;                   // first workgroup of the class
     long long w0;              // first 16-byte unit of its packed weights
 };
@@ -326,6 +359,7 @@ struct ConvParams {
     int in_sc, in_sy, in_sx, out_sc, out_sy, out_sx;      // channel, row, column
     int w_sco, w_sci;                                     // weights: output channel of the product, contraction channel
     int MT, NT, WM;    // 32-row tiles and 32-column tiles per wave, waves along the output channels
+    FastDiv dNMT, dks, dksl;   // quotients by NMT and by the k-steps per tap of a full and of the last chunk
     int NMT, NMB;      // tiles of output channels, blocks of 32 packed output channels
     int vec, swap, big;   // how the input is read, which side of the accumulator the channels are on, 64-bit addresses
     int pair;             // 16-bit outputs: neighbouring positions (channels-last: channels) share an aligned 4-byte word

@@ -96,9 +96,9 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
     const ConvSub &S = P.sub[cls];
     id -= S.wg0;
-    const int mtile = id % P.NMT;
-    id /= P.NMT;
-    const int strip = id / S.TPS, tile = id - strip * S.TPS;
+    int mtile, strip, tile;
+    P.dNMT.divmod(id, id, mtile);
+    S.dTPS.divmod(id, strip, tile);
 
     const int WN = 4 / P.WM, wm = wave % P.WM, wn = wave / P.WM;
     const int TN = 32 * NT * WN;
@@ -113,15 +113,13 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     uint4 *alds = stab;                                                         // !PACKED: [2][KS][MT * WM][64] weight fragments of a tap
 
     // ---- the tile: positions q0 .. q0 + TU - 1 of this strip (TU < TN where the patch of TN would not fit into LDS), rows R0 .. R1 counted over the batch
-    const int TU = S.TU;
-    const uint32_t q0 = (uint32_t)tile * (uint32_t)TU;       // below 2^31 (host)
-    const int NR = P.B * S.Ho;
-    const int R0 = (int)(q0 / (uint32_t)S.SW);
-    const int x0 = (int)(q0 - (uint32_t)R0 * (uint32_t)S.SW);
-    int R1 = R0 + (x0 + TU - 1) / S.SW;
+    const int TU = S.TU, NR = P.B * S.Ho;
+    int R0, x0, b0, oyA;
+    S.dSW.divmod(tile * TU, R0, x0);       // tile * TU below 2^31 (host)
+    int R1 = R0 + S.dSW.div(x0 + TU - 1);
     R1 = R1 < NR - 1 ? R1 : NR - 1;
-    const int b0 = R0 / S.Ho, oyA = R0 - b0 * S.Ho;
-    const int b1 = R1 / S.Ho;
+    S.dHo.divmod(R0, b0, oyA);
+    const int b1 = S.dHo.div(R1);
     const int HV = (S.Ho - 1) * S.sth + S.kH;                                   // staged rows of a whole image
     const int NPR = (R1 - R0) * S.sth + (b1 - b0) * (S.kH - S.sth) + S.kH;      // staged rows of this tile
     const int xs = strip * S.SW * P.sw - S.pw;                                  // source column of patch column `xa`
@@ -129,16 +127,10 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int npp = S.kH > 0 ? NPR * S.PWv : 0;   // a class without taps stages nothing
 
     {
-        const float rp = frcp(S.PWv), rh = frcp(HV), rs = frcp(S.SW), ro = frcp(S.Ho);
-        // image and row of row n of a stack of images of d rows (n < d + the rows of a tile)
-        auto image_row = [](int n, int d, float rd, int &img, int &row) {
-            if (d < (1 << 21)) fast_divmod(n, d, rd, img, row);
-            else { img = n >= d ? 1 : 0; row = n - img * d; }
-        };
         for (int pp = tid; pp < npp; pp += kThreads) {
             int prow, pc, bi, l;
-            fast_divmod(pp, S.PWv, rp, prow, pc);
-            image_row(oyA * S.sth + prow, HV, rh, bi, l);
+            S.dPWv.divmod(pp, prow, pc);
+            S.dHV.divmod(oyA * S.sth + prow, bi, l);
             const int c = pc * VW;
             const int iy = (S.kH >= P.sh ? l : (l / S.kH) * P.sh + l % S.kH) - S.ph;
             const int ix = xs - xa + (S.kW >= P.sw ? c : (c / S.kW) * P.sw + c % S.kW);
@@ -153,9 +145,9 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         }
         for (int n = tid; n < TN; n += kThreads) {
             int dr, x, bi, oy;
-            fast_divmod(x0 + n, S.SW, rs, dr, x);
+            S.dSW.divmod(x0 + n, dr, x);
             const int row = R0 + dr, ox = strip * S.SW + x;
-            image_row(oyA + dr, S.Ho, ro, bi, oy);
+            S.dHo.divmod(oyA + dr, bi, oy);
             const bool in_batch = row < NR && n < TU, ok = in_batch && ox < S.Wo;
             const uint32_t off = (uint32_t)bi * (uint32_t)P.out_sb + (uint32_t)(S.oy0 + oy * P.osy) * (uint32_t)P.out_sy +
                                  (uint32_t)(S.ox0 + ox * P.osx) * (uint32_t)P.out_sx;
@@ -177,8 +169,11 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         int *t = reinterpret_cast<int *>(stab);
         const int cap = conv_step_list(taps, RES ? nks : KS) * 4;
         for (int i = tid; i < (RES ? cap : 2 * cap); i += kThreads) {
-            const int list = i >= cap ? 1 : 0, k = i - list * cap, per = list ? nks_last : RES ? nks : KS, tap = k / per, ky = tap / S.kW;
-            t[i] = k < taps * per ? (tap_offset(ky, tap - ky * S.kW) + 2 * (k - tap * per) * S.NPOS) * 16 : 0;
+            const int list = i >= cap ? 1 : 0, k = i - list * cap;
+            int tap, ks, ky, kx;
+            (list ? P.dksl : P.dks).divmod(k, tap, ks);
+            S.dkW.divmod(tap, ky, kx);
+            t[i] = tap < taps ? (tap_offset(ky, kx) + 2 * ks * S.NPOS) * 16 : 0;
         }
     }
     __syncthreads();

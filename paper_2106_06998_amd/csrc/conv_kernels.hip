@@ -1,10 +1,13 @@
 // Host side of the forward convolution and the exact input gradient: classes of output positions, tiles, launches
 // (the kernels are in conv_core.h).
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "common.h"
@@ -24,6 +27,22 @@ namespace {
 constexpr int kLdsMax = 160 * 1024;
 constexpr long long kMaxPos = 1LL << 30;       // positions over the batch in one launch (32-bit tile arithmetic)
 
+// see expected_cycles
+constexpr struct {
+    double e24, e22, e12, e11;   // share of the 16-bit matrix rate of the wave tiles (MT, NT)
+    double ef32;                 // ... of the fp32 rate
+    double task;                 // cycles per staging task
+    double in_bpc, out_bpc;      // bytes per cycle and compute unit
+    double chunk, overlap;       // k-steps per overlapping step, how completely steps overlap
+    double start;                // cycles per round
+    double alone, pair;          // surcharges for one and two workgroups per unit
+} kConvModel = {0.58, 0.465, 0.55, 0.575, 1.0, 367, 30.7, 15.1, 16, 0.634, 13900, 1.5, 0.145};
+
+int env_value(const char *name)
+{
+    const char *e = getenv(name);
+    return e ? atoi(e) : 0;
+}
 int units_elems(int dtype) { return dtype == XCONV_F32 ? 4 : 8; }
 int elem_size(int dtype) { return dtype == XCONV_F32 ? 4 : 2; }
 
@@ -81,95 +100,135 @@ long long conv_lds(const ConvParams &P, const ConvSub &c, int TN, int nks)
            (P.res ? conv_step_list(taps, nks) : 2 * conv_step_list(taps, kConvUnits / 2)) * 16;
 }
 
-// Strips and LDS extents of a class for tiles of TN positions: the strip width with the least work in all (products for
-// positions of ragged tiles and strips, staging of the halo).  Returns the cost per launch in cycles of one compute unit.
-double plan_sub(ConvSub &s, const ConvParams &P, int TN, double mma_clk, int nks, int lds_max)
+// What a launch has to do, summed over its workgroups
+struct Work {
+    double mma = 0;        // 32x32 fragment pairs per wave
+    double tasks = 0;      // staging tasks per thread
+    double in = 0, out = 0;   // bytes of the cache lines touched (a strip narrower than the image uses lines partly)
+    long long wgs = 0;
+    int lds = 0;
+};
+
+// Lays one class out for tiles of TU of the TN positions on nst strips and adds up its work; false when the patch does not fit.
+bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN, int lds_extra, Work &w)
 {
-    const int VW = P.vec == 1 ? 2 : 1;
-    const int taps = s.kH * s.kW;
-    double best = -1;
-    // fewer positions per tile only where the patch of a full tile does not fit (large strides or kernels on narrow images)
-    for (int TU = TN; TU >= 1 && best < 0; TU /= 2) {
-        ConvSub bs = s;
-        for (int nst = 1; nst <= s.Wo; ++nst) {
-            const int SW = ceil_div(s.Wo, nst);
-            if (nst > 1 && SW < 8 && TU == TN) break;
-            if (nst > 1 && ceil_div(s.Wo, SW) != nst) continue;
-            ConvSub c = s;
-            c.SW = SW;
-            c.TU = TU;
-            c.sth = std::max(1, std::min(P.sh, s.kH));
-            c.stw = std::max(1, std::min(P.sw, s.kW));
-            const long long NR = (long long)P.B * s.Ho;
-            const int nr = (int)std::min<long long>((SW + TU - 2) / SW + 1, NR);
-            const int nb = std::min(nr >= 2 ? (nr - 2) / s.Ho + 1 : 0, P.B - 1);
-            const int NPR = std::max(1, (nr - 1) * c.sth + nb * std::max(0, s.kH - c.sth) + s.kH);
-            const int PWl = (SW - 1) * c.stw + s.kW + (VW - 1);
-            c.PWv = std::max(1, ceil_div(PWl, VW));
-            c.PH = ceil_div(c.PWv * VW, c.stw);
-            c.PWs = c.stw * c.PH;
-            c.NPOS = round_up(NPR * c.PWs, 16);
-            c.NPPmax = NPR * c.PWv;
-            c.TPS = (int)((NR * SW + TU - 1) / TU);
-            if (conv_lds(P, c, TN, nks) > lds_max || c.NPOS > 65535) continue;
-            const double ntask = (double)c.NPPmax * 2 * nks / kThreads;
-            const double cost = (double)nst * c.TPS * (taps * nks * mma_clk + ntask * 120.0 + 2500.0);
-            if (best < 0 || cost < best) { best = cost; bs = c; }
-        }
-        s = bs;
+    const int es = elem_size(dtype), nks = ksteps(dtype, P.Cin), VW = P.vec == 1 ? 2 : 1;
+    const int taps = s.kH * s.kW, SW = ceil_div(s.Wo, std::min(nst, s.Wo));
+    s.SW = SW;
+    s.TU = TU;
+    s.sth = std::max(1, std::min(P.sh, s.kH));
+    s.stw = std::max(1, std::min(P.sw, s.kW));
+    const long long NR = (long long)P.B * s.Ho;
+    const bool rows = TU % SW == 0;              // tiles begin at the start of a row
+    const int nr = (int)std::min<long long>(rows ? TU / SW : (SW + TU - 2) / SW + 1, NR);
+    const int nb = rows && s.Ho % nr == 0 ? 0 : std::min(nr >= 2 ? (nr - 2) / s.Ho + 1 : 0, P.B - 1);
+    const int NPR = std::max(1, (nr - 1) * s.sth + nb * std::max(0, s.kH - s.sth) + s.kH);
+    const int PWl = (SW - 1) * s.stw + s.kW + (VW - 1);
+    s.PWv = std::max(1, ceil_div(PWl, VW));
+    s.PH = ceil_div(s.PWv * VW, s.stw);
+    s.PWs = s.stw * s.PH;
+    s.NPOS = round_up(NPR * s.PWs, 16);
+    s.NPPmax = NPR * s.PWv;
+    s.TPS = (int)((NR * SW + TU - 1) / TU);
+    const long long lds = conv_lds(P, s, TN, nks) + lds_extra;
+    if (lds > kLdsMax || s.NPOS > 65535) return false;
+    const double n = (double)ceil_div(s.Wo, SW) * s.TPS * P.NMT;
+    const int TM = std::min(32 * P.MT * P.WM, P.Cout);
+    const bool cl = P.swap;
+    const double in_row = cl ? (double)PWl * P.Cin * es : nst == 1 ? (double)P.Wi * es : PWl * es + 64.0;
+    const double out_row = cl ? (double)TU * TM * es : nst == 1 ? TU * es + 32.0 : (double)nr * (SW * es + 48.0);
+    w.mma += n * taps * nks * P.MT * P.NT;
+    if (taps) {
+        w.tasks += n * s.NPPmax * 2.0 * nks / kThreads;
+        w.in += n * NPR * in_row * (cl ? 1 : P.Cin);
     }
-    return best;
+    w.out += n * out_row * (cl ? 1 : TM);
+    w.wgs += (long long)n;
+    w.lds = std::max(w.lds, (int)lds);
+    return true;
 }
 
-struct Shape { int MT, NT; double eff; };
-// wave tiles of the kernel, with the share of the matrix rate each was measured at on large layers (16-bit storage)
-const Shape kShapes[] = {{2, 4, 0.60}, {2, 2, 0.45}, {1, 2, 0.33}, {1, 1, 0.22}};
+// Expected cycles of a launch.  The matrix instructions of the busiest compute unit and its staging and stores (issue or memory,
+// whichever is slower) overlap where the unit has several workgroups in turn or a workgroup has several chunks; each round of
+// workgroups pays a start-up.  The constants are a fit to the measured times of 3300 tile configurations of 60 products (fp32
+// and 16-bit, both layouts, 1x1 to 5x5, strides 1 and 2); picking by them costs 1 % against the best configuration of each.
+double expected_cycles(const ConvParams &P, int dtype, const Work &w, int ncu)
+{
+    const int shape = P.MT * 10 + P.NT, nks = ksteps(dtype, P.Cin);
+    const double eff = shape == 24 ? kConvModel.e24 : shape == 22 ? kConvModel.e22 : shape == 12 ? kConvModel.e12 : kConvModel.e11;
+    const double clk = dtype == XCONV_F32 ? 256.0 / kConvModel.ef32 : 32.0 / eff;
+    const int occ = std::max(1, std::min(kLdsMax / w.lds, P.MT * P.NT >= 8 || !P.wp ? 2 : P.MT * P.NT >= 4 ? 3 : 4));
+    const double q = (double)((w.wgs + ncu - 1) / ncu), rounds = (double)((w.wgs + (long long)ncu * occ - 1) / ((long long)ncu * occ));
+    const double tm = w.mma / w.wgs * clk * q;
+    const double ts = std::max(w.tasks / w.wgs * kConvModel.task * q, w.in / ncu / kConvModel.in_bpc) + w.out / ncu / kConvModel.out_bpc;
+    const double steps = rounds * (P.res ? 1.0 : std::max(1.0, nks / kConvModel.chunk));
+    double t = kConvModel.start * rounds + std::max(tm, ts) + std::min(tm, ts) / std::pow(steps, kConvModel.overlap);
+    if (occ == 1) t += kConvModel.alone * ts;
+    if (occ == 2) t += kConvModel.pair * tm;
+    return t;
+}
 
 bool plan(ConvParams &P, int dtype, int ncu)
 {
-    int force = 0, force_wm = 0;
-    if (const char *e = getenv("XCONV_CONV_SHAPE")) force = atoi(e);
-    if (const char *e = getenv("XCONV_CONV_WM")) force_wm = atoi(e);
+    const int force = env_value("XCONV_CONV_SHAPE"), force_wm = env_value("XCONV_CONV_WM");
+    const int force_strips = env_value("XCONV_CONV_STRIPS"), force_rows = env_value("XCONV_CONV_ROWS");
     const int nks = ksteps(dtype, P.Cin);
+    int wide = 1;
+    for (int i = 0; i < P.nsub; ++i) wide = std::max(wide, P.sub[i].Wo);
     double best = -1;
     ConvParams bp = P;
-    for (const Shape &sh : kShapes)
-        for (int WM = 1; WM <= 4; WM *= 2) {
-            if (force && !P.big && (P.wp || force != 24) && sh.MT * 10 + sh.NT != force) continue;
-            if (force_wm && WM != force_wm) continue;
-            if (!P.wp && (sh.NT > 2 || 32 * sh.MT * WM > kConvGatherM)) continue;
-            if (P.big && sh.MT * sh.NT != 4) continue;
-            if (WM > 1 && 32 * sh.MT * (WM / 2) >= P.Cout) continue;         // half of the waves would have no channels
-            ConvParams C = P;
-            C.MT = sh.MT; C.NT = sh.NT; C.WM = WM;
-            const int extra = P.wp ? 0 : 2 * (kConvUnits / 2) * sh.MT * WM * 1024;   // LDS of the gathered weights
-            const int TM = 32 * sh.MT * WM, TN = 32 * sh.NT * (4 / WM);
-            C.NMT = ceil_div(P.Cout, TM);
-            // cycles of a wave's products of one k-step
-            const double per = sh.MT * sh.NT * (dtype == XCONV_F32 ? 256.0 / 0.85 : 32.0 / sh.eff);
-            double cost = 0;
-            long long nwg = 0;
-            int lds = 0;
-            bool ok = true;
-            for (int i = 0; i < P.nsub && ok; ++i) {
-                const double c = plan_sub(C.sub[i], C, TN, per, nks, kLdsMax - extra);
-                if (c < 0) { ok = false; break; }
-                cost += c * C.NMT;
-                C.sub[i].wg0 = (int)nwg;
-                nwg += (long long)ceil_div(C.sub[i].Wo, C.sub[i].SW) * C.sub[i].TPS * C.NMT;
-                lds = std::max(lds, (int)conv_lds(P, C.sub[i], TN, nks) + extra);
+    // tiles of TN positions or of whole rows only (fewer positions, but no partly used row and halo); only where no patch fits
+    // (large strides or kernels on narrow images), less
+    for (int part = 1; part <= 512 && best < 0; part *= 2)
+        for (const int shape : {24, 22, 12, 11})
+            for (int WM = 1; WM <= 4; WM *= 2) {
+                ConvParams C = P;
+                C.MT = shape / 10; C.NT = shape % 10; C.WM = WM;
+                const int TM = 32 * C.MT * WM, TN = 32 * C.NT * (4 / WM);
+                if (force && !P.big && (P.wp || force != 24) && shape != force) continue;
+                if (force_wm && WM != force_wm) continue;
+                if (!P.wp && (C.NT > 2 || TM > kConvGatherM)) continue;
+                if (P.big && shape != 22) continue;
+                if (WM > 1 && TM / 2 >= P.Cout) continue;                           // half of the waves would have no channels
+                if (TN / part < 1) continue;
+                C.NMT = ceil_div(P.Cout, TM);
+                const int extra = P.wp ? 0 : 2 * (kConvUnits / 2) * C.MT * WM * 1024;   // LDS of the gathered weights
+                for (int nst2 = 2; nst2 <= 2 * wide + 1; ++nst2) {
+                    const int nst = nst2 / 2, SW = ceil_div(wide, nst);
+                    int TU = TN / part;
+                    if (part == 1 && nst > 1 && SW < 8) break;
+                    if (nst > 1 && ceil_div(wide, SW) != nst) continue;
+                    if (force_strips && part == 1 && (nst != force_strips || (nst2 & 1) != force_rows)) continue;
+                    if (nst2 & 1) {
+                        if (TU % SW == 0 || SW > TU) continue;
+                        TU = TU / SW * SW;
+                    }
+                    Work w;
+                    bool fits = true;
+                    for (int i = 0; i < P.nsub && fits; ++i) {
+                        C.sub[i] = P.sub[i];
+                        C.sub[i].wg0 = (int)w.wgs;
+                        fits = lay_out(C.sub[i], C, dtype, nst, TU, TN, extra, w) && w.wgs < 0x3fffffff;
+                    }
+                    if (!fits) continue;
+                    const double t = expected_cycles(C, dtype, w, ncu);
+                    if (best >= 0 && t >= best) continue;
+                    best = t;
+                    bp = C;
+                    bp.nwg = (int)w.wgs;
+                    bp.lds_bytes = w.lds;
+                }
             }
-            if (!ok || nwg > 0x3fffffff) continue;
-            C.nwg = (int)nwg;
-            C.lds_bytes = lds;
-            // average workgroup times the workgroups of the busiest compute unit
-            const double rounds = (double)((nwg + ncu - 1) / ncu);
-            double t = cost / nwg * rounds;
-            if (rounds < 2 || lds > kLdsMax / 2) t *= 1.3;               // one wave per SIMD: its latencies are not covered
-            if (best < 0 || t < best) { best = t; bp = C; }
-        }
     if (best < 0) return false;
     P = bp;
+    P.dNMT = fast_div(P.NMT);
+    P.dks = fast_div(P.res ? nks : kConvUnits / 2);
+    P.dksl = fast_div(P.res ? nks : nks - (nks - 1) / (kConvUnits / 2) * (kConvUnits / 2));
+    for (int i = 0; i < P.nsub; ++i) {
+        ConvSub &s = P.sub[i];
+        s.dSW = fast_div(s.SW); s.dHo = fast_div(s.Ho); s.dHV = fast_div((s.Ho - 1) * s.sth + s.kH);
+        s.dPWv = fast_div(s.PWv); s.dTPS = fast_div(s.TPS); s.dkW = fast_div(s.kW);
+    }
     return true;
 }
 
@@ -193,12 +252,12 @@ struct ConvLaunch {
     bool pack;                // the weights of these classes are packed in front of it
 };
 struct ConvPlan {
-    int key[20];
     std::vector<ConvLaunch> launches;
 };
 std::mutex g_conv_mu;
-std::vector<std::shared_ptr<const ConvPlan>> g_conv_plans;   // the last 64 products, handed out by reference
-constexpr size_t kConvPlans = 64;
+// plans by their key (the raw integers), handed out by reference; emptied when a program has gone through very many shapes
+std::unordered_map<std::string, std::shared_ptr<const ConvPlan>> g_conv_plans;
+constexpr size_t kConvPlans = 4096;
 
 int device_cus()
 {
@@ -212,6 +271,13 @@ int device_cus()
 // align, oalign: alignment of the input and the output pointer in bytes, up to 16
 bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, int align, int oalign, int ncu)
 {
+    // a 1x1 convolution at unit stride knows no rows: one row of H*W positions per image
+    xconv_desc flat = *d;
+    if (d->kH == 1 && d->kW == 1 && d->stride_h == 1 && d->stride_w == 1 && d->pad_h == 0 && d->pad_w == 0) {
+        flat.W = d->H * d->W;
+        flat.H = 1;
+        d = &flat;
+    }
     const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
     const int es = elem_size(d->dtype), ue = units_elems(d->dtype);
     ConvParams P{};
@@ -277,21 +343,22 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
 
 std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, bool packed, int align, int oalign)
 {
-    const char *fs = getenv("XCONV_CONV_SHAPE"), *fw = getenv("XCONV_CONV_WM");   // overrides of tests and sweeps
     const int ncu = device_cus();
-    const int key[20] = {d->B, d->C_in, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dtype, d->layout,
-                         transposed, packed, align, ncu, fs ? atoi(fs) : 0, fw ? atoi(fw) : 0, oalign};
+    // (the overrides of tests and sweeps are part of the key)
+    const int key[24] = {d->B, d->C_in, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dtype, d->layout,
+                         transposed, packed, align, ncu, env_value("XCONV_CONV_SHAPE"), env_value("XCONV_CONV_WM"), oalign,
+                         env_value("XCONV_CONV_STRIPS"), env_value("XCONV_CONV_ROWS"), 0, 0};
+    const std::string k(reinterpret_cast<const char *>(key), sizeof(key));
     {
         std::lock_guard<std::mutex> lk(g_conv_mu);
-        for (const auto &p : g_conv_plans)
-            if (memcmp(p->key, key, sizeof(key)) == 0) return p;
+        const auto it = g_conv_plans.find(k);
+        if (it != g_conv_plans.end()) return it->second;
     }
     auto p = std::make_shared<ConvPlan>();
-    memcpy(p->key, key, sizeof(key));
     if (!make_plan(*p, d, transposed, packed, align, oalign, ncu)) return nullptr;
     std::lock_guard<std::mutex> lk(g_conv_mu);
-    if (g_conv_plans.size() >= kConvPlans) g_conv_plans.erase(g_conv_plans.begin());
-    g_conv_plans.push_back(p);
+    if (g_conv_plans.size() >= kConvPlans) g_conv_plans.clear();
+    g_conv_plans.emplace(k, p);
     return p;
 }
 
