@@ -234,6 +234,11 @@ struct CorrParams {
     float *zout;
     int nz, zdist;
     uint64_t zseed;
+    // Volumetric layers: kernel-depth offset `set` is a third extent of the grid and reads A that many bytes further on; its
+    // partial tiles follow those of the offset before.  One launch with nsets times fewer K-splits each in place of nsets
+    // launches: the start of a workgroup and the partial tiles are paid once for all of them.
+    int nsets, set_sd;
+    long long set_run, set_slice;   // bytes of a run of depth slices and of one slice (set_offset)
 };
 
 
@@ -265,7 +270,45 @@ struct WsParams {
     float *zout;
     int nz, zdist;
     uint64_t zseed;
+    int nsets, set_sd;      // kernel-depth offsets of the launch and where each finds its A (see CorrParams)
+    long long set_run, set_slice;
 };
+
+// (kernel-depth offset, offset group) of a workgroup: the third extent of the grid counts both
+__device__ inline void set_and_group(int nog, int &set, int &group)
+{
+    set = 0;
+    group = blockIdx.z;
+    while (group >= nog) {
+        group -= nog;
+        ++set;
+    }
+}
+
+// Bytes from A to the slices of kernel-depth offset `set`
+__device__ inline long long set_offset(int set, int sd, long long run, long long slice)
+{
+    long long off = 0;
+    while (set >= sd) { set -= sd; off += slice; }
+    return off + set * run;
+}
+
+// Number of K-splits: `target` workgroups or up to a quarter fewer, the count that leaves the fewest idle steps (ties go to the
+// smaller count: as many steps per workgroup, fewer partial tiles).  With several kernel-depth offsets per launch only whole
+// multiples of 8, which xcd_block needs.
+inline int choose_splits(int target, int NS, int nsets)
+{
+    target = target < 1 ? 1 : target;
+    target = target > NS ? NS : target;
+    const int step = nsets > 1 && target >= 16 ? 8 : 1;
+    int bestS = target / step * step;
+    double best_eff = 0.0;
+    for (int S = bestS; S >= 1 && S >= target * 3 / 4; S -= step) {
+        const double eff = (double)NS / ((double)S * ceil_div(NS, S)) * ((double)S / target);
+        if (eff > best_eff - 1e-9) { best_eff = eff > best_eff ? eff : best_eff; bestS = S; }
+    }
+    return bestS;
+}
 
 // Entries wg*threads + tid, + (workgroups * threads), ... of Z[s], drawn by the calling thread (Alg. 1 backward
 // step 2: the probing matrix is regenerated from the seed, never stored between the passes).

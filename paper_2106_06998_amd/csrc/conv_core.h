@@ -74,8 +74,10 @@ constexpr uint32_t kConvOob = 0x80000000u;   // byte offset past every buffer de
 // VEC: how a staging task reads `in`: 0 element by element (any strides), 1 pairs of columns (16-bit planes of even width),
 //      2 whole units (channels-last, channels a multiple of the unit).
 // SWAP: output positions in the rows of the accumulator tile (channels-last output: lanes along the channels), else in its columns.
+// MULTI: several classes in one launch (an index into the argument struct that is not a constant makes the compiler load every
+//      argument where it is used: a launch of one class does without).
 // PACKED: weights in fragment order.  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES>
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI>
 __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvParams P)
 {
     typedef typename ConvElem<DT>::t elem_t;
@@ -93,7 +95,9 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     int id = xcd_block(blockIdx.x, gridDim.x);
     if (id >= P.nwg) return;
     int cls = 0;
-    while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
+    if constexpr (MULTI) {
+        while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
+    }
     const ConvSub &S = P.sub[cls];
     id -= S.wg0;
     int mtile, strip, tile;
@@ -120,7 +124,6 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     R1 = R1 < NR - 1 ? R1 : NR - 1;
     S.dHo.divmod(R0, b0, oyA);
     const int b1 = S.dHo.div(R1);
-    const int HV = (S.Ho - 1) * S.sth + S.kH;                                   // staged rows of a whole image
     const int NPR = (R1 - R0) * S.sth + (b1 - b0) * (S.kH - S.sth) + S.kH;      // staged rows of this tile
     const int xs = strip * S.SW * P.sw - S.pw;                                  // source column of patch column `xa`
     const int xa = VW == 2 ? (xs & 1) : 0;
@@ -569,10 +572,10 @@ __global__ __launch_bounds__(kThreads) void conv_pack_kernel(const ConvParams P,
     }
 }
 
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false>
-static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI>
+static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
 {
-    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES>);
+    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI>);
     if (P.lds_bytes > 64 * 1024) {
         static bool attr_set[64] = {};   // per device; a repeated call only sets it again
         int dev = 0;
@@ -583,9 +586,16 @@ static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
             if (dev >= 0 && dev < 64) attr_set[dev] = true;
         }
     }
-    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
+    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
                        (unsigned)P.lds_bytes, st, P);
     return hipGetLastError();
+}
+
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false>
+static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
+{
+    if (P.nsub == 1) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, false>(P, st);
+    return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, true>(P, st);
 }
 
 template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const ConvParams &P, hipStream_t st)

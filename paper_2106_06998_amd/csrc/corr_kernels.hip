@@ -129,7 +129,8 @@ __device__ inline StepPos next_step(const CorrParams &P, StepPos s)
 // AL: every row segment of dY that a step stages starts on a 16-byte vector (W' and the
 // strip width are multiples of the vector length); the staging of dY then has fixed LDS
 // addresses per thread and needs no per-element predicates.
-template <int DT, int MT, int NA, int NB, int NOFF, bool AL>
+// SETS: the third extent of the grid also counts kernel-depth offsets (volumetric layers)
+template <int DT, int MT, int NA, int NB, int NOFF, bool AL, bool SETS>
 __global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) void corr_kernel(const CorrParams P)
 {
     draw_z_slice(P.zout, P.nz, P.zdist, P.zseed);
@@ -158,11 +159,13 @@ __global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) v
     fast_divmod((int)blockIdx.y, P.NTM, frcp(P.NTM), tj, tm);
     const int m0 = tm * P.M_WG;   // first output channel of the workgroup tile
     const int jb = tj * P.J_WG;   // first column of A of the workgroup tile
-    const int o_first = blockIdx.z * NOFF;
+    int set = 0, og = blockIdx.z;
+    if constexpr (SETS) set_and_group(P.NOG, set, og);
+    const int o_first = og * NOFF;
     const int noff = (P.K2 - o_first) < NOFF ? (P.K2 - o_first) : NOFF;
 
     const elem_t *dY = static_cast<const elem_t *>(P.dY);
-    const elem_t *Ag = static_cast<const elem_t *>(P.A);
+    const elem_t *Ag = reinterpret_cast<const elem_t *>(static_cast<const char *>(P.A) + (SETS ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
 
     // my share of the steps
     const int bx = xcd_block(blockIdx.x, gridDim.x);   // K-split of this workgroup: neighbouring splits on one die (C3: 32.0 -> 29.3 us: the rows of dY, 56 bytes, share cache lines with the rows of the neighbouring splits)
@@ -624,7 +627,7 @@ __global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) v
 #pragma unroll
         for (int o = 0; o < NOFF; ++o) {
             if (o < noff) {
-                float *dst = P.part + (size_t)bx * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + (wm * MT) * 16 + 4 * g, P.JP, P.MP);
+                float *dst = P.part + (size_t)(SETS ? set * P.S + bx : bx) * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + (wm * MT) * 16 + 4 * g, P.JP, P.MP);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<f32x4 *>(dst + (size_t)16 * mt * P.JP) = acc[mt][o];   // 16 rows = four channel quads
             }
@@ -634,7 +637,7 @@ __global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) v
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         ts_[6] = __builtin_amdgcn_s_memrealtime(); ts_[7] = __builtin_readcyclecounter();
         if (tid == 0 && t_begin < t_end) {
-            unsigned long long *d = reinterpret_cast<unsigned long long *>(P.part + (size_t)bx * P.K2 * P.JP * P.MP + tile_index(o_first, jb, m0, P.JP, P.MP));
+            unsigned long long *d = reinterpret_cast<unsigned long long *>(P.part + (size_t)(SETS ? set * P.S + bx : bx) * P.K2 * P.JP * P.MP + tile_index(o_first, jb, m0, P.JP, P.MP));
             for (int q = 0; q < 8; ++q) d[q] = ts_[q];
         }
     }
@@ -694,17 +697,17 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const f32x4 *
 // ---------------------------------------------------------------------------
 // nnz_norm: rows are scaled by 1 / nnz(Z_n), the number of non-zero entries of row n of Z (Eq. (8),
 // block-sparse probing vectors), instead of 1 / r; a row without any gives zeros.
-// one value of dW in the type the caller keeps its weights in (dt: an xconv_dtype, the same for the whole launch)
-__device__ inline void store_dw(void *dW, size_t i, float v, int dt)
+// one value of dW in the type the caller keeps its weights in
+template <int WT> __device__ inline void store_dw(void *dW, size_t i, float v)
 {
-    if (dt == XCONV_F32) static_cast<float *>(dW)[i] = v;
-    else static_cast<uint16_t *>(dW)[i] = dt == XCONV_BF16 ? f32_to_bf16_rne(v) : f32_to_f16_rne(v);
+    if constexpr (WT == XCONV_F32) static_cast<float *>(dW)[i] = v;
+    else static_cast<uint16_t *>(dW)[i] = f32_to_st16<WT>(v);
 }
 
-template <int OG>
+template <int OG, int WT>
 __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T, const float *__restrict__ Z,
                                                     void *__restrict__ dW, int K2, int JP, int MP, int C_out, int C_in, int r,
-                                                    int NTN, int nnz_norm, int dt)
+                                                    int NTN, int nnz_norm)
 {
     const int lane = threadIdx.x, l16 = lane & 15, g = lane >> 4;
     const int nt = blockIdx.x % NTN, mt = blockIdx.x / NTN;
@@ -754,7 +757,7 @@ __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T,
                 const size_t dst = ((size_t)m * C_in + ncol) * K2 + o0;
 #pragma unroll
                 for (int o = 0; o < OG; ++o)
-                    if (o0 + o < K2) store_dw(dW, dst + o, acc[o][v] * inv_r, dt);
+                    if (o0 + o < K2) store_dw<WT>(dW, dst + o, acc[o][v] * inv_r);
             }
         }
     }
@@ -817,8 +820,9 @@ template <int NC> __device__ inline f32x4 once_sum(const f32x4 *p, int first, in
 // kernel-depth offset), og = set * K2 + o, K2T = nsets * K2.  The grid's first extent is a multiple of 8, so
 // the workgroups that write the K2T offsets of one (m, n) run of dW share an L2, which merges their 4-byte stores.
 // ---------------------------------------------------------------------------
+template <int WT>
 __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__restrict__ part, void *__restrict__ dW, int S, int K2,
-                                                               int K2T, int JP, int MQ, int JC, int C_out, int C_in, int dt)
+                                                               int K2T, int JP, int MQ, int JC, int C_out, int C_in)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [JC], then the thread groups' sums [NG][NE] (few-element slabs only)
     const int tid = threadIdx.x;
@@ -849,7 +853,7 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
     for (int e = tid; e < JC * 4; e += kThreads) {
         const int mi = e & 3, j = e >> 2;
         const int m = 4 * mq + mi, n = j0 + j;
-        if (m < C_out && n < C_in) store_dw(dW, ((size_t)m * C_in + n) * K2T + og, slab[e], dt);
+        if (m < C_out && n < C_in) store_dw<WT>(dW, ((size_t)m * C_in + n) * K2T + og, slab[e]);
     }
 }
 
@@ -870,10 +874,10 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
 // ---------------------------------------------------------------------------
 constexpr int kP2Threads = 1024;
 
-template <int QW>
+template <int QW, int WT>
 __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__restrict__ part, const float *__restrict__ Z,
                                                                 void *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
-                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, int dt)
+                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [QW][JP], then the thread groups' sums [NG][NE] (few-element slabs only) and, after them, rows of Z [NR][ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -981,7 +985,7 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int m = 4 * (mg * QW + q4) + v;
-                    if (m < C_out) store_dw(dW, ((size_t)m * C_in + n) * K2T + og, acc[v] * inv_r, dt);
+                    if (m < C_out) store_dw<WT>(dW, ((size_t)m * C_in + n) * K2T + og, acc[v] * inv_r);
                 }
             }
         }
@@ -989,8 +993,9 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 }
 
 // Exact path: dW[m,n,o] = T[o,n,m] (a transpose of the reduced tile).
+template <int WT>
 __global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restrict__ T, void *__restrict__ dW, int K2, int JP,
-                                                          int MP, int C_out, int C_in, int dt)
+                                                          int MP, int C_out, int C_in)
 {
     const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
     const long long total = (long long)C_out * C_in * K2;
@@ -998,7 +1003,7 @@ __global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restric
     const int o = (int)(i % K2);
     const long long mn = i / K2;
     const int n = (int)(mn % C_in), m = (int)(mn / C_in);
-    store_dw(dW, (size_t)i, T[tile_index(o, n, m, JP, MP)], dt);
+    store_dw<WT>(dW, (size_t)i, T[tile_index(o, n, m, JP, MP)]);
 }
 
 // dY planes whose size is not a whole number of 16-byte vectors are copied once into planes
@@ -1107,7 +1112,7 @@ static bool geometry_fits(const CorrParams &P, int dtype, int MT)
 }
 
 bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
-               int CS, bool dy_aligned)
+               int CS, bool dy_aligned, int nsets)
 {
     const bool f32 = dtype == XCONV_F32;
     const int BI = f32 ? 1 : 8, EPV = f32 ? 4 : 8;
@@ -1177,20 +1182,13 @@ bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH,
     // K-split: fill the 256 compute units (two workgroups each when LDS allows)
     const size_t lds = lds_bytes_of(P, dtype, MT);
     const int per_cu = env_int("XCONV_CORR_WGS_PER_CU", lds <= 72 * 1024 ? 2 : 1);
-    const int ny = P.NTM * P.NTJ * P.NOG;
+    const int ny = P.NTM * P.NTJ * P.NOG * nsets;
     int target = env_int("XCONV_CORR_SPLITS", 0);
     if (target <= 0) {
         target = (256 * per_cu) / ny;
         if (target < 1) target = 1;
         if (target > P.NS) target = P.NS;
-        // prefer a split count that divides the steps evenly
-        int bestS = target;
-        double best_eff = 0.0;
-        for (int S = target; S >= 1 && S >= target * 3 / 4; --S) {
-            const double eff = (double)P.NS / ((double)S * ceil_div(P.NS, S)) * ((double)S / target);
-            if (eff > best_eff - 1e-9) { best_eff = eff > best_eff ? eff : best_eff; bestS = S; }   // (ties go to the smaller count: as many steps per workgroup, fewer partial tiles)
-        }
-        target = bestS;
+        target = choose_splits(target, P.NS, nsets);
     }
     if (target > P.NS) target = P.NS;
     if (target < 1) target = 1;
@@ -1206,14 +1204,14 @@ size_t corr_partial_bytes(const CorrParams &P)
     return ((size_t)P.S + 1) * P.K2 * P.JP * P.MP * sizeof(float);
 }
 
-template <int DT, int MT, int NA, int NB, int NOFF, bool AL>
-static hipError_t launch_corr_cfg(const CorrParams &P, size_t lds, hipStream_t st)
+template <int DT, int MT, int NA, int NB, int NOFF, bool AL, bool SETS>
+static hipError_t launch_corr_sets(const CorrParams &P, size_t lds, hipStream_t st)
 {
     if (lds > 64 * 1024) {
         static bool done = false;  // per instantiation: the attribute sticks to the function
         static size_t done_bytes = 0;
         if (!done || lds > done_bytes) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(corr_kernel<DT, MT, NA, NB, NOFF, AL>),
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(corr_kernel<DT, MT, NA, NB, NOFF, AL, SETS>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
             if (e != hipSuccess) return e;
             done = true;
@@ -1223,8 +1221,14 @@ static hipError_t launch_corr_cfg(const CorrParams &P, size_t lds, hipStream_t s
     CorrParams Q = P;
     Q.SQ = P.NS / P.S;
     Q.SR = P.NS % P.S;
-    hipLaunchKernelGGL((corr_kernel<DT, MT, NA, NB, NOFF, AL>), dim3(P.S, P.NTM * P.NTJ, P.NOG), dim3(kThreads), lds, st, Q);
+    hipLaunchKernelGGL((corr_kernel<DT, MT, NA, NB, NOFF, AL, SETS>), dim3(P.S, P.NTM * P.NTJ, P.NOG * (P.nsets > 1 ? P.nsets : 1)), dim3(kThreads), lds, st, Q);
     return hipGetLastError();
+}
+
+template <int DT, int MT, int NA, int NB, int NOFF, bool AL>
+static hipError_t launch_corr_cfg(const CorrParams &P, size_t lds, hipStream_t st)
+{
+    return P.nsets > 1 ? launch_corr_sets<DT, MT, NA, NB, NOFF, AL, true>(P, lds, st) : launch_corr_sets<DT, MT, NA, NB, NOFF, AL, false>(P, lds, st);
 }
 
 template <int DT, int MT, int NA, int NB> static hipError_t launch_corr_noff(const CorrParams &P, size_t lds, hipStream_t st)
@@ -1306,8 +1310,9 @@ bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in,
     return (long long)K2T * (MQ / (exact ? 1 : pass2_quads(MQ, K2T))) <= 256;
 }
 
-hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
-                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype)
+template <int WT>
+static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm,
+                                          int nsets, hipStream_t st)
 {
     const int MQ = P.MP / 4;
     const int K2T = nsets * P.K2;
@@ -1321,7 +1326,7 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
         const int NG = NE >= kThreads ? 1 : kThreads / NE;
         const size_t lds = (size_t)NE * 16 + (NG > 1 ? (size_t)NG * NE * 16 : 0);
         const dim3 grid((unsigned)round_up(MQ, 8), (unsigned)K2T, (unsigned)(P.JP / JC));
-        hipLaunchKernelGGL(pass2_exact_kernel, grid, dim3(kThreads), lds, st, part, dW, P.S, P.K2, K2T, P.JP, MQ, JC, P.C_out, C_in, dw_dtype);
+        hipLaunchKernelGGL(pass2_exact_kernel<WT>, grid, dim3(kThreads), lds, st, part, dW, P.S, P.K2, K2T, P.JP, MQ, JC, P.C_out, C_in);
     } else {
         int QW = env_int("XCONV_PASS2_QW", pass2_quads(MQ, K2T));
         if ((QW != 1 && QW != 2 && QW != 4) || MQ % QW != 0) QW = 1;
@@ -1339,13 +1344,13 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
     {                                                                                                                    \
         static bool done = false;                                                                                        \
         if (!done) {                                                                                                     \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pass2_mfma_kernel<Q>),                      \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pass2_mfma_kernel<Q, WT>),                      \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                  \
             if (e != hipSuccess) return e;                                                                               \
             done = true;                                                                                                 \
         }                                                                                                                \
-        hipLaunchKernelGGL(pass2_mfma_kernel<Q>, grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
-                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, dw_dtype);                                 \
+        hipLaunchKernelGGL((pass2_mfma_kernel<Q, WT>), grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
+                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS);                                           \
     }
         if (QW == 4) XC_P2M(4) else if (QW == 2) XC_P2M(2) else XC_P2M(1)
 #undef XC_P2M
@@ -1353,8 +1358,19 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
     return hipGetLastError();
 }
 
-hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
-                         const float *Tin, int K2in, int dw_dtype)
+hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
+                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype)
+{
+    (void)dist;
+    (void)seed;
+    if (dw_dtype == XCONV_BF16) return launch_reduce_expand_as<XCONV_BF16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
+    if (dw_dtype == XCONV_F16) return launch_reduce_expand_as<XCONV_F16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
+    return launch_reduce_expand_as<XCONV_F32>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
+}
+
+template <int WT>
+static hipError_t launch_expand_as(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
+                                   const float *Tin, int K2in)
 {
     const int nn = nnz_norm ? 1 : 0;
     const int K2 = K2in > 0 ? K2in : P.K2;
@@ -1367,18 +1383,26 @@ hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in
         og = env_int("XCONV_EXPAND_OG", og);
         const dim3 grid((unsigned)tiles, (unsigned)ceil_div(K2, og));
         if (og == 9)
-            hipLaunchKernelGGL(expand_kernel<9>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn, dw_dtype);
+            hipLaunchKernelGGL((expand_kernel<9, WT>), grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn);
         else if (og == 3)
-            hipLaunchKernelGGL(expand_kernel<3>, grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn, dw_dtype);
+            hipLaunchKernelGGL((expand_kernel<3, WT>), grid, dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP, P.C_out, C_in, r, NTN, nn);
         else
-            hipLaunchKernelGGL(expand_kernel<1>, dim3((unsigned)tiles, (unsigned)K2), dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP,
-                               P.C_out, C_in, r, NTN, nn, dw_dtype);
+            hipLaunchKernelGGL((expand_kernel<1, WT>), dim3((unsigned)tiles, (unsigned)K2), dim3(64), 0, st, T, Z, dW, K2, P.JP, P.MP,
+                               P.C_out, C_in, r, NTN, nn);
     } else {
         const long long total = (long long)P.C_out * C_in * K2;
-        hipLaunchKernelGGL(untile_kernel, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, T, dW, K2,
-                           P.JP, P.MP, P.C_out, C_in, dw_dtype);
+        hipLaunchKernelGGL(untile_kernel<WT>, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, T, dW, K2,
+                           P.JP, P.MP, P.C_out, C_in);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm, const float *Tin,
+                         int K2in, int dw_dtype)
+{
+    if (dw_dtype == XCONV_BF16) return launch_expand_as<XCONV_BF16>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
+    if (dw_dtype == XCONV_F16) return launch_expand_as<XCONV_F16>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
+    return launch_expand_as<XCONV_F32>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
 }
 
 }  // namespace xc

@@ -44,7 +44,9 @@ __global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const Ws
     fast_divmod((int)blockIdx.y, P.NTM, frcp(P.NTM), tj, tm);
     const int m0 = tm * P.M_WG;
     const int jb = tj * P.J_WG;
-    const int o_first = blockIdx.z * NOFF;
+    int set = 0, og = blockIdx.z;
+    if constexpr (VOL) set_and_group(P.NOG, set, og);
+    const int o_first = og * NOFF;
     const int noff = (P.K2 - o_first) < NOFF ? (P.K2 - o_first) : NOFF;
 
     // K-split of this workgroup: neighbouring splits on one die (C4: 97.5 -> 95.5 us), except for volumes read in place, whose
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const Ws
 #pragma unroll
         for (int o = 0; o < NOFF; ++o) {
             if (o < noff) {
-                float *dst = P.part + (size_t)bx * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + wm * 16 + 4 * g, P.JP, P.MP);
+                float *dst = P.part + (size_t)(VOL ? set * P.S + bx : bx) * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + wm * 16 + 4 * g, P.JP, P.MP);
                 *reinterpret_cast<f32x4 *>(dst) = acc[o];
             }
         }
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const Ws
         __builtin_amdgcn_s_setprio(0);
         const int p = tid - kProducers;
         const float *dY = static_cast<const float *>(P.dY);
-        const float *Ag = static_cast<const float *>(P.A);
+        const float *Ag = reinterpret_cast<const float *>(static_cast<const char *>(P.A) + (VOL ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
         const int HoWo = P.Ho * P.Wo;
         constexpr bool vol = VOL;
         // bytes between the planes of consecutive channels and between consecutive images of the batch
@@ -427,7 +429,7 @@ size_t corr_ws32_lds_bytes(const WsParams &P)
     return ((size_t)2 * P.a_units + (size_t)P.NRING * P.b_row_units) * 16;
 }
 
-bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS)
+bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets)
 {
     if (dtype != XCONV_F32) return false;
     if (ws32_env_int("XCONV_CORR_WS32", 1) == 0) return false;
@@ -497,7 +499,7 @@ bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int 
     P.NS = P.NBG * P.NSTRIP * P.Ho;
 
     // K-split: one workgroup per compute unit
-    const int ny = P.NTM * P.NTJ * P.NOG;
+    const int ny = P.NTM * P.NTJ * P.NOG * nsets;
     int target = ws32_env_int("XCONV_WS32_SPLITS", 0);
     if (target <= 0) {
         target = 256 * per_cu / ny;
@@ -506,15 +508,7 @@ bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int 
         // (C2, 2048 steps: 512 splits 33.1 + 10.7 us for correlation + second pass, 256 splits 32.3 + 9.7 us;
         // C4, 8192 steps: 95.2 against 103.7 us)
         if (per_cu == 2 && target >= 2 && P.NS / target < 8) target /= 2;
-        if (target < 1) target = 1;
-        if (target > P.NS) target = P.NS;
-        int bestS = target;
-        double best_eff = 0.0;
-        for (int S = target; S >= 1 && S >= target * 3 / 4; --S) {
-            const double eff = (double)P.NS / ((double)S * ceil_div(P.NS, S)) * ((double)S / target);
-            if (eff > best_eff - 1e-9) { best_eff = eff > best_eff ? eff : best_eff; bestS = S; }   // (ties go to the smaller count: as many steps per workgroup, fewer partial tiles)
-        }
-        target = bestS;
+        target = choose_splits(target, P.NS, nsets);
     }
     if (target > P.NS) target = P.NS;
     if (target < 1) target = 1;
@@ -535,7 +529,7 @@ template <int NTASK, int D, int OCC, bool VOL> static hipError_t launch_ws32_vol
     WsParams Q = P;
     Q.SQ = P.NS / P.S;
     Q.SR = P.NS % P.S;
-    hipLaunchKernelGGL((corr_ws32_kernel<9, NTASK, D, OCC, VOL>), dim3(P.S, P.NTM * P.NTJ, P.NOG), dim3(kWsThreads), lds, st, Q);
+    hipLaunchKernelGGL((corr_ws32_kernel<9, NTASK, D, OCC, VOL>), dim3(P.S, P.NTM * P.NTJ, P.NOG * (P.nsets > 1 ? P.nsets : 1)), dim3(kWsThreads), lds, st, Q);
     return hipGetLastError();
 }
 

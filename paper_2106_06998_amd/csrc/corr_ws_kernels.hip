@@ -64,7 +64,9 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const WsParams P)
     fast_divmod((int)blockIdx.y, P.NTM, frcp(P.NTM), tj, tm);
     const int m0 = tm * P.M_WG;
     const int jb = tj * P.J_WG;
-    const int o_first = blockIdx.z * NOFF;
+    int set = 0, og = blockIdx.z;
+    if constexpr (VOL) set_and_group(P.NOG, set, og);
+    const int o_first = og * NOFF;
     const int noff = (P.K2 - o_first) < NOFF ? (P.K2 - o_first) : NOFF;
 
     const int bx = xcd_block(blockIdx.x, gridDim.x);   // K-split of this workgroup: neighbouring splits on one die (V2: 37.2 -> 34.0 us per launch)
@@ -419,7 +421,7 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const WsParams P)
 #pragma unroll
         for (int o = 0; o < NOFF; ++o) {
             if (o < noff) {
-                float *dst = P.part + (size_t)bx * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + wm * 32 + 4 * g, P.JP, P.MP);
+                float *dst = P.part + (size_t)(VOL ? set * P.S + bx : bx) * P.K2 * P.JP * P.MP + tile_index(o_first + o, jcol, m0 + wm * 32 + 4 * g, P.JP, P.MP);
 #pragma unroll
                 for (int v = 0; v < 4; ++v)   // rows 8v + 4g ..: two channel quads further on
                     *reinterpret_cast<f32x4 *>(dst + (size_t)8 * v * P.JP) = f32x4{acc[o][4 * v], acc[o][4 * v + 1], acc[o][4 * v + 2], acc[o][4 * v + 3]};
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const WsParams P)
         __builtin_amdgcn_s_setprio(0);
         const int p = tid - kProducers;
         const uint16_t *dY = static_cast<const uint16_t *>(P.dY);
-        const uint16_t *Ag = static_cast<const uint16_t *>(P.A);
+        const uint16_t *Ag = reinterpret_cast<const uint16_t *>(static_cast<const char *>(P.A) + (VOL ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
         const int HoWo = P.Ho * P.Wo;
         constexpr bool vol = VOL;
         // bytes between the planes of consecutive channels and between consecutive images of the batch
@@ -814,7 +816,7 @@ static bool ws_geometry(WsParams &P, int CW, int NSUB)
     return true;
 }
 
-bool plan_corr_ws(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS)
+bool plan_corr_ws(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets)
 {
     if (dtype == XCONV_F32) return false;
     if (ws_env_int("XCONV_CORR_WS", 1) == 0) return false;
@@ -881,19 +883,11 @@ bool plan_corr_ws(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH
     if (!found) return false;
 
     // K-split: one workgroup per compute unit
-    const int ny = P.NTM * P.NTJ * P.NOG;
+    const int ny = P.NTM * P.NTJ * P.NOG * nsets;
     int target = ws_env_int("XCONV_WS_SPLITS", 0);
     if (target <= 0) {
         target = 256 / ny;
-        if (target < 1) target = 1;
-        if (target > P.NS) target = P.NS;
-        int bestS = target;
-        double best_eff = 0.0;
-        for (int S = target; S >= 1 && S >= target * 3 / 4; --S) {
-            const double eff = (double)P.NS / ((double)S * ceil_div(P.NS, S)) * ((double)S / target);
-            if (eff > best_eff - 1e-9) { best_eff = eff > best_eff ? eff : best_eff; bestS = S; }   // (ties go to the smaller count: as many steps per workgroup, fewer partial tiles)
-        }
-        target = bestS;
+        target = choose_splits(target, P.NS, nsets);
     }
     if (target > P.NS) target = P.NS;
     if (target < 1) target = 1;
@@ -915,7 +909,7 @@ static hipError_t launch_ws_vol(const WsParams &P, hipStream_t st)
     WsParams Q = P;
     Q.SQ = P.NS / P.S;
     Q.SR = P.NS % P.S;
-    hipLaunchKernelGGL((corr_ws_kernel<DT, 9, NTASK, D, CB, RU, VOL>), dim3(P.S, P.NTM * P.NTJ, P.NOG), dim3(kWsThreads), lds, st, Q);
+    hipLaunchKernelGGL((corr_ws_kernel<DT, 9, NTASK, D, CB, RU, VOL>), dim3(P.S, P.NTM * P.NTJ, P.NOG * (P.nsets > 1 ? P.nsets : 1)), dim3(kWsThreads), lds, st, Q);
     return hipGetLastError();
 }
 

@@ -57,7 +57,7 @@ hipError_t launch_pad_channels(int dtype, const void *src, void *out, long long 
 // probe/activation columns that carry data (r, or C_in on the exact path), CS
 // their padded stride.  Returns false when no launch shape fits the device.
 bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
-               int CS, bool dy_aligned);
+               int CS, bool dy_aligned, int nsets);   // nsets: kernel-depth offsets per launch (1: 2-D layers)
 size_t corr_partial_bytes(const CorrParams &P);
 size_t corr_lds_bytes(int dtype, const CorrParams &P);
 hipError_t launch_corr(int dtype, const CorrParams &P, hipStream_t st);
@@ -85,7 +85,7 @@ hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in
 
 // corr_ws_kernels.hip: producer/consumer variant for 16-bit storage.  plan_corr_ws returns
 // false when the layer does not fit it (the caller then uses plan_corr / launch_corr).
-bool plan_corr_ws(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS);
+bool plan_corr_ws(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets);
 size_t corr_ws_lds_bytes(const WsParams &P);
 hipError_t launch_corr_ws(int dtype, const WsParams &P, hipStream_t st);
 
@@ -96,7 +96,7 @@ size_t corr_row_lds_bytes(const WsParams &P);
 hipError_t launch_corr_row(int dtype, const WsParams &P, hipStream_t st);
 
 // corr_ws32_kernels.hip: the producer/consumer kernel for fp32 storage (same plan structure)
-bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS);
+bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets);
 size_t corr_ws32_lds_bytes(const WsParams &P);
 hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st);
 

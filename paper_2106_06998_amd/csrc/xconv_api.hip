@@ -94,12 +94,12 @@ int plan_override_hash()
     return (int)h;
 }
 
-// allow_row: the row-sweep kernel may be chosen (2-D layers; the volumetric entry points, which hand the kernels
-// depth slices through an offset table, keep to the kernels that know that table)
+// nsets > 0: kernel-depth offsets per launch.  2-D layers (nsets == 1 with plane == true) may take the row-sweep kernel; the
+// volumetric entry points, which hand the kernels depth slices through an offset table, keep to the kernels that know that table
 bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS,
-              bool dy_aligned, bool allow_row = true)
+              bool dy_aligned, int nsets = 1, bool plane = true)
 {
-    PlanKey k{{dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, (dy_aligned ? 1 : 0) | (allow_row ? 2 : 0), plan_override_hash()}};
+    PlanKey k{{dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, (dy_aligned ? 1 : 0) | (plane ? 2 : 0) | nsets << 2, plan_override_hash()}};
     {
         std::lock_guard<std::mutex> lk(g_plan_mu);
         for (const PlanEntry &e : g_plans)
@@ -113,9 +113,9 @@ bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH,
     e.P = CorrParams{};
     e.Wp = WsParams{};
     // the producer/consumer kernel reads dY in place, so the caller's planes must be usable as they are
-    e.ws = (dy_aligned && allow_row && plan_corr_row(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS)) ? 3 : 0;
-    if (!e.ws && dy_aligned && plan_corr_ws(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS)) e.ws = 1;
-    if (!e.ws && dy_aligned && plan_corr_ws32(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS)) e.ws = 2;
+    e.ws = (dy_aligned && plane && plan_corr_row(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS)) ? 3 : 0;
+    if (!e.ws && dy_aligned && plan_corr_ws(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets)) e.ws = 1;
+    if (!e.ws && dy_aligned && plan_corr_ws32(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets)) e.ws = 2;
     if (e.ws) {
         e.ok = true;
         e.P.C_out = C_out;
@@ -123,7 +123,7 @@ bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH,
         e.P.K2 = e.Wp.K2; e.P.JP = e.Wp.JP; e.P.MP = e.Wp.MP;
         e.P.Ho = e.Wp.Ho; e.P.Wo = e.Wp.Wo;
     } else {
-        e.ok = plan_corr(e.P, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, dy_aligned);
+        e.ok = plan_corr(e.P, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, dy_aligned, nsets);
     }
     out = e;
     std::lock_guard<std::mutex> lk(g_plan_mu);
@@ -344,8 +344,6 @@ bool vol_dy_in_place(const xconv3d_desc *v, const Vol &g, PlanEntry &E, const vo
 // scratch of the correlations of a volumetric layer: kD sets of S partial tiles, then the kD reduced tiles
 size_t vol_tile_bytes(const CorrParams &P) { return (size_t)P.K2 * P.JP * P.MP * sizeof(float); }
 size_t vol_partial_bytes(const CorrParams &P, int kD) { return align_up((size_t)kD * P.S * vol_tile_bytes(P), 256); }
-// first slice of Xt (or of X in slice form) that kernel-depth offset kz pairs with slice 0 of dY
-size_t vol_offset_slices(const Vol &g, int kz) { return (size_t)(kz % g.sd) * (size_t)g.run + (size_t)(kz / g.sd); }
 // plane pitch of the slice-major copy of dY for the kernel the plan selects
 int vol_dy_pitch(const xconv3d_desc *v, const PlanEntry &E)
 {
@@ -358,7 +356,47 @@ bool vol_plan(PlanEntry &E, const xconv3d_desc *v, int CS)
     const xconv_desc *d = &v->l;
     const Vol g = vol_of(v);
     if (g.B2 > 0x7fffffffLL) return false;
-    return get_plan(E, d->dtype, (int)g.B2, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CS, true, false);
+    return get_plan(E, d->dtype, (int)g.B2, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CS, true, v->kD, false);
+}
+
+// All kernel-depth offsets of a volumetric layer in one launch: offset kz pairs slice 0 of dY with slice kz / sd of run kz % sd
+// of A, and
+// writes its S partial tiles behind those of kz - 1
+xconv_status vol_correlate(PlanEntry &E, int dtype, const Vol &g, int kD, const void *A, size_t slice_bytes, float *part, hipStream_t st)
+{
+    CorrParams &P = E.P;
+    P.A = E.Wp.A = A;
+    P.part = E.Wp.part = part;
+    P.nsets = E.Wp.nsets = kD;
+    P.set_sd = E.Wp.set_sd = g.sd;
+    P.set_run = E.Wp.set_run = (long long)((size_t)g.run * slice_bytes);
+    P.set_slice = E.Wp.set_slice = (long long)slice_bytes;
+    E.Wp.dY = P.dY;
+    if (!E.ws) {
+        XC_LAUNCH(K_CORR, st, launch_corr(dtype, P, st));
+        return XCONV_OK;
+    }
+    if (E.Wp.vol_period == 0) {
+        // a slice-major copy of dY: the same table, every slice a volume of its own
+        const long long bytes = (long long)g.B2 * P.C_out * P.Ho * P.Wo * (long long)elem_bytes(dtype);
+        if (bytes <= (1LL << 30) && g.B2 < (1LL << 22)) {
+            E.Wp.vol_period = E.Wp.vol_Do = 1;
+            E.Wp.vol_bytes = (uint32_t)bytes;
+        }
+    }
+    if (E.Wp.vol_period != 0) {
+        XC_LAUNCH(K_CORR, st, launch_ws_plan(dtype, E, st));
+        return XCONV_OK;
+    }
+    // beyond the table's offsets: a launch per kernel-depth offset
+    E.Wp.nsets = 1;
+    for (int kz = 0; kz < kD; ++kz) {
+        E.Wp.A = static_cast<const char *>(A) + (size_t)(kz % g.sd) * g.run * slice_bytes + (size_t)(kz / g.sd) * slice_bytes;
+        E.Wp.part = part + (size_t)kz * P.S * (vol_tile_bytes(P) / sizeof(float));
+        XC_LAUNCH(K_CORR, st, launch_ws_plan(dtype, E, st));
+        E.Wp.zout = nullptr;
+    }
+    return XCONV_OK;
 }
 
 }  // namespace
@@ -776,24 +814,14 @@ xconv_status xconv3d_dw_estimate(const xconv3d_desc *v, const void *dY_dev, cons
     }
     float *part0 = reinterpret_cast<float *>(ws + zb);
     const bool fused = reduce_expand_fused(P, Z_dev != nullptr, false, d->C_in, d->r, probe_code(d), v->kD);
-    for (int kz = 0; kz < v->kD; ++kz) {
-        // (the first correlation launch also redraws Z[s] for the fused second pass)
-        P.zout = E.Wp.zout = (fused && zw && kz == 0) ? zw : nullptr;
+    if (fused && zw) {   // the correlation launch also redraws Z[s] for the fused second pass
+        P.zout = E.Wp.zout = zw;
         P.nz = E.Wp.nz = d->C_in * d->r;
         P.zdist = E.Wp.zdist = probe_code(d);
         P.zseed = E.Wp.zseed = d->seed;
-        const void *A = static_cast<const char *>(Xt_dev) + vol_offset_slices(g, kz) * g.slice_bytes;
-        P.A = A;
-        P.part = part0 + (size_t)kz * P.S * (tile / sizeof(float));
-        if (E.ws) {
-            E.Wp.dY = P.dY;
-            E.Wp.A = A;
-            E.Wp.part = P.part;
-            XC_LAUNCH(K_CORR, st, launch_ws_plan(d->dtype, E, st));
-        } else {
-            XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
-        }
     }
+    s = vol_correlate(E, d->dtype, g, v->kD, Xt_dev, g.slice_bytes, part0, st);
+    if (s != XCONV_OK) return s;
     // one reduction for all kernel-depth offsets; its spare workgroups redraw Z[s] for the expansion
     P.part = part0;
     if (fused) {
@@ -847,19 +875,8 @@ xconv_status xconv3d_dw_exact(const xconv3d_desc *v, const void *dY_dev, const v
         P.dY = dy_slices;
     }
     float *part0 = reinterpret_cast<float *>(ws + xb);
-    for (int kz = 0; kz < v->kD; ++kz) {
-        const void *A = ws + vol_offset_slices(g, kz) * xslice;
-        P.A = A;
-        P.part = part0 + (size_t)kz * P.S * (tile / sizeof(float));
-        if (E.ws) {
-            E.Wp.dY = P.dY;
-            E.Wp.A = A;
-            E.Wp.part = P.part;
-            XC_LAUNCH(K_CORR, st, launch_ws_plan(d->dtype, E, st));
-        } else {
-            XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
-        }
-    }
+    s = vol_correlate(E, d->dtype, g, v->kD, ws, xslice, part0, st);
+    if (s != XCONV_OK) return s;
     P.part = part0;
     if (reduce_expand_fused(P, false, true, d->C_in, d->r, 0)) {
         XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, nullptr, true, dW_dev, d->C_in, d->r, false, 0, 0, v->kD, st));
