@@ -296,6 +296,17 @@ xconv_status xconv_pixel_dw_estimate(const xconv_desc *desc, const void *dY_dev,
 xconv_status xconv_pixel_dw_estimate_as(const xconv_desc *desc, const void *dY_dev, const float *Xbar_dev,
                                         void *dW_dev, int dw_dtype, void *ws_dev, size_t ws_bytes, void *stream);
 
+/* The passes of a layer in one call each: forward = xconv_conv_fwd_ws and the probe of the mode (state_dev: Xt or Xbar);
+ * backward = weight-gradient estimate, input gradient (dX_dev null: not wanted) and bias gradient (db_dev null: not wanted).
+ * Results are those of the separate calls; the small launches among them are merged.  Z from the seed; keep_q15 = 0 for
+ * multi-channel probing with a 16-bit dw_dtype. */
+typedef enum { XCONV_LAYER_CHANNEL = 0, XCONV_LAYER_MULTI = 1 } xconv_layer_mode;
+size_t xconv_layer_workspace_bytes(const xconv_desc *desc, int mode, int backward);
+xconv_status xconv_layer_fwd(const xconv_desc *desc, int mode, const void *X_dev, const void *W_dev, const void *bias_dev,
+                             void *Y_dev, void *state_dev, void *ws_dev, size_t ws_bytes, void *stream);
+xconv_status xconv_layer_bwd(const xconv_desc *desc, int mode, const void *dY_dev, const void *W_dev, const void *state_dev,
+                             void *dX_dev, void *dW_dev, int dw_dtype, void *db_dev, void *ws_dev, size_t ws_bytes, void *stream);
+
 /* Independent probing (Sec. 3: trace estimation applied to every input/output channel
  * pair on its own, the alternative that the multi-channel case of Eq. (6) is set
  * against; the experiments' "Indep." curves): input channel n has r probing vectors of

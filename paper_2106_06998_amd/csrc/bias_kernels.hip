@@ -1,8 +1,8 @@
 // Bias gradient of a convolution layer: db[m] = sum_{b,oy,ox} dY[b,m,oy,ox], in fp32, rounded once to the storage type.
 // One streaming read of dY; bound by HBM.  Planes: a workgroup sums a piece of one channel's values (the channel's planes over
 // the batch counted as one run of vectors, S pieces so that about two workgroups per compute unit are resident); channels-last:
-// a workgroup sums a run of pixels, its threads along the channels.  S > 1: a second, tiny launch adds the pieces in order, so
-// the result does not depend on timing.
+// a workgroup sums a run of pixels, its threads along the channels.  S > 1: the pieces are added in order afterwards, so that
+// the result does not depend on timing, in the launch of the weight gradient's second pass or in one of their own.
 #include <algorithm>
 
 #include "common.h"
@@ -139,17 +139,6 @@ __global__ __launch_bounds__(kThreads) void bias_nhwc_kernel(const void *dY, flo
     }
 }
 
-template <int DT> __global__ __launch_bounds__(64) void bias_sum_kernel(const float *part, void *db, int C, int S)
-{
-    // one wave per channel: lanes take the pieces lane, lane + 64, ...
-    const int c = blockIdx.x, lane = threadIdx.x;
-    float s = 0.f;
-    for (int i = lane; i < S; i += 64) s += part[(size_t)i * C + c];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) bias_put<DT>(db, c, s);
-}
-
 // pieces of a channel's values (planes) or of the pixels (channels-last): enough workgroups for two per compute unit, pieces
 // of at least 32 KB
 int bias_pieces(long long bytes, int groups)
@@ -159,7 +148,7 @@ int bias_pieces(long long bytes, int groups)
 }
 
 template <int DT>
-hipError_t launch_bias_dt(const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st)
+hipError_t launch_bias_dt(const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st, SideJobs *J)
 {
     constexpr int V = DT == XCONV_F32 ? 4 : 8, ES = DT == XCONV_F32 ? 4 : 2;
     const bool al = (reinterpret_cast<uintptr_t>(dY) & 15u) == 0;
@@ -180,19 +169,24 @@ hipError_t launch_bias_dt(const void *dY, float *part, void *db, int B, int C, i
         if (vec) hipLaunchKernelGGL((bias_planes_kernel<DT, true>), dim3(C, S), dim3(kThreads), 0, st, dY, S > 1 ? part : nullptr, db, B, C, hwv, len);
         else hipLaunchKernelGGL((bias_planes_kernel<DT, false>), dim3(C, S), dim3(kThreads), 0, st, dY, S > 1 ? part : nullptr, db, B, C, hwv, len);
     }
-    if (S > 1) hipLaunchKernelGGL((bias_sum_kernel<DT>), dim3(C), dim3(64), 0, st, part, db, C, S);
-    return hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (S == 1 || e != hipSuccess) return e;
+    SideJobs alone{};
+    SideJobs &q = J ? *J : alone;
+    q.part = part; q.db = db; q.C = C; q.S = S; q.dtype = DT;
+    q.total += C;
+    return J ? hipSuccess : launch_side_jobs(alone, st);
 }
 
 }  // namespace
 
 size_t bias_ws_bytes(int C) { return (size_t)C * 1024 * sizeof(float); }
 
-hipError_t launch_bias_grad(int dtype, const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st)
+hipError_t launch_bias_grad(int dtype, const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st, SideJobs *J)
 {
-    if (dtype == XCONV_F32) return launch_bias_dt<XCONV_F32>(dY, part, db, B, C, HW, nhwc, st);
-    if (dtype == XCONV_BF16) return launch_bias_dt<XCONV_BF16>(dY, part, db, B, C, HW, nhwc, st);
-    return launch_bias_dt<XCONV_F16>(dY, part, db, B, C, HW, nhwc, st);
+    if (dtype == XCONV_F32) return launch_bias_dt<XCONV_F32>(dY, part, db, B, C, HW, nhwc, st, J);
+    if (dtype == XCONV_BF16) return launch_bias_dt<XCONV_BF16>(dY, part, db, B, C, HW, nhwc, st, J);
+    return launch_bias_dt<XCONV_F16>(dY, part, db, B, C, HW, nhwc, st, J);
 }
 
 }  // namespace xc

@@ -390,7 +390,7 @@ struct ConvSub {
 struct ConvParams {
     const void *in;    // activation-like tensor the contraction runs over (X, or dY for the input gradient)
     const void *w;     // weights [C_out, C_in, kH, kW] in the storage type
-    const void *wp;    // the same in fragment order (conv_pack_kernel), or null: fragments are gathered from w
+    const void *wp;    // the same in fragment order (side_jobs.h), or null: fragments are gathered from w
     const void *bias;  // per output channel in the storage type, or null
     void *out;         // Y, or dX
     int B, Cin, Cout;  // images, contraction channels and output channels of this product
@@ -410,6 +410,26 @@ struct ConvParams {
     int res;              // all channels of a patch resident
     int nsub, nwg, lds_bytes;
     ConvSub sub[kConvSubs];
+};
+
+// Small jobs that a launch carries along in workgroups of its own, in place of a launch each (4-6 us on the stream for work
+// of 1 us): the weights of a convolution in fragment order, and the sum of the pieces of a bias gradient.  The probe (forward)
+// and the second pass of the weight gradient (backward) carry them; the convolution that reads the weights follows.
+struct PackClass {
+    int kH, kW, ky0, kx0, kys, kxs;   // as in ConvSub
+    int n;                            // fragments (64 x 16 bytes)
+    long long w0;
+};
+struct SideJobs {
+    int total;                        // fragments and channels: one wave each
+    int nsub, NMB, Cin, Cout, w_sco, w_sci, kWfull;
+    int res, il, es;                  // resident patches, even and odd channels apart (conv_unit_channel), bytes per element
+    int C, S, dtype;                  // bias gradient: channels, pieces, storage type
+    const void *w;
+    void *packed;
+    const float *part;
+    void *db;
+    PackClass sub[kConvSubs];
 };
 
 }  // namespace xc

@@ -21,7 +21,7 @@
 //   !RES  chunks of kConvUnits units: the next chunk's patch is on its way through registers while the current one is multiplied
 //         (two LDS buffers, one barrier per chunk).
 // Strided layers keep the patch columns split by their remainder modulo the stride, so that the lanes' reads stay consecutive.
-// Weights come packed in fragment order (conv_pack_kernel, one coalesced kilobyte per fragment, read through the L1 by
+// Weights come packed in fragment order (pack_fragment, one coalesced kilobyte per fragment, read through the L1 by
 // every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, tap by tap.
 #pragma once
 #include <algorithm>
@@ -538,40 +538,6 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     }
 }
 
-// Weights in fragment order, [block of 32 output channels][chunk][tap][k-step][lane] of 16 bytes per class of taps (a chunk =
-// kConvUnits / 2 k-steps of channels, or all of them for resident patches); zero beyond the channels.  One thread per 16 bytes.
-template <int DT, bool IL>
-__global__ __launch_bounds__(kThreads) void conv_pack_kernel(const ConvParams P, uint4 *out)
-{
-    typedef typename ConvElem<DT>::t elem_t;
-    constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
-    const ConvSub &S = P.sub[blockIdx.y];
-    const int taps = S.kH * S.kW, nks = (P.Cin + 2 * UE - 1) / (2 * UE), nk = taps * nks;
-    const int cks = P.res ? nks : kConvUnits / 2;             // k-steps of a full chunk
-    const elem_t *w = static_cast<const elem_t *>(P.w);
-    const int lane = threadIdx.x & 63;
-    const long long n = (long long)P.NMB * nk;
-    for (long long i = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); i < n; i += (long long)gridDim.x * (kThreads / 64)) {
-        const int mb = (int)(i / nk), k = (int)(i - (long long)mb * nk);
-        const int ck = k / (taps * cks), r = k - ck * taps * cks;
-        const int per = min(cks, nks - ck * cks), tap = r / per, s = r - tap * per;
-        const int ky = tap / S.kW, kx = tap - ky * S.kW;
-        const int o = (S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs;
-        const int co = mb * 32 + (lane & 31), u = 2 * (ck * cks + s) + (lane >> 5);
-        const elem_t *src = w + (size_t)co * P.w_sco + o;
-        uint32_t v[UE];
-#pragma unroll
-        for (int e = 0; e < UE; ++e) {
-            const int c = conv_unit_channel<UE, IL>(u, e);
-            elem_t x = elem_t(0);
-            if (co < P.Cout && c < P.Cin) x = src[(size_t)c * P.w_sci];
-            v[e] = ES == 4 ? __builtin_bit_cast(uint32_t, (float)x) : (uint32_t)x;
-        }
-        if constexpr (ES == 4) out[S.w0 + i * 64 + lane] = uint4{v[0], v[1], v[2], v[3]};
-        else out[S.w0 + i * 64 + lane] = uint4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
-    }
-}
-
 template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI>
 static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
 {
@@ -630,20 +596,6 @@ template <int DT> static hipError_t launch_conv_dt(const ConvParams &P, hipStrea
     }
     if (P.vec == 2) return launch_conv_shape<DT, 2, true>(P, st);
     return P.swap ? launch_conv_shape<DT, 0, true>(P, st) : launch_conv_shape<DT, 0, false>(P, st);
-}
-
-template <int DT> static hipError_t launch_conv_pack_dt(const ConvParams &P, void *out, hipStream_t st)
-{
-    const int nks = ceil_div(P.Cin, 2 * ConvElem<DT>::UE);
-    long long n = 0;
-    for (int i = 0; i < P.nsub; ++i) n = std::max(n, (long long)P.NMB * nks * P.sub[i].kH * P.sub[i].kW);
-    if (n == 0) return hipSuccess;
-    const unsigned wgs = (unsigned)std::min<long long>((n + kThreads / 64 - 1) / (kThreads / 64), 8192);
-    if (DT == XCONV_F32 && P.vec != 2)
-        hipLaunchKernelGGL((conv_pack_kernel<DT, DT == XCONV_F32>), dim3(wgs, (unsigned)P.nsub), dim3(kThreads), 0, st, P, static_cast<uint4 *>(out));
-    else
-        hipLaunchKernelGGL((conv_pack_kernel<DT, false>), dim3(wgs, (unsigned)P.nsub), dim3(kThreads), 0, st, P, static_cast<uint4 *>(out));
-    return hipGetLastError();
 }
 
 }  // namespace xc

@@ -3,5 +3,4 @@
 
 namespace xc {
 hipError_t launch_conv_f16(const ConvParams &P, hipStream_t st) { return launch_conv_dt<XCONV_F16>(P, st); }
-hipError_t launch_conv_pack_f16(const ConvParams &P, void *out, hipStream_t st) { return launch_conv_pack_dt<XCONV_F16>(P, out, st); }
 }  // namespace xc

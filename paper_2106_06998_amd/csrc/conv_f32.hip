@@ -3,5 +3,4 @@
 
 namespace xc {
 hipError_t launch_conv_f32(const ConvParams &P, hipStream_t st) { return launch_conv_dt<XCONV_F32>(P, st); }
-hipError_t launch_conv_pack_f32(const ConvParams &P, void *out, hipStream_t st) { return launch_conv_pack_dt<XCONV_F32>(P, out, st); }
 }  // namespace xc

@@ -12,15 +12,13 @@
 
 #include "common.h"
 #include "launch.h"
+#include "side_jobs.h"
 
 namespace xc {
 
 hipError_t launch_conv_f32(const ConvParams &P, hipStream_t st);
 hipError_t launch_conv_bf16(const ConvParams &P, hipStream_t st);
 hipError_t launch_conv_f16(const ConvParams &P, hipStream_t st);
-hipError_t launch_conv_pack_f32(const ConvParams &P, void *out, hipStream_t st);
-hipError_t launch_conv_pack_bf16(const ConvParams &P, void *out, hipStream_t st);
-hipError_t launch_conv_pack_f16(const ConvParams &P, void *out, hipStream_t st);
 
 namespace {
 
@@ -243,8 +241,6 @@ size_t conv_ws_bytes(const xconv_desc *d, int transposed)
     return (size_t)n * 16 + kConvOverread;
 }
 
-namespace {
-
 // One launch of a product: a class group of a run of images.  The pointers of P are filled in per call.
 struct ConvLaunch {
     ConvParams P;
@@ -252,8 +248,12 @@ struct ConvLaunch {
     bool pack;                // the weights of these classes are packed in front of it
 };
 struct ConvPlan {
+    int dtype;
     std::vector<ConvLaunch> launches;
 };
+
+namespace {
+
 std::mutex g_conv_mu;
 // plans by their key (the raw integers), handed out by reference; emptied when a program has gone through very many shapes
 std::unordered_map<std::string, std::shared_ptr<const ConvPlan>> g_conv_plans;
@@ -355,6 +355,7 @@ std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, b
         if (it != g_conv_plans.end()) return it->second;
     }
     auto p = std::make_shared<ConvPlan>();
+    p->dtype = d->dtype;
     if (!make_plan(*p, d, transposed, packed, align, oalign, ncu)) return nullptr;
     std::lock_guard<std::mutex> lk(g_conv_mu);
     if (g_conv_plans.size() >= kConvPlans) g_conv_plans.clear();
@@ -364,25 +365,70 @@ std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, b
 
 }  // namespace
 
-hipError_t launch_conv(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out, void *ws,
-                       hipStream_t st)
+// the jobs alone in a launch
+__global__ __launch_bounds__(kThreads) void side_jobs_kernel(const SideJobs J) { side_jobs<0, kThreads>(J, blockIdx.x, gridDim.x); }
+
+hipError_t launch_side_jobs(const SideJobs &J, hipStream_t st)
+{
+    if (J.total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(side_jobs_kernel, dim3((unsigned)side_groups<kThreads>(&J)), dim3(kThreads), 0, st, J);
+    return hipGetLastError();
+}
+
+ConvPlanRef find_conv_plan(const xconv_desc *d, int transposed, const void *in, const void *out, bool packed)
 {
     const uintptr_t ia = reinterpret_cast<uintptr_t>(in);
-    const auto plan = conv_plan(d, transposed, ws != nullptr, ia % 16 == 0 ? 16 : ia % 4 == 0 ? 4 : 2, reinterpret_cast<uintptr_t>(out) % 4 == 0 ? 4 : 2);
-    if (!plan) return hipErrorInvalidConfiguration;
-    for (const ConvLaunch &L : plan->launches) {
+    return conv_plan(d, transposed, packed, ia % 16 == 0 ? 16 : ia % 4 == 0 ? 4 : 2, reinterpret_cast<uintptr_t>(out) % 4 == 0 ? 4 : 2);
+}
+
+// the packing of one launch's weights as a job
+static void add_pack_job(SideJobs &J, const ConvLaunch &L, int dtype, const void *w, void *ws)
+{
+    const ConvParams &P = L.P;
+    J.nsub = P.nsub;
+    J.NMB = P.NMB; J.Cin = P.Cin; J.Cout = P.Cout; J.w_sco = P.w_sco; J.w_sci = P.w_sci; J.kWfull = P.kWfull; J.res = P.res;
+    J.es = elem_size(dtype);
+    J.il = dtype == XCONV_F32 && P.vec != 2;
+    J.w = w;
+    J.packed = ws;
+    const int nks = ceil_div(P.Cin, 2 * units_elems(dtype));
+    for (int i = 0; i < P.nsub; ++i) {
+        const ConvSub &s = P.sub[i];
+        J.sub[i] = PackClass{s.kH, s.kW, s.ky0, s.kx0, s.kys, s.kxs, P.NMB * nks * s.kH * s.kW, s.w0};
+        J.total += J.sub[i].n;
+    }
+}
+
+bool conv_pack_job(const ConvPlan &plan, const void *w, void *ws, SideJobs &J)
+{
+    const ConvLaunch *one = nullptr;
+    for (const ConvLaunch &L : plan.launches) {
+        if (!L.pack) continue;
+        if (one) return false;      // more classes than a job holds
+        one = &L;
+    }
+    if (!one) return false;
+    add_pack_job(J, *one, plan.dtype, w, ws);
+    return true;
+}
+
+hipError_t launch_conv(const ConvPlan &plan, const void *in, const void *w, const void *bias, void *out, void *ws, bool packed, hipStream_t st)
+{
+    for (const ConvLaunch &L : plan.launches) {
+        hipError_t e = hipSuccess;
+        if (L.pack && !packed) {
+            SideJobs J{};
+            add_pack_job(J, L, plan.dtype, w, ws);
+            e = launch_side_jobs(J, st);
+            if (e != hipSuccess) return e;
+        }
         ConvParams P = L.P;
         P.in = static_cast<const char *>(in) + L.in_off;
         P.out = static_cast<char *>(out) + L.out_off;
         P.w = w;
         P.bias = bias;
         P.wp = P.wp ? ws : nullptr;
-        hipError_t e = hipSuccess;
-        if (L.pack) {
-            e = d->dtype == XCONV_F32 ? launch_conv_pack_f32(P, ws, st) : d->dtype == XCONV_BF16 ? launch_conv_pack_bf16(P, ws, st) : launch_conv_pack_f16(P, ws, st);
-            if (e != hipSuccess) return e;
-        }
-        e = d->dtype == XCONV_F32 ? launch_conv_f32(P, st) : d->dtype == XCONV_BF16 ? launch_conv_bf16(P, st) : launch_conv_f16(P, st);
+        e = plan.dtype == XCONV_F32 ? launch_conv_f32(P, st) : plan.dtype == XCONV_BF16 ? launch_conv_bf16(P, st) : launch_conv_f16(P, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -38,6 +38,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "side_jobs.h"
 
 // Timing experiments only (never defined in the shipped build): bit 5 leaves time stamps of the first thread in the partial tile.
 #ifndef XCONV_CORR_DBG
@@ -877,11 +878,15 @@ constexpr int kP2Threads = 1024;
 template <int QW, int WT>
 __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__restrict__ part, const float *__restrict__ Z,
                                                                 void *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
-                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS)
+                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, const SideJobs J)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [QW][JP], then the thread groups' sums [NG][NE] (few-element slabs only) and, after them, rows of Z [NR][ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q4 = lane >> 4;
+    if ((int)blockIdx.y >= K2T) {   // small jobs carried along
+        side_jobs<0, kP2Threads>(J, ((int)blockIdx.y - K2T) * gridDim.x + blockIdx.x, ((int)gridDim.y - K2T) * gridDim.x);
+        return;
+    }
     const int mg = blockIdx.x;
     if (mg * QW >= MQ) return;   // (padding of the grid)
     const int og = blockIdx.y, set = og / K2, o = og - set * K2;
@@ -1312,7 +1317,7 @@ bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in,
 
 template <int WT>
 static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm,
-                                          int nsets, hipStream_t st)
+                                          int nsets, hipStream_t st, const SideJobs *Jp)
 {
     const int MQ = P.MP / 4;
     const int K2T = nsets * P.K2;
@@ -1339,7 +1344,8 @@ static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, b
         const size_t lds = (size_t)NE * 16 + (red > zs ? red : zs);
         // rows of Z are read 16 bytes at a time where every row starts on such a boundary
         const int z_vec = (r % 4 == 0 && (reinterpret_cast<uintptr_t>(Z) & 15u) == 0) ? 1 : 0;
-        const dim3 grid((unsigned)round_up(MQ / QW, 8), (unsigned)K2T);
+        const int gx = round_up(MQ / QW, 8);
+        const dim3 grid((unsigned)gx, (unsigned)(K2T + ceil_div(side_groups<kP2Threads>(Jp), gx)));
 #define XC_P2M(Q)                                                                                                        \
     {                                                                                                                    \
         static bool done = false;                                                                                        \
@@ -1350,7 +1356,7 @@ static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, b
             done = true;                                                                                                 \
         }                                                                                                                \
         hipLaunchKernelGGL((pass2_mfma_kernel<Q, WT>), grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
-                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS);                                           \
+                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, Jp ? *Jp : SideJobs{});                                        \
     }
         if (QW == 4) XC_P2M(4) else if (QW == 2) XC_P2M(2) else XC_P2M(1)
 #undef XC_P2M
@@ -1359,13 +1365,13 @@ static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, b
 }
 
 hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
-                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype)
+                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype, const SideJobs *J)
 {
     (void)dist;
     (void)seed;
-    if (dw_dtype == XCONV_BF16) return launch_reduce_expand_as<XCONV_BF16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
-    if (dw_dtype == XCONV_F16) return launch_reduce_expand_as<XCONV_F16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
-    return launch_reduce_expand_as<XCONV_F32>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st);
+    if (dw_dtype == XCONV_BF16) return launch_reduce_expand_as<XCONV_BF16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
+    if (dw_dtype == XCONV_F16) return launch_reduce_expand_as<XCONV_F16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
+    return launch_reduce_expand_as<XCONV_F32>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
 }
 
 template <int WT>

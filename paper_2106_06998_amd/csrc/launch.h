@@ -1,5 +1,7 @@
 // Host-side launch wrappers implemented next to their kernels.
 #pragma once
+#include <memory>
+
 #include "common.h"
 
 namespace xc {
@@ -16,8 +18,9 @@ hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, 
                          bool nhwc, hipStream_t st, float zmul = 1.0f);
 // sm: where the output goes in Xt (SliceMap{} = plain order; volumetric layers: depth slices in slot order)
 // Z == nullptr and zpack == nullptr: every workgroup draws its fragments of Z from (dist, seed) itself
+// J: small jobs to carry along
 hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zpack, void *Xt, int B, int C_in, int HW, int r,
-                        int CS, bool z_exact16, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st);
+                        int CS, bool z_exact16, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J = nullptr);
 hipError_t launch_probe_generic(int dtype, const void *X, const float *Z, void *Xt, int B, int C_in, int HW, int r, int CS,
                                 bool nhwc, SliceMap sm, hipStream_t st);
 // volumetric layers: zero the slots of Xt without image data; X -> channels-last slices in slot order;
@@ -36,7 +39,7 @@ hipError_t launch_dy_slices(int dtype, const void *src, void *dst, int B, int C,
 // indep != 0: nch*r vectors over the channel window [n0, n0+nch), vector nl*r + j = column j of Z on the rows of channel
 // n0+nl, zero elsewhere (n0 = 0, nch = C_in: all channels); with cl_cs > 0 the channel slots are the window's channels
 hipError_t launch_gen_zimg(int dtype, void *out, long long K, int r, int nimg, int dist, uint64_t seed, int C_in, int cl_cs,
-                           int indep, int n0, int nch, hipStream_t st);
+                           int indep, int n0, int nch, hipStream_t st, const SideJobs *J = nullptr);
 hipError_t launch_scale(const float *in, float *out, int n, float f, hipStream_t st);
 hipError_t launch_scale_cols(const float *in, float *out, int rows, int ld, int c0, int ncol, float f, hipStream_t st);
 hipError_t launch_scatter_channels(const float *part, float *dW, int C_out, int C_in, int K2, int n0, int nch, hipStream_t st);
@@ -73,9 +76,9 @@ hipError_t launch_reduce_raw(const float *part, float *T, int S, int E4, hipStre
 // gradient, the transposed store, straight into dW [C_out, C_in, nsets*K2].  reduce_expand_fused says whether this launch applies (otherwise launch_reduce
 // followed by launch_expand do the same in two).
 bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in, int r, int dist, int nsets = 1);
-// dw_dtype: storage type dW is rounded to (XCONV_F32: stored as it is)
+// dw_dtype: storage type dW is rounded to (XCONV_F32: stored as it is); J: carried along (not by the exact gradient)
 hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm, int dist,
-                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype = XCONV_F32);
+                                uint64_t seed, int nsets, hipStream_t st, int dw_dtype = XCONV_F32, const SideJobs *J = nullptr);
 // dW[m,n,o] = (1/r) * sum_j Z[n,j] * T[o,j,m]   (Z != nullptr)
 // dW[m,n,o] = T[o,n,m]                          (Z == nullptr, exact path)
 // T != nullptr: K2 tiles [K2, JP, MP] are read from there (volumetric layers: kD * kH * kW offsets).
@@ -103,12 +106,19 @@ hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st);
 // conv_kernels.hip: forward convolution (transposed = 0) and exact input gradient (1) of a layer.  `ws` (conv_ws_bytes)
 // holds the weights in fragment order; null: the kernel gathers them from w.
 size_t conv_ws_bytes(const xconv_desc *d, int transposed);
-hipError_t launch_conv(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out, void *ws,
-                       hipStream_t st);
+struct ConvPlan;
+typedef std::shared_ptr<const ConvPlan> ConvPlanRef;
+// the plan of a product (kept between calls); null: no launch shape fits.  packed: there is a workspace
+ConvPlanRef find_conv_plan(const xconv_desc *d, int transposed, const void *in, const void *out, bool packed);
+// adds the packing of the weights to J, for a launch in front of launch_conv(packed = true); false: launch_conv packs by itself
+bool conv_pack_job(const ConvPlan &plan, const void *w, void *ws, SideJobs &J);
+hipError_t launch_conv(const ConvPlan &plan, const void *in, const void *w, const void *bias, void *out, void *ws, bool packed, hipStream_t st);
+hipError_t launch_side_jobs(const SideJobs &J, hipStream_t st);
 
-// bias_kernels.hip: db[m] = sum of dY over images and positions, rounded to the storage type; part: bias_ws_bytes(C) bytes
+// bias_kernels.hip: db[m] = sum of dY over images and positions, rounded to the storage type; part: bias_ws_bytes(C) bytes.
+// J: the sum of the pieces becomes one of these jobs instead of a launch
 size_t bias_ws_bytes(int C);
-hipError_t launch_bias_grad(int dtype, const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st);
+hipError_t launch_bias_grad(int dtype, const void *dY, float *part, void *db, int B, int C, int HW, bool nhwc, hipStream_t st, SideJobs *J = nullptr);
 
 // pixel_kernels.hip: Xbar[b, j] = sum_k X[b, k] Zimg[j, k] (forward product of the pixel x channel probes)
 bool pixel_fwd_ok(int dtype, long long K, const void *X);

@@ -32,6 +32,9 @@ struct Lib {
     decltype(&xconv_pixel_probe_fwd) pixel_probe_fwd, indep_probe_fwd;
     decltype(&xconv_pixel_dw_estimate_as) pixel_dw_estimate;
     decltype(&xconv_pixel_indep_dw_estimate) indep_dw_estimate;
+    decltype(&xconv_layer_workspace_bytes) layer_workspace_bytes;
+    decltype(&xconv_layer_fwd) layer_fwd;
+    decltype(&xconv_layer_bwd) layer_bwd;
     decltype(&xconv_relu_mask_bytes) relu_mask_bytes;
     decltype(&xconv_relu_fwd) relu_fwd;
     decltype(&xconv_relu_bwd) relu_bwd;
@@ -75,6 +78,12 @@ Tensor bytes_on(size_t n, const Tensor &like)
     return at::empty({(int64_t)(n < 16 ? 16 : n)}, like.options().dtype(at::kByte));
 }
 void *ptr(const Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
+
+[[noreturn]] void unsupported(const xconv_desc &d)
+{
+    throw std::runtime_error("XConv2d: layer not supported by the library in this mode (C_in=" + std::to_string(d.C_in) + ", " + std::to_string(d.H) + "x" +
+                             std::to_string(d.W) + ", r=" + std::to_string(d.r) + ")");
+}
 
 // One Python call: unpacks, runs `body` without the interpreter lock, turns failures into Python errors.
 template <class F> bool run(F &&body)
@@ -156,32 +165,40 @@ PyObject *layer_forward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             d.stride_h = (int)v[0]; d.stride_w = (int)v[1]; d.pad_h = (int)v[2]; d.pad_w = (int)v[3];
             d.r = (int)v[4]; d.probe = (int)v[5]; d.dtype = dtype_code(x.scalar_type()); d.layout = layout;
             d.seed = (uint64_t)v[7];
+            Tensor w, b;
             if (own) {
-                const Tensor w = weight.contiguous(), b = bias.defined() ? bias.contiguous() : bias;
+                w = weight.contiguous();
+                b = bias.defined() ? bias.contiguous() : bias;
                 const int64_t Ho = (d.H + 2 * d.pad_h - d.kH) / d.stride_h + 1, Wo = (d.W + 2 * d.pad_w - d.kW) / d.stride_w + 1;
                 y = at::empty({d.B, d.C_out, Ho, Wo}, x.options(), format_of(layout));
-                const size_t n = L.conv_workspace_bytes(&d, 0);
+            }
+            if (want_state) {
+                const size_t n = mode == kChannel ? L.xt_bytes(&d) : (mode == kIndependent ? L.indep_xbar_bytes : L.pixel_xbar_bytes)(&d);
+                if (n == 0) unsupported(d);
+                state = mode == kChannel ? bytes_on(n, x) : at::empty({(int64_t)(n / 4)}, x.options().dtype(at::kFloat));
+            }
+            if (own && want_state && mode != kIndependent) {
+                const size_t n = L.layer_workspace_bytes(&d, mode, 0);
+                if (n == 0 || (mode == kChannel && L.workspace_bytes(&d, XCONV_OP_ESTIMATE) == 0)) unsupported(d);
                 const Tensor ws = bytes_on(n, x);
+                check(L.layer_fwd(&d, mode, ptr(xs), ptr(w), ptr(b), ptr(y), ptr(state), ptr(ws), (size_t)ws.numel(), stream), "xconv_layer_fwd");
+                return;
+            }
+            if (own) {
+                const Tensor ws = bytes_on(L.conv_workspace_bytes(&d, 0), x);
                 check(L.conv_fwd(&d, ptr(xs), ptr(w), ptr(b), ptr(y), ptr(ws), (size_t)ws.numel(), stream), "xconv_conv_fwd_ws");
             }
             if (!want_state) return;
             if (mode == kChannel) {
-                const size_t n = L.xt_bytes(&d), w = L.workspace_bytes(&d, XCONV_OP_PROBE);
-                if (n == 0 || L.workspace_bytes(&d, XCONV_OP_ESTIMATE) == 0)
-                    throw std::runtime_error("XConv2d: layer not supported by the library (C_in=" + std::to_string(d.C_in) + ", " + std::to_string(d.H) +
-                                             "x" + std::to_string(d.W) + ", r=" + std::to_string(d.r) + ")");
-                state = bytes_on(n, x);
-                const Tensor ws = bytes_on(w, x);
+                const size_t n = L.workspace_bytes(&d, XCONV_OP_PROBE);
+                if (L.workspace_bytes(&d, XCONV_OP_ESTIMATE) == 0) unsupported(d);
+                const Tensor ws = bytes_on(n, x);
                 check(L.probe_fwd(&d, ptr(xs), ptr(state), nullptr, ptr(ws), (size_t)ws.numel(), stream), "xconv_probe_fwd");
             } else {
                 const bool indep = mode == kIndependent;
-                const size_t n = (indep ? L.indep_xbar_bytes : L.pixel_xbar_bytes)(&d);
-                const size_t w = (indep ? L.indep_workspace_bytes : L.pixel_workspace_bytes)(&d, XCONV_OP_PROBE);
-                if (n == 0 || w == 0)
-                    throw std::runtime_error("XConv2d: layer not supported in this mode (C_in=" + std::to_string(d.C_in) + ", " + std::to_string(d.H) + "x" +
-                                             std::to_string(d.W) + ", r=" + std::to_string(d.r) + ")");
-                state = at::empty({(int64_t)(n / 4)}, x.options().dtype(at::kFloat));
-                const Tensor ws = bytes_on(w, x);
+                const size_t n = (indep ? L.indep_workspace_bytes : L.pixel_workspace_bytes)(&d, XCONV_OP_PROBE);
+                if (n == 0) unsupported(d);
+                const Tensor ws = bytes_on(n, x);
                 check((indep ? L.indep_probe_fwd : L.pixel_probe_fwd)(&d, ptr(xs), state.data_ptr<float>(), ptr(ws), (size_t)ws.numel(), stream),
                       "xconv_pixel_probe_fwd");
             }
@@ -214,6 +231,19 @@ PyObject *layer_backward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             const at::ScalarType xt = d.dtype == XCONV_F32 ? at::kFloat : d.dtype == XCONV_BF16 ? at::kBFloat16 : at::kHalf;
             int layout;
             Tensor dys = in_layout(dy, layout);
+            // the gradient comes in the weight's type where that is a storage type (independent probing adds up fp32 pieces first)
+            const at::ScalarType wst = weight.scalar_type();
+            const bool direct = mode != kIndependent && (wst == at::kFloat || wst == at::kBFloat16 || wst == at::kHalf);
+            if (v[2] && direct && layout == d.layout && dys.scalar_type() == xt) {
+                const Tensor w = v[1] ? weight.contiguous() : weight;
+                if (v[1]) dx = at::empty({d.B, d.C_in, d.H, d.W}, dy.options(), format_of(layout));
+                if (v[3]) db = at::empty({d.C_out}, dy.options());
+                dw = at::empty(weight.sizes(), weight.options(), at::MemoryFormat::Contiguous);
+                const Tensor ws = bytes_on(L.layer_workspace_bytes(&d, mode, 1), dy);
+                check(L.layer_bwd(&d, mode, ptr(dys), ptr(w), ptr(state), ptr(dx), ptr(dw), dtype_code(wst), ptr(db), ptr(ws), (size_t)ws.numel(), stream),
+                      "xconv_layer_bwd");
+                return;
+            }
             if (v[1]) {
                 xconv_desc q = d;
                 q.layout = layout;
@@ -238,9 +268,6 @@ PyObject *layer_backward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                 }
                 if (layout != d.layout) dys = aligned(dys.contiguous(format_of(d.layout)));
                 const bool indep = mode == kIndependent;
-                // the gradient comes in the weight's type where that is a storage type (independent probing adds up fp32 pieces first)
-                const at::ScalarType wst = weight.scalar_type();
-                const bool direct = !indep && (wst == at::kFloat || wst == at::kBFloat16 || wst == at::kHalf);
                 dw = at::empty(weight.sizes(), weight.options().dtype(direct ? wst : at::kFloat), at::MemoryFormat::Contiguous);
                 const int wt = dtype_code(dw.scalar_type());
                 const size_t n = mode == kChannel ? L.workspace_bytes(&d, XCONV_OP_ESTIMATE)
@@ -348,6 +375,9 @@ PyObject *glue_init(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     get(L.indep_probe_fwd, "xconv_pixel_indep_probe_fwd");
     get(L.pixel_dw_estimate, "xconv_pixel_dw_estimate_as");
     get(L.indep_dw_estimate, "xconv_pixel_indep_dw_estimate");
+    get(L.layer_workspace_bytes, "xconv_layer_workspace_bytes");
+    get(L.layer_fwd, "xconv_layer_fwd");
+    get(L.layer_bwd, "xconv_layer_bwd");
     get(L.relu_mask_bytes, "xconv_relu_mask_bytes");
     get(L.relu_fwd, "xconv_relu_fwd");
     get(L.relu_bwd, "xconv_relu_bwd");

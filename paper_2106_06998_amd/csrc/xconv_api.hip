@@ -241,8 +241,14 @@ bool probe_scales_z(const xconv_desc *d, int HWv, const void *X_dev, const void 
     return ws_dev && probe_fast_path_ok(d->dtype, d->C_in, HWv, d->layout == XCONV_NHWC) && aligned16(X_dev);
 }
 
+// J (here and below): small jobs for a launch to carry along; emptied where one takes them
+void taken(SideJobs *J)
+{
+    if (J) *J = SideJobs{};
+}
+
 xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const void *X_dev, void *Xt_dev, const float *Z_dev,
-                        void *ws_dev, size_t ws_bytes, hipStream_t st, float zmul = 1.0f)
+                        void *ws_dev, size_t ws_bytes, hipStream_t st, float zmul = 1.0f, SideJobs *J = nullptr)
 {
     if (!X_dev || !Xt_dev) return XCONV_EINVAL;
     if (!aligned16(Xt_dev) || (reinterpret_cast<uintptr_t>(X_dev) & (elem_bytes(d->dtype) - 1)) != 0) return XCONV_EINVAL;
@@ -273,7 +279,8 @@ xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const
         }
         if (zpack) XC_LAUNCH(K_PACK_Z, st, launch_pack_z(d->dtype, Z_dev, zpack, d->C_in, d->r, z_exact16, probe_code(d), d->seed, nhwc, st, zmul));
         XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, nhwc, sm,
-                                            probe_code(d), d->seed, st));
+                                            probe_code(d), d->seed, st, J));
+        taken(J);
     } else {
         const float *Z = Z_dev;
         if (!Z) {
@@ -413,7 +420,7 @@ xconv_status xconv_probe_fwd(const xconv_desc *d, const void *X_dev, void *Xt_de
 
 // dw_dtype: the type dW is rounded to
 static xconv_status estimate_impl(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, void *dW_dev, int dw_dtype,
-                                  void *ws_dev, size_t ws_bytes, void *stream)
+                                  void *ws_dev, size_t ws_bytes, void *stream, SideJobs *J = nullptr)
 {
     xconv_status s = xconv_check_desc(d);
     if (s != XCONV_OK) return s;
@@ -468,7 +475,8 @@ static xconv_status estimate_impl(const xconv_desc *d, const void *dY_dev, const
         XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
     }
     if (fused) {
-        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, Z, false, dW_dev, d->C_in, d->r, d->keep_q15 != 0, probe_code(d), d->seed, 1, st, dw_dtype));
+        XC_LAUNCH(K_PASS2, st, launch_reduce_expand(P, Z, false, dW_dev, d->C_in, d->r, d->keep_q15 != 0, probe_code(d), d->seed, 1, st, dw_dtype, J));
+        taken(J);
         return XCONV_OK;
     }
     XC_LAUNCH(K_REDUCE, st, launch_reduce(P, st, zw, d->C_in * d->r, probe_code(d), d->seed));
@@ -632,14 +640,14 @@ xconv_status xconv_dw_exact(const xconv_desc *d, const void *dY_dev, const void 
 }
 
 // ---- forward convolution and exact input gradient (Sec. 2; Alg. 1 forward step 1) ----
-static xconv_status conv_impl(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out,
-                              void *ws, size_t ws_bytes, void *stream)
+static xconv_status conv_check(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, const void *out,
+                               const void *ws, size_t ws_bytes)
 {
     xconv_status s = xconv_check_desc(d);
     if (s != XCONV_OK) return s;
     if (!in || !w || !out) return XCONV_EINVAL;
     const uintptr_t em = elem_bytes(d->dtype) - 1;
-    for (const void *p : {in, w, bias, (const void *)out})
+    for (const void *p : {in, w, bias, out})
         if (reinterpret_cast<uintptr_t>(p) & em) return XCONV_EINVAL;
     const int Ho = out_extent(d->H, d->kH, d->stride_h, d->pad_h), Wo = out_extent(d->W, d->kW, d->stride_w, d->pad_w);
     if ((long long)d->C_in * d->H * d->W > 0x7fffffffLL || (long long)d->C_out * Ho * Wo > 0x7fffffffLL) return XCONV_EUNSUPPORTED;
@@ -647,8 +655,18 @@ static xconv_status conv_impl(const xconv_desc *d, int transposed, const void *i
         if (!aligned16(ws)) return XCONV_EINVAL;
         if (ws_bytes < conv_ws_bytes(d, transposed)) return XCONV_EWORKSPACE;
     }
+    return XCONV_OK;
+}
+
+static xconv_status conv_impl(const xconv_desc *d, int transposed, const void *in, const void *w, const void *bias, void *out,
+                              void *ws, size_t ws_bytes, void *stream)
+{
+    xconv_status s = conv_check(d, transposed, in, w, bias, out, ws, ws_bytes);
+    if (s != XCONV_OK) return s;
+    const ConvPlanRef plan = find_conv_plan(d, transposed, in, out, ws != nullptr);
+    if (!plan) return XCONV_EHIP;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    XC_LAUNCH(K_CONV, st, launch_conv(d, transposed, in, w, bias, out, ws, st));
+    XC_LAUNCH(K_CONV, st, launch_conv(*plan, in, w, bias, out, ws, false, st));
     return XCONV_OK;
 }
 
@@ -1021,7 +1039,7 @@ size_t pixel_workspace_bytes(const xconv_desc *d, bool indep, int op)
 }
 
 xconv_status pixel_probe_fwd(const xconv_desc *d, bool indep, const void *X_dev, float *Xbar_dev, void *ws_dev, size_t ws_bytes,
-                             void *stream)
+                             void *stream, SideJobs *J = nullptr)
 {
     PixelGeom g;
     xconv_status s = pixel_geom(d, indep, g);
@@ -1042,7 +1060,8 @@ xconv_status pixel_probe_fwd(const xconv_desc *d, bool indep, const void *X_dev,
     }
     // probing vectors as rows in the order X keeps its values in: (n, y, x), or (y, x, n) for channels-last
     XC_LAUNCH(K_GEN_ZIMG, st, launch_gen_zimg(d->dtype, ws, g.K, d->r, g.R, probe_code(d), d->seed, d->C_in,
-                                              d->layout == XCONV_NHWC ? d->C_in : 0, indep, 0, d->C_in, st));
+                                              d->layout == XCONV_NHWC ? d->C_in : 0, indep, 0, d->C_in, st, J));
+    taken(J);
     if (pixel_fwd_ok(d->dtype, g.K, X_dev)) {
         XC_LAUNCH(K_PIXEL_FWD, st, launch_pixel_fwd(d->dtype, X_dev, ws, reinterpret_cast<float *>(ws + g.zimg_f), Xbar_dev, g.K, d->B,
                                                     g.R, st));
@@ -1054,7 +1073,7 @@ xconv_status pixel_probe_fwd(const xconv_desc *d, bool indep, const void *X_dev,
 
 // dw_dtype other than fp32: multi-channel probing with dense vectors only (the other modes work on dW after it is written)
 xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_dev, const float *Xbar_dev, void *dW_out,
-                               void *ws_dev, size_t ws_bytes, void *stream, int dw_dtype = XCONV_F32)
+                               void *ws_dev, size_t ws_bytes, void *stream, int dw_dtype = XCONV_F32, SideJobs *J = nullptr)
 {
     PixelGeom g;
     xconv_status s = pixel_geom(d, indep, g);
@@ -1104,7 +1123,8 @@ xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_d
     // Z[s] again (Alg. 1 backward step 2), CS images, channels-last as the correlation reads an activation:
     // the images past r are zero like the matching images of L
     XC_LAUNCH(K_GEN_ZIMG, st, launch_gen_zimg(d->dtype, zimg, g.K, d->r, g.CS, probe_code(d), d->seed, d->C_in, round_up(d->C_in, 16),
-                                              0, 0, d->C_in, st));
+                                              0, 0, d->C_in, st, J));
+    taken(J);
     // Lt[p, j] = sum_b dY[b, p] Xbar[b, j] / r, rounded to the storage type (Alg. 1 backward step 3); p runs over
     // an image of dY in its own order, so the images of L come out in dY's layout.  The factor 1/r goes on Xbar where
     // the product brings it into fragment order, or in a launch of its own for the shapes that do not pass there
@@ -1153,6 +1173,85 @@ xconv_status xconv_pixel_indep_dw_estimate(const xconv_desc *d, const void *dY_d
                                            size_t ws_bytes, void *stream)
 {
     return pixel_dw_estimate(d, true, dY_dev, Xbar_dev, dW_dev, ws_dev, ws_bytes, stream);
+}
+
+// ---- a layer's passes ---------------------------------------------------------------
+// The same kernels as the calls above, with the small ones (weights into fragment order, last sum of the bias gradient)
+// carried by a launch of the estimator: 3-5 launches of a layer's 11 less (layer C1 on the host, stack bf16 on the GPU).
+static size_t layer_est_bytes(const xconv_desc *d, int mode, int op)
+{
+    return mode == XCONV_LAYER_CHANNEL ? xconv_workspace_bytes(d, op) : mode == XCONV_LAYER_MULTI ? xconv_pixel_workspace_bytes(d, op) : 0;
+}
+
+size_t xconv_layer_workspace_bytes(const xconv_desc *d, int mode, int backward)
+{
+    if (xconv_check_desc(d) != XCONV_OK) return 0;
+    const size_t est = layer_est_bytes(d, mode, backward ? XCONV_OP_ESTIMATE : XCONV_OP_PROBE);
+    if (est == 0) return 0;
+    return align_up(est, 256) + align_up(conv_ws_bytes(d, backward != 0), 256) + (backward ? bias_ws_bytes(d->C_out) : 0);
+}
+
+xconv_status xconv_layer_fwd(const xconv_desc *d, int mode, const void *X_dev, const void *W_dev, const void *bias_dev, void *Y_dev,
+                             void *state_dev, void *ws_dev, size_t ws_bytes, void *stream)
+{
+    xconv_status s = xconv_check_desc(d);
+    if (s != XCONV_OK) return s;
+    const size_t eb = align_up(layer_est_bytes(d, mode, XCONV_OP_PROBE), 256);
+    if (eb == 0) return mode == XCONV_LAYER_CHANNEL || mode == XCONV_LAYER_MULTI ? XCONV_EUNSUPPORTED : XCONV_EINVAL;
+    if (!state_dev || !ws_dev || !aligned16(ws_dev)) return XCONV_EINVAL;
+    if (ws_bytes < xconv_layer_workspace_bytes(d, mode, 0)) return XCONV_EWORKSPACE;
+    char *cws = static_cast<char *>(ws_dev) + eb;
+    s = conv_check(d, 0, X_dev, W_dev, bias_dev, Y_dev, cws, conv_ws_bytes(d, 0));
+    if (s != XCONV_OK) return s;
+    const ConvPlanRef plan = find_conv_plan(d, 0, X_dev, Y_dev, true);
+    if (!plan) return XCONV_EHIP;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    SideJobs J{};
+    const bool packed = conv_pack_job(*plan, W_dev, cws, J);
+    s = mode == XCONV_LAYER_CHANNEL
+            ? probe_impl(d, d->H * d->W, d->H * d->W, SliceMap{}, X_dev, state_dev, nullptr, ws_dev, eb, st, 1.0f, &J)
+            : pixel_probe_fwd(d, false, X_dev, static_cast<float *>(state_dev), ws_dev, eb, stream, &J);
+    if (s != XCONV_OK) return s;
+    if (J.total) XC_LAUNCH(K_CONV, st, launch_side_jobs(J, st));
+    XC_LAUNCH(K_CONV, st, launch_conv(*plan, X_dev, W_dev, bias_dev, Y_dev, cws, packed, st));
+    return XCONV_OK;
+}
+
+xconv_status xconv_layer_bwd(const xconv_desc *d, int mode, const void *dY_dev, const void *W_dev, const void *state_dev, void *dX_dev,
+                             void *dW_dev, int dw_dtype, void *db_dev, void *ws_dev, size_t ws_bytes, void *stream)
+{
+    xconv_status s = xconv_check_desc(d);
+    if (s != XCONV_OK) return s;
+    const size_t eb = align_up(layer_est_bytes(d, mode, XCONV_OP_ESTIMATE), 256);
+    if (eb == 0) return mode == XCONV_LAYER_CHANNEL || mode == XCONV_LAYER_MULTI ? XCONV_EUNSUPPORTED : XCONV_EINVAL;
+    if (!ws_dev || !aligned16(ws_dev) || !dY_dev || (reinterpret_cast<uintptr_t>(db_dev) & (elem_bytes(d->dtype) - 1))) return XCONV_EINVAL;
+    if (ws_bytes < xconv_layer_workspace_bytes(d, mode, 1)) return XCONV_EWORKSPACE;
+    char *cws = static_cast<char *>(ws_dev) + eb;
+    char *bws = cws + align_up(conv_ws_bytes(d, 1), 256);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    ConvPlanRef plan;
+    SideJobs J{};
+    bool packed = false;
+    if (dX_dev) {
+        s = conv_check(d, 1, dY_dev, W_dev, nullptr, dX_dev, cws, conv_ws_bytes(d, 1));
+        if (s != XCONV_OK) return s;
+        plan = find_conv_plan(d, 1, dY_dev, dX_dev, true);
+        if (!plan) return XCONV_EHIP;
+        packed = conv_pack_job(*plan, W_dev, cws, J);
+    }
+    if (db_dev) {
+        const int Ho = out_extent(d->H, d->kH, d->stride_h, d->pad_h), Wo = out_extent(d->W, d->kW, d->stride_w, d->pad_w);
+        XC_LAUNCH(K_BIAS, st, launch_bias_grad(d->dtype, dY_dev, reinterpret_cast<float *>(bws), db_dev, d->B, d->C_out, Ho * Wo,
+                                               d->layout == XCONV_NHWC, st, &J));
+    }
+    // (multi-channel probing draws its vectors before anything else: the jobs go with that launch)
+    s = mode == XCONV_LAYER_CHANNEL
+            ? estimate_impl(d, dY_dev, state_dev, nullptr, dW_dev, dw_dtype, ws_dev, eb, stream, &J)
+            : pixel_dw_estimate(d, false, dY_dev, static_cast<const float *>(state_dev), dW_dev, ws_dev, eb, stream, dw_dtype, &J);
+    if (s != XCONV_OK) return s;
+    if (J.total) XC_LAUNCH(K_CONV, st, launch_side_jobs(J, st));
+    if (dX_dev) XC_LAUNCH(K_CONV, st, launch_conv(*plan, dY_dev, W_dev, nullptr, dX_dev, cws, packed, st));
+    return XCONV_OK;
 }
 
 // ---- ReLU that keeps signs only -----------------------------------------------------
