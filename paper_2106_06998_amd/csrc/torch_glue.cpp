@@ -158,6 +158,9 @@ PyObject *layer_forward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
     Tensor y, state;
     if (!run([&] {
             const c10::DeviceGuard guard(x.device());
+            // the kernels take the weight's extents from the descriptor
+            if (x.dim() != 4 || weight.dim() != 4 || x.size(1) != weight.size(1))
+                throw std::runtime_error("XConv2d: expected an input of 4 dimensions with " + std::to_string(weight.size(1)) + " channels");
             int layout;
             const Tensor xs = in_layout(x, layout);
             d.B = (int)x.size(0); d.C_in = (int)x.size(1); d.H = (int)x.size(2); d.W = (int)x.size(3);
@@ -166,9 +169,16 @@ PyObject *layer_forward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             d.r = (int)v[4]; d.probe = (int)v[5]; d.dtype = dtype_code(x.scalar_type()); d.layout = layout;
             d.seed = (uint64_t)v[7];
             Tensor w, b;
+            // the kernel reads one bias per output channel in the storage type; any other bias (a float32 one of a half-precision
+            // layer, say) is added behind it
+            const bool apart = own && bias.defined() &&
+                               (bias.scalar_type() != x.scalar_type() || bias.device() != x.device() || bias.dim() != 1 || bias.size(0) != weight.size(0));
+            auto add_apart = [&] {
+                if (apart) y.add_(bias.view({1, -1, 1, 1}));
+            };
             if (own) {
                 w = weight.contiguous();
-                b = bias.defined() ? bias.contiguous() : bias;
+                if (bias.defined() && !apart) b = bias.contiguous();
                 const int64_t Ho = (d.H + 2 * d.pad_h - d.kH) / d.stride_h + 1, Wo = (d.W + 2 * d.pad_w - d.kW) / d.stride_w + 1;
                 y = at::empty({d.B, d.C_out, Ho, Wo}, x.options(), format_of(layout));
             }
@@ -182,11 +192,13 @@ PyObject *layer_forward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
                 if (n == 0 || (mode == kChannel && L.workspace_bytes(&d, XCONV_OP_ESTIMATE) == 0)) unsupported(d);
                 const Tensor ws = bytes_on(n, x);
                 check(L.layer_fwd(&d, mode, ptr(xs), ptr(w), ptr(b), ptr(y), ptr(state), ptr(ws), (size_t)ws.numel(), stream), "xconv_layer_fwd");
+                add_apart();
                 return;
             }
             if (own) {
                 const Tensor ws = bytes_on(L.conv_workspace_bytes(&d, 0), x);
                 check(L.conv_fwd(&d, ptr(xs), ptr(w), ptr(b), ptr(y), ptr(ws), (size_t)ws.numel(), stream), "xconv_conv_fwd_ws");
+                add_apart();
             }
             if (!want_state) return;
             if (mode == kChannel) {
