@@ -431,5 +431,8 @@ struct SideJobs {
     void *db;
     PackClass sub[kConvSubs];
 };
+// the argument of a launch that carries none: the estimator's own entry points run kernels without the jobs' code and argument
+// (C4 estimate 134.5 -> 133.9 us, 133.6 before there were any jobs)
+struct NoSideJobs {};
 
 }  // namespace xc

@@ -875,17 +875,19 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
 // ---------------------------------------------------------------------------
 constexpr int kP2Threads = 1024;
 
-template <int QW, int WT>
+template <int QW, int WT, class SJ>
 __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__restrict__ part, const float *__restrict__ Z,
                                                                 void *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
-                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, const SideJobs J)
+                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, const SJ J)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [QW][JP], then the thread groups' sums [NG][NE] (few-element slabs only) and, after them, rows of Z [NR][ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q4 = lane >> 4;
-    if ((int)blockIdx.y >= K2T) {   // small jobs carried along
-        side_jobs<0, kP2Threads>(J, ((int)blockIdx.y - K2T) * gridDim.x + blockIdx.x, ((int)gridDim.y - K2T) * gridDim.x);
-        return;
+    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
+        if ((int)blockIdx.y >= K2T) {
+            side_jobs<0, kP2Threads>(J, ((int)blockIdx.y - K2T) * gridDim.x + blockIdx.x, ((int)gridDim.y - K2T) * gridDim.x);
+            return;
+        }
     }
     const int mg = blockIdx.x;
     if (mg * QW >= MQ) return;   // (padding of the grid)
@@ -1345,20 +1347,23 @@ static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, b
         // rows of Z are read 16 bytes at a time where every row starts on such a boundary
         const int z_vec = (r % 4 == 0 && (reinterpret_cast<uintptr_t>(Z) & 15u) == 0) ? 1 : 0;
         const int gx = round_up(MQ / QW, 8);
-        const dim3 grid((unsigned)gx, (unsigned)(K2T + ceil_div(side_groups<kP2Threads>(Jp), gx)));
-#define XC_P2M(Q)                                                                                                        \
+        const int nside = side_groups<kP2Threads>(Jp);
+        const dim3 grid((unsigned)gx, (unsigned)(K2T + ceil_div(nside, gx)));
+#define XC_P2M(Q, SJ, J)                                                                                                        \
     {                                                                                                                    \
         static bool done = false;                                                                                        \
         if (!done) {                                                                                                     \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pass2_mfma_kernel<Q, WT>),                      \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pass2_mfma_kernel<Q, WT, SJ>),                      \
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                  \
             if (e != hipSuccess) return e;                                                                               \
             done = true;                                                                                                 \
         }                                                                                                                \
-        hipLaunchKernelGGL((pass2_mfma_kernel<Q, WT>), grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
-                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, Jp ? *Jp : SideJobs{});                                        \
+        hipLaunchKernelGGL((pass2_mfma_kernel<Q, WT, SJ>), grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
+                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, J);                                        \
     }
-        if (QW == 4) XC_P2M(4) else if (QW == 2) XC_P2M(2) else XC_P2M(1)
+#define XC_P2M_SIDE(Q) { if (nside) XC_P2M(Q, SideJobs, *Jp) else XC_P2M(Q, NoSideJobs, NoSideJobs{}) }
+        if (QW == 4) XC_P2M_SIDE(4) else if (QW == 2) XC_P2M_SIDE(2) else XC_P2M_SIDE(1)
+#undef XC_P2M_SIDE
 #undef XC_P2M
     }
     return hipGetLastError();

@@ -159,17 +159,21 @@ __global__ __launch_bounds__(kThreads) void pack_z_16_kernel(const float *__rest
 // NHWC: X is [pixels, C_in]; a lane then loads four consecutive channels (16 bytes) of one pixel,
 // MFMA u uses element u of every lane (see f32_frag_channel), and the wave's tile is four
 // sub-tiles of 16 pixels; `ngroups` is the number of pixels.
-template <int JT, bool NHWC>
+template <int JT, bool NHWC, class SJ>
 __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const float *__restrict__ X, const float *__restrict__ Z,
                                                              const float *__restrict__ zpack, float *__restrict__ Xt, int C_in,
                                                              int HW, int r, int CS, int j0, long long ngroups, int ntiles,
-                                                             SliceMap sm, int dist, uint64_t seed, int nside, const SideJobs J)
+                                                             SliceMap sm, int dist, uint64_t seed, int nside, const SJ J)
 {
-    if ((int)blockIdx.x < nside) {   // small jobs carried along
-        side_jobs<4, kThreads>(J, blockIdx.x, nside);
-        return;
+    int wg = blockIdx.x, nwg = gridDim.x;
+    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
+        if (wg < nside) {
+            side_jobs<4, kThreads>(J, wg, nside);
+            return;
+        }
+        wg -= nside;
+        nwg -= nside;
     }
-    const int wg = blockIdx.x - nside, nwg = gridDim.x - nside;
     extern __shared__ float zs[];  // [KQ4][JT][64] A-operand fragments, zero beyond C_in
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int KQ4 = ((C_in + 15) >> 4) << 2;
@@ -332,17 +336,21 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 // ---------------------------------------------------------------------------
 // NHWC: X is [pixels, C_in]; the 8 channels a lane supplies are then one 16-byte load, no
 // transpose; the wave's tile is PT sub-tiles of 16 pixels and `ngroups` is the number of pixels.
-template <int DT, int JT, int PT, bool SPLIT, bool NHWC>
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class SJ>
 __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *__restrict__ X, const float *__restrict__ Z,
                                                             const uint4 *__restrict__ zpack, uint16_t *__restrict__ Xt, int C_in,
                                                             int HW, int r, int CS, int j0, long long ngroups, int ntiles,
-                                                            SliceMap sm, int dist, uint64_t seed, int nword, int nt, int nside, const SideJobs J)
+                                                            SliceMap sm, int dist, uint64_t seed, int nword, int nt, int nside, const SJ J)
 {
-    if ((int)blockIdx.x < nside) {   // small jobs carried along
-        side_jobs<2, kThreads>(J, blockIdx.x, nside);
-        return;
+    int wg = blockIdx.x, nwg = gridDim.x;
+    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
+        if (wg < nside) {
+            side_jobs<2, kThreads>(J, wg, nside);
+            return;
+        }
+        wg -= nside;
+        nwg -= nside;
     }
-    const int wg = blockIdx.x - nside, nwg = gridDim.x - nside;
     extern __shared__ uint4 zf[];  // [SPLIT?2:1][KK][JT][64] A-operand fragments, then (nword > 0) the generator words of a +-1 matrix
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int KK = (C_in + 31) >> 5;
@@ -745,18 +753,43 @@ static int probe_grid(int ntiles, int wgs_per_cu)
     return want < slots ? want : slots;
 }
 
-template <int JT, bool NHWC>
-static hipError_t launch_probe_f32_jt(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
-                                      int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
+template <int JT, bool NHWC, class SJ>
+static hipError_t launch_probe_f32_side(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
+                                      int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const SJ &J)
 {
     // a lane owns 4 consecutive pixels of a plane (NCHW) or one pixel of each of 4 sub-tiles (NHWC)
     const long long ngroups = NHWC ? npix : npix / 4;
     const int ntiles = (int)(NHWC ? (npix + 63) / 64 : (ngroups + 15) / 16);
     const size_t lds = (size_t)ceil_div(C_in, 16) * 4 * JT * 64 * sizeof(float);
-    hipError_t e = set_lds(probe_f32_kernel<JT, NHWC>, lds);
+    hipError_t e = set_lds(probe_f32_kernel<JT, NHWC, SJ>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_f32_kernel<JT, NHWC>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + side_groups<kThreads>(J)), dim3(kThreads), lds, st, X, Z, zpack, Xt, C_in, HW, r,
-                       CS, j0, ngroups, ntiles, sm, dist, seed, side_groups<kThreads>(J), J ? *J : SideJobs{});
+    hipLaunchKernelGGL((probe_f32_kernel<JT, NHWC, SJ>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st, X, Z, zpack, Xt, C_in, HW, r,
+                       CS, j0, ngroups, ntiles, sm, dist, seed, nside, J);
+    return hipGetLastError();
+}
+
+template <int JT, bool NHWC>
+static hipError_t launch_probe_f32_jt(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
+                                      int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
+{
+    const int nside = side_groups<kThreads>(J);
+    if (nside) return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, *J);
+    return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0, NoSideJobs{});
+}
+
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class SJ>
+static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
+                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const SJ &J)
+{
+    const long long ngroups = NHWC ? npix : npix / PT;
+    const int ntiles = (int)(NHWC ? (npix + 16 * PT - 1) / (16 * PT) : (ngroups + 15) / 16);
+    // a dense +-1 matrix that comes from the seed and has no fragments in scratch is drawn by the workgroups from its generator words
+    const int nword = (!Z && !zpack && probe_draws_words(C_in, r, dist)) ? (int)(((long long)C_in * r + 63) / 64) : 0;
+    const size_t lds = (size_t)(SPLIT ? 2 : 1) * ceil_div(C_in, 32) * JT * 64 * sizeof(uint4) + (size_t)round_up(nword, 2) * 8;
+    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, SJ>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, SJ>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
+                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), nside, J);
     return hipGetLastError();
 }
 
@@ -764,17 +797,9 @@ template <int DT, int JT, int PT, bool SPLIT, bool NHWC>
 static hipError_t launch_probe_16_cfg(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
                                       int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
-    const long long ngroups = NHWC ? npix : npix / PT;
-    const int ntiles = (int)(NHWC ? (npix + 16 * PT - 1) / (16 * PT) : (ngroups + 15) / 16);
-    // a dense +-1 matrix that comes from the seed and has no fragments in scratch is drawn by the workgroups from its generator words
-    const int nword = (!Z && !zpack && probe_draws_words(C_in, r, dist)) ? (int)(((long long)C_in * r + 63) / 64) : 0;
-    const size_t lds = (size_t)(SPLIT ? 2 : 1) * ceil_div(C_in, 32) * JT * 64 * sizeof(uint4) + (size_t)round_up(nword, 2) * 8;
-    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC>), dim3(probe_grid(ntiles, 2) + side_groups<kThreads>(J)), dim3(kThreads), lds, st, X, Z, zpack,
-                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), side_groups<kThreads>(J),
-                       J ? *J : SideJobs{});
-    return hipGetLastError();
+    const int nside = side_groups<kThreads>(J);
+    if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, *J);
+    return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0, NoSideJobs{});
 }
 
 template <int DT, int JT>
