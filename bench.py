@@ -309,12 +309,12 @@ def measure_volume(name, steps, warmup, dev, with_cpu, with_exact=True):
     es = elem_bytes(dtype)
     vox = B * D * H * W
     probe_bytes = (C_in + r) * vox * es
-    corr_flops = 2.0 * vox * C_out * r * k * k          # one launch: the k*k in-plane offsets of one kernel-depth offset
-    corr_bytes = vox * C_out * es + vox * r * es + C_out * r * k * k * 4
+    corr_flops = 2.0 * vox * C_out * r * k * k * k      # one launch: all offsets of the kernel
+    corr_bytes = vox * C_out * es + vox * r * es + C_out * r * k * k * k * 4
     tp, tc = kt.get("probe_kernel", kt.get("probe_generic_kernel")), kt["corr_kernel"]
     out = dict(name=name, dtype=dtype, ms_per_layer=ms_step, kernels_ms=kt,
                probe=dict(ms=tp, gbps=probe_bytes / tp / 1e6, hbm_frac=probe_bytes / tp / 1e6 / PEAK_HBM_GBS),
-               corr=dict(ms=tc, launches_per_layer=k, gflops=corr_flops / tc / 1e6, gbps=corr_bytes / tc / 1e6,
+               corr=dict(ms=tc, launches_per_layer=1, gflops=corr_flops / tc / 1e6, gbps=corr_bytes / tc / 1e6,
                          mfma_frac=corr_flops / tc / 1e9 / PEAK_MFMA_TFLOPS[dtype]),
                act_bytes_saved=(C_in - r) * vox * es, exact_ms=ms_exact, estimate_vs_exact_speedup=(ms_exact / ms_step if ms_exact else None),
                workload="%s: B=%d C_in=%d C_out=%d D=H=W=%d k=%dx%dx%d pad=%d r=%d %s probes, %s storage, NCDHW" % (
