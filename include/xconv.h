@@ -190,6 +190,13 @@ xconv_status xconv_conv_fwd_ws(const xconv_desc *desc, const void *X_dev, const 
 xconv_status xconv_dx_exact_ws(const xconv_desc *desc, const void *dY_dev, const void *W_dev, void *dX_dev,
                                void *ws_dev, size_t ws_bytes, void *stream);
 
+/* Launch plan of xconv_conv_fwd (input_gradient 0) or xconv_dx_exact (1), with a workspace or without, for reports and
+ * tests (host only; 16-byte aligned tensors assumed).  Fills out[0..15] with launches, launches that weights are packed for, wave
+ * tile (10 * MT + NT), waves along the output channels, resident patches, 64-bit addresses, input read (0 elements, 1 pairs
+ * of columns, 2 channel units), paired stores, and of the class whose tiles touch most images: classes and images of its
+ * launch, output rows and columns, columns per strip, positions per tile, images per tile, LDS bytes. */
+xconv_status xconv_conv_plan_info(const xconv_desc *desc, int input_gradient, int with_ws, int32_t *out);
+
 /* Launch plan of the correlation kernel for op XCONV_OP_ESTIMATE or
  * XCONV_OP_EXACT, for reports and tests (host only).  Fills out[0..15] with
  * K-splits S, steps NS, rows per step RB, columns per step CW, waves along

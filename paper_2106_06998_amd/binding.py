@@ -93,6 +93,8 @@ def lib():
         L.xconv_dw_estimate_static.argtypes = [P, vp, vp, vp, vp, vp]
         L.xconv_static_scratch_bytes.restype = sz
         L.xconv_static_scratch_bytes.argtypes = []
+        L.xconv_conv_plan_info.restype = i32
+        L.xconv_conv_plan_info.argtypes = [P, i32, i32, vp]
         L.xconv_plan_info.restype = i32
         L.xconv_plan_info.argtypes = [P, i32, vp]
         L.xconv_xt_unpack.restype = i32
@@ -284,6 +286,16 @@ def xconv_plan_info(desc, op):
     out = (ctypes.c_int32 * 16)()
     _check(lib().xconv_plan_info(ctypes.byref(desc), int(op), ctypes.cast(out, ctypes.c_void_p)), "xconv_plan_info")
     return dict(zip(PLAN_FIELDS, [int(v) for v in out]))
+
+
+CONV_PLAN_FIELDS = ("launches", "pack_launches", "shape", "WM", "res", "big", "vec", "pair", "classes", "B", "Ho", "Wo", "SW", "TU", "images", "lds_bytes")
+
+
+def xconv_conv_plan_info(desc, input_gradient, with_ws=True):
+    out = (ctypes.c_int32 * 16)()
+    _check(lib().xconv_conv_plan_info(ctypes.byref(desc), int(input_gradient), int(with_ws), ctypes.cast(out, ctypes.c_void_p)),
+           "xconv_conv_plan_info")
+    return dict(zip(CONV_PLAN_FIELDS, [int(v) for v in out]))
 
 
 def xconv_xt_unpack(desc, Xt_dev, out_dev, stream=None):

@@ -24,6 +24,8 @@ namespace {
 
 constexpr int kLdsMax = 160 * 1024;
 constexpr long long kMaxPos = 1LL << 30;       // positions over the batch in one launch (32-bit tile arithmetic)
+constexpr long long kMaxReach = 0x7f000000;    // bytes a tile reads or writes from its first image on (32-bit offsets in a 2 GiB buffer descriptor)
+constexpr long long kMaxReachBig = 0xfffffffe; // elements of the same with 64-bit addresses (32-bit tables, all ones marks the outside)
 
 // see expected_cycles
 constexpr struct {
@@ -107,7 +109,8 @@ struct Work {
     int lds = 0;
 };
 
-// Lays one class out for tiles of TU of the TN positions on nst strips and adds up its work; false when the patch does not fit.
+// Lays one class out for tiles of TU of the TN positions on nst strips and adds up its work; false when the patch does not fit
+// or a tile's offsets from its first image would not.
 bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN, int lds_extra, Work &w)
 {
     const int es = elem_size(dtype), nks = ksteps(dtype, P.Cin), VW = P.vec == 1 ? 2 : 1;
@@ -120,6 +123,10 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     const bool rows = TU % SW == 0;              // tiles begin at the start of a row
     const int nr = (int)std::min<long long>(rows ? TU / SW : (SW + TU - 2) / SW + 1, NR);
     const int nb = rows && s.Ho % nr == 0 ? 0 : std::min(nr >= 2 ? (nr - 2) / s.Ho + 1 : 0, P.B - 1);
+    // (a strip takes a row of every image in turn: a narrow one of images with few rows crosses many of them)
+    s.images = nb + 1;
+    const long long reach = s.images * std::max(P.in_sb, P.out_sb);
+    if (P.big ? reach > kMaxReachBig : reach * es > kMaxReach) return false;
     const int NPR = std::max(1, (nr - 1) * s.sth + nb * std::max(0, s.kH - s.sth) + s.kH);
     const int PWl = (SW - 1) * s.stw + s.kW + (VW - 1);
     s.PWv = std::max(1, ceil_div(PWl, VW));
@@ -312,25 +319,29 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
         for (int i = 0; i < P.nsub; ++i) P.sub[i] = subs[s0 + i];
         for (int bb = 0; bb < d->B; bb += bstep) {
             P.B = std::min(bstep, d->B - bb);
-            // a tile reads the images of at most 512 positions: offsets from its first image fit a 2 GiB buffer descriptor
-            // unless a few images exceed that
-            const long long span = (512 / std::max(1, (Hout / P.osy) * (Wout / P.osx)) + 2) * std::max(P.in_sb, P.out_sb) * es;
-            P.big = span >= 0x7f000000LL;
-            P.vec = 0;
-            if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
-            bool pairs = !P.big && !nhwc && es == 2 && P.Wi % 2 == 0 && align % 4 == 0;
-            for (int i = 0; i < P.nsub; ++i) pairs = pairs && P.sub[i].kW >= P.sw;
-            if (pairs) P.vec = 1;
+            // 32-bit offsets where an image fits them and a tile layout does that keeps to few enough images (lay_out); 64-bit
+            // addresses otherwise.  Further runs take the kernel of the first, which the weights are packed for: what fits that
+            // many images fits fewer
+            const ConvLaunch *first = bb ? &out.launches.back() : nullptr;
             ConvLaunch L{};
-            L.P = P;
-            L.P.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
-            L.P.res = L.P.wp && P.Cin <= kConvResident;
-            if (!plan(L.P, d->dtype, ncu)) {
-                L.P.res = 0;
-                if (!plan(L.P, d->dtype, ncu)) return false;
+            bool found = false;
+            for (int big = first ? first->P.big : std::max(P.in_sb, P.out_sb) * es > kMaxReach; big <= 1 && !found; ++big) {
+                P.big = big;
+                P.vec = 0;
+                if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
+                bool pairs = !P.big && !nhwc && es == 2 && P.Wi % 2 == 0 && align % 4 == 0;
+                for (int i = 0; i < P.nsub; ++i) pairs = pairs && P.sub[i].kW >= P.sw;
+                if (pairs) P.vec = 1;
+                for (int res = first ? first->P.res : packed && !big && P.Cin <= kConvResident; res >= 0 && !found; --res) {
+                    L.P = P;
+                    L.P.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
+                    L.P.res = res;
+                    found = plan(L.P, d->dtype, ncu);
+                }
             }
+            if (!found) return false;
             // words of two outputs: channels-last, neighbouring channels; planes, neighbouring columns of an even strip of a unit-step class
-            L.P.pair = es == 2 && !P.big && oalign % 4 == 0 && (nhwc ? P.Cout % 2 == 0 : P.osx == 1 && Wout % 2 == 0);
+            L.P.pair = es == 2 && !L.P.big && oalign % 4 == 0 && (nhwc ? P.Cout % 2 == 0 : P.osx == 1 && Wout % 2 == 0);
             for (int i = 0; i < P.nsub && !nhwc; ++i) L.P.pair = L.P.pair && L.P.sub[i].SW % 2 == 0 && L.P.sub[i].TU % 2 == 0;
             L.in_off = (size_t)bb * P.in_sb * es;
             L.out_off = (size_t)bb * P.out_sb * es;
@@ -364,6 +375,25 @@ std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, b
 }
 
 }  // namespace
+
+bool conv_plan_info(const xconv_desc *d, int transposed, bool packed, int32_t *out)
+{
+    const auto p = conv_plan(d, transposed, packed, 16, 4);
+    if (!p) return false;
+    int npack = 0;
+    const ConvLaunch *worst = nullptr;
+    const ConvSub *cls = nullptr;
+    for (const ConvLaunch &L : p->launches) {
+        npack += L.pack;
+        for (int i = 0; i < L.P.nsub; ++i)
+            if (!cls || L.P.sub[i].images > cls->images) { worst = &L; cls = &L.P.sub[i]; }
+    }
+    const ConvParams &P = worst->P;
+    const int32_t v[16] = {(int32_t)p->launches.size(), npack, P.MT * 10 + P.NT, P.WM, P.res, P.big, P.vec, P.pair,
+                           P.nsub, P.B, cls->Ho, cls->Wo, cls->SW, cls->TU, cls->images, P.lds_bytes};
+    std::copy(v, v + 16, out);
+    return true;
+}
 
 // the jobs alone in a launch
 __global__ __launch_bounds__(kThreads) void side_jobs_kernel(const SideJobs J) { side_jobs<0, kThreads>(J, blockIdx.x, gridDim.x); }

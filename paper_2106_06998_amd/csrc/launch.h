@@ -110,6 +110,8 @@ struct ConvPlan;
 typedef std::shared_ptr<const ConvPlan> ConvPlanRef;
 // the plan of a product (kept between calls); null: no launch shape fits.  packed: there is a workspace
 ConvPlanRef find_conv_plan(const xconv_desc *d, int transposed, const void *in, const void *out, bool packed);
+// what xconv_conv_plan_info reports (host only)
+bool conv_plan_info(const xconv_desc *d, int transposed, bool packed, int32_t *out);
 // adds the packing of the weights to J, for a launch in front of launch_conv(packed = true); false: launch_conv packs by itself
 bool conv_pack_job(const ConvPlan &plan, const void *w, void *ws, SideJobs &J);
 hipError_t launch_conv(const ConvPlan &plan, const void *in, const void *w, const void *bias, void *out, void *ws, bool packed, hipStream_t st);

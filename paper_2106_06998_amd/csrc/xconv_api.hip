@@ -698,6 +698,14 @@ xconv_status xconv_dx_exact_ws(const xconv_desc *d, const void *dY_dev, const vo
     return conv_impl(d, 1, dY_dev, W_dev, nullptr, dX_dev, ws_dev, ws_bytes, stream);
 }
 
+xconv_status xconv_conv_plan_info(const xconv_desc *d, int input_gradient, int with_ws, int32_t *out)
+{
+    xconv_status s = xconv_check_desc(d);
+    if (s != XCONV_OK) return s;
+    if (!out) return XCONV_EINVAL;
+    return conv_plan_info(d, input_gradient != 0, with_ws != 0, out) ? XCONV_OK : XCONV_EUNSUPPORTED;
+}
+
 xconv_status xconv_plan_info(const xconv_desc *d, int op, int32_t *out)
 {
     xconv_status s = xconv_check_desc(d);

@@ -1,0 +1,62 @@
+"""Launch plans of the forward convolution and the input gradient on the host (no GPU): the byte offsets of a tile, which count
+from its first image, fit the descriptor (or, with 64-bit addresses, the 32-bit element tables) of the kernel that the plan takes,
+whatever the layer.  A tile of a strip of SW columns takes SW positions of every row, so it crosses TU / (Ho * SW) images."""
+import random
+
+import numpy as np
+import pytest
+
+from paper_2106_06998_amd import binding as xb
+
+# B, C_in, C_out, H, W, k, stride, pad, dtype, channels-last
+LARGE = [
+    (8, 256, 1024, 500, 500, 1, 1, 0, "bf16", True),       # one row of 250000 positions per image, 512 MB of output each
+    (8, 384, 192, 500, 500, 1, 1, 0, "f32", True),
+    (8, 16, 1024, 512, 512, 1, 1, 0, "bf16", True),
+    (64, 8, 512, 512, 512, 1, 1, 0, "f16", False),
+    (16, 192, 192, 4, 50000, 3, 1, 1, "f32", False),       # few long rows
+    (40, 512, 512, 28, 602, 4, 5, 0, "f32", False),        # few output rows and large images
+    (3, 64, 8, 4000, 4000, 3, 1, 1, "f16", False),         # one image is past the descriptor
+    (300, 2000, 2000, 1, 5000, 1, 1, 0, "f32", True),
+]
+
+
+def offsets_fit(case):
+    B, C_in, C_out, H, W, k, s, p, dtype, nhwc = case
+    Ho, Wo, es = (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1, 4 if dtype == "f32" else 2
+    d = xb.make_desc(B, C_in, C_out, H, W, k, s, p, 1, dtype, layout=xb.XCONV_NHWC if nhwc else xb.XCONV_NCHW)
+    assert xb.xconv_check_desc(d) == xb.XCONV_OK
+    image = max(C_in * H * W, C_out * Ho * Wo)
+    for transposed in (0, 1):
+        for ws in (0, 1):
+            v = xb.xconv_conv_plan_info(d, transposed, ws)
+            rows = v["B"] * v["Ho"]
+            first = np.arange(min(-(-rows * v["SW"] // v["TU"]), 1 << 18), dtype=np.int64) * v["TU"]
+            last = np.minimum((first + v["TU"] - 1) // v["SW"], rows - 1)
+            images = int(np.max(last // v["Ho"] - first // v["SW"] // v["Ho"])) + 1
+            assert images <= v["images"], (case, transposed, ws, v)
+            reach = images * image
+            assert reach < 2 ** 32 - 1 if v["big"] else reach * es < 2 ** 31, (case, transposed, ws, reach, v)
+            assert v["lds_bytes"] <= 160 * 1024
+            assert v["big"] or image * es < 2 ** 31
+
+
+@pytest.mark.parametrize("case", LARGE, ids=["-".join(str(v) for v in c) for c in LARGE])
+def test_offsets_of_a_tile_fit_large_layers(case):
+    offsets_fit(case)
+
+
+def test_offsets_of_a_tile_fit_drawn_layers():
+    rng = random.Random(5)
+    n = 0
+    while n < 150:
+        k = rng.choice([1, 1, 1, 2, 3, 4, 5, 7])
+        s = rng.choice([1, 1, 1, 2, 3, 5])
+        H, W = int(2 ** rng.uniform(0, 12)), int(2 ** rng.uniform(3, 16))
+        C_in, C_out = int(2 ** rng.uniform(0, 11)), int(2 ** rng.uniform(0, 11))
+        p = rng.choice([0, k // 2])
+        Ho, Wo = (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1
+        if H + 2 * p < k or W + 2 * p < k or max(C_in * H * W, C_out * Ho * Wo) >= 2 ** 31 or max(C_in * H * W, C_out * Ho * Wo) < 2 ** 22:
+            continue
+        n += 1
+        offsets_fit((rng.choice([2, 5, 16, 64, 300]), C_in, C_out, H, W, k, s, p, rng.choice(["f32", "bf16", "f16"]), rng.random() < 0.5))
