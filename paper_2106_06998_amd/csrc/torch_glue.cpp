@@ -18,6 +18,7 @@ namespace {
 using at::Tensor;
 
 struct Lib {
+    decltype(&xconv_check_desc) check_desc;
     decltype(&xconv_xt_bytes) xt_bytes;
     decltype(&xconv_workspace_bytes) workspace_bytes;
     decltype(&xconv_conv_workspace_bytes) conv_workspace_bytes;
@@ -168,6 +169,8 @@ PyObject *layer_forward(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             d.stride_h = (int)v[0]; d.stride_w = (int)v[1]; d.pad_h = (int)v[2]; d.pad_w = (int)v[3];
             d.r = (int)v[4]; d.probe = (int)v[5]; d.dtype = dtype_code(x.scalar_type()); d.layout = layout;
             d.seed = (uint64_t)v[7];
+            // before anything is computed from it (a stride of 0, an empty output); what the library does not support is reported below
+            if (L.check_desc(&d) == XCONV_EINVAL) throw Failed{XCONV_EINVAL, "xconv_check_desc"};
             Tensor w, b;
             // the kernel reads one bias per output channel in the storage type; any other bias (a float32 one of a half-precision
             // layer, say) is added behind it
@@ -370,6 +373,7 @@ PyObject *glue_init(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         f = reinterpret_cast<std::remove_reference_t<decltype(f)>>(dlsym(h, name));
         if (!f) missing = name;
     };
+    get(L.check_desc, "xconv_check_desc");
     get(L.xt_bytes, "xconv_xt_bytes");
     get(L.workspace_bytes, "xconv_workspace_bytes");
     get(L.conv_workspace_bytes, "xconv_conv_workspace_bytes");

@@ -1,5 +1,9 @@
 """Host-side behaviour of the drop-in layer: construction, argument checks, conversion of a network,
 and a loud refusal to estimate without a GPU (there is no CPU fallback)."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -34,6 +38,27 @@ def test_layer_refuses_to_estimate_on_the_cpu():
     layer = XConv2d(8, 4, 3, r=4, padding=1)
     with pytest.raises(RuntimeError, match="GPU only"):
         layer(torch.randn(2, 8, 6, 6))
+
+
+def test_native_forward_refuses_what_no_convolution_is():
+    # in a process of its own: a division by such a stride would end it
+    code = """
+import torch
+from paper_2106_06998_amd import binding as xb, layer
+x, w = torch.zeros(2, 8, 6, 6), torch.zeros(4, 8, 3, 3)
+for stride, pad in (((0, 1), (1, 1)), ((1, 0), (1, 1)), ((-1, 1), (1, 1)), ((1, 1), (-1, 0)), ((1, 1), (-3, -3))):
+    for own, state in ((True, True), (True, False), (False, True)):
+        try:
+            layer._glue().forward(x, w, None, *stride, *pad, 4, xb.PROBES["rademacher"], 0, 1, own, state, 0)
+        except xb.XConvError as e:
+            assert e.status == xb.XCONV_EINVAL
+        else:
+            raise SystemExit("accepted: %s %s" % (stride, pad))
+print("refused")
+"""
+    p = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert p.returncode == 0 and "refused" in p.stdout, (p.returncode, p.stdout)
 
 
 def test_convert_net_replaces_only_what_the_layer_supports():
