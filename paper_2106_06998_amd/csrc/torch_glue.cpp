@@ -7,8 +7,10 @@
 
 #include <ATen/ATen.h>
 #include <c10/core/DeviceGuard.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
 #include <string>
 
 #include "../../include/xconv.h"
@@ -86,10 +88,11 @@ void *ptr(const Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
                              std::to_string(d.W) + ", r=" + std::to_string(d.r) + ")");
 }
 
-// One Python call: unpacks, runs `body` without the interpreter lock, turns failures into Python errors.
+// One Python call: runs `body` without the interpreter lock, turns failures into Python errors: a status of the library into
+// XConvError, everything else into what torch makes of it (torch.OutOfMemoryError for an allocation, say)
 template <class F> bool run(F &&body)
 {
-    std::string what;
+    std::exception_ptr other;
     int status = -1;
     const char *where = "";
     Py_BEGIN_ALLOW_THREADS
@@ -100,8 +103,8 @@ template <class F> bool run(F &&body)
     } catch (const Failed &f) {
         status = f.status;
         where = f.where;
-    } catch (const std::exception &e) {
-        what = e.what();
+    } catch (...) {
+        other = std::current_exception();
     }
     Py_END_ALLOW_THREADS
     if (status == 0) return true;
@@ -112,7 +115,7 @@ template <class F> bool run(F &&body)
             Py_DECREF(e);
         }
     } else {
-        PyErr_SetString(PyExc_RuntimeError, what.c_str());
+        torch::translate_exception_to_python(other);
     }
     return false;
 }
