@@ -95,7 +95,9 @@ class _XConvFunction(torch.autograd.Function):
         want_dx, want_dw, want_db = ctx.needs_input_grad[0], ctx.has_state and ctx.needs_input_grad[1], ctx.has_bias and ctx.needs_input_grad[2]
         native = dy.is_cuda and dy.dtype in _DTYPE
         # exact input gradient (Sec. 2: backpropagation through the layer stays exact) and bias gradient on the library's kernels
-        own_dx, own_db = want_dx and ctx.own and dy.dtype == weight.dtype, want_db and native and (ctx.own or ctx.has_state)
+        # (a bias gradient that carries a graph itself, under create_graph=True, is the framework's sum)
+        own_dx = want_dx and ctx.own and dy.dtype == weight.dtype
+        own_db = want_db and native and (ctx.own or ctx.has_state) and not torch.is_grad_enabled()
         dx = dw = db = None
         if own_dx or want_dw or own_db:
             dx, dw, db = _glue().backward(dy, weight, saved[1] if want_dw else None, ctx.desc, ctx.mode, own_dx, want_dw, own_db,
