@@ -333,15 +333,25 @@ SliceMap vol_map(const xconv3d_desc *v, const Vol &g)
     sm.run = g.run;
     return sm;
 }
-// The producer/consumer kernels read the caller's dY [B, C_out, Do, H'*W'] in place (depth slots of volumes,
-// WsParams::vol_*) when its byte offsets fit; otherwise dY is first copied into slice-major planes.
+// What the depth-slot table of the producer/consumer kernels addresses (WsParams::vol_*): byte offsets of dY and depth slices
+bool vol_table_fits(const Vol &g, long long bytes)
+{
+    const char *v = getenv("XCONV_VOL_TABLE_BYTES");   // tests: a smaller limit
+    return bytes <= (v ? atoll(v) : 1LL << 30) && g.B2 < (1LL << 22);
+}
+long long vol_dy_bytes(const xconv_desc *d, const CorrParams &P, long long slices)
+{
+    return slices * d->C_out * P.Ho * P.Wo * (long long)elem_bytes(d->dtype);
+}
+// The producer/consumer kernels read the caller's dY [B, C_out, Do, H'*W'] in place (depth slots of volumes) when its byte
+// offsets fit the table; otherwise dY is first copied into slice-major planes.
 bool vol_dy_in_place(const xconv3d_desc *v, const Vol &g, PlanEntry &E, const void *dY_dev)
 {
     const xconv_desc *d = &v->l;
     const char *force_copy = getenv("XCONV_VOL_COPY");   // tests: take the copy route also where in-place reads fit
     if (E.ws == 0 || d->layout != XCONV_NCHW || !aligned16(dY_dev) || (force_copy && *force_copy == '1')) return false;
-    const long long bytes = (long long)d->B * d->C_out * g.Do * E.P.Ho * E.P.Wo * (long long)elem_bytes(d->dtype);
-    if (bytes > (1LL << 30) || g.B2 >= (1LL << 22)) return false;
+    const long long bytes = vol_dy_bytes(d, E.P, (long long)d->B * g.Do);
+    if (!vol_table_fits(g, bytes)) return false;
     E.Wp.vol_period = g.period;
     E.Wp.vol_Do = g.Do;
     E.Wp.vol_bytes = (uint32_t)bytes;
@@ -363,13 +373,21 @@ bool vol_plan(PlanEntry &E, const xconv3d_desc *v, int CS)
     const xconv_desc *d = &v->l;
     const Vol g = vol_of(v);
     if (g.B2 > 0x7fffffffLL) return false;
-    return get_plan(E, d->dtype, (int)g.B2, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CS, true, v->kD, false);
+    auto plan = [&](int nsets) {
+        return get_plan(E, d->dtype, (int)g.B2, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CS, true, nsets, false);
+    };
+    if (!plan(v->kD)) return false;
+    // one launch over all kernel-depth offsets shares the chip between them; where neither dY nor its copy fits the table that
+    // such a launch needs, each offset has a launch, and the splits that fill the chip, to itself
+    if (!E.ws || v->kD == 1 || vol_table_fits(g, vol_dy_bytes(d, E.P, g.B2)) ||
+        (d->layout == XCONV_NCHW && vol_table_fits(g, vol_dy_bytes(d, E.P, (long long)d->B * g.Do))))
+        return true;
+    return plan(1);
 }
 
 // All kernel-depth offsets of a volumetric layer in one launch: offset kz pairs slice 0 of dY with slice kz / sd of run kz % sd
-// of A, and
-// writes its S partial tiles behind those of kz - 1
-xconv_status vol_correlate(PlanEntry &E, int dtype, const Vol &g, int kD, const void *A, size_t slice_bytes, float *part, hipStream_t st)
+// of A, and writes its S partial tiles behind those of kz - 1
+xconv_status vol_correlate(PlanEntry &E, const xconv_desc *d, const Vol &g, int kD, const void *A, size_t slice_bytes, float *part, hipStream_t st)
 {
     CorrParams &P = E.P;
     P.A = E.Wp.A = A;
@@ -380,19 +398,19 @@ xconv_status vol_correlate(PlanEntry &E, int dtype, const Vol &g, int kD, const 
     P.set_slice = E.Wp.set_slice = (long long)slice_bytes;
     E.Wp.dY = P.dY;
     if (!E.ws) {
-        XC_LAUNCH(K_CORR, st, launch_corr(dtype, P, st));
+        XC_LAUNCH(K_CORR, st, launch_corr(d->dtype, P, st));
         return XCONV_OK;
     }
     if (E.Wp.vol_period == 0) {
         // a slice-major copy of dY: the same table, every slice a volume of its own
-        const long long bytes = (long long)g.B2 * P.C_out * P.Ho * P.Wo * (long long)elem_bytes(dtype);
-        if (bytes <= (1LL << 30) && g.B2 < (1LL << 22)) {
+        const long long bytes = vol_dy_bytes(d, P, g.B2);
+        if (vol_table_fits(g, bytes)) {
             E.Wp.vol_period = E.Wp.vol_Do = 1;
             E.Wp.vol_bytes = (uint32_t)bytes;
         }
     }
     if (E.Wp.vol_period != 0) {
-        XC_LAUNCH(K_CORR, st, launch_ws_plan(dtype, E, st));
+        XC_LAUNCH(K_CORR, st, launch_ws_plan(d->dtype, E, st));
         return XCONV_OK;
     }
     // beyond the table's offsets: a launch per kernel-depth offset
@@ -400,7 +418,7 @@ xconv_status vol_correlate(PlanEntry &E, int dtype, const Vol &g, int kD, const 
     for (int kz = 0; kz < kD; ++kz) {
         E.Wp.A = static_cast<const char *>(A) + (size_t)(kz % g.sd) * g.run * slice_bytes + (size_t)(kz / g.sd) * slice_bytes;
         E.Wp.part = part + (size_t)kz * P.S * (vol_tile_bytes(P) / sizeof(float));
-        XC_LAUNCH(K_CORR, st, launch_ws_plan(dtype, E, st));
+        XC_LAUNCH(K_CORR, st, launch_ws_plan(d->dtype, E, st));
         E.Wp.zout = nullptr;
     }
     return XCONV_OK;
@@ -846,7 +864,7 @@ xconv_status xconv3d_dw_estimate(const xconv3d_desc *v, const void *dY_dev, cons
         P.zdist = E.Wp.zdist = probe_code(d);
         P.zseed = E.Wp.zseed = d->seed;
     }
-    s = vol_correlate(E, d->dtype, g, v->kD, Xt_dev, g.slice_bytes, part0, st);
+    s = vol_correlate(E, d, g, v->kD, Xt_dev, g.slice_bytes, part0, st);
     if (s != XCONV_OK) return s;
     // one reduction for all kernel-depth offsets; its spare workgroups redraw Z[s] for the expansion
     P.part = part0;
@@ -901,7 +919,7 @@ xconv_status xconv3d_dw_exact(const xconv3d_desc *v, const void *dY_dev, const v
         P.dY = dy_slices;
     }
     float *part0 = reinterpret_cast<float *>(ws + xb);
-    s = vol_correlate(E, d->dtype, g, v->kD, ws, xslice, part0, st);
+    s = vol_correlate(E, d, g, v->kD, ws, xslice, part0, st);
     if (s != XCONV_OK) return s;
     P.part = part0;
     if (reduce_expand_fused(P, false, true, d->C_in, d->r, 0)) {

@@ -115,6 +115,14 @@ def test_volumetric_layers_through_the_dy_copy(e, monkeypatch):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("nhwc", [False, True], ids=["planes", "channels-last"])
+@pytest.mark.parametrize("e", [VOL[0], VOL[2], VOL[7], VOL[14], VOL[16]], ids=[VOL[i][0] for i in (0, 2, 7, 14, 16)])
+def test_volumes_beyond_the_offset_table(e, nhwc, monkeypatch):
+    # a launch per kernel-depth offset, as volumes with more than 1 GiB of dY take
+    monkeypatch.setenv("XCONV_VOL_TABLE_BYTES", "1")
+    run_volume(e, nhwc)
+
+
 @pytest.mark.parametrize("fused", ["0", "1"], ids=["two-launches", "one-launch"])
 def test_volumetric_second_pass_routes(fused, monkeypatch):
     monkeypatch.setenv("XCONV_FUSED_PASS2", fused)

@@ -192,6 +192,22 @@ def test_volumetric_descriptor_and_sizes():
     assert L.xconv3d_xt_unpack(p, None, one, None) == xb.XCONV_EINVAL
 
 
+def test_large_volumes_split_every_launch_over_the_chip(monkeypatch):
+    # dY beyond the offset table (1 GiB): a launch per kernel-depth offset, each with the splits of a launch of its own
+    def partial_tiles(v, r, C_out, kD, slots, plane, es):
+        tile = 9 * r * C_out * 4                         # kernel offsets in the plane, columns, output channels
+        free = xb.xconv3d_workspace_bytes(v, xb.XCONV_OP_ESTIMATE) - v.l.C_in * r * 4 - kD * tile - slots * C_out * plane * es
+        return free // tile // kD
+
+    for dtype, es, B, C, n, r, enough in (("f16", 2, 8, 128, 96, 32, 192), ("f16", 2, 2, 128, 160, 32, 192), ("f32", 4, 4, 64, 128, 16, 192)):
+        v = xb.make_desc3d(B, C, C, n, n, n, 3, 1, 1, r=r, dtype=dtype)
+        assert partial_tiles(v, r, C, 3, B * (n + 1), n * n, es) >= enough
+    small = xb.make_desc3d(1, 128, 128, 48, 48, 48, 3, 1, 1, r=32, dtype="f16")
+    joint = partial_tiles(small, 32, 128, 3, 49, 48 * 48, 2)
+    monkeypatch.setenv("XCONV_VOL_TABLE_BYTES", "1")
+    assert 2 * joint < partial_tiles(small, 32, 128, 3, 49, 48 * 48, 2) <= 256
+
+
 def test_pixel_probe_sizes_and_argument_checks():
     d = _good()                                            # B=4, C_in=16, 32x32, r=8, fp32
     assert xb.xconv_pixel_xbar_bytes(d) == 4 * 8 * 4
