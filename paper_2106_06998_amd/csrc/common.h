@@ -333,7 +333,7 @@ __device__ inline int xcd_block(int b, int grid)
 
 // ---- forward convolution / exact input gradient as implicit GEMMs (conv_core.h, conv_kernels.hip) ----
 constexpr int kConvUnits = 8;   // 16-byte units of channels per staged chunk
-constexpr int kConvGatherM = 64;   // most output channels of a tile whose weights are gathered (no workspace)
+constexpr int kConvGatherM = 64;   // output channels that a group of kConvUnits / 2 k-steps of gathered weights covers (no workspace)
 constexpr int kConvResident = 128;   // most contraction channels whose whole patch is kept in LDS
 constexpr int kConvOverread = 4096; // bytes behind the packed weights that the last requests may touch
 constexpr int kConvSubs = 4;    // classes of output positions per launch

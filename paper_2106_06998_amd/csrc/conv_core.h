@@ -22,7 +22,8 @@
 //         (two LDS buffers, one barrier per chunk).
 // Strided layers keep the patch columns split by their remainder modulo the stride, so that the lanes' reads stay consecutive.
 // Weights come packed in fragment order (pack_fragment, one coalesced kilobyte per fragment, read through the L1 by
-// every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, tap by tap.
+// every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, a group of k-steps at a time; patches are
+// then chunks, as many units of one as there are channels for.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -76,8 +77,8 @@ constexpr uint32_t kConvOob = 0x80000000u;   // byte offset past every buffer de
 // SWAP: output positions in the rows of the accumulator tile (channels-last output: lanes along the channels), else in its columns.
 // MULTI: several classes in one launch (an index into the argument struct that is not a constant makes the compiler load every
 //      argument where it is used: a launch of one class does without).
-// PACKED: weights in fragment order.  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI>
+// PACKED: weights in fragment order; else GW waves along the output channels (P.WM).  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI, int GW>
 __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvParams P)
 {
     typedef typename ConvElem<DT>::t elem_t;
@@ -108,13 +109,13 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int TN = 32 * NT * WN;
     const int npp_max = S.NPPmax;
     const int nks = (P.Cin + 2 * UE - 1) / (2 * UE);                            // k-steps of all channels
-    const int NU = RES ? 2 * nks : kConvUnits;                                  // units of a staged patch
-    uint4 *patch = conv_lds;                                                    // [RES ? 1 : 2][NU][NPOS]
-    const int patch_units = (RES ? 1 : 2) * NU * S.NPOS;
+    const int NU = RES ? 2 * nks : PACKED ? kConvUnits : std::min(2 * nks, kConvUnits);   // units of a staged patch
+    uint4 *patch = conv_lds;                                                    // [1 or 2][NU][NPOS]
+    const int patch_units = (RES || (!PACKED && nks <= KS) ? 1 : 2) * NU * S.NPOS;
     uint2 *ptab = reinterpret_cast<uint2 *>(conv_lds + patch_units);             // [NPPmax] {source byte offset, LDS positions}
     uint2 *otab = ptab + npp_max;                                               // [TN] {output offset, LDS position of tap (0, 0)}
     uint4 *stab = conv_lds + patch_units + (npp_max + TN + 1) / 2;           // PACKED: LDS offsets of the k-steps' fragments, two lists
-    uint4 *alds = stab;                                                         // !PACKED: [2][KS][MT * WM][64] weight fragments of a tap
+    uint2 *gtab = reinterpret_cast<uint2 *>(stab);                              // !PACKED: per k-step {LDS offset | step of its tap, weight offset}, two lists
 
     // ---- the tile: positions q0 .. q0 + TU - 1 of this strip (TU < TN where the patch of TN would not fit into LDS), rows R0 .. R1 counted over the batch
     const int TU = S.TU, NR = P.B * S.Ho;
@@ -168,6 +169,18 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     // for the last chunk.  One 16-byte read serves four steps, so the loop over the steps has no index arithmetic of its own.
     const int nks_last = RES ? nks : nks - (nck - 1) * KS;
     const int n_full = taps * (RES ? nks : KS), n_last = taps * nks_last;
+    const int cap0 = !PACKED && nck > 1 ? (n_full + 7) / 8 * 8 : 0, cap1 = (n_last + 7) / 8 * 8;   // !PACKED: entries of the lists, whole groups
+    uint4 *alds = stab + (cap0 + cap1) / 2;                                     // !PACKED: [2][steps of a group][MT * WM][64] weight fragments
+    if constexpr (!PACKED) {
+        for (int i = tid; i < cap0 + cap1; i += kThreads) {
+            const int list = i >= cap0 ? 1 : 0, k = i - list * cap0, ks = k / taps, tap = k - ks * taps;
+            int ky, kx;
+            S.dkW.divmod(tap, ky, kx);
+            gtab[i] = ks < (list ? nks_last : KS) ? uint2{(uint32_t)((tap_offset(ky, kx) + 2 * ks * S.NPOS) * 16 + ks),
+                                                  (uint32_t)((S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs + ks * 2 * UE * P.w_sci)}
+                                          : uint2{0, kConvOob};
+        }
+    }
     if constexpr (PACKED) {
         int *t = reinterpret_cast<int *>(stab);
         const int cap = conv_step_list(taps, RES ? nks : KS) * 4;
@@ -290,37 +303,60 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         }
     }
     const uint32_t lane16 = (uint32_t)lane * 16u;
-    // without packed weights the workgroup gathers a tap's fragments (32*MT*WM output channels x CK channels) through LDS, the
-    // elements of the next tap on their way in registers; the lanes run along whichever channel index has the smaller stride
+    // Without packed weights the workgroup gathers the fragments of a group of k-steps through LDS, one barrier each, the elements
+    // of the next group on their way in registers.  A group has as many steps as 4096 (fp32: 2048) elements make, 16 (8) for each
+    // thread: 8 for a tile of 32 output channels, 2 for 128.  The steps of a chunk run through the kernel offsets of one pair of
+    // units, then of the next: the weights of a channel lie next to each other, and a layer of few channels fills its groups with
+    // several offsets.  (A group per kernel offset, for chunks of kConvUnits units whatever the channels: 3 -> 64 channels 7x7 at
+    // stride 4, 224x224, batch 16, bf16, took 1970 us, now 43; 16 -> 16 channels 3x3, 32x32, batch 4, fp32, 21 us, now 9.8.)
     constexpr int NEL = PACKED ? 1 : kConvGatherM * CK / kThreads;
     elem_t wg[NEL];
     const elem_t *wraw = static_cast<const elem_t *>(P.w);
-    const int TMW = 32 * MT * P.WM, co_t = mtile * TMW;
-    auto gather_at = [&](int i, int &cl, int &col) {
-        const int idx = tid + kThreads * i;
-        if (P.w_sci < P.w_sco) { cl = idx & (CK - 1); col = idx / CK; }
-        else { col = idx & (TMW - 1); cl = idx / TMW; }
-        return cl < CK && col < TMW;
-    };
-    auto gather_load = [&](int c0, int tap) {
-        const int ky = tap / S.kW, kx = tap - ky * S.kW;
-        const int o = (S.ky0 + ky * S.kys) * P.kWfull + S.kx0 + kx * S.kxs;
+    constexpr int TMW = 32 * MT * GW, KG = std::max(1, KS * kConvGatherM / TMW), SG = std::min(KS, KG);   // output channels of the tile, k-steps of a group and of a block
+    const int co_t = mtile * TMW;
+    const bool along = !P.rev;    // lanes along the inner channel index of the weights: the contraction channels, or (input gradient) the output channels
+    // element i of a thread: output channel gc + i * gcs of the tile or, the other way round, channel gk + i * gks of the group's
+    // steps; both divide 32 and 2 * UE, so that an offset is the thread's own plus one of the element.  Channels past the last of
+    // the outer index lie behind the end of the weights, where the descriptor ends; those of the inner one are masked
+    const int gk = along ? tid & (KG * 2 * UE - 1) : tid / TMW, gc = along ? tid / (KG * 2 * UE) : tid & (TMW - 1);
+    constexpr int gks = kThreads / TMW, gcs = kThreads / (KG * 2 * UE);
+    const uint32_t gw = ((uint32_t)(along ? gk % (2 * UE) : gk) * (uint32_t)P.w_sci + (uint32_t)gc * (uint32_t)P.w_sco) * ES;
+    const int gd = ((along ? gk / (2 * UE) : 0) * MT * GW * 64 + (IL ? gk & 1 : gk / UE % 2) * 32 + gc / 32 * 64 + gc % 32) * UE +
+                   (IL ? gk % (2 * UE) / 2 : gk % UE);
+    auto gather_load = [&](const uint2 *list, int c0, int g) {
+        const size_t first = (size_t)c0 * P.w_sci + (size_t)co_t * P.w_sco, all = std::max((size_t)P.w_sci * P.Cin, (size_t)P.w_sco * P.Cout);
+        const auto wsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<elem_t *>(wraw + first), 0,
+                                                            (int)std::min((all - first) * ES, (size_t)kConvOob - 1), 0x00020000);
+        auto load = [&](uint32_t off) -> elem_t {
+            if constexpr (ES == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wsrc, (int)off, 0, 0));
+            else return (elem_t)__builtin_amdgcn_raw_buffer_load_b16(wsrc, (int)off, 0, 0);
+        };
+        if (along) {
+            const uint2 e = list[g * KG + gk / (2 * UE)];
+            const bool on = e.y != kConvOob && c0 + (int)(e.x & 15u) * 2 * UE + gk % (2 * UE) < P.Cin;
+            const uint32_t off = on ? gw + e.y * ES : kConvOob;
 #pragma unroll
-        for (int i = 0; i < NEL; ++i) {
-            int cl, col;
-            wg[i] = elem_t(0);
-            if (gather_at(i, cl, col) && co_t + col < P.Cout && c0 + cl < P.Cin)
-                wg[i] = wraw[(size_t)(co_t + col) * P.w_sco + (size_t)(c0 + cl) * P.w_sci + o];
+            for (int i = 0; i < NEL; ++i) wg[i] = load(off + (uint32_t)(i * gcs) * (uint32_t)P.w_sco * ES);
+        } else {
+            const uint32_t off = co_t + gc < P.Cout ? gw : kConvOob;
+#pragma unroll
+            for (int i = 0; i < NEL; ++i) {
+                const uint32_t o = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[g * KG + i * gks / (2 * UE)].y);
+                wg[i] = load(o == kConvOob ? kConvOob : off + (o + (uint32_t)(i * gks % (2 * UE)) * (uint32_t)P.w_sci) * ES);
+            }
         }
     };
     auto gather_write = [&](int buf) {
-        elem_t *d = reinterpret_cast<elem_t *>(alds + (size_t)buf * KS * MT * P.WM * 64);
+        elem_t *d = reinterpret_cast<elem_t *>(alds + buf * KG * MT * GW * 64) + gd;
+        if (along) {
 #pragma unroll
-        for (int i = 0; i < NEL; ++i) {
-            int cl, col;
-            if (gather_at(i, cl, col)) {
-                const int hh = IL ? cl & 1 : cl / UE & 1, e = IL ? cl % (2 * UE) / 2 : cl % UE;
-                d[(((cl / (2 * UE)) * MT * P.WM + col / 32) * 64 + hh * 32 + col % 32) * UE + e] = wg[i];
+            for (int i = 0; i < NEL; ++i) d[(i * gcs / 32 * 64 + i * gcs % 32) * UE] = wg[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < NEL; ++i) {
+                constexpr int W = 2 * UE;
+                const int x = i * gks % W;
+                d[(i * gks / W * MT * GW * 64 + (IL ? 0 : x / UE) * 32) * UE + (IL ? x / 2 : x % UE)] = wg[i];
             }
         }
     };
@@ -387,7 +423,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             load_a(std::integral_constant<int, 1>{});
             load_a(std::integral_constant<int, 2>{});
         } else {
-            gather_load(0, 0);
+            gather_load(nck > 1 ? gtab : gtab + cap0, 0, 0);
             gather_write(0);
         }
         for (int ph = 0; ph < nphase; ++ph) {
@@ -419,30 +455,38 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             for (int ck = 0; ck < nck; ++ck) {
                 const int c0 = ck * CK;
                 const bool more = ck + 1 < nck;
-                const int base = (ck & 1) * NU * S.NPOS * 16;
-                int tap = 0, ky = 0, kx = 0;
+                const int base = (ck & 1) * NU * S.NPOS * 16, n = more ? n_full : n_last, ng = (n + KG - 1) / KG;
+                const uint2 *list = more ? gtab : gtab + cap0;
+                int g = 0;
                 for (int ph = 0; ph < nphase; ++ph) {
                     if (more) stage_load(c0 + CK, ph);
-                    const int tend = taps * (ph + 1) / nphase;
-                    for (; tap < tend; ++tap) {
-                        const bool next = tap + 1 < taps || more;
-                        if (next) gather_load(tap + 1 < taps ? c0 : c0 + CK, tap + 1 < taps ? tap + 1 : 0);
-                        const int toff = tap_offset(ky, kx);
+                    for (const int gend = ng * (ph + 1) / nphase; g < gend; ++g) {
+                        const bool next = g + 1 < ng || more;
+                        if (g + 1 < ng) gather_load(list, c0, g + 1);
+                        else if (more) gather_load(ck + 2 < nck ? gtab : gtab + cap0, c0 + CK, 0);
+                        for (int q = 0; q < KG; q += SG) {
+                            const int left = n - (g * KG + q);      // (a step past the last has weights of zero, but the patch may hold infinities)
+                            const uint2 *l = list + g * KG + q;
+                            const u32x4c *af = reinterpret_cast<const u32x4c *>(alds) + ((abuf * KG + q) * GW + wm) * MT * 64 + lane;
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
+                            for (int j = 0; j < SG; ++j)
 #pragma unroll
-                            for (int mt = 0; mt < MT; ++mt)
-                                a[s][mt] = reinterpret_cast<const u32x4c *>(alds)[((abuf * KS + s) * MT * P.WM + wm * MT + mt) * 64 + lane];
-                            load_b(std::integral_constant<int, 0>{}, base + (toff + 2 * s * S.NPOS) * 16);
-                            if (s == 0) multiply(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
-                            if (s == 1) multiply(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
-                            if (s == 2) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
-                            if (s == 3) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, 0>{});
+                                for (int mt = 0; mt < MT; ++mt) a[j][mt] = af[(j * GW * MT + mt) * 64];
+                            auto off = [&](int j) { return base + (int)(l[j].x & ~15u); };
+                            load_b(std::integral_constant<int, 0>{}, off(0));
+                            load_b(std::integral_constant<int, 1>{}, off(1));
+                            if (left > 0) multiply(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+                            if constexpr (SG > 2) load_b(std::integral_constant<int, 0>{}, off(2));
+                            if (left > 1) multiply(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+                            if constexpr (SG > 2) {
+                                load_b(std::integral_constant<int, 1>{}, off(3));
+                                if (left > 2) multiply(std::integral_constant<int, 2>{}, std::integral_constant<int, 0>{});
+                                if (left > 3) multiply(std::integral_constant<int, 3>{}, std::integral_constant<int, 1>{});
+                            }
                         }
                         abuf ^= 1;
                         if (next) gather_write(abuf);
                         __syncthreads();
-                        if (++kx == S.kW) { kx = 0; ++ky; }
                     }
                     if (more) stage_write((ck + 1) & 1, ph);
                 }
@@ -542,10 +586,10 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     }
 }
 
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI>
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI, int GW>
 static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
 {
-    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI>);
+    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI, GW>);
     if (P.lds_bytes > 64 * 1024) {
         static bool attr_set[64] = {};   // per device; a repeated call only sets it again
         int dev = 0;
@@ -556,16 +600,16 @@ static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
             if (dev >= 0 && dev < 64) attr_set[dev] = true;
         }
     }
-    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
+    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI, GW>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
                        (unsigned)P.lds_bytes, st, P);
     return hipGetLastError();
 }
 
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false>
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false, int GW = 1>
 static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
 {
-    if (P.nsub == 1) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, false>(P, st);
-    return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, true>(P, st);
+    if (P.nsub == 1) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, false, GW>(P, st);
+    return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, true, GW>(P, st);
 }
 
 template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const ConvParams &P, hipStream_t st)
@@ -589,6 +633,8 @@ template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const 
     }
     if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, false>(P, st);
     if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, false, false>(P, st);
+    if (P.WM == 4) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 4>(P, st);
+    if (P.WM == 2) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 2>(P, st);
     return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false>(P, st);
 }
 

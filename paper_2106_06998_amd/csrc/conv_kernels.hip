@@ -36,7 +36,8 @@ constexpr struct {
     double chunk, overlap;       // k-steps per overlapping step, how completely steps overlap
     double start;                // cycles per round
     double alone, pair;          // surcharges for one and two workgroups per unit
-} kConvModel = {0.58, 0.465, 0.55, 0.575, 1.0, 367, 30.7, 15.1, 16, 0.634, 13900, 1.5, 0.145};
+    double gather;               // cycles per gathered group of k-steps
+} kConvModel = {0.58, 0.465, 0.55, 0.575, 1.0, 367, 30.7, 15.1, 16, 0.634, 13900, 1.5, 0.145, 600};
 
 int env_value(const char *name)
 {
@@ -92,18 +93,24 @@ long long packed_units(const ConvSub &s, int dtype, int Cin, int Cout)
     return (long long)ceil_div(Cout, 32) * ksteps(dtype, Cin) * s.kH * s.kW * 64;
 }
 
-// LDS of a workgroup: patch, tables, step lists (conv_kernel's layout; gathered weights come on top)
+// LDS of a workgroup: patch, tables, lists of the k-steps, gathered weights (conv_kernel's layout)
 long long conv_lds(const ConvParams &P, const ConvSub &c, int TN, int nks)
 {
+    constexpr int KS = kConvUnits / 2;
     const int taps = c.kH * c.kW;
-    return (P.res ? 2LL * nks : 2LL * kConvUnits) * c.NPOS * 16 + (c.NPPmax + TN + 1) / 2 * 16 +
-           (P.res ? conv_step_list(taps, nks) : 2 * conv_step_list(taps, kConvUnits / 2)) * 16;
+    const long long tables = (c.NPPmax + TN + 1) / 2 * 16;
+    if (P.res) return 2LL * nks * c.NPOS * 16 + tables + conv_step_list(taps, nks) * 16;
+    if (P.wp) return 2LL * kConvUnits * c.NPOS * 16 + tables + 2 * conv_step_list(taps, KS) * 16;
+    const int last = nks - (nks - 1) / KS * KS;
+    return (nks > KS ? 2LL * kConvUnits : 2LL * nks) * c.NPOS * 16 + tables +
+           ((nks > KS ? round_up(taps * KS, 8) : 0) + round_up(taps * last, 8)) * 8 + 2 * KS * kConvGatherM / 32 * 1024;
 }
 
 // What a launch has to do, summed over its workgroups
 struct Work {
     double mma = 0;        // 32x32 fragment pairs per wave
     double tasks = 0;      // staging tasks per thread
+    double groups = 0;     // gathered groups of k-steps
     double in = 0, out = 0;   // bytes of the cache lines touched (a strip narrower than the image uses lines partly)
     long long wgs = 0;
     int lds = 0;
@@ -111,7 +118,7 @@ struct Work {
 
 // Lays one class out for tiles of TU of the TN positions on nst strips and adds up its work; false when the patch does not fit
 // or a tile's offsets from its first image would not.
-bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN, int lds_extra, Work &w)
+bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN, Work &w)
 {
     const int es = elem_size(dtype), nks = ksteps(dtype, P.Cin), VW = P.vec == 1 ? 2 : 1;
     const int taps = s.kH * s.kW, SW = ceil_div(s.Wo, std::min(nst, s.Wo));
@@ -135,7 +142,7 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     s.NPOS = round_up(NPR * s.PWs, 16);
     s.NPPmax = NPR * s.PWv;
     s.TPS = (int)((NR * SW + TU - 1) / TU);
-    const long long lds = conv_lds(P, s, TN, nks) + lds_extra;
+    const long long lds = conv_lds(P, s, TN, nks);
     if (lds > kLdsMax || s.NPOS > 65535) return false;
     const double n = (double)ceil_div(s.Wo, SW) * s.TPS * P.NMT;
     const int TM = std::min(32 * P.MT * P.WM, P.Cout);
@@ -143,6 +150,7 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     const double in_row = cl ? (double)PWl * P.Cin * es : nst == 1 ? (double)P.Wi * es : PWl * es + 64.0;
     const double out_row = cl ? (double)TU * TM * es : nst == 1 ? TU * es + 32.0 : (double)nr * (SW * es + 48.0);
     w.mma += n * taps * nks * P.MT * P.NT;
+    w.groups += n * taps * nks * (P.MT * P.WM) / (kConvUnits / 2 * kConvGatherM / 32);
     if (taps) {
         w.tasks += n * s.NPPmax * 2.0 * nks / kThreads;
         w.in += n * NPR * in_row * (cl ? 1 : P.Cin);
@@ -162,12 +170,13 @@ double expected_cycles(const ConvParams &P, int dtype, const Work &w, int ncu)
     const int shape = P.MT * 10 + P.NT, nks = ksteps(dtype, P.Cin);
     const double eff = shape == 24 ? kConvModel.e24 : shape == 22 ? kConvModel.e22 : shape == 12 ? kConvModel.e12 : kConvModel.e11;
     const double clk = dtype == XCONV_F32 ? 256.0 / kConvModel.ef32 : 32.0 / eff;
-    const int occ = std::max(1, std::min(kLdsMax / w.lds, P.MT * P.NT >= 8 || !P.wp ? 2 : P.MT * P.NT >= 4 ? 3 : 4));
+    const int occ = std::max(1, std::min(kLdsMax / w.lds, P.MT * P.NT >= 8 ? 2 : P.MT * P.NT >= 4 ? (P.wp ? 3 : 2) : P.wp ? 4 : 3));
     const double q = (double)((w.wgs + ncu - 1) / ncu), rounds = (double)((w.wgs + (long long)ncu * occ - 1) / ((long long)ncu * occ));
     const double tm = w.mma / w.wgs * clk * q;
     const double ts = std::max(w.tasks / w.wgs * kConvModel.task * q, w.in / ncu / kConvModel.in_bpc) + w.out / ncu / kConvModel.out_bpc;
     const double steps = rounds * (P.res ? 1.0 : std::max(1.0, nks / kConvModel.chunk));
     double t = kConvModel.start * rounds + std::max(tm, ts) + std::min(tm, ts) / std::pow(steps, kConvModel.overlap);
+    if (!P.wp) t += kConvModel.gather * w.groups / w.wgs * q;
     if (occ == 1) t += kConvModel.alone * ts;
     if (occ == 2) t += kConvModel.pair * tm;
     return t;
@@ -192,12 +201,11 @@ bool plan(ConvParams &P, int dtype, int ncu)
                 const int TM = 32 * C.MT * WM, TN = 32 * C.NT * (4 / WM);
                 if (force && !P.big && (P.wp || force != 24) && shape != force) continue;
                 if (force_wm && WM != force_wm) continue;
-                if (!P.wp && (C.NT > 2 || TM > kConvGatherM)) continue;
+                if (!P.wp && (C.NT > 2 || (WM > 1 && shape != 11))) continue;   // (the gathers there are)
                 if (P.big && shape != 22) continue;
                 if (WM > 1 && TM / 2 >= P.Cout) continue;                           // half of the waves would have no channels
                 if (TN / part < 1) continue;
                 C.NMT = ceil_div(P.Cout, TM);
-                const int extra = P.wp ? 0 : 2 * (kConvUnits / 2) * C.MT * WM * 1024;   // LDS of the gathered weights
                 for (int nst2 = 2; nst2 <= 2 * wide + 1; ++nst2) {
                     const int nst = nst2 / 2, SW = ceil_div(wide, nst);
                     int TU = TN / part;
@@ -213,7 +221,7 @@ bool plan(ConvParams &P, int dtype, int ncu)
                     for (int i = 0; i < P.nsub && fits; ++i) {
                         C.sub[i] = P.sub[i];
                         C.sub[i].wg0 = (int)w.wgs;
-                        fits = lay_out(C.sub[i], C, dtype, nst, TU, TN, extra, w) && w.wgs < 0x3fffffff;
+                        fits = lay_out(C.sub[i], C, dtype, nst, TU, TN, w) && w.wgs < 0x3fffffff;
                     }
                     if (!fits) continue;
                     const double t = expected_cycles(C, dtype, w, ncu);

@@ -60,3 +60,12 @@ def test_offsets_of_a_tile_fit_drawn_layers():
             continue
         n += 1
         offsets_fit((rng.choice([2, 5, 16, 64, 300]), C_in, C_out, H, W, k, s, p, rng.choice(["f32", "bf16", "f16"]), rng.random() < 0.5))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_few_channels_stage_few_units_without_a_workspace(dtype):
+    # a chunk of 8 units for 3 channels leaves no room in LDS for the patch of a whole tile of a strided layer
+    for B, C_in, C_out, n, k, s, p in ((16, 3, 64, 224, 7, 4, 3), (36, 6, 283, 149, 4, 2, 2), (53, 8, 8, 254, 5, 2, 2)):
+        d = xb.make_desc(B, C_in, C_out, n, n, k, s, p, 1, dtype)
+        v = xb.xconv_conv_plan_info(d, 0, False)
+        assert 4 * v["TU"] >= 3 * 32 * (v["shape"] % 10) * (4 // v["WM"]), v

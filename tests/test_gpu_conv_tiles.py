@@ -32,10 +32,32 @@ CASES = [
 ]
 
 
+# weights gathered for one, two and four waves of 32 output channels: groups of 8, 4 and 2 k-steps that kernel offsets and channels
+# do not fill evenly
+GATHERS = [
+    (2, 150, 136, 8, 10, 3, 1, 1, "f16", False),
+    (1, 168, 200, 7, 6, 3, 1, 1, "bf16", True),
+    (2, 133, 70, 9, 7, 3, 2, 1, "f32", False),
+    (3, 68, 72, 5, 9, (1, 5), 1, (0, 2), "f32", True),
+    (2, 100, 66, 6, 8, 1, 1, 0, "bf16", False),
+]
+
+
+@pytest.mark.parametrize("waves", ["1", "2", "4"])
+@pytest.mark.parametrize("case", GATHERS, ids=["%s-c%d-%d-k%s-s%s" % (c[8], c[1], c[2], c[5], c[6]) for c in GATHERS])
+def test_gathered_weights_of_several_waves(case, waves, monkeypatch):
+    monkeypatch.setenv("XCONV_CONV_WM", waves)
+    run_tiles(case, False, "11", monkeypatch)
+
+
 @pytest.mark.parametrize("shape", ["0", "24", "22", "12", "11"])
 @pytest.mark.parametrize("packed", [True, False], ids=["packed", "gathered"])
 @pytest.mark.parametrize("case", CASES, ids=["%s-c%d-%d-k%s-s%s" % (c[8], c[1], c[2], c[5], c[6]) for c in CASES])
 def test_conv_tiles(case, packed, shape, monkeypatch):
+    run_tiles(case, packed, shape, monkeypatch)
+
+
+def run_tiles(case, packed, shape, monkeypatch):
     B, C_in, C_out, H, W, k, s, p, dtype, nhwc = case
     monkeypatch.setenv("XCONV_CONV_SHAPE", shape)
     (kH, kW), (ph, pw) = (k, k) if isinstance(k, int) else k, (p, p) if isinstance(p, int) else p
