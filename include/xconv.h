@@ -174,8 +174,10 @@ xconv_status xconv_dw_exact(const xconv_desc *desc, const void *dY_dev, const vo
  *
  * (zero padding, cross-correlation, no bias).  X, Y, dY, dX in desc->dtype and desc->layout
  * ([B,C,H,W] or [B,H,W,C]); W_dev: [C_out,C_in,kH,kW] in desc->dtype, row-major, for both layouts.
- * Sums are fp32, the output is rounded once (nearest even) and overwritten.  No scratch; one
- * kernel launch each; desc->r, probe and seed are ignored.  Pointers aligned to the element size.
+ * Sums are fp32, the output is rounded once (nearest even) and overwritten.  No scratch;
+ * desc->r, probe and seed are ignored.  One kernel launch each (per 2^30 output positions); a strided input gradient
+ * clears dX first where no kernel offset reaches some of it, and takes a launch per 16 remainders of the position modulo
+ * the stride that some reach (4 for tensors past 2 GiB per image).  Pointers aligned to the element size.
  * XCONV_EUNSUPPORTED when an image of X or Y has more than 2^31-1 elements. */
 xconv_status xconv_conv_fwd(const xconv_desc *desc, const void *X_dev, const void *W_dev, void *Y_dev, void *stream);
 xconv_status xconv_dx_exact(const xconv_desc *desc, const void *dY_dev, const void *W_dev, void *dX_dev, void *stream);

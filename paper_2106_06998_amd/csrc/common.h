@@ -336,7 +336,8 @@ constexpr int kConvUnits = 8;   // 16-byte units of channels per staged chunk
 constexpr int kConvGatherM = 64;   // output channels that a group of kConvUnits / 2 k-steps of gathered weights covers (no workspace)
 constexpr int kConvResident = 128;   // most contraction channels whose whole patch is kept in LDS
 constexpr int kConvOverread = 4096; // bytes behind the packed weights that the last requests may touch
-constexpr int kConvSubs = 4;    // classes of output positions per launch
+constexpr int kConvSubs = 4;    // classes of output positions per launch ...
+constexpr int kConvSubsMany = 16;   // ... of the kernels that take many (conv_many)
 
 // 16-byte entries of a list of k-steps (four steps each, one more that only prefetches touch)
 __host__ __device__ inline int conv_step_list(int taps, int steps_per_tap) { return (taps * steps_per_tap + 3) / 4 + 1; }
@@ -374,9 +375,10 @@ inline FastDiv fast_div(int d)
 }
 
 // One class of output positions: an ordinary convolution with its own taps.  The forward convolution is one class; the
-// input gradient of a strided layer is sh*sw of them (output positions by their remainder modulo the stride).
+// input gradient of a strided layer is up to sh*sw of them (output positions by their remainder modulo the stride; those that no
+// kernel offset reaches are zeros and no class).
 struct ConvSub {
-    int kH, kW, ph, pw;        // taps and padding in front (negative: the first source row lies inside); no taps: zeros
+    int kH, kW, ph, pw;        // taps and padding in front (negative: the first source row lies inside)
     int Ho, Wo;                // output positions of the class
     int oy0, ox0;              // its first output row and column (the steps are ConvParams::osy, osx)
     int ky0, kx0, kys, kxs;    // kernel offset of tap (i, j): (ky0 + i*kys, kx0 + j*kxs), in the order they are summed
@@ -388,7 +390,7 @@ struct ConvSub {
     int images;                // most images a tile touches (host)
     long long w0;              // first 16-byte unit of its packed weights
 };
-struct ConvParams {
+struct ConvHead {
     const void *in;    // activation-like tensor the contraction runs over (X, or dY for the input gradient)
     const void *w;     // weights [C_out, C_in, kH, kW] in the storage type
     const void *wp;    // the same in fragment order (side_jobs.h), or null: fragments are gathered from w
@@ -410,8 +412,15 @@ struct ConvParams {
     int rev;              // taps reach back: tap (i, j) reads patch position (kH-1-i, kW-1-j) (input gradient)
     int res;              // all channels of a patch resident
     int nsub, nwg, lds_bytes;
-    ConvSub sub[kConvSubs];
 };
+// The argument of a launch of up to N classes: one, kConvSubs or kConvSubsMany (3.4 KB: 0.3-0.6 us more per launch than the 1 KB of
+// kConvSubs, 27 -> 14 us for the nine classes of 64 -> 32 channels 3x3 at stride 3, 57x57, batch 16, bf16, in one launch for three)
+template <int N> struct ConvArgs : ConvHead {
+    ConvSub sub[N];
+};
+typedef ConvArgs<kConvSubsMany> ConvParams;
+// tiles and weights of which there are kernels for many classes: the classes of a large stride have few taps each
+constexpr bool conv_many(int MT, int NT, bool packed, bool big, bool res) { return MT == NT && !big && (res || !packed); }
 
 // Small jobs that a launch carries along in workgroups of its own, in place of a launch each (4-6 us on the stream for work
 // of 1 us): the weights of a convolution in fragment order, and the sum of the pieces of a bias gradient.  The probe (forward)
@@ -421,7 +430,7 @@ struct PackClass {
     int n;                            // fragments (64 x 16 bytes)
     long long w0;
 };
-struct SideJobs {
+template <int N> struct PackJobs {
     int total;                        // fragments and channels: one wave each
     int nsub, NMB, Cin, Cout, w_sco, w_sci, kWfull;
     int res, il, es;                  // resident patches, even and odd channels apart (conv_unit_channel), bytes per element
@@ -430,8 +439,9 @@ struct SideJobs {
     void *packed;
     const float *part;
     void *db;
-    PackClass sub[kConvSubs];
+    PackClass sub[N];
 };
+typedef PackJobs<kConvSubs> SideJobs;   // those that other launches carry
 // the argument of a launch that carries none: the estimator's own entry points run kernels without the jobs' code and argument
 // (C4 estimate 134.5 -> 133.9 us, 133.6 before there were any jobs)
 struct NoSideJobs {};

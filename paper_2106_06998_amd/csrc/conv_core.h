@@ -75,11 +75,11 @@ constexpr uint32_t kConvOob = 0x80000000u;   // byte offset past every buffer de
 // VEC: how a staging task reads `in`: 0 element by element (any strides), 1 pairs of columns (16-bit planes of even width),
 //      2 whole units (channels-last, channels a multiple of the unit).
 // SWAP: output positions in the rows of the accumulator tile (channels-last output: lanes along the channels), else in its columns.
-// MULTI: several classes in one launch (an index into the argument struct that is not a constant makes the compiler load every
+// NC: most classes in one launch (above one, an index into the argument struct that is not a constant makes the compiler load every
 //      argument where it is used: a launch of one class does without).
 // PACKED: weights in fragment order; else GW waves along the output channels (P.WM).  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI, int GW>
-__global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvParams P)
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, int NC, int GW>
+__global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvArgs<NC> P)
 {
     typedef typename ConvElem<DT>::t elem_t;
     constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     int id = xcd_block(blockIdx.x, gridDim.x);
     if (id >= P.nwg) return;
     int cls = 0;
-    if constexpr (MULTI) {
+    if constexpr (NC > 1) {
         while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
     }
     const ConvSub &S = P.sub[cls];
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int NPR = (R1 - R0) * S.sth + (b1 - b0) * (S.kH - S.sth) + S.kH;      // staged rows of this tile
     const int xs = strip * S.SW * P.sw - S.pw;                                  // source column of patch column `xa`
     const int xa = VW == 2 ? (xs & 1) : 0;
-    const int npp = S.kH > 0 ? NPR * S.PWv : 0;   // a class without taps stages nothing
+    const int npp = NPR * S.PWv;
 
     {
         for (int pp = tid; pp < npp; pp += kThreads) {
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         }
     }
     const int taps = S.kH * S.kW;
-    const int nck = taps == 0 ? 0 : RES ? 1 : (P.Cin + CK - 1) / CK;
+    const int nck = RES ? 1 : (P.Cin + CK - 1) / CK;
     auto tap_offset = [&](int ky, int kx) {
         const int cy = P.rev ? S.kH - 1 - ky : ky, cx = (P.rev ? S.kW - 1 - kx : kx) + xa;
         return cy * S.PWs + (S.stw == 1 ? cx : (cx % S.stw) * S.PH + cx / S.stw);
@@ -586,10 +586,10 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     }
 }
 
-template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, bool MULTI, int GW>
-static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
+template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, int NC, int GW>
+static hipError_t launch_conv_classes(const ConvHead &P, const ConvSub *sub, hipStream_t st)
 {
-    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI, GW>);
+    const void *k = reinterpret_cast<const void *>(conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, NC, GW>);
     if (P.lds_bytes > 64 * 1024) {
         static bool attr_set[64] = {};   // per device; a repeated call only sets it again
         int dev = 0;
@@ -600,52 +600,59 @@ static hipError_t launch_conv_classes(const ConvParams &P, hipStream_t st)
             if (dev >= 0 && dev < 64) attr_set[dev] = true;
         }
     }
-    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, MULTI, GW>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
-                       (unsigned)P.lds_bytes, st, P);
+    ConvArgs<NC> A;
+    static_cast<ConvHead &>(A) = P;
+    std::copy(sub, sub + P.nsub, A.sub);
+    hipLaunchKernelGGL((conv_kernel<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, NC, GW>), dim3((unsigned)((P.nwg + 7) / 8 * 8)), dim3(kThreads),
+                       (unsigned)P.lds_bytes, st, A);
     return hipGetLastError();
 }
 
 template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES = false, int GW = 1>
-static hipError_t launch_conv_one(const ConvParams &P, hipStream_t st)
+static hipError_t launch_conv_one(const ConvHead &P, const ConvSub *sub, hipStream_t st)
 {
-    if (P.nsub == 1) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, false, GW>(P, st);
-    return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, true, GW>(P, st);
+    if (P.nsub == 1) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, 1, GW>(P, sub, st);
+    if constexpr (conv_many(MT, NT, PACKED, BIG, RES)) {
+        if (P.nsub > kConvSubs) return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, kConvSubsMany, GW>(P, sub, st);
+    }
+    if (P.nsub > kConvSubs) return hipErrorInvalidValue;
+    return launch_conv_classes<DT, VEC, SWAP, MT, NT, PACKED, BIG, RES, kConvSubs, GW>(P, sub, st);
 }
 
-template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const ConvParams &P, hipStream_t st)
+template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const ConvHead &P, const ConvSub *sub, hipStream_t st)
 {
     if (P.big) {
-        if constexpr (VEC == 0) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, true>(P, st);
+        if constexpr (VEC == 0) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, true>(P, sub, st);
         else return hipErrorInvalidValue;
     }
     const int shape = P.MT * 10 + P.NT;
     if (P.res) {
-        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false, true>(P, st);
-        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false, true>(P, st);
-        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false, true>(P, st);
-        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false, true>(P, st);
+        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false, true>(P, sub, st);
+        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false, true>(P, sub, st);
+        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false, true>(P, sub, st);
+        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false, true>(P, sub, st);
     }
     if (P.wp) {
-        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false>(P, st);
-        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false>(P, st);
-        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false>(P, st);
-        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false>(P, st);
+        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false>(P, sub, st);
+        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false>(P, sub, st);
+        if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false>(P, sub, st);
+        return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false>(P, sub, st);
     }
-    if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, false>(P, st);
-    if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, false, false>(P, st);
-    if (P.WM == 4) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 4>(P, st);
-    if (P.WM == 2) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 2>(P, st);
-    return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false>(P, st);
+    if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, false, false>(P, sub, st);
+    if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, false, false>(P, sub, st);
+    if (P.WM == 4) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 4>(P, sub, st);
+    if (P.WM == 2) return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false, false, 2>(P, sub, st);
+    return launch_conv_one<DT, VEC, SWAP, 1, 1, false, false>(P, sub, st);
 }
 
-template <int DT> static hipError_t launch_conv_dt(const ConvParams &P, hipStream_t st)
+template <int DT> static hipError_t launch_conv_dt(const ConvHead &P, const ConvSub *sub, hipStream_t st)
 {
     if (P.vec == 1) {
         if constexpr (DT == XCONV_F32) return hipErrorInvalidValue;
-        else return launch_conv_shape<DT, 1, false>(P, st);
+        else return launch_conv_shape<DT, 1, false>(P, sub, st);
     }
-    if (P.vec == 2) return launch_conv_shape<DT, 2, true>(P, st);
-    return P.swap ? launch_conv_shape<DT, 0, true>(P, st) : launch_conv_shape<DT, 0, false>(P, st);
+    if (P.vec == 2) return launch_conv_shape<DT, 2, true>(P, sub, st);
+    return P.swap ? launch_conv_shape<DT, 0, true>(P, sub, st) : launch_conv_shape<DT, 0, false>(P, sub, st);
 }
 
 }  // namespace xc

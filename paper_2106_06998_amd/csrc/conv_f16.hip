@@ -2,5 +2,5 @@
 #include "conv_core.h"
 
 namespace xc {
-hipError_t launch_conv_f16(const ConvParams &P, hipStream_t st) { return launch_conv_dt<XCONV_F16>(P, st); }
+hipError_t launch_conv_f16(const ConvHead &P, const ConvSub *sub, hipStream_t st) { return launch_conv_dt<XCONV_F16>(P, sub, st); }
 }  // namespace xc

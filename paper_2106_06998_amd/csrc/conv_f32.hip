@@ -2,5 +2,5 @@
 #include "conv_core.h"
 
 namespace xc {
-hipError_t launch_conv_f32(const ConvParams &P, hipStream_t st) { return launch_conv_dt<XCONV_F32>(P, st); }
+hipError_t launch_conv_f32(const ConvHead &P, const ConvSub *sub, hipStream_t st) { return launch_conv_dt<XCONV_F32>(P, sub, st); }
 }  // namespace xc

@@ -16,9 +16,9 @@
 
 namespace xc {
 
-hipError_t launch_conv_f32(const ConvParams &P, hipStream_t st);
-hipError_t launch_conv_bf16(const ConvParams &P, hipStream_t st);
-hipError_t launch_conv_f16(const ConvParams &P, hipStream_t st);
+hipError_t launch_conv_f32(const ConvHead &P, const ConvSub *sub, hipStream_t st);
+hipError_t launch_conv_bf16(const ConvHead &P, const ConvSub *sub, hipStream_t st);
+hipError_t launch_conv_f16(const ConvHead &P, const ConvSub *sub, hipStream_t st);
 
 namespace {
 
@@ -77,7 +77,7 @@ std::vector<ConvSub> make_subs(const xconv_desc *d, int transposed, int Ho, int 
             ConvSub s{};
             axis(a, d->kH, d->stride_h, d->pad_h, s.kH, s.ky0, s.ph);
             axis(b, d->kW, d->stride_w, d->pad_w, s.kW, s.kx0, s.pw);
-            if (s.kH == 0 || s.kW == 0) s.kH = s.kW = s.ph = s.pw = 0;
+            if (s.kH == 0 || s.kW == 0) continue;     // zeros (ConvPlan::fill)
             s.kys = d->stride_h; s.kxs = d->stride_w;
             s.oy0 = a; s.ox0 = b;
             s.Ho = (d->H - a + d->stride_h - 1) / d->stride_h;
@@ -124,8 +124,8 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     const int taps = s.kH * s.kW, SW = ceil_div(s.Wo, std::min(nst, s.Wo));
     s.SW = SW;
     s.TU = TU;
-    s.sth = std::max(1, std::min(P.sh, s.kH));
-    s.stw = std::max(1, std::min(P.sw, s.kW));
+    s.sth = std::min(P.sh, s.kH);
+    s.stw = std::min(P.sw, s.kW);
     const long long NR = (long long)P.B * s.Ho;
     const bool rows = TU % SW == 0;              // tiles begin at the start of a row
     const int nr = (int)std::min<long long>(rows ? TU / SW : (SW + TU - 2) / SW + 1, NR);
@@ -134,7 +134,7 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     s.images = nb + 1;
     const long long reach = s.images * std::max(P.in_sb, P.out_sb);
     if (P.big ? reach > kMaxReachBig : reach * es > kMaxReach) return false;
-    const int NPR = std::max(1, (nr - 1) * s.sth + nb * std::max(0, s.kH - s.sth) + s.kH);
+    const int NPR = (nr - 1) * s.sth + nb * (s.kH - s.sth) + s.kH;
     const int PWl = (SW - 1) * s.stw + s.kW + (VW - 1);
     s.PWv = std::max(1, ceil_div(PWl, VW));
     s.PH = ceil_div(s.PWv * VW, s.stw);
@@ -151,10 +151,8 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     const double out_row = cl ? (double)TU * TM * es : nst == 1 ? TU * es + 32.0 : (double)nr * (SW * es + 48.0);
     w.mma += n * taps * nks * P.MT * P.NT;
     w.groups += n * taps * nks * (P.MT * P.WM) / (kConvUnits / 2 * kConvGatherM / 32);
-    if (taps) {
-        w.tasks += n * s.NPPmax * 2.0 * nks / kThreads;
-        w.in += n * NPR * in_row * (cl ? 1 : P.Cin);
-    }
+    w.tasks += n * s.NPPmax * 2.0 * nks / kThreads;
+    w.in += n * NPR * in_row * (cl ? 1 : P.Cin);
     w.out += n * out_row * (cl ? 1 : TM);
     w.wgs += (long long)n;
     w.lds = std::max(w.lds, (int)lds);
@@ -199,10 +197,11 @@ bool plan(ConvParams &P, int dtype, int ncu)
                 ConvParams C = P;
                 C.MT = shape / 10; C.NT = shape % 10; C.WM = WM;
                 const int TM = 32 * C.MT * WM, TN = 32 * C.NT * (4 / WM);
-                if (force && !P.big && (P.wp || force != 24) && shape != force) continue;
+                if (force && !P.big && (P.wp || force != 24) && P.nsub <= kConvSubs && shape != force) continue;
                 if (force_wm && WM != force_wm) continue;
                 if (!P.wp && (C.NT > 2 || (WM > 1 && shape != 11))) continue;   // (the gathers there are)
                 if (P.big && shape != 22) continue;
+                if (P.nsub > kConvSubs && !conv_many(C.MT, C.NT, P.wp != nullptr, P.big, P.res)) continue;
                 if (WM > 1 && TM / 2 >= P.Cout) continue;                           // half of the waves would have no channels
                 if (TN / part < 1) continue;
                 C.NMT = ceil_div(P.Cout, TM);
@@ -264,6 +263,7 @@ struct ConvLaunch {
 };
 struct ConvPlan {
     int dtype;
+    size_t fill;                      // bytes of the output, cleared in front of the launches where no kernel offset reaches some of it; else 0
     std::vector<ConvLaunch> launches;
 };
 
@@ -315,15 +315,21 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
     const bool nhwc = d->layout == XCONV_NHWC;
     P.swap = nhwc;
     std::vector<ConvSub> subs = make_subs(d, transposed, Ho, Wo);
-    long long w0 = 0;
+    long long covered = 0, w0 = 0;
+    for (const ConvSub &s : subs) covered += (long long)s.Ho * s.Wo;
+    out.fill = covered < (long long)Hout * Wout ? (size_t)d->B * P.out_sb * es : 0;
     for (ConvSub &s : subs) {
         s.w0 = w0;
         w0 += packed_units(s, d->dtype, P.Cin, P.Cout);
     }
     // images per launch: 32-bit row and tile arithmetic
     const int bstep = (int)std::max<long long>(1, std::min<long long>(d->B, kMaxPos / ((long long)Hout * Wout)));
-    for (size_t s0 = 0; s0 < subs.size(); s0 += kConvSubs) {
-        P.nsub = (int)std::min<size_t>(kConvSubs, subs.size() - s0);
+    // (an image that fits 32-bit offsets never needs 64-bit addresses, and patches of so few channels are resident: a tile of one
+    // position fits)
+    const bool huge = std::max(P.in_sb, P.out_sb) * es > kMaxReach;
+    const size_t per = !huge && (!packed || P.Cin <= kConvResident) ? kConvSubsMany : kConvSubs;
+    for (size_t s0 = 0; s0 < subs.size(); s0 += per) {
+        P.nsub = (int)std::min<size_t>(per, subs.size() - s0);
         for (int i = 0; i < P.nsub; ++i) P.sub[i] = subs[s0 + i];
         for (int bb = 0; bb < d->B; bb += bstep) {
             P.B = std::min(bstep, d->B - bb);
@@ -333,7 +339,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
             const ConvLaunch *first = bb ? &out.launches.back() : nullptr;
             ConvLaunch L{};
             bool found = false;
-            for (int big = first ? first->P.big : std::max(P.in_sb, P.out_sb) * es > kMaxReach; big <= 1 && !found; ++big) {
+            for (int big = first ? first->P.big : huge; big <= 1 && !found; ++big) {
                 P.big = big;
                 P.vec = 0;
                 if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
@@ -396,6 +402,10 @@ bool conv_plan_info(const xconv_desc *d, int transposed, bool packed, int32_t *o
         for (int i = 0; i < L.P.nsub; ++i)
             if (!cls || L.P.sub[i].images > cls->images) { worst = &L; cls = &L.P.sub[i]; }
     }
+    if (!cls) {      // nothing but zeros
+        std::fill(out, out + 16, 0);
+        return true;
+    }
     const ConvParams &P = worst->P;
     const int32_t v[16] = {(int32_t)p->launches.size(), npack, P.MT * 10 + P.NT, P.WM, P.res, P.big, P.vec, P.pair,
                            P.nsub, P.B, cls->Ho, cls->Wo, cls->SW, cls->TU, cls->images, P.lds_bytes};
@@ -404,14 +414,16 @@ bool conv_plan_info(const xconv_desc *d, int transposed, bool packed, int32_t *o
 }
 
 // the jobs alone in a launch
-__global__ __launch_bounds__(kThreads) void side_jobs_kernel(const SideJobs J) { side_jobs<0, kThreads>(J, blockIdx.x, gridDim.x); }
+template <int N> __global__ __launch_bounds__(kThreads) void side_jobs_kernel(const PackJobs<N> J) { side_jobs<0, kThreads>(J, blockIdx.x, gridDim.x); }
 
-hipError_t launch_side_jobs(const SideJobs &J, hipStream_t st)
+template <int N> static hipError_t launch_jobs(const PackJobs<N> &J, hipStream_t st)
 {
     if (J.total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(side_jobs_kernel, dim3((unsigned)side_groups<kThreads>(&J)), dim3(kThreads), 0, st, J);
+    hipLaunchKernelGGL(side_jobs_kernel<N>, dim3((unsigned)side_groups<kThreads>(&J)), dim3(kThreads), 0, st, J);
     return hipGetLastError();
 }
+
+hipError_t launch_side_jobs(const SideJobs &J, hipStream_t st) { return launch_jobs(J, st); }
 
 ConvPlanRef find_conv_plan(const xconv_desc *d, int transposed, const void *in, const void *out, bool packed)
 {
@@ -420,7 +432,7 @@ ConvPlanRef find_conv_plan(const xconv_desc *d, int transposed, const void *in, 
 }
 
 // the packing of one launch's weights as a job
-static void add_pack_job(SideJobs &J, const ConvLaunch &L, int dtype, const void *w, void *ws)
+template <int N> static void add_pack_job(PackJobs<N> &J, const ConvLaunch &L, int dtype, const void *w, void *ws)
 {
     const ConvParams &P = L.P;
     J.nsub = P.nsub;
@@ -442,7 +454,7 @@ bool conv_pack_job(const ConvPlan &plan, const void *w, void *ws, SideJobs &J)
     const ConvLaunch *one = nullptr;
     for (const ConvLaunch &L : plan.launches) {
         if (!L.pack) continue;
-        if (one) return false;      // more classes than a job holds
+        if (one || L.P.nsub > kConvSubs) return false;      // more classes than a job holds
         one = &L;
     }
     if (!one) return false;
@@ -450,23 +462,46 @@ bool conv_pack_job(const ConvPlan &plan, const void *w, void *ws, SideJobs &J)
     return true;
 }
 
+// zeros; words of 16 bytes between the first and the last that are whole
+__global__ __launch_bounds__(kThreads) void zero_fill_kernel(char *out, size_t n)
+{
+    const size_t head = std::min<size_t>(-reinterpret_cast<uintptr_t>(out) & 15u, n), words = (n - head) / 16;
+    const size_t i0 = (size_t)blockIdx.x * kThreads + threadIdx.x, step = (size_t)gridDim.x * kThreads;
+    uint4 *w = reinterpret_cast<uint4 *>(out + head);
+    for (size_t i = i0; i < words; i += step) w[i] = uint4{0, 0, 0, 0};
+    if (i0 < head) out[i0] = 0;
+    for (size_t i = head + words * 16 + i0; i < n; i += step) out[i] = 0;
+}
+
 hipError_t launch_conv(const ConvPlan &plan, const void *in, const void *w, const void *bias, void *out, void *ws, bool packed, hipStream_t st)
 {
+    if (plan.fill) {
+        hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)std::min<size_t>((plan.fill + kThreads * 64 - 1) / (kThreads * 64), 2048)), dim3(kThreads), 0, st,
+                           static_cast<char *>(out), plan.fill);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     for (const ConvLaunch &L : plan.launches) {
         hipError_t e = hipSuccess;
         if (L.pack && !packed) {
-            SideJobs J{};
-            add_pack_job(J, L, plan.dtype, w, ws);
-            e = launch_side_jobs(J, st);
+            if (L.P.nsub > kConvSubs) {
+                PackJobs<kConvSubsMany> J{};
+                add_pack_job(J, L, plan.dtype, w, ws);
+                e = launch_jobs(J, st);
+            } else {
+                SideJobs J{};
+                add_pack_job(J, L, plan.dtype, w, ws);
+                e = launch_jobs(J, st);
+            }
             if (e != hipSuccess) return e;
         }
-        ConvParams P = L.P;
+        ConvHead P = L.P;
         P.in = static_cast<const char *>(in) + L.in_off;
         P.out = static_cast<char *>(out) + L.out_off;
         P.w = w;
         P.bias = bias;
         P.wp = P.wp ? ws : nullptr;
-        e = plan.dtype == XCONV_F32 ? launch_conv_f32(P, st) : plan.dtype == XCONV_BF16 ? launch_conv_bf16(P, st) : launch_conv_f16(P, st);
+        e = plan.dtype == XCONV_F32 ? launch_conv_f32(P, L.P.sub, st) : plan.dtype == XCONV_BF16 ? launch_conv_bf16(P, L.P.sub, st) : launch_conv_f16(P, L.P.sub, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

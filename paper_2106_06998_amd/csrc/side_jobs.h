@@ -9,7 +9,7 @@ namespace xc {
 
 // Fragment i of a class: weights in the order [block of 32 output channels][chunk][tap][k-step][lane] of 16 bytes (a chunk =
 // kConvUnits / 2 k-steps of channels, or all of them for resident patches); zero beyond the channels.
-template <int ES> __device__ inline void pack_fragment(const SideJobs &J, const PackClass &S, int i, int lane)
+template <int ES, class SJ> __device__ inline void pack_fragment(const SJ &J, const PackClass &S, int i, int lane)
 {
     constexpr int UE = 16 / ES;
     const int taps = S.kH * S.kW, nks = (J.Cin + 2 * UE - 1) / (2 * UE), nk = taps * nks;
@@ -35,7 +35,7 @@ template <int ES> __device__ inline void pack_fragment(const SideJobs &J, const 
 }
 
 // one wave adds the S pieces of channel c in a fixed order: lanes take the pieces lane, lane + 64, ...
-__device__ inline void bias_sum_channel(const SideJobs &J, int c, int lane)
+template <class SJ> __device__ inline void bias_sum_channel(const SJ &J, int c, int lane)
 {
     float s = 0.f;
     for (int i = lane; i < J.S; i += 64) s += J.part[(size_t)i * J.C + c];
@@ -47,7 +47,7 @@ __device__ inline void bias_sum_channel(const SideJobs &J, int c, int lane)
 }
 
 // workgroup wg of nwg, of THREADS threads.  ES: bytes per element where the carrying kernel knows them, else 0
-template <int ES, int THREADS> __device__ inline void side_jobs(const SideJobs &J, int wg, int nwg)
+template <int ES, int THREADS, class SJ> __device__ inline void side_jobs(const SJ &J, int wg, int nwg)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(wg * (THREADS / 64) + (int)(threadIdx.x >> 6));
     for (int i = wave; i < J.total; i += nwg * (THREADS / 64)) {
@@ -60,7 +60,7 @@ template <int ES, int THREADS> __device__ inline void side_jobs(const SideJobs &
 }
 
 // workgroups that carry the jobs; a multiple of 8 keeps the dies of the others (xcd_block)
-template <int THREADS> inline int side_groups(const SideJobs *J)
+template <int THREADS, class SJ> inline int side_groups(const SJ *J)
 {
     if (!J || J->total <= 0) return 0;
     const int n = (J->total + THREADS / 64 - 1) / (THREADS / 64);

@@ -69,3 +69,13 @@ def test_few_channels_stage_few_units_without_a_workspace(dtype):
         d = xb.make_desc(B, C_in, C_out, n, n, k, s, p, 1, dtype)
         v = xb.xconv_conv_plan_info(d, 0, False)
         assert 4 * v["TU"] >= 3 * 32 * (v["shape"] % 10) * (4 // v["WM"]), v
+
+
+def test_strided_input_gradients_take_few_launches():
+    # one launch for the positions that kernel offsets reach, up to 16 remainders of the stride, whatever the stride
+    for k, s, launches in ((3, 1, 1), (3, 2, 1), (3, 3, 1), (4, 4, 1), (1, 8, 1), (3, 5, 1), (2, 64, 1), (5, 7, 2), (7, 16, 4), (7, 64, 4)):
+        for ws in (0, 1):
+            v = xb.xconv_conv_plan_info(xb.make_desc(2, 16, 24, 224, 224, k, s, 0, 1, "f16"), 1, ws)
+            assert (v["launches"], v["pack_launches"]) == (launches, launches * ws), (k, s, v)
+    v = xb.xconv_conv_plan_info(xb.make_desc(2, 4, 6, 1, 1, 1, 5, 2, 1, "f16"), 1, 1)
+    assert v["launches"] == 0

@@ -24,6 +24,10 @@ CASES = [
     (2, 12, 20, 10, 10, 1, 2, 0, "f32", True),       # input gradient: classes without taps
     (2, 9, 17, 15, 14, 3, 3, 0, "f16", True),        # channels that are no whole units
     (3, 8, 8, 21, 14, 7, 7, 0, "f16", False),        # a stride as large as the kernel
+    (2, 24, 16, 19, 22, 3, 5, 1, "bf16", False),     # more classes without taps than with
+    (3, 16, 9, 17, 30, 1, 8, 0, "f16", False),
+    (2, 12, 10, 13, 11, 5, 5, 2, "f32", True),       # more classes than a launch takes
+    (2, 4, 6, 1, 1, 1, 5, 2, "f16", False),          # an output that reads the padding only: no class has taps
     (40, 16, 16, 1, 1, (7, 1), 1, (3, 0), "f32", False),   # one position per image
     (1, 64, 32, 3, 300, 3, 1, 1, "bf16", False),     # strips of a wide row
     (2, 150, 136, 8, 10, 3, 1, 1, "f16", False),     # more channels than a resident patch: chunks
