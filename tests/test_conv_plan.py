@@ -2,6 +2,7 @@
 from its first image, fit the descriptor (or, with 64-bit addresses, the 32-bit element tables) of the kernel that the plan takes,
 whatever the layer.  A tile of a strip of SW columns takes SW positions of every row, so it crosses TU / (Ho * SW) images."""
 import random
+import time
 
 import numpy as np
 import pytest
@@ -79,3 +80,12 @@ def test_strided_input_gradients_take_few_launches():
             assert (v["launches"], v["pack_launches"]) == (launches, launches * ws), (k, s, v)
     v = xb.xconv_conv_plan_info(xb.make_desc(2, 4, 6, 1, 1, 1, 5, 2, 1, "f16"), 1, 1)
     assert v["launches"] == 0
+
+
+def test_the_search_does_not_grow_with_the_image():
+    xb.xconv_conv_plan_info(xb.make_desc(1, 8, 8, 64, 64, 3, 1, 1, 1, "f16"), 0, 1)
+    for n in (3000, 10000):
+        d = xb.make_desc(1, 8, 8, n, n, 1, 1, 0, 1, "f16")
+        t = time.perf_counter()
+        xb.xconv_conv_plan_info(d, 0, 1)
+        assert time.perf_counter() - t < 0.03           # 0.3 ms; 70 and 490 ms when every number of strips was tried
