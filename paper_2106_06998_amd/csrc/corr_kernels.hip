@@ -93,7 +93,7 @@ __device__ inline StepPos uniform_pos(StepPos s)
     return s;
 }
 
-__device__ inline StepPos decode_step(const CorrParams &P, int t)
+__device__ inline StepPos decode_step(const CorrArgs &P, int t)
 {
     StepPos s;
     if (t < (1 << 22)) {
@@ -110,7 +110,7 @@ __device__ inline StepPos decode_step(const CorrParams &P, int t)
     s.x0 = s.strip * P.CW;
     return uniform_pos(s);
 }
-__device__ inline StepPos next_step(const CorrParams &P, StepPos s)
+__device__ inline StepPos next_step(const CorrArgs &P, StepPos s)
 {
     if (++s.band == P.NBAND) {
         s.band = 0;
@@ -132,7 +132,7 @@ __device__ inline StepPos next_step(const CorrParams &P, StepPos s)
 // addresses per thread and needs no per-element predicates.
 // SETS: the third extent of the grid also counts kernel-depth offsets (volumetric layers)
 template <int DT, int MT, int NA, int NB, int NOFF, bool AL, bool SETS>
-__global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) void corr_kernel(const CorrParams P)
+__global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) void corr_kernel(const std::conditional_t<SETS, CorrParams, CorrArgs> P)
 {
     draw_z_slice(P.zout, P.nz, P.zdist, P.zseed);
     constexpr bool F32 = (DT == XCONV_F32);
@@ -166,7 +166,8 @@ __global__ __launch_bounds__(kThreads, ((DT == XCONV_F32 && MT <= 2) ? 2 : 1)) v
     const int noff = (P.K2 - o_first) < NOFF ? (P.K2 - o_first) : NOFF;
 
     const elem_t *dY = static_cast<const elem_t *>(P.dY);
-    const elem_t *Ag = reinterpret_cast<const elem_t *>(static_cast<const char *>(P.A) + (SETS ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
+    const elem_t *Ag = static_cast<const elem_t *>(P.A);
+    if constexpr (SETS) Ag = reinterpret_cast<const elem_t *>(static_cast<const char *>(P.A) + set_offset(set, P.set_sd, P.set_run, P.set_slice));
 
     // my share of the steps
     const int bx = xcd_block(blockIdx.x, gridDim.x);   // K-split of this workgroup: neighbouring splits on one die (C3: 32.0 -> 29.3 us: the rows of dY, 56 bytes, share cache lines with the rows of the neighbouring splits)

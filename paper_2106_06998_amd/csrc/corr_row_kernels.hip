@@ -73,7 +73,7 @@ template <int N> using IC = std::integral_constant<int, N>;
 // REM = (Qr - 1) % 3: window position at which the last k-step of a row starts.
 // CB  = bytes of one staged column of A (BSTR * 16): the three columns of the window are immediates.
 template <int DT, int REM, int CB>
-__global__ __launch_bounds__(kWsThreads) void corr_row_kernel(const WsParams P)
+__global__ __launch_bounds__(kWsThreads) void corr_row_kernel(const WsArgs P)
 {
     draw_z_slice(P.zout, P.nz, P.zdist, P.zseed);
     extern __shared__ uint4 row_lds[];

@@ -29,7 +29,7 @@ namespace xc {
 // which the fp32 MFMA needs to issue at its full rate).
 // VOL: dY is read in place as the depth slots of volumes (WsParams::vol_*)
 template <int NOFF, int NTASK, int D, int OCC, bool VOL>
-__global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const WsParams P)
+__global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const std::conditional_t<VOL, WsParams, WsArgs> P)
 {
     draw_z_slice(P.zout, P.nz, P.zdist, P.zseed);
     extern __shared__ uint4 ws32_lds[];
@@ -191,7 +191,8 @@ __global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const Ws
         __builtin_amdgcn_s_setprio(0);
         const int p = tid - kProducers;
         const float *dY = static_cast<const float *>(P.dY);
-        const float *Ag = reinterpret_cast<const float *>(static_cast<const char *>(P.A) + (VOL ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
+        const float *Ag = static_cast<const float *>(P.A);
+        if constexpr (VOL) Ag = reinterpret_cast<const float *>(static_cast<const char *>(P.A) + set_offset(set, P.set_sd, P.set_run, P.set_slice));
         const int HoWo = P.Ho * P.Wo;
         constexpr bool vol = VOL;
         // bytes between the planes of consecutive channels and between consecutive images of the batch

@@ -51,7 +51,7 @@ template <int DT> __device__ inline f32x16 mfma32(const uint4 &a, const uint4 &b
 // the three column offsets of a kernel row are then immediates of one address register.
 // VOL: dY is read in place as the depth slots of volumes (WsParams::vol_*)
 template <int DT, int NOFF, int NTASK, int D, int CB, bool RU, bool VOL>
-__global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const WsParams P)
+__global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const std::conditional_t<VOL, WsParams, WsArgs> P)
 {
     draw_z_slice(P.zout, P.nz, P.zdist, P.zseed);
     extern __shared__ uint4 ws_lds[];
@@ -432,7 +432,8 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const WsParams P)
         __builtin_amdgcn_s_setprio(0);
         const int p = tid - kProducers;
         const uint16_t *dY = static_cast<const uint16_t *>(P.dY);
-        const uint16_t *Ag = reinterpret_cast<const uint16_t *>(static_cast<const char *>(P.A) + (VOL ? set_offset(set, P.set_sd, P.set_run, P.set_slice) : 0));
+        const uint16_t *Ag = static_cast<const uint16_t *>(P.A);
+        if constexpr (VOL) Ag = reinterpret_cast<const uint16_t *>(static_cast<const char *>(P.A) + set_offset(set, P.set_sd, P.set_run, P.set_slice));
         const int HoWo = P.Ho * P.Wo;
         constexpr bool vol = VOL;
         // bytes between the planes of consecutive channels and between consecutive images of the batch

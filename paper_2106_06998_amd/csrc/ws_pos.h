@@ -38,7 +38,7 @@ __device__ inline WsPos ws_uniform(WsPos p)
     return p;
 }
 
-__device__ inline WsPos ws_pos_of(const WsParams &P, int t)
+__device__ inline WsPos ws_pos_of(const WsArgs &P, int t)
 {
     WsPos p;
     p.t = t;
@@ -58,7 +58,7 @@ __device__ inline WsPos ws_pos_of(const WsParams &P, int t)
     return ws_uniform(p);
 }
 
-__device__ inline WsPos ws_next_row(const WsParams &P, WsPos p)
+__device__ inline WsPos ws_next_row(const WsArgs &P, WsPos p)
 {
     ++p.t;
     p.rowmod += P.sh;
@@ -74,7 +74,7 @@ __device__ inline WsPos ws_next_row(const WsParams &P, WsPos p)
     return p;
 }
 
-__device__ inline WsPos ws_advance(const WsParams &P, WsPos p)
+__device__ inline WsPos ws_advance(const WsArgs &P, WsPos p)
 {
     if (++p.u == P.NSUB) {
         p.u = 0;
@@ -84,7 +84,7 @@ __device__ inline WsPos ws_advance(const WsParams &P, WsPos p)
 }
 
 // output columns of the sub-step that exist (the rest of its CWs slots is zero padding)
-__device__ inline int ws_cw_sub(const WsParams &P, const WsPos &p)
+__device__ inline int ws_cw_sub(const WsArgs &P, const WsPos &p)
 {
     const int x0 = p.strip * P.CW;
     int cw = P.Wo - x0;
