@@ -437,6 +437,7 @@ struct PackClass {
 };
 template <int N> struct PackJobs {
     int total;                        // fragments and channels: one wave each
+    int groups;                       // workgroups of the carrying launch that do them, in front of its own
     int nsub, NMB, Cin, Cout, w_sco, w_sci, kWfull;
     int res, il, es;                  // resident patches, even and odd channels apart (conv_unit_channel), bytes per element
     int C, S, dtype;                  // bias gradient: channels, pieces, storage type
@@ -446,9 +447,8 @@ template <int N> struct PackJobs {
     void *db;
     PackClass sub[N];
 };
-typedef PackJobs<kConvSubs> SideJobs;   // those that other launches carry
-// the argument of a launch that carries none: the estimator's own entry points run kernels without the jobs' code and argument
-// (C4 estimate 134.5 -> 133.9 us, 133.6 before there were any jobs)
-struct NoSideJobs {};
+// Those that other launches carry.  The kernels take them as one more argument, so that a launch without any runs a kernel without
+// the code and the argument (C4 estimate 134.5 -> 133.9 us, 133.6 before there were any jobs).
+typedef PackJobs<kConvSubs> SideJobs;
 
 }  // namespace xc

@@ -697,18 +697,19 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const f32x4 *
 // from global memory, and a lane ends up with all OG offsets of its (m, n) pairs, which are
 // adjacent in dW.
 // ---------------------------------------------------------------------------
-// nnz_norm: rows are scaled by 1 / nnz(Z_n), the number of non-zero entries of row n of Z (Eq. (8),
-// block-sparse probing vectors), instead of 1 / r; a row without any gives zeros.
-// one value of dW in the type the caller keeps its weights in
-template <int WT> __device__ inline void store_dw(void *dW, size_t i, float v)
+// dW in the type the caller keeps its weights in
+template <int WT> using dw_elem = std::conditional_t<WT == XCONV_F32, float, uint16_t>;
+template <int WT> __device__ inline dw_elem<WT> dw_value(float v)
 {
-    if constexpr (WT == XCONV_F32) static_cast<float *>(dW)[i] = v;
-    else static_cast<uint16_t *>(dW)[i] = f32_to_st16<WT>(v);
+    if constexpr (WT == XCONV_F32) return v;
+    else return f32_to_st16<WT>(v);
 }
 
+// nnz_norm: rows are scaled by 1 / nnz(Z_n), the number of non-zero entries of row n of Z (Eq. (8),
+// block-sparse probing vectors), instead of 1 / r; a row without any gives zeros.
 template <int OG, int WT>
 __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T, const float *__restrict__ Z,
-                                                    void *__restrict__ dW, int K2, int JP, int MP, int C_out, int C_in, int r,
+                                                    dw_elem<WT> *__restrict__ dW, int K2, int JP, int MP, int C_out, int C_in, int r,
                                                     int NTN, int nnz_norm)
 {
     const int lane = threadIdx.x, l16 = lane & 15, g = lane >> 4;
@@ -756,10 +757,10 @@ __global__ __launch_bounds__(64) void expand_kernel(const float *__restrict__ T,
         for (int v = 0; v < 4; ++v) {
             const int m = mt * 16 + 4 * g + v;
             if (m < C_out) {
-                const size_t dst = ((size_t)m * C_in + ncol) * K2 + o0;
+                dw_elem<WT> *dst = dW + ((size_t)m * C_in + ncol) * K2 + o0;
 #pragma unroll
                 for (int o = 0; o < OG; ++o)
-                    if (o0 + o < K2) store_dw<WT>(dW, dst + o, acc[o][v] * inv_r);
+                    if (o0 + o < K2) dst[o] = dw_value<WT>(acc[o][v] * inv_r);
             }
         }
     }
@@ -823,7 +824,7 @@ template <int NC> __device__ inline f32x4 once_sum(const f32x4 *p, int first, in
 // the workgroups that write the K2T offsets of one (m, n) run of dW share an L2, which merges their 4-byte stores.
 // ---------------------------------------------------------------------------
 template <int WT>
-__global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__restrict__ part, void *__restrict__ dW, int S, int K2,
+__global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__restrict__ part, dw_elem<WT> *__restrict__ dW, int S, int K2,
                                                                int K2T, int JP, int MQ, int JC, int C_out, int C_in)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [JC], then the thread groups' sums [NG][NE] (few-element slabs only)
@@ -855,7 +856,7 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
     for (int e = tid; e < JC * 4; e += kThreads) {
         const int mi = e & 3, j = e >> 2;
         const int m = 4 * mq + mi, n = j0 + j;
-        if (m < C_out && n < C_in) store_dw<WT>(dW, ((size_t)m * C_in + n) * K2T + og, slab[e]);
+        if (m < C_out && n < C_in) dW[((size_t)m * C_in + n) * K2T + og] = dw_value<WT>(slab[e]);
     }
 }
 
@@ -876,17 +877,18 @@ __global__ __launch_bounds__(kThreads) void pass2_exact_kernel(const f32x4 *__re
 // ---------------------------------------------------------------------------
 constexpr int kP2Threads = 1024;
 
-template <int QW, int WT, class SJ>
+// JOBS: nothing, or the small jobs that the launch carries along
+template <int QW, int WT, class... JOBS>
 __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__restrict__ part, const float *__restrict__ Z,
-                                                                void *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
-                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, const SJ J)
+                                                                dw_elem<WT> *__restrict__ dW, int S, int K2, int K2T, int JP, int MQ,
+                                                                int C_out, int C_in, int r, int nnz_norm, int z_vec, int NR, int ZS, const JOBS... jobs)
 {
     extern __shared__ f32x4 p2_lds[];   // slab [QW][JP], then the thread groups' sums [NG][NE] (few-element slabs only) and, after them, rows of Z [NR][ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, q4 = lane >> 4;
-    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
+    if constexpr (sizeof...(JOBS) > 0) {
         if ((int)blockIdx.y >= K2T) {
-            side_jobs<0, kP2Threads>(J, ((int)blockIdx.y - K2T) * gridDim.x + blockIdx.x, ((int)gridDim.y - K2T) * gridDim.x);
+            side_jobs<0, kP2Threads>(jobs..., ((int)blockIdx.y - K2T) * gridDim.x + blockIdx.x, ((int)gridDim.y - K2T) * gridDim.x);
             return;
         }
     }
@@ -993,7 +995,7 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int m = 4 * (mg * QW + q4) + v;
-                    if (m < C_out) store_dw<WT>(dW, ((size_t)m * C_in + n) * K2T + og, acc[v] * inv_r);
+                    if (m < C_out) dW[((size_t)m * C_in + n) * K2T + og] = dw_value<WT>(acc[v] * inv_r);
                 }
             }
         }
@@ -1002,7 +1004,7 @@ __global__ __launch_bounds__(kP2Threads) void pass2_mfma_kernel(const f32x4 *__r
 
 // Exact path: dW[m,n,o] = T[o,n,m] (a transpose of the reduced tile).
 template <int WT>
-__global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restrict__ T, void *__restrict__ dW, int K2, int JP,
+__global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restrict__ T, dw_elem<WT> *__restrict__ dW, int K2, int JP,
                                                           int MP, int C_out, int C_in)
 {
     const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(kThreads) void untile_kernel(const float *__restric
     const int o = (int)(i % K2);
     const long long mn = i / K2;
     const int n = (int)(mn % C_in), m = (int)(mn / C_in);
-    store_dw<WT>(dW, (size_t)i, T[tile_index(o, n, m, JP, MP)]);
+    dW[i] = dw_value<WT>(T[tile_index(o, n, m, JP, MP)]);
 }
 
 // dY planes whose size is not a whole number of 16-byte vectors are copied once into planes
@@ -1319,7 +1321,7 @@ bool reduce_expand_fused(const CorrParams &P, bool have_z, bool exact, int C_in,
 }
 
 template <int WT>
-static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, bool exact, void *dW, int C_in, int r, bool nnz_norm,
+static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, bool exact, dw_elem<WT> *dW, int C_in, int r, bool nnz_norm,
                                           int nsets, hipStream_t st, const SideJobs *Jp)
 {
     const int MQ = P.MP / 4;
@@ -1350,22 +1352,25 @@ static hipError_t launch_reduce_expand_as(const CorrParams &P, const float *Z, b
         const int gx = round_up(MQ / QW, 8);
         const int nside = side_groups<kP2Threads>(Jp);
         const dim3 grid((unsigned)gx, (unsigned)(K2T + ceil_div(nside, gx)));
-#define XC_P2M(Q, SJ, J)                                                                                                        \
-    {                                                                                                                    \
-        static bool done = false;                                                                                        \
-        if (!done) {                                                                                                     \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(pass2_mfma_kernel<Q, WT, SJ>),                      \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                  \
-            if (e != hipSuccess) return e;                                                                               \
-            done = true;                                                                                                 \
-        }                                                                                                                \
-        hipLaunchKernelGGL((pass2_mfma_kernel<Q, WT, SJ>), grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, \
-                           P.C_out, C_in, r, nnz_norm ? 1 : 0, z_vec, NR, ZS, J);                                        \
-    }
-#define XC_P2M_SIDE(Q) { if (nside) XC_P2M(Q, SideJobs, *Jp) else XC_P2M(Q, NoSideJobs, NoSideJobs{}) }
-        if (QW == 4) XC_P2M_SIDE(4) else if (QW == 2) XC_P2M_SIDE(2) else XC_P2M_SIDE(1)
-#undef XC_P2M_SIDE
-#undef XC_P2M
+        auto launch = [&](auto quads, const auto &...jobs) {
+            constexpr auto kernel = pass2_mfma_kernel<decltype(quads)::value, WT, std::decay_t<decltype(jobs)>...>;
+            static bool done = false;
+            if (!done) {
+                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                if (e != hipSuccess) return e;
+                done = true;
+            }
+            hipLaunchKernelGGL(kernel, grid, dim3(kP2Threads), lds, st, part, Z, dW, P.S, P.K2, K2T, P.JP, MQ, P.C_out, C_in, r, nnz_norm ? 1 : 0,
+                               z_vec, NR, ZS, jobs...);
+            return hipSuccess;
+        };
+        auto launch_quads = [&](const auto &...jobs) {
+            if (QW == 4) return launch(std::integral_constant<int, 4>{}, jobs...);
+            if (QW == 2) return launch(std::integral_constant<int, 2>{}, jobs...);
+            return launch(std::integral_constant<int, 1>{}, jobs...);
+        };
+        const hipError_t e = nside ? launch_quads(*Jp) : launch_quads();
+        if (e != hipSuccess) return e;
     }
     return hipGetLastError();
 }
@@ -1375,13 +1380,13 @@ hipError_t launch_reduce_expand(const CorrParams &P, const float *Z, bool exact,
 {
     (void)dist;
     (void)seed;
-    if (dw_dtype == XCONV_BF16) return launch_reduce_expand_as<XCONV_BF16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
-    if (dw_dtype == XCONV_F16) return launch_reduce_expand_as<XCONV_F16>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
-    return launch_reduce_expand_as<XCONV_F32>(P, Z, exact, dW, C_in, r, nnz_norm, nsets, st, J);
+    if (dw_dtype == XCONV_BF16) return launch_reduce_expand_as<XCONV_BF16>(P, Z, exact, static_cast<dw_elem<XCONV_BF16> *>(dW), C_in, r, nnz_norm, nsets, st, J);
+    if (dw_dtype == XCONV_F16) return launch_reduce_expand_as<XCONV_F16>(P, Z, exact, static_cast<dw_elem<XCONV_F16> *>(dW), C_in, r, nnz_norm, nsets, st, J);
+    return launch_reduce_expand_as<XCONV_F32>(P, Z, exact, static_cast<dw_elem<XCONV_F32> *>(dW), C_in, r, nnz_norm, nsets, st, J);
 }
 
 template <int WT>
-static hipError_t launch_expand_as(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
+static hipError_t launch_expand_as(const CorrParams &P, const float *Z, dw_elem<WT> *dW, int C_in, int r, hipStream_t st, bool nnz_norm,
                                    const float *Tin, int K2in)
 {
     const int nn = nnz_norm ? 1 : 0;
@@ -1412,9 +1417,9 @@ static hipError_t launch_expand_as(const CorrParams &P, const float *Z, void *dW
 hipError_t launch_expand(const CorrParams &P, const float *Z, void *dW, int C_in, int r, hipStream_t st, bool nnz_norm, const float *Tin,
                          int K2in, int dw_dtype)
 {
-    if (dw_dtype == XCONV_BF16) return launch_expand_as<XCONV_BF16>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
-    if (dw_dtype == XCONV_F16) return launch_expand_as<XCONV_F16>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
-    return launch_expand_as<XCONV_F32>(P, Z, dW, C_in, r, st, nnz_norm, Tin, K2in);
+    if (dw_dtype == XCONV_BF16) return launch_expand_as<XCONV_BF16>(P, Z, static_cast<dw_elem<XCONV_BF16> *>(dW), C_in, r, st, nnz_norm, Tin, K2in);
+    if (dw_dtype == XCONV_F16) return launch_expand_as<XCONV_F16>(P, Z, static_cast<dw_elem<XCONV_F16> *>(dW), C_in, r, st, nnz_norm, Tin, K2in);
+    return launch_expand_as<XCONV_F32>(P, Z, static_cast<dw_elem<XCONV_F32> *>(dW), C_in, r, st, nnz_norm, Tin, K2in);
 }
 
 }  // namespace xc

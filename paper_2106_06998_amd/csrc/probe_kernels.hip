@@ -159,20 +159,15 @@ __global__ __launch_bounds__(kThreads) void pack_z_16_kernel(const float *__rest
 // NHWC: X is [pixels, C_in]; a lane then loads four consecutive channels (16 bytes) of one pixel,
 // MFMA u uses element u of every lane (see f32_frag_channel), and the wave's tile is four
 // sub-tiles of 16 pixels; `ngroups` is the number of pixels.
-template <int JT, bool NHWC, class SJ>
+// JOBS: nothing, or the small jobs that the launch carries along
+template <int JT, bool NHWC, class... JOBS>
 __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const float *__restrict__ X, const float *__restrict__ Z,
                                                              const float *__restrict__ zpack, float *__restrict__ Xt, int C_in,
                                                              int HW, int r, int CS, int j0, long long ngroups, int ntiles,
-                                                             SliceMap sm, int dist, uint64_t seed, int nside, const SJ J)
+                                                             SliceMap sm, int dist, uint64_t seed, const JOBS... jobs)
 {
-    int wg = blockIdx.x, nwg = gridDim.x;
-    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
-        if (wg < nside) {
-            side_jobs<4, kThreads>(J, wg, nside);
-            return;
-        }
-        wg -= nside;
-        nwg -= nside;
+    if constexpr (sizeof...(JOBS) > 0) {
+        if (do_side_jobs<4, kThreads>(jobs...)) return;
     }
     extern __shared__ float zs[];  // [KQ4][JT][64] A-operand fragments, zero beyond C_in
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -251,7 +246,7 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
     };
 
     // The first tile's loads are in flight while the Z fragments are staged.
-    const int wv = xcd_block(wg, nwg) * 4 + wave, NWV = nwg * 4;
+    const int wv = xcd_block(own_group(jobs...), own_groups(jobs...)) * 4 + wave, NWV = own_groups(jobs...) * 4;
     int it = 0;
     int tile = wave_tile(wv, 0, NWV, ntiles);
     Tile cur;
@@ -336,20 +331,14 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 // ---------------------------------------------------------------------------
 // NHWC: X is [pixels, C_in]; the 8 channels a lane supplies are then one 16-byte load, no
 // transpose; the wave's tile is PT sub-tiles of 16 pixels and `ngroups` is the number of pixels.
-template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class SJ>
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
 __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *__restrict__ X, const float *__restrict__ Z,
                                                             const uint4 *__restrict__ zpack, uint16_t *__restrict__ Xt, int C_in,
                                                             int HW, int r, int CS, int j0, long long ngroups, int ntiles,
-                                                            SliceMap sm, int dist, uint64_t seed, int nword, int nt, int nside, const SJ J)
+                                                            SliceMap sm, int dist, uint64_t seed, int nword, int nt, const JOBS... jobs)
 {
-    int wg = blockIdx.x, nwg = gridDim.x;
-    if constexpr (std::is_same_v<SJ, SideJobs>) {   // small jobs carried along
-        if (wg < nside) {
-            side_jobs<2, kThreads>(J, wg, nside);
-            return;
-        }
-        wg -= nside;
-        nwg -= nside;
+    if constexpr (sizeof...(JOBS) > 0) {
+        if (do_side_jobs<2, kThreads>(jobs...)) return;
     }
     extern __shared__ uint4 zf[];  // [SPLIT?2:1][KK][JT][64] A-operand fragments, then (nword > 0) the generator words of a +-1 matrix
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -496,7 +485,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
     };
 
     // The first tile's loads are in flight while the Z fragments are staged.
-    const int wv = xcd_block(wg, nwg) * 4 + wave, NWV = nwg * 4;
+    const int wv = xcd_block(own_group(jobs...), own_groups(jobs...)) * 4 + wave, NWV = own_groups(jobs...) * 4;
     int it = 0;
     int tile = wave_tile(wv, 0, NWV, ntiles);
     Tile cur;
@@ -753,18 +742,24 @@ static int probe_grid(int ntiles, int wgs_per_cu)
     return want < slots ? want : slots;
 }
 
-template <int JT, bool NHWC, class SJ>
+static SideJobs with_groups(SideJobs J, int groups)
+{
+    J.groups = groups;
+    return J;
+}
+
+template <int JT, bool NHWC, class... JOBS>
 static hipError_t launch_probe_f32_side(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
-                                      int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const SJ &J)
+                                      int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
     // a lane owns 4 consecutive pixels of a plane (NCHW) or one pixel of each of 4 sub-tiles (NHWC)
     const long long ngroups = NHWC ? npix : npix / 4;
     const int ntiles = (int)(NHWC ? (npix + 63) / 64 : (ngroups + 15) / 16);
     const size_t lds = (size_t)ceil_div(C_in, 16) * 4 * JT * 64 * sizeof(float);
-    hipError_t e = set_lds(probe_f32_kernel<JT, NHWC, SJ>, lds);
+    hipError_t e = set_lds(probe_f32_kernel<JT, NHWC, JOBS...>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_f32_kernel<JT, NHWC, SJ>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st, X, Z, zpack, Xt, C_in, HW, r,
-                       CS, j0, ngroups, ntiles, sm, dist, seed, nside, J);
+    hipLaunchKernelGGL((probe_f32_kernel<JT, NHWC, JOBS...>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st, X, Z, zpack, Xt, C_in, HW, r,
+                       CS, j0, ngroups, ntiles, sm, dist, seed, jobs...);
     return hipGetLastError();
 }
 
@@ -773,23 +768,23 @@ static hipError_t launch_probe_f32_jt(const float *X, const float *Z, const floa
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
-    if (nside) return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, *J);
-    return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0, NoSideJobs{});
+    if (nside) return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
+    return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
 }
 
-template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class SJ>
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
 static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
-                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const SJ &J)
+                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
     const long long ngroups = NHWC ? npix : npix / PT;
     const int ntiles = (int)(NHWC ? (npix + 16 * PT - 1) / (16 * PT) : (ngroups + 15) / 16);
     // a dense +-1 matrix that comes from the seed and has no fragments in scratch is drawn by the workgroups from its generator words
     const int nword = (!Z && !zpack && probe_draws_words(C_in, r, dist)) ? (int)(((long long)C_in * r + 63) / 64) : 0;
     const size_t lds = (size_t)(SPLIT ? 2 : 1) * ceil_div(C_in, 32) * JT * 64 * sizeof(uint4) + (size_t)round_up(nword, 2) * 8;
-    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, SJ>, lds);
+    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, JOBS...>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, SJ>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
-                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), nside, J);
+    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, JOBS...>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
+                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), jobs...);
     return hipGetLastError();
 }
 
@@ -798,8 +793,8 @@ static hipError_t launch_probe_16_cfg(const uint16_t *X, const float *Z, const u
                                       int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
-    if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, *J);
-    return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0, NoSideJobs{});
+    if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
+    return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
 }
 
 template <int DT, int JT>
@@ -1163,16 +1158,14 @@ hipError_t launch_dy_slices(int dtype, const void *src, void *dst, int B, int C,
 // indep != 0: independent probing over the channel window [n0, n0 + nch): nch * r images; image nl * r + j is probing
 // vector j of channel n0 + nl, the values of column j of Z on the rows of that channel and zero on every other channel.
 // With cl_cs > 0 the cl_cs channel slots of an image are the channels of the window (slot = channel - n0).
-template <int DT>
+template <int DT, class... JOBS>
 __global__ __launch_bounds__(kThreads) void gen_zimg_kernel(void *__restrict__ out, long long K, int r, int nimg, int dist,
-                                                            uint64_t seed, int C_in, int cl_cs, int indep, int n0, int nch, int nside,
-                                                            const SideJobs J)
+                                                            uint64_t seed, int C_in, int cl_cs, int indep, int n0, int nch, const JOBS... jobs)
 {
-    if ((int)blockIdx.x < nside) {   // small jobs carried along
-        side_jobs<0, kThreads>(J, blockIdx.x, nside);
-        return;
+    if constexpr (sizeof...(JOBS) > 0) {
+        if (do_side_jobs<0, kThreads>(jobs...)) return;
     }
-    const long long i = (long long)((int)blockIdx.x - nside) * kThreads + threadIdx.x;
+    const long long i = (long long)own_group(jobs...) * kThreads + threadIdx.x;
     const long long N = K / C_in;
     const int ncol = indep ? nch * r : r;
     float z = 0.0f;
@@ -1209,16 +1202,15 @@ __global__ __launch_bounds__(kThreads) void gen_zimg_kernel(void *__restrict__ o
 // draws a word only when a row's bit position crosses into the next one: C5 8 + 8 words for 128 values where the kernel
 // above draws one per value.  LINE = 8 consecutive k (cl_cs == 0; K a multiple of 8) or the 8 channel slots 8s .. 8s + 7 of
 // one pixel (cl_cs > 0, a multiple of 8; slots from C_in on are zero).
-template <int DT>
+template <int DT, class... JOBS>
 __global__ __launch_bounds__(kThreads) void gen_zimg_pm1_kernel(void *__restrict__ out, long long K, int r, int nimg, uint64_t seed,
-                                                                int C_in, int cl_cs, int nj, int nside, const SideJobs J)
+                                                                int C_in, int cl_cs, int nj, const JOBS... jobs)
 {
-    if ((int)blockIdx.x < nside) {   // small jobs carried along
-        if (blockIdx.y == 0) side_jobs<0, kThreads>(J, blockIdx.x, nside);
-        return;
+    if constexpr (sizeof...(JOBS) > 0) {
+        if (do_side_jobs<0, kThreads>(jobs...)) return;
     }
     const long long N = K / C_in;
-    const long long t = (long long)((int)blockIdx.x - nside) * kThreads + threadIdx.x;
+    const long long t = (long long)own_group(jobs...) * kThreads + threadIdx.x;
     const long long nline = cl_cs == 0 ? K / 8 : N * (cl_cs / 8);
     if (t >= nline) return;
     const int j0 = blockIdx.y * nj;
@@ -1266,34 +1258,35 @@ __global__ __launch_bounds__(kThreads) void gen_zimg_pm1_kernel(void *__restrict
 
 // n0, nch: channel window of the images (0, C_in for all channels); with cl_cs > 0 an image has cl_cs channel slots
 // for the channels n0 .. n0 + nch - 1 and N = K / C_in pixels
-hipError_t launch_gen_zimg(int dtype, void *out, long long K, int r, int nimg, int dist, uint64_t seed, int C_in, int cl_cs,
-                           int indep, int n0, int nch, hipStream_t st, const SideJobs *Jp)
+template <int DT, class... JOBS>
+static hipError_t launch_gen_zimg_dt(void *out, long long K, int r, int nimg, int dist, uint64_t seed, int C_in, int cl_cs, int indep, int n0,
+                                     int nch, hipStream_t st, int nside, const JOBS &...jobs)
 {
-    const SideJobs J = Jp ? *Jp : SideJobs{};
-    const int nside = side_groups<kThreads>(Jp);
     // dense +-1 vectors over all channels, whole 16-byte lines: one generator word per 64 entries
     if ((dist & 0xff) == XCONV_RADEMACHER && (dist >> 8) == 0 && !indep && n0 == 0 && nch == C_in &&
         (cl_cs == 0 ? K % 8 == 0 : cl_cs % 8 == 0) && (reinterpret_cast<uintptr_t>(out) & 15u) == 0) {
         const long long nline = cl_cs == 0 ? K / 8 : (K / C_in) * (cl_cs / 8);
         const int nj = 8;    // images per thread: enough threads for the chip, few redrawn words (C5, 64 images: 13.4 us; 15.0 with 16, 15.4 with 2)
         dim3 grid((unsigned)(nside + (nline + kThreads - 1) / kThreads), (unsigned)ceil_div(nimg, nj));
-        if (dtype == XCONV_F32)
-            hipLaunchKernelGGL(gen_zimg_pm1_kernel<XCONV_F32>, grid, dim3(kThreads), 0, st, out, K, r, nimg, seed, C_in, cl_cs, nj, nside, J);
-        else if (dtype == XCONV_BF16)
-            hipLaunchKernelGGL(gen_zimg_pm1_kernel<XCONV_BF16>, grid, dim3(kThreads), 0, st, out, K, r, nimg, seed, C_in, cl_cs, nj, nside, J);
-        else
-            hipLaunchKernelGGL(gen_zimg_pm1_kernel<XCONV_F16>, grid, dim3(kThreads), 0, st, out, K, r, nimg, seed, C_in, cl_cs, nj, nside, J);
+        hipLaunchKernelGGL((gen_zimg_pm1_kernel<DT, JOBS...>), grid, dim3(kThreads), 0, st, out, K, r, nimg, seed, C_in, cl_cs, nj, jobs...);
         return hipGetLastError();
     }
     const long long total = cl_cs ? (K / C_in) * nimg * cl_cs : K * nimg;
     dim3 grid((unsigned)(nside + (total + kThreads - 1) / kThreads));
-    if (dtype == XCONV_F32)
-        hipLaunchKernelGGL(gen_zimg_kernel<XCONV_F32>, grid, dim3(kThreads), 0, st, out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, nside, J);
-    else if (dtype == XCONV_BF16)
-        hipLaunchKernelGGL(gen_zimg_kernel<XCONV_BF16>, grid, dim3(kThreads), 0, st, out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, nside, J);
-    else
-        hipLaunchKernelGGL(gen_zimg_kernel<XCONV_F16>, grid, dim3(kThreads), 0, st, out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, nside, J);
+    hipLaunchKernelGGL((gen_zimg_kernel<DT, JOBS...>), grid, dim3(kThreads), 0, st, out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, jobs...);
     return hipGetLastError();
+}
+
+hipError_t launch_gen_zimg(int dtype, void *out, long long K, int r, int nimg, int dist, uint64_t seed, int C_in, int cl_cs,
+                           int indep, int n0, int nch, hipStream_t st, const SideJobs *J)
+{
+    const int nside = side_groups<kThreads>(J);
+    auto launch = [&](const auto &...jobs) {
+        if (dtype == XCONV_F32) return launch_gen_zimg_dt<XCONV_F32>(out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, st, nside, jobs...);
+        if (dtype == XCONV_BF16) return launch_gen_zimg_dt<XCONV_BF16>(out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, st, nside, jobs...);
+        return launch_gen_zimg_dt<XCONV_F16>(out, K, r, nimg, dist, seed, C_in, cl_cs, indep, n0, nch, st, nside, jobs...);
+    };
+    return nside ? launch(with_groups(*J, nside)) : launch();
 }
 
 // Eq. (8) for probes over pixels and channels: the estimate of input channel n, which carries the factor 1/r,

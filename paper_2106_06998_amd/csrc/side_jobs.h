@@ -59,6 +59,19 @@ template <int ES, int THREADS, class SJ> __device__ inline void side_jobs(const 
     }
 }
 
+// In a kernel that may carry jobs (an empty pack or one SideJobs): does those of this workgroup, if it is one of theirs; number
+// and count of the kernel's own workgroups along the grid
+template <int ES, int THREADS> __device__ inline bool do_side_jobs(const SideJobs &J)
+{
+    if ((int)blockIdx.x >= J.groups) return false;
+    if (blockIdx.y == 0) side_jobs<ES, THREADS>(J, blockIdx.x, J.groups);
+    return true;
+}
+__device__ inline unsigned own_group() { return blockIdx.x; }
+__device__ inline unsigned own_groups() { return gridDim.x; }
+__device__ inline unsigned own_group(const SideJobs &J) { return blockIdx.x - J.groups; }
+__device__ inline unsigned own_groups(const SideJobs &J) { return gridDim.x - J.groups; }
+
 // workgroups that carry the jobs; a multiple of 8 keeps the dies of the others (xcd_block)
 template <int THREADS, class SJ> inline int side_groups(const SJ *J)
 {
