@@ -46,7 +46,7 @@ typedef enum {
     XCONV_EINVAL = 1,       /* null pointer, non-positive extent, empty output, bad enum   */
     XCONV_EUNSUPPORTED = 2, /* valid but not implemented (see xconv_check_desc)             */
     XCONV_EWORKSPACE = 3,   /* ws_bytes smaller than xconv_workspace_bytes()                */
-    XCONV_EHIP = 4          /* the HIP runtime reported an error while enqueuing            */
+    XCONV_EHIP = 4          /* the HIP runtime reported an error while enqueuing, or no host memory for a plan */
 } xconv_status;
 
 typedef enum { XCONV_F32 = 0, XCONV_BF16 = 1, XCONV_F16 = 2 } xconv_dtype;   /* storage of X, dY, Xt; sums and dW are fp32 */

@@ -250,13 +250,11 @@ bool plan(ConvParams &P, int dtype, int ncu)
 
 }  // namespace
 
+// every kernel offset belongs to one class at most
 size_t conv_ws_bytes(const xconv_desc *d, int transposed)
 {
-    const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
-    long long n = 0;
-    for (const ConvSub &s : make_subs(d, transposed, Ho, Wo))
-        n += packed_units(s, d->dtype, transposed ? d->C_out : d->C_in, transposed ? d->C_in : d->C_out);
-    return (size_t)n * 16 + kConvOverread;
+    const int Cin = transposed ? d->C_out : d->C_in, Cout = transposed ? d->C_in : d->C_out;
+    return (size_t)ceil_div(Cout, 32) * ksteps(d->dtype, Cin) * d->kH * d->kW * 64 * 16 + kConvOverread;
 }
 
 // One launch of a product: a class group of a run of images.  The pointers of P are filled in per call.
@@ -371,7 +369,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
 }
 
 std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, bool packed, int align, int oalign)
-{
+try {
     const int ncu = device_cus();
     // (the overrides of tests and sweeps are part of the key)
     const int key[24] = {d->B, d->C_in, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, d->dtype, d->layout,
@@ -390,6 +388,8 @@ std::shared_ptr<const ConvPlan> conv_plan(const xconv_desc *d, int transposed, b
     if (g_conv_plans.size() >= kConvPlans) g_conv_plans.clear();
     g_conv_plans.emplace(k, p);
     return p;
+} catch (...) {
+    return nullptr;      // out of host memory: the entry points are C
 }
 
 }  // namespace

@@ -1,7 +1,10 @@
 """Launch plans of the forward convolution and the input gradient on the host (no GPU): the byte offsets of a tile, which count
 from its first image, fit the descriptor (or, with 64-bit addresses, the 32-bit element tables) of the kernel that the plan takes,
 whatever the layer.  A tile of a strip of SW columns takes SW positions of every row, so it crosses TU / (Ho * SW) images."""
+import os
 import random
+import subprocess
+import sys
 import time
 
 import numpy as np
@@ -89,3 +92,39 @@ def test_the_search_does_not_grow_with_the_image():
         t = time.perf_counter()
         xb.xconv_conv_plan_info(d, 0, 1)
         assert time.perf_counter() - t < 0.03           # 0.3 ms; 70 and 490 ms when every number of strips was tried
+
+
+def test_running_out_of_host_memory_is_a_status(tmp_path):
+    # operator new of a process of its own fails on request; an exception would end it at the C boundary
+    src = tmp_path / "new.cpp"
+    src.write_text("""#include <cstdlib>
+#include <new>
+static int fail = 0;
+extern "C" void set_fail(int on) { fail = on; }
+void *operator new(std::size_t n) { void *p = fail ? nullptr : std::malloc(n ? n : 1); if (!p) throw std::bad_alloc(); return p; }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, std::size_t) noexcept { std::free(p); }
+""")
+    so = str(tmp_path / "new.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(src), "-o", so], check=True)
+    code = """
+import ctypes, sys
+new = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+from paper_2106_06998_amd import binding as xb
+L, out = xb.lib(), (ctypes.c_int32 * 16)()
+warm, d = (xb.make_desc(2, 64, 64, n, n, 3, 2, 1, 8, "f16") for n in (28, 30))
+assert L.xconv_conv_plan_info(ctypes.byref(warm), 1, 1, out) == 0
+one = ctypes.c_void_p(4096)
+new.set_fail(1)
+status = [L.xconv_conv_plan_info(ctypes.byref(d), t, 1, out) for t in (0, 1)]
+status.append(L.xconv_conv_fwd(ctypes.byref(d), one, one, one, None))
+size = L.xconv_conv_workspace_bytes(ctypes.byref(d), 1)
+new.set_fail(0)
+assert size == L.xconv_conv_workspace_bytes(ctypes.byref(d), 1) > 0
+assert all(s != 0 for s in status), status
+assert L.xconv_conv_plan_info(ctypes.byref(d), 1, 1, out) == 0
+print("statuses", status)
+"""
+    p = subprocess.run([sys.executable, "-c", code, so], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert p.returncode == 0 and "statuses" in p.stdout, (p.returncode, p.stdout)
