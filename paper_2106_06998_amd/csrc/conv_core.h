@@ -232,13 +232,10 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                     const int cu = conv_unit_channel<UE, IL>(u, 0), left = P.Cin - c0 - cu;
                     const uint32_t vo = off + (uint32_t)cu * cs;
                     constexpr int step = IL ? 2 : 1;
-                    // (no lane reads a channel past the last: its scalar offset stays below the descriptor's 2 GiB, which the hardware's
-                    // bounds check subtracts it from)
                     auto load = [&](auto part) {
 #pragma unroll
                         for (int e = 0; e < UE; ++e) {
-                            const int ce = decltype(part)::value ? std::min(c0 + e * step, P.Cin - 1) : c0 + e * step;
-                            const int v = (int)(!decltype(part)::value || e * step < left ? vo : kConvOob), so = (int)((uint32_t)ce * cs);
+                            const int v = (int)(!decltype(part)::value || e * step < left ? vo : kConvOob), so = (int)((uint32_t)(c0 + e * step) * cs);
                             if constexpr (VEC == 1 || ES == 4) sr[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, v, so, 0);
                             else sr[i][e] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, v, so, 0);
                         }
@@ -517,7 +514,6 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const auto orsrc = __builtin_amdgcn_make_buffer_rsrc(out_b, 0, (int)kConvOob, 0x00020000);
     const uint32_t cs = (uint32_t)P.out_sc * ES;
     const uint32_t odd = (uint32_t)lane & 1u;
-    auto first_of = [&](int co) { return (uint32_t)std::min(co, P.Cout - 1); };   // (scalar offsets of channels that exist, as above)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int cb = co_w + mt * 32;          // channels cb .. cb + 31
@@ -565,7 +561,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                     for (int i = 0; i < 16; i += 2) {
                         const int r = 8 * (i / 4) + i % 4;      // + 4 * h + odd
                         const uint32_t v = full || cb + r + 4 * h + (int)odd < P.Cout ? vo : kConvOob;
-                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)v, (int)(first_of(cb + r) * cs), 0);
+                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)v, (int)((uint32_t)(cb + r) * cs), 0);
                     }
                 }
             } else {
@@ -576,7 +572,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                     const int r = 8 * (i / 4) + i % 4;          // + 4 * h
                     const uint32_t off = SWAP ? otab[(wn * NT + nt) * 32 + r + 4 * h].x : offl;
                     const bool on = full || cb + (SWAP ? l32 : r + 4 * h) < P.Cout;
-                    const int vo = (int)(on && off != kConvOob ? off + lo : kConvOob), so = (int)(first_of(SWAP ? cb : cb + r) * cs);
+                    const int vo = (int)(on && off != kConvOob ? off + lo : kConvOob), so = (int)((uint32_t)(SWAP ? cb : cb + r) * cs);
                     const elem_t v = stored(acc[mt][nt][i]);
                     if constexpr (ES == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, vo, so, 0);
                     else __builtin_amdgcn_raw_buffer_store_b16((short)v, orsrc, vo, so, 0);

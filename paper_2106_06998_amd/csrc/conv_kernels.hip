@@ -326,9 +326,15 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
     }
     // images per launch: 32-bit row and tile arithmetic
     const int bstep = (int)std::max<long long>(1, std::min<long long>(d->B, kMaxPos / ((long long)Hout * Wout)));
+    // 64-bit addresses for images past the descriptor, and for few channels on very large planes: lanes past the last channel are
+    // masked by an offset past the descriptor, but the scalar offset of their channel, up to a whole unit or block, counts as
+    // well, and the hardware's bounds check subtracts it from the size.  (Stopping it at the last channel in the kernel cost the 1x1
+    // layers 2-4 %.)
+    const int in_ch = round_up(P.Cin, P.Cin > kConvUnits * ue ? kConvUnits * ue : 2 * ue);
+    const bool huge = std::max(P.in_sb, P.out_sb) * es > kMaxReach || (long long)in_ch * P.in_sc * es > kMaxReach ||
+                      (long long)round_up(P.Cout, 32) * P.out_sc * es > kMaxReach;
     // (an image that fits 32-bit offsets never needs 64-bit addresses, and patches of so few channels are resident: a tile of one
     // position fits)
-    const bool huge = std::max(P.in_sb, P.out_sb) * es > kMaxReach;
     const size_t per = !huge && (!packed || P.Cin <= kConvResident) ? kConvSubsMany : kConvSubs;
     for (size_t s0 = 0; s0 < subs.size(); s0 += per) {
         P.nsub = (int)std::min<size_t>(per, subs.size() - s0);

@@ -22,6 +22,8 @@ LARGE = [
     (40, 512, 512, 28, 602, 4, 5, 0, "f32", False),        # few output rows and large images
     (3, 64, 8, 4000, 4000, 3, 1, 1, "f16", False),         # one image is past the descriptor
     (300, 2000, 2000, 1, 5000, 1, 1, 0, "f32", True),
+    (1, 1, 2, 11000, 11000, 3, 1, 1, "f32", False),        # few channels on large planes
+    (2, 3, 1, 12000, 12000, 3, 1, 1, "f16", False),
 ]
 
 
@@ -43,6 +45,12 @@ def offsets_fit(case):
             assert reach < 2 ** 32 - 1 if v["big"] else reach * es < 2 ** 31, (case, transposed, ws, reach, v)
             assert v["lds_bytes"] <= 160 * 1024
             assert v["big"] or image * es < 2 ** 31
+            # scalar offsets of whole units of input channels and blocks of 32 output channels
+            if not v["big"] and not nhwc:
+                cin, cout, ue = (C_out, C_in, 16 // es) if transposed else (C_in, C_out, 16 // es)
+                unit = 2 * ue if cin <= 8 * ue else 8 * ue
+                planes = (Ho * Wo, H * W) if transposed else (H * W, Ho * Wo)
+                assert -(-cin // unit) * unit * planes[0] * es < 2 ** 31 and -(-cout // 32) * 32 * planes[1] * es < 2 ** 31
 
 
 @pytest.mark.parametrize("case", LARGE, ids=["-".join(str(v) for v in c) for c in LARGE])

@@ -14,9 +14,10 @@ CASES = [
     (8, 256, 1024, 500, 500, 1, 0, "bf16", True, False),
     (8, 384, 192, 500, 500, 1, 0, "f32", True, False),
     (24, 128, 64, 3, 80000, 3, 1, "f16", False, False),
-    (1, 1, 2, 11000, 11000, 3, 1, "f32", False, False),    # few channels of planes that fill a unit past 2 GiB
-    (2, 3, 1, 12000, 12000, 3, 1, "f16", False, False),
-    (1, 3, 2, 9001, 12001, 1, 0, "bf16", False, False),
+    (1, 1, 2, 11000, 11000, 3, 1, "f32", False, True),     # few channels of planes that fill a unit past 2 GiB
+    (2, 3, 1, 12000, 12000, 3, 1, "f16", False, True),
+    (1, 3, 2, 9001, 12001, 1, 0, "bf16", False, True),
+    (2, 3, 5, 5500, 5500, 3, 1, "f16", False, False),      # just below
     (2, 64, 8, 4200, 4200, 3, 1, "f16", False, True),
     (2, 8, 64, 3000, 3000, 3, 1, "f32", True, True),
 ]
