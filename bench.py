@@ -196,7 +196,8 @@ def measure_config(cfg, steps, warmup, dev, with_exact=False, nhwc=False):
         out["exact_ms"] = ms_x
         out["exact_gflops"] = alg["exact_flops"] / ms_x / 1e6
         out["estimate_vs_exact_speedup"] = ms_x / ms_step
-        # the rest of the layer on the library's own kernels (forward convolution, exact input gradient)
+        # the rest of the layer on the library's own kernels (forward convolution, exact input gradient): the entry points without
+        # scratch and, *_ws, those with packed weights, which the layers use
         if not nhwc:
             import torch
             td = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[cfg.dtype]
@@ -206,6 +207,9 @@ def measure_config(cfg, steps, warmup, dev, with_exact=False, nhwc=False):
             n_fast = max(steps // 10, 3)
             ms_f = time_region(lambda i: xb.xconv_conv_fwd(L.desc, L.sets[i % len(L.sets)]["X"], Wd, Yd), n_fast, 2)
             ms_b = time_region(lambda i: xb.xconv_dx_exact(L.desc, L.sets[i % len(L.sets)]["dY"], Wd, dXd), n_fast, 2)
+            ws = [xb.alloc_bytes(xb.xconv_conv_workspace_bytes(L.desc, g), dev) for g in (0, 1)]
+            out["conv_fwd_ws_ms"] = time_region(lambda i: xb.xconv_conv_fwd_ws(L.desc, L.sets[i % len(L.sets)]["X"], Wd, None, Yd, ws[0]), n_fast, 2)
+            out["dx_exact_ws_ms"] = time_region(lambda i: xb.xconv_dx_exact_ws(L.desc, L.sets[i % len(L.sets)]["dY"], Wd, dXd, ws[1]), n_fast, 2)
             out["conv_fwd_ms"], out["dx_exact_ms"] = ms_f, ms_b
             out["conv_fwd_gflops"] = alg["exact_flops"] / ms_f / 1e6
             out["dx_exact_gflops"] = alg["exact_flops"] / ms_b / 1e6

@@ -72,18 +72,20 @@ std::vector<ConvSub> make_subs(const xconv_desc *d, int transposed, int Ho, int 
         n = first < k ? (k - 1 - first) / s + 1 : 0;
         pad = (n - 1) - (a + p - first) / s;
     };
-    for (int a = 0; a < std::min(d->stride_h, d->H); ++a)
+    for (int a = 0; a < std::min(d->stride_h, d->H); ++a) {
+        ConvSub s{};
+        axis(a, d->kH, d->stride_h, d->pad_h, s.kH, s.ky0, s.ph);
+        if (s.kH == 0) continue;                      // zeros (ConvPlan::fill)
         for (int b = 0; b < std::min(d->stride_w, d->W); ++b) {
-            ConvSub s{};
-            axis(a, d->kH, d->stride_h, d->pad_h, s.kH, s.ky0, s.ph);
             axis(b, d->kW, d->stride_w, d->pad_w, s.kW, s.kx0, s.pw);
-            if (s.kH == 0 || s.kW == 0) continue;     // zeros (ConvPlan::fill)
+            if (s.kW == 0) continue;
             s.kys = d->stride_h; s.kxs = d->stride_w;
             s.oy0 = a; s.ox0 = b;
             s.Ho = (d->H - a + d->stride_h - 1) / d->stride_h;
             s.Wo = (d->W - b + d->stride_w - 1) / d->stride_w;
             v.push_back(s);
         }
+    }
     return v;
 }
 
@@ -163,6 +165,8 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
 // whichever is slower) overlap where the unit has several workgroups in turn or a workgroup has several chunks; each round of
 // workgroups pays a start-up.  The constants are a fit to the measured times of 3300 tile configurations of 60 products (fp32
 // and 16-bit, both layouts, 1x1 to 5x5, strides 1 and 2); picking by them costs 1 % against the best configuration of each.
+// Gathered weights add a share for each group (453 products of strides 1 to 4, 1x1 to 7x7, in up to five configurations: 1.8 %;
+// 2.0 to 3.3 % with a third of that share up to seven times as much, 5 % without).
 double expected_cycles(const ConvParams &P, int dtype, const Work &w, int ncu)
 {
     const int shape = P.MT * 10 + P.NT, nks = ksteps(dtype, P.Cin);

@@ -1203,7 +1203,7 @@ xconv_status xconv_pixel_indep_dw_estimate(const xconv_desc *d, const void *dY_d
 
 // ---- a layer's passes ---------------------------------------------------------------
 // The same kernels as the calls above, with the small ones (weights into fragment order, last sum of the bias gradient)
-// carried by a launch of the estimator: 3-5 launches of a layer's 11 less (layer C1 on the host, stack bf16 on the GPU).
+// carried by a launch of the estimator: up to three launches less for a forward and a backward pass.
 static size_t layer_est_bytes(const xconv_desc *d, int mode, int op)
 {
     return mode == XCONV_LAYER_CHANNEL ? xconv_workspace_bytes(d, op) : mode == XCONV_LAYER_MULTI ? xconv_pixel_workspace_bytes(d, op) : 0;
