@@ -4,8 +4,8 @@ UndefinedBehaviorSanitizer.
     python tests/run_host_sanitizers.py
 
 Builds oracle/libxconv_oracle_san.so (gcc) and paper_2106_06998_amd/libxconv_san.so (hipcc, host code only
-instrumented), then runs the oracle pins and the host ABI tests in a child process that preloads the sanitizer
-runtimes.  No GPU is touched: those tests make no compute calls.  Leak checking is off (the interpreter itself
+instrumented), then runs the oracle pins, the host ABI tests and the convolution plans (but for the test that brings an
+allocator of its own and the one that takes times) in a child process that preloads the sanitizer runtimes.  No GPU is touched: those tests make no compute calls.  Leak checking is off (the interpreter itself
 never frees everything).  Not collected by pytest; exits with the child's status."""
 import os
 import shutil
@@ -28,7 +28,8 @@ def main():
     pre = [runtime("gcc", "libasan.so"), runtime("gcc", "libubsan.so")]
     env.update(LD_PRELOAD=":".join(pre), ASAN_OPTIONS="detect_leaks=0:abort_on_error=1", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1",
                XCONV_LIB=os.path.join(ROOT, "paper_2106_06998_amd", "libxconv_san.so"))
-    cmd = [sys.executable, "-m", "pytest", "-x", "-q", "-m", "not gpu", "tests/test_oracle_pins.py", "tests/test_host_abi.py"]
+    cmd = [sys.executable, "-m", "pytest", "-x", "-q", "-m", "not gpu", "-k", "not host_memory and not search", "tests/test_oracle_pins.py", "tests/test_host_abi.py",
+           "tests/test_conv_plan.py"]
     rc = subprocess.run(cmd, cwd=ROOT, env=env).returncode
     if "--keep" not in sys.argv:   # the instrumented builds are only for this run
         for p in ("oracle/libxconv_oracle_san.so", "paper_2106_06998_amd/libxconv_san.so"):
