@@ -351,14 +351,14 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
             const ConvLaunch *first = bb ? &out.launches.back() : nullptr;
             ConvLaunch L{};
             bool found = false;
-            for (int big = first ? first->P.big : huge; big <= 1 && !found; ++big) {
+            for (int big = first ? first->P.big : huge; big <= (first ? first->P.big : 1) && !found; ++big) {
                 P.big = big;
                 P.vec = 0;
                 if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
                 bool pairs = !P.big && !nhwc && es == 2 && P.Wi % 2 == 0 && align % 4 == 0;
                 for (int i = 0; i < P.nsub; ++i) pairs = pairs && P.sub[i].kW >= P.sw;
                 if (pairs) P.vec = 1;
-                for (int res = first ? first->P.res : packed && !big && P.Cin <= kConvResident; res >= 0 && !found; --res) {
+                for (int res = first ? first->P.res : packed && !big && P.Cin <= kConvResident; res >= (first ? first->P.res : 0) && !found; --res) {
                     L.P = P;
                     L.P.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
                     L.P.res = res;

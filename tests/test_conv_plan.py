@@ -136,3 +136,11 @@ print("statuses", status)
     p = subprocess.run([sys.executable, "-c", code, so], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), stdout=subprocess.PIPE,
                        stderr=subprocess.STDOUT, text=True, timeout=120)
     assert p.returncode == 0 and "statuses" in p.stdout, (p.returncode, p.stdout)
+
+
+def test_many_positions_take_runs_of_images_on_one_kernel():
+    d = xb.make_desc(300, 2, 3, 2048, 2048, 3, 1, 1, 1, "f16")
+    for transposed in (0, 1):
+        for ws in (0, 1):
+            v = xb.xconv_conv_plan_info(d, transposed, ws)
+            assert (v["launches"], v["pack_launches"], v["big"]) == (2, ws, 0)

@@ -18,6 +18,7 @@ CASES = [
     (2, 3, 1, 12000, 12000, 3, 1, "f16", False, True),
     (1, 3, 2, 9001, 12001, 1, 0, "bf16", False, True),
     (2, 3, 5, 5500, 5500, 3, 1, "f16", False, False),      # just below
+    (300, 2, 3, 2048, 2048, 3, 1, "f16", False, False),    # more positions than a launch counts: two runs of images
     (2, 64, 8, 4200, 4200, 3, 1, "f16", False, True),
     (2, 8, 64, 3000, 3000, 3, 1, "f32", True, True),
 ]
@@ -63,7 +64,7 @@ def test_large_layers(case, packed):
         wt = w64.flip(2, 3).transpose(0, 1).contiguous() if transposed else w64
         for b in range(B):
             assert not bool(torch.isnan(out[b]).any())
-            if b % 3 and b != B - 1:
+            if b % (1 + B // 3) and b not in (B - 1, 255, 256):      # (the two runs above meet at image 256)
                 continue
             for c0 in (0, W // 2 - 5, W - 8):
                 want = windows(src, wt, b, (c0, c0 + 8), W, p)
