@@ -107,3 +107,44 @@ def test_two_layers_on_two_streams_at_once():
         sb.synchronize()
         assert torch.equal(a.dW, want_a) and torch.equal(b.dW, want_b), rep
 
+
+
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "gathered"])
+@pytest.mark.parametrize("e", [("f32", 4, 16, 24, 30, 3, 1, 1), ("f16", 3, 20, 40, 33, 3, 5, 1), ("bf16", 2, 24, 9, 28, 4, 4, 0)],
+                         ids=["s1", "cleared", "sixteen-classes"])
+def test_captured_products_replay_the_eager_result(e, packed):
+    # forward product and input gradient, among them strided ones whose dX is cleared by a kernel in front
+    dtype, B, C_in, C_out, n, k, s, p = e
+    say("graph capture of the products %s packed %s" % (e, packed))
+    td, m = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype], (n + 2 * p - k) // s + 1
+    d = xb.make_desc(B, C_in, C_out, n, n, k, s, p, 1, dtype)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    x, w, dy = (torch.empty(shape, dtype=td, device=DEV) for shape in ((B, C_in, n, n), (C_out, C_in, k, k), (B, C_out, m, m)))
+    y, dx = torch.empty_like(dy), torch.empty_like(x)
+    ws = [xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d, t)) if packed else None for t in (0, 1)]
+
+    def step():
+        xb.xconv_conv_fwd_ws(d, x, w, None, y, ws[0])
+        xb.xconv_dx_exact_ws(d, dy, w, dx, ws[1])
+
+    def refill():
+        for t in (x, w, dy):
+            t.normal_(generator=g)
+
+    refill()
+    step()                              # eager once: kernel attributes are set outside the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for rep in range(3):
+        refill()
+        step()
+        torch.cuda.synchronize()
+        want = y.clone(), dx.clone()
+        y.fill_(float("nan"))
+        dx.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want[0]) and torch.equal(dx, want[1]), rep
+        assert bool(torch.isfinite(dx).all())
