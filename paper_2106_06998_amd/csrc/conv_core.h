@@ -416,9 +416,13 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
 
     if (nck > 0) {
         if constexpr (PACKED) {
+            // in the order of the steps: loads complete in order, and what the loop waits for counts those behind it
             load_a(std::integral_constant<int, 0>{});
+            __builtin_amdgcn_sched_barrier(0);
             load_a(std::integral_constant<int, 1>{});
+            __builtin_amdgcn_sched_barrier(0);
             load_a(std::integral_constant<int, 2>{});
+            __builtin_amdgcn_sched_barrier(0);
         } else {
             gather_load(nck > 1 ? gtab : gtab + cap0, 0, 0);
             gather_write(0);
@@ -444,9 +448,11 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                     run_blocks(list, base, nblk * ph / nphase, nblk * (ph + 1) / nphase);
                     if (more) stage_write((ck + 1) & 1, ph);
                 }
-                if (!more) run_tail(base, n_last & 3);
                 __syncthreads();
             }
+            // behind the loop: with a path from the tail back into the blocks (a ring that is one or two steps further), the
+            // compiler would have every block wait for all but the last step's weights
+            run_tail(((nck - 1) & 1) * NU * S.NPOS * 16, n_last & 3);
         } else {
             int abuf = 0;
             for (int ck = 0; ck < nck; ++ck) {
