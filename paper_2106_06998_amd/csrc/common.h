@@ -391,7 +391,7 @@ struct ConvSub {
     int sth, stw;              // staged rows (columns) per output row (column): min(stride, taps)
     int PWv, PH, PWs, NPOS, NPPmax;   // staging tasks per patch row, columns per remainder class, LDS positions per row and in all, tasks per unit
     FastDiv dSW, dHo, dHV, dPWv, dTPS, dkW;   // quotients by SW, Ho, staged rows of a whole image, PWv, TPS, kW
-    int wg0;                   // first workgroup of the class
+    int wgs;                   // workgroups of the class
     int images;                // most images a tile touches (host)
     long long w0;              // first 16-byte unit of its packed weights
 };

@@ -97,10 +97,13 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     if (id >= P.nwg) return;
     int cls = 0;
     if constexpr (NC > 1) {
-        while (cls + 1 < P.nsub && id >= P.sub[cls + 1].wg0) ++cls;
+        // a tile of each class in turn: they read the same rows of `in` and write the same cache lines of `out`, which one L2 then
+        // fetches once and puts together
+        cls = id % P.nsub;
+        id /= P.nsub;
+        if (id >= P.sub[cls].wgs) return;
     }
     const ConvSub &S = P.sub[cls];
-    id -= S.wg0;
     int mtile, strip, tile;
     P.dNMT.divmod(id, id, mtile);
     S.dTPS.divmod(id, strip, tile);

@@ -224,17 +224,21 @@ bool plan(ConvParams &P, int dtype, int ncu)
                         }
                         Work w;
                         bool fits = true;
+                        long long most = 0;      // workgroups of the largest class
                         for (int i = 0; i < P.nsub && fits; ++i) {
                             C.sub[i] = P.sub[i];
-                            C.sub[i].wg0 = (int)w.wgs;
-                            fits = lay_out(C.sub[i], C, dtype, nst, TU, TN, w) && w.wgs < 0x3fffffff;
+                            const long long before = w.wgs;
+                            fits = lay_out(C.sub[i], C, dtype, nst, TU, TN, w);
+                            most = std::max(most, w.wgs - before);
+                            fits = fits && most * P.nsub < 0x3fffffff;
+                            C.sub[i].wgs = (int)(w.wgs - before);
                         }
                         if (!fits) continue;
                         const double t = expected_cycles(C, dtype, w, ncu);
                         if (best >= 0 && t >= best) continue;
                         best = t;
                         bp = C;
-                        bp.nwg = (int)w.wgs;
+                        bp.nwg = (int)(most * P.nsub);
                         bp.lds_bytes = w.lds;
                     }
                 }

@@ -61,6 +61,21 @@ def test_conv_tiles(case, packed, shape, monkeypatch):
     run_tiles(case, packed, shape, monkeypatch)
 
 
+# classes of unequal size take turns in the grid: a tile past the last of its class does nothing
+UNEQUAL = [
+    (3, 16, 24, 1, 5, 3, 2, 1, "bf16", False),
+    (2, 40, 16, 3, 301, 5, 2, 2, "f32", False),
+    (1, 24, 40, 33, 2, 3, 2, 1, "f16", True),
+    (4, 144, 24, 5, 3, 3, 2, 1, "f16", False),
+]
+
+
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "gathered"])
+@pytest.mark.parametrize("case", UNEQUAL, ids=["%s-%dx%d" % (c[8], c[3], c[4]) for c in UNEQUAL])
+def test_classes_of_unequal_size(case, packed, monkeypatch):
+    run_tiles(case, packed, "0", monkeypatch)
+
+
 def run_tiles(case, packed, shape, monkeypatch):
     B, C_in, C_out, H, W, k, s, p, dtype, nhwc = case
     monkeypatch.setenv("XCONV_CONV_SHAPE", shape)
