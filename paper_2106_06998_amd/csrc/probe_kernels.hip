@@ -30,26 +30,58 @@ namespace xc {
 // stores of Xt never carry it: the correlation reads them next (with the hint on the stores the correlation got slower);
 // nor do the correlation's loads of dY, whose rows share cache lines with the rows of the next row-step (with the hint
 // the C5 correlation took 69.7 instead of 62.9 us).
+// The loads assume no more than the alignment of an element (the memory system takes vectors at any address): planes of a ragged
+// number of pixels run here too (PlaneGroups).
+typedef unsigned int u32x4e __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x2e __attribute__((ext_vector_type(2), aligned(2)));
 template <bool NT> __device__ inline uint4 load_x16(const void *p)
 {
     if constexpr (NT) {
-        typedef unsigned int u32x4nt __attribute__((ext_vector_type(4)));
-        const u32x4nt v = __builtin_nontemporal_load(static_cast<const u32x4nt *>(p));
+        const u32x4e v = __builtin_nontemporal_load(static_cast<const u32x4e *>(p));
         return uint4{v.x, v.y, v.z, v.w};
     } else {
-        return *static_cast<const uint4 *>(p);
+        const u32x4e v = *static_cast<const u32x4e *>(p);
+        return uint4{v.x, v.y, v.z, v.w};
     }
 }
 template <bool NT> __device__ inline uint2 load_x8(const void *p)
 {
     if constexpr (NT) {
-        typedef unsigned int u32x2nt __attribute__((ext_vector_type(2)));
-        const u32x2nt v = __builtin_nontemporal_load(static_cast<const u32x2nt *>(p));
+        const u32x2e v = __builtin_nontemporal_load(static_cast<const u32x2e *>(p));
         return uint2{v.x, v.y};
     } else {
-        return *static_cast<const uint2 *>(p);
+        const u32x2e v = *static_cast<const u32x2e *>(p);
+        return uint2{v.x, v.y};
     }
 }
+// Groups of PT pixels, one for each lane, of NCHW planes (a volume's depth slices): each plane has as many as cover it, the last
+// one moved back to end with the plane.  Pixels of a ragged plane that two groups share are computed and stored twice, the same
+// value each time (a pixel's sum does not depend on its place in the tile).
+template <int PT> struct PlaneGroups {
+    // first: offset of the lane's first pixel of channel 0 from the tensor's start; out: its pixel in Xt
+    static __device__ inline void locate(long long pg, int C_in, int HW, const SliceMap &sm, size_t &first, long long &out)
+    {
+        const int HWs = sm.sd ? sm.HWs : HW, per = (HWs + PT - 1) / PT;
+        const long long plane = pg / per;
+        int p = (int)(pg - plane * per) * PT;
+        p = p < HWs - PT ? p : HWs - PT;
+        if (sm.sd == 0) {
+            first = (size_t)plane * C_in * HW + p;
+            out = plane * HW + p;
+        } else {
+            const long long img = plane / sm.D;
+            const int z = (int)(plane - img * sm.D);
+            first = (size_t)img * C_in * HW + (size_t)z * HWs + p;
+            out = sm.slice_of(img, z) * HWs + p;
+        }
+    }
+    static long long count(long long npix, int HW, const SliceMap &sm)
+    {
+        const int HWs = sm.sd ? sm.HWs : HW;
+        return npix / HWs * ((HWs + PT - 1) / PT);
+    }
+};
+
 // whether the planes of an NCHW tensor (pitch bytes apart) are whole cache lines; channels-last rows always take the hint
 static int probe_nt(bool nhwc, long long pitch_bytes) { return (nhwc || pitch_bytes % 128 == 0) ? 1 : 0; }
 
@@ -197,7 +229,6 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
     // pixel (or group of 4 pixels) of this lane; lanes past the end redo the last one and store nothing
     struct Tile {
         const float *xb[NP];
-        long long first[NP];
         long long out[NP];  // pixel index in Xt
         bool valid[NP];
     };
@@ -207,17 +238,16 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
             for (int t = 0; t < 4; ++t) {
                 const long long pp = (long long)tile * 64 + 16 * t + n;
                 tl.valid[t] = pp < ngroups;
-                tl.first[t] = tl.valid[t] ? pp : last_group;
-                tl.xb[t] = X + (size_t)tl.first[t] * C_in;
-                tl.out[t] = sm.out_pixel(tl.first[t], HW);
+                const long long first = tl.valid[t] ? pp : last_group;
+                tl.xb[t] = X + (size_t)first * C_in;
+                tl.out[t] = sm.out_pixel(first, HW);
             }
         } else {
             const long long pg_raw = (long long)tile * 16 + n;
             tl.valid[0] = pg_raw < ngroups;
-            tl.first[0] = (tl.valid[0] ? pg_raw : last_group) * 4;
-            const long long img = tl.first[0] / HW;
-            tl.xb[0] = X + (size_t)img * C_in * HW + (int)(tl.first[0] % HW);
-            tl.out[0] = sm.out_pixel(tl.first[0], HW);
+            size_t first;
+            PlaneGroups<4>::locate(tl.valid[0] ? pg_raw : last_group, C_in, HW, sm, first, tl.out[0]);
+            tl.xb[0] = X + first;
         }
     };
     // Channels past the end re-read the last channels against zero fragment entries.
@@ -423,7 +453,6 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
     // pixel (NHWC) or group of PT pixels (NCHW) of this lane; lanes past the end redo the last one and store nothing
     struct Tile {
         const uint16_t *xb[NP];
-        long long first[NP];
         long long out[NP];  // pixel index in Xt
         bool valid[NP];
     };
@@ -433,17 +462,16 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
             for (int t = 0; t < PT; ++t) {
                 const long long pp = (long long)tile * (16 * PT) + 16 * t + n;
                 tl.valid[t] = pp < ngroups;
-                tl.first[t] = tl.valid[t] ? pp : last_group;
-                tl.xb[t] = X + (size_t)tl.first[t] * C_in;
-                tl.out[t] = sm.out_pixel(tl.first[t], HW);
+                const long long first = tl.valid[t] ? pp : last_group;
+                tl.xb[t] = X + (size_t)first * C_in;
+                tl.out[t] = sm.out_pixel(first, HW);
             }
         } else {
             const long long pg_raw = (long long)tile * 16 + n;
             tl.valid[0] = pg_raw < ngroups;
-            tl.first[0] = (tl.valid[0] ? pg_raw : last_group) * PT;
-            const long long img = tl.first[0] / HW;
-            tl.xb[0] = X + (size_t)img * C_in * HW + (int)(tl.first[0] % HW);
-            tl.out[0] = sm.out_pixel(tl.first[0], HW);
+            size_t first;
+            PlaneGroups<PT>::locate(tl.valid[0] ? pg_raw : last_group, C_in, HW, sm, first, tl.out[0]);
+            tl.xb[0] = X + first;
         }
     };
     // MFMA operands of one K-step: cols[t] = the 8 channels 32kk + 8g .. +7 of pixel t.
@@ -753,7 +781,7 @@ static hipError_t launch_probe_f32_side(const float *X, const float *Z, const fl
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
     // a lane owns 4 consecutive pixels of a plane (NCHW) or one pixel of each of 4 sub-tiles (NHWC)
-    const long long ngroups = NHWC ? npix : npix / 4;
+    const long long ngroups = NHWC ? npix : PlaneGroups<4>::count(npix, HW, sm);
     const int ntiles = (int)(NHWC ? (npix + 63) / 64 : (ngroups + 15) / 16);
     const size_t lds = (size_t)ceil_div(C_in, 16) * 4 * JT * 64 * sizeof(float);
     hipError_t e = set_lds(probe_f32_kernel<JT, NHWC, JOBS...>, lds);
@@ -776,7 +804,7 @@ template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
 static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
                                       int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
-    const long long ngroups = NHWC ? npix : npix / PT;
+    const long long ngroups = NHWC ? npix : PlaneGroups<PT>::count(npix, HW, sm);
     const int ntiles = (int)(NHWC ? (npix + 16 * PT - 1) / (16 * PT) : (ngroups + 15) / 16);
     // a dense +-1 matrix that comes from the seed and has no fragments in scratch is drawn by the workgroups from its generator words
     const int nword = (!Z && !zpack && probe_draws_words(C_in, r, dist)) ? (int)(((long long)C_in * r + 63) / 64) : 0;
@@ -807,7 +835,8 @@ static hipError_t launch_probe_16_jt(const uint16_t *X, const float *Z, const ui
     }
     // 8 pixels per lane when the accumulators stay small, 4 for wide probe blocks
     if constexpr (JT <= 2) {
-        if ((sm.sd ? sm.HWs : HW) % 8 == 0) {
+        const int HWs = sm.sd ? sm.HWs : HW;
+        if (HWs % 8 == 0 || (HWs % 4 != 0 && HWs > 8)) {
             if (split) return launch_probe_16_cfg<DT, JT, 8, true, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
             return launch_probe_16_cfg<DT, JT, 8, false, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
         }
@@ -825,10 +854,10 @@ bool probe_draws_words(int C_in, int r, int dist)
 
 bool probe_fast_path_ok(int dtype, int C_in, int HW, bool nhwc)
 {
-    // aligned vector loads: 4 pixels (16 bytes fp32, 8 bytes 16-bit) per channel row, or (NHWC)
+    // vector loads: 4 pixels (16 bytes fp32, 8 bytes 16-bit) per channel row, or (NHWC)
     // 16 bytes of consecutive channels per pixel; LDS for the Z fragments (worst case JT = 4,
     // split) must fit
-    if (nhwc ? (C_in % (dtype == XCONV_F32 ? 4 : 8) != 0) : (HW % 4 != 0)) return false;
+    if (nhwc ? (C_in % (dtype == XCONV_F32 ? 4 : 8) != 0) : HW < 4) return false;
     const size_t lds = dtype == XCONV_F32 ? (size_t)ceil_div(C_in, 16) * 4 * 4 * 64 * 4 : (size_t)2 * ceil_div(C_in, 32) * 4 * 64 * 16;
     return lds <= 128 * 1024;
 }
