@@ -1121,42 +1121,20 @@ static bool geometry_fits(const CorrParams &P, int dtype, int MT)
     return true;
 }
 
-bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
-               int CS, bool dy_aligned, int nsets)
+static int corr_per_cu(const CorrParams &P, int dtype) { return lds_bytes_of(P, dtype, corr_mt(dtype, P.C_out)) <= 72 * 1024 ? 2 : 1; }
+
+// Tile of WM waves along the output channels, step shape and K-split; false when no step shape fits
+static bool shape_corr(CorrParams &P, int dtype, int WM, int nsets)
 {
     const bool f32 = dtype == XCONV_F32;
-    const int BI = f32 ? 1 : 8, EPV = f32 ? 4 : 8;
-    P.B = B; P.C_out = C_out; P.H = H; P.W = W;
-    P.kH = kH; P.kW = kW; P.sh = sh; P.sw = sw; P.ph = ph; P.pw = pw;
-    P.Ho = (H + 2 * ph - kH) / sh + 1;
-    P.Wo = (W + 2 * pw - kW) / sw + 1;
-    P.CS = CS;
-    P.NBG = ceil_div(B, BI);
-    P.K2 = kH * kW;
-    P.NOG = ceil_div(P.K2, P.K2 == 1 ? 1 : kMaxOff);
-    P.dy_plane = round_up(P.Ho * P.Wo, EPV);  // the kernel reads dY planes of this pitch (repacked by the caller if needed)
-    (void)dy_aligned;
-
-    // the kernel addresses a batch group (BI images) with 32-bit byte offsets
-    const long long es = f32 ? 4 : 2;
-    if ((long long)BI * C_out * round_up(P.Ho * P.Wo, EPV) * es > (1LL << 30) || (long long)BI * H * W * CS * es > (1LL << 30)) return false;
-
-    const int MT = corr_mt(dtype, C_out);
-    const int nwm = ceil_div(C_out, 16 * MT), nwj = CS / 16;
-    // waves along the A columns share dY through LDS, so prefer them; WJ must divide the column tiles
-    int WJ = env_int("XCONV_CORR_WJ", 0);
-    if (WJ != 1 && WJ != 2 && WJ != 4) WJ = (nwj % 4 == 0) ? 4 : (nwj % 2 == 0) ? 2 : 1;
-    if (nwj % WJ != 0) WJ = 1;
-    int WM = env_int("XCONV_CORR_WM", 0);
-    if (WM != 1 && WM != 2 && WM != 4) WM = nwm >= 4 ? 4 : nwm >= 2 ? 2 : 1;
-    while (WM * WJ > 4) WM >>= 1;
-    P.WM = WM; P.WJ = WJ; P.WK = 4 / (WM * WJ);
+    const int MT = corr_mt(dtype, P.C_out), WJ = P.WJ;
+    P.WM = WM; P.WK = 4 / (WM * WJ);
     P.M_WG = WM * MT * 16;
     P.J_WG = WJ * 16;
-    P.NTM = ceil_div(C_out, P.M_WG);
-    P.NTJ = CS / P.J_WG;
+    P.NTM = ceil_div(P.C_out, P.M_WG);
+    P.NTJ = P.CS / P.J_WG;
     P.MP = P.NTM * P.M_WG;
-    P.JP = CS;
+    P.JP = P.CS;
 
     // Step shape: the widest strip that fits, then the tallest band under the slot cap.
     const int slots_cap = env_int("XCONV_CORR_SLOTS", f32 ? 128 : 64);
@@ -1190,8 +1168,7 @@ bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH,
     if (!geometry_fits(P, dtype, MT)) return false;
 
     // K-split: fill the 256 compute units (two workgroups each when LDS allows)
-    const size_t lds = lds_bytes_of(P, dtype, MT);
-    const int per_cu = env_int("XCONV_CORR_WGS_PER_CU", lds <= 72 * 1024 ? 2 : 1);
+    const int per_cu = env_int("XCONV_CORR_WGS_PER_CU", corr_per_cu(P, dtype));
     const int ny = P.NTM * P.NTJ * P.NOG * nsets;
     int target = env_int("XCONV_CORR_SPLITS", 0);
     if (target <= 0) {
@@ -1203,6 +1180,70 @@ bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH,
     if (target > P.NS) target = P.NS;
     if (target < 1) target = 1;
     P.S = target;
+    return true;
+}
+
+// Expected microseconds of the correlation and its second pass at 16-bit storage: partial tiles written and read again, steps in a row
+// per round of workgroups, matrix instructions and starts of workgroups per compute unit.  A fit to 260 launch shapes of 106
+// layers (1x1 to 5x5, strides 1 and 2, 4 to 64 probes), 18 % off on average.
+static double corr_cost(const CorrParams &P, int dtype, int nsets)
+{
+    const int MT = corr_mt(dtype, P.C_out), per_cu = corr_per_cu(P, dtype);
+    const long long groups = (long long)P.S * P.NTM * P.NTJ * P.NOG * nsets;
+    const double steps = ceil_div(P.NS, P.S), q = (double)((groups + 255) / 256), rounds = (double)((groups + 256 * per_cu - 1) / (256 * per_cu));
+    const double offs = P.K2 < kMaxOff ? P.K2 : kMaxOff;
+    return 9.2 + 0.25e-6 * (double)groups * P.M_WG * P.J_WG * offs * 4 + 2.6 * steps * rounds +
+           0.034 * steps * q * P.RB * P.CWp / 4 / P.WK * MT * offs + 6.5 * q;
+}
+
+bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
+               int CS, bool dy_aligned, int nsets)
+{
+    const bool f32 = dtype == XCONV_F32;
+    const int BI = f32 ? 1 : 8, EPV = f32 ? 4 : 8;
+    P.B = B; P.C_out = C_out; P.H = H; P.W = W;
+    P.kH = kH; P.kW = kW; P.sh = sh; P.sw = sw; P.ph = ph; P.pw = pw;
+    P.Ho = (H + 2 * ph - kH) / sh + 1;
+    P.Wo = (W + 2 * pw - kW) / sw + 1;
+    P.CS = CS;
+    P.NBG = ceil_div(B, BI);
+    P.K2 = kH * kW;
+    P.NOG = ceil_div(P.K2, P.K2 == 1 ? 1 : kMaxOff);
+    P.dy_plane = round_up(P.Ho * P.Wo, EPV);  // the kernel reads dY planes of this pitch (repacked by the caller if needed)
+    (void)dy_aligned;
+
+    // the kernel addresses a batch group (BI images) with 32-bit byte offsets
+    const long long es = f32 ? 4 : 2;
+    if ((long long)BI * C_out * round_up(P.Ho * P.Wo, EPV) * es > (1LL << 30) || (long long)BI * H * W * CS * es > (1LL << 30)) return false;
+
+    const int MT = corr_mt(dtype, C_out);
+    const int nwm = ceil_div(C_out, 16 * MT), nwj = CS / 16;
+    // waves along the A columns share dY through LDS, so prefer them; WJ must divide the column tiles
+    int WJ = env_int("XCONV_CORR_WJ", 0);
+    if (WJ != 1 && WJ != 2 && WJ != 4) WJ = (nwj % 4 == 0) ? 4 : (nwj % 2 == 0) ? 2 : 1;
+    if (nwj % WJ != 0) WJ = 1;
+    P.WJ = WJ;
+    int WM = env_int("XCONV_CORR_WM", 0);
+    const bool forced = WM == 1 || WM == 2 || WM == 4;
+    if (!forced) WM = nwm >= 4 ? 4 : nwm >= 2 ? 2 : 1;
+    while (WM * WJ > 4) WM >>= 1;
+    const CorrParams given = P;
+    const bool widest = shape_corr(P, dtype, WM, nsets);
+    if (f32 || forced || !widest) return widest;
+    // Fewer waves along the output channels, so a smaller tile: more steps per workgroup, but as many times fewer bytes of partial
+    // tiles, wider strips and a split of the k-steps over the waves.  Where the estimate sees 15 % in it (on 106 layers none is
+    // slower for it and they are 5 % faster in the geometric mean): 256 channels 28x28 3x3 r = 16, batch 256, bf16 123 -> 60 us
+    // with second pass, 128 -> 256 channels 56x56 at stride 2 r = 16 55 -> 32 us, 219 -> 200 channels 144x98 1x1 r = 4 1176 -> 396.
+    const double limit = 0.85 * corr_cost(P, dtype, nsets);
+    double best = limit;
+    for (int wm = WM >> 1; wm >= 1; wm >>= 1) {
+        CorrParams C = given;
+        if (!shape_corr(C, dtype, wm, nsets) || corr_partial_bytes(C) > corr_partial_bytes(P)) continue;
+        const double t = corr_cost(C, dtype, nsets);
+        if (t >= best) continue;
+        best = t;
+        P = C;
+    }
     return true;
 }
 
