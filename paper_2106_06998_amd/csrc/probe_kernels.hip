@@ -594,8 +594,8 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
 }
 
 // ---------------------------------------------------------------------------
-// Any-shape probe on the vector ALUs (used when image planes are not a
-// multiple of the vector width, so the MFMA path's aligned loads do not apply).
+// Any-shape probe on the vector ALUs (planes below four pixels, unaligned tensors, channels-last channels that are no
+// whole vectors).
 // One thread per (pixel, block of 16 probe columns).
 // ---------------------------------------------------------------------------
 template <int DT>
