@@ -13,6 +13,8 @@ hipError_t launch_gen_z(float *Z, int n, int dist, uint64_t seed, hipStream_t st
 bool probe_fast_path_ok(int dtype, int C_in, int HW, bool nhwc);
 // the 16-bit probe kernel draws this matrix from (dist, seed) itself, from one generator word per 64 entries
 bool probe_draws_words(int C_in, int r, int dist);
+// 16-bit planes that are probed in fp32 arithmetic; pm1: Z drawn from the seed with entries +-1 (and 0)
+bool probe_in_f32(int dtype, int HW, bool nhwc, bool pm1);
 size_t zpack_bytes(int dtype, int C_in, int r, bool z_exact16);
 hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, bool z_exact16, int dist, uint64_t seed,
                          bool nhwc, hipStream_t st, float zmul = 1.0f);
@@ -20,7 +22,8 @@ hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, 
 // Z == nullptr and zpack == nullptr: every workgroup draws its fragments of Z from (dist, seed) itself
 // J: small jobs to carry along
 hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zpack, void *Xt, int B, int C_in, int HW, int r,
-                        int CS, bool z_exact16, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J = nullptr);
+                        int CS, bool z_exact16, bool arith32, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
+                        const SideJobs *J = nullptr);
 hipError_t launch_probe_generic(int dtype, const void *X, const float *Z, void *Xt, int B, int C_in, int HW, int r, int CS,
                                 bool nhwc, SliceMap sm, hipStream_t st);
 // volumetric layers: zero the slots of Xt without image data; X -> channels-last slices in slot order;

@@ -112,6 +112,26 @@ __device__ inline int wave_tile(int w, int it, int NW, int ntiles)
     return ntiles;
 }
 
+template <int DT> using elem_of = std::conditional_t<DT == XCONV_F32, float, uint16_t>;
+
+// 4*JT consecutive probe columns of a pixel, rounded to the storage type: one run of 8*JT bytes
+template <int DT, int JT> __device__ inline void store_16(uint16_t *o, const f32x4 (&row)[JT])
+{
+    uint32_t w[2 * JT];
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) {
+        w[2 * jt] = (uint32_t)f32_to_st16<DT>(row[jt][0]) | ((uint32_t)f32_to_st16<DT>(row[jt][1]) << 16);
+        w[2 * jt + 1] = (uint32_t)f32_to_st16<DT>(row[jt][2]) | ((uint32_t)f32_to_st16<DT>(row[jt][3]) << 16);
+    }
+    if constexpr (JT % 2 == 0) {
+#pragma unroll
+        for (int k = 0; k < JT / 2; ++k) *reinterpret_cast<uint4 *>(o + 8 * k) = uint4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
+    } else {
+#pragma unroll
+        for (int k = 0; k < JT; ++k) *reinterpret_cast<uint2 *>(o + 4 * k) = uint2{w[2 * k], w[2 * k + 1]};
+    }
+}
+
 // Row i of MFMA tile jt holds probe column j0 + jmap: lane group g = i/4 then
 // owns the 4*JT consecutive columns g*4*JT .. (g+1)*4*JT-1 of the 16*JT block.
 __device__ inline int jmap(int jt, int i, int JT) { return (i >> 2) * (4 * JT) + jt * 4 + (i & 3); }
@@ -191,15 +211,19 @@ __global__ __launch_bounds__(kThreads) void pack_z_16_kernel(const float *__rest
 // NHWC: X is [pixels, C_in]; a lane then loads four consecutive channels (16 bytes) of one pixel,
 // MFMA u uses element u of every lane (see f32_frag_channel), and the wave's tile is four
 // sub-tiles of 16 pixels; `ngroups` is the number of pixels.
+// DT of 16 bits (NCHW): X is widened on its way into the matrix instructions and the sums are rounded once.  It serves the calls
+// that probe_in_f32 names: Z keeps the bits and the range of fp32, where probe_16_kernel would take it as a sum of two values of
+// the storage type.
 // JOBS: nothing, or the small jobs that the launch carries along
-template <int JT, bool NHWC, class... JOBS>
-__global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const float *__restrict__ X, const float *__restrict__ Z,
-                                                             const float *__restrict__ zpack, float *__restrict__ Xt, int C_in,
+template <int DT, int JT, bool NHWC, class... JOBS>
+__global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const elem_of<DT> *__restrict__ X, const float *__restrict__ Z,
+                                                             const float *__restrict__ zpack, elem_of<DT> *__restrict__ Xt, int C_in,
                                                              int HW, int r, int CS, int j0, long long ngroups, int ntiles,
                                                              SliceMap sm, int dist, uint64_t seed, const JOBS... jobs)
 {
+    static_assert(DT == XCONV_F32 || !NHWC, "16-bit storage: planes only");
     if constexpr (sizeof...(JOBS) > 0) {
-        if (do_side_jobs<4, kThreads>(jobs...)) return;
+        if (do_side_jobs<(int)sizeof(elem_of<DT>), kThreads>(jobs...)) return;
     }
     extern __shared__ float zs[];  // [KQ4][JT][64] A-operand fragments, zero beyond C_in
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -220,7 +244,8 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
         }
     };
 
-    constexpr int D = JT == 1 ? 3 : 4;  // groups of 16 channels a wave keeps in flight (16 registers each)
+    // groups of 16 channels a wave keeps in flight (16 registers each, 8 at 16 bits)
+    constexpr int D = (JT == 1 ? 3 : 4) * (DT == XCONV_F32 ? 1 : 2);
     constexpr int NP = NHWC ? 4 : 1;
     const int n = lane & 15, g = lane >> 4;
     const long long last_group = ngroups - 1;
@@ -228,7 +253,7 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 
     // pixel (or group of 4 pixels) of this lane; lanes past the end redo the last one and store nothing
     struct Tile {
-        const float *xb[NP];
+        const elem_of<DT> *xb[NP];
         long long out[NP];  // pixel index in Xt
         bool valid[NP];
     };
@@ -252,7 +277,7 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
     };
     // Channels past the end re-read the last channels against zero fragment entries.
     struct Staged {
-        float4 v[4];
+        std::conditional_t<DT == XCONV_F32, float4, uint2> v[4];
     };
     auto load16 = [&](Staged &sg, const Tile &tl, int kk) {
         const int c0 = kk * 16;
@@ -265,7 +290,8 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
             } else {
                 int c = c0 + 4 * u + g;
                 c = c < C_in ? c : C_in - 1;
-                sg.v[u] = __builtin_bit_cast(float4, load_x16<true>(tl.xb[0] + (size_t)c * HW));
+                if constexpr (DT == XCONV_F32) sg.v[u] = __builtin_bit_cast(float4, load_x16<true>(tl.xb[0] + (size_t)c * HW));
+                else sg.v[u] = load_x8<false>(tl.xb[0] + (size_t)c * HW);
             }
         }
     };
@@ -295,7 +321,13 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[jt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
         auto process = [&](const Staged &sg, int kk) {
-            const float4(&v)[4] = sg.v;
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (DT == XCONV_F32) v[u] = sg.v[u];
+                else v[u] = float4{st16_to_f32<DT>((uint16_t)sg.v[u].x), st16_to_f32<DT>((uint16_t)(sg.v[u].x >> 16)),
+                                   st16_to_f32<DT>((uint16_t)sg.v[u].y), st16_to_f32<DT>((uint16_t)(sg.v[u].y >> 16))};
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int kq = kk * 4 + u;
@@ -344,9 +376,16 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (!done.valid[NHWC ? t : 0]) continue;
-            float *out = Xt + (size_t)(NHWC ? done.out[NHWC ? t : 0] : done.out[0] + t) * CS + j0 + g * (4 * JT);
+            elem_of<DT> *out = Xt + (size_t)(NHWC ? done.out[NHWC ? t : 0] : done.out[0] + t) * CS + j0 + g * (4 * JT);
+            if constexpr (DT == XCONV_F32) {
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) *reinterpret_cast<f32x4 *>(out + jt * 4) = acc[jt][t];
+                for (int jt = 0; jt < JT; ++jt) *reinterpret_cast<f32x4 *>(out + jt * 4) = acc[jt][t];
+            } else {
+                f32x4 row[JT];
+#pragma unroll
+                for (int jt = 0; jt < JT; ++jt) row[jt] = acc[jt][t];
+                store_16<DT, JT>(out, row);
+            }
         }
     }
 }
@@ -574,21 +613,10 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
 #pragma unroll
         for (int t = 0; t < PT; ++t) {
             if (!done.valid[NHWC ? t : 0]) continue;
-            uint32_t w[2 * JT];
+            f32x4 row[JT];
 #pragma unroll
-            for (int jt = 0; jt < JT; ++jt) {
-                w[2 * jt] = (uint32_t)f32_to_st16<DT>(acc[jt][t][0]) | ((uint32_t)f32_to_st16<DT>(acc[jt][t][1]) << 16);
-                w[2 * jt + 1] = (uint32_t)f32_to_st16<DT>(acc[jt][t][2]) | ((uint32_t)f32_to_st16<DT>(acc[jt][t][3]) << 16);
-            }
-            uint16_t *o = Xt + (size_t)(NHWC ? done.out[NHWC ? t : 0] : done.out[0] + t) * CS + j0 + g * (4 * JT);
-            if constexpr (JT % 2 == 0) {
-#pragma unroll
-                for (int k = 0; k < JT / 2; ++k)
-                    *reinterpret_cast<uint4 *>(o + 8 * k) = uint4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]};
-            } else {
-#pragma unroll
-                for (int k = 0; k < JT; ++k) *reinterpret_cast<uint2 *>(o + 4 * k) = uint2{w[2 * k], w[2 * k + 1]};
-            }
+            for (int jt = 0; jt < JT; ++jt) row[jt] = acc[jt][t];
+            store_16<DT, JT>(Xt + (size_t)(NHWC ? done.out[NHWC ? t : 0] : done.out[0] + t) * CS + j0 + g * (4 * JT), row);
         }
     }
 }
@@ -776,28 +804,29 @@ static SideJobs with_groups(SideJobs J, int groups)
     return J;
 }
 
-template <int JT, bool NHWC, class... JOBS>
-static hipError_t launch_probe_f32_side(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
+template <int DT, int JT, bool NHWC, class... JOBS>
+static hipError_t launch_probe_f32_side(const void *X, const float *Z, const float *zpack, void *Xt, int C_in, int HW, int r, int CS,
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
     // a lane owns 4 consecutive pixels of a plane (NCHW) or one pixel of each of 4 sub-tiles (NHWC)
     const long long ngroups = NHWC ? npix : PlaneGroups<4>::count(npix, HW, sm);
     const int ntiles = (int)(NHWC ? (npix + 63) / 64 : (ngroups + 15) / 16);
     const size_t lds = (size_t)ceil_div(C_in, 16) * 4 * JT * 64 * sizeof(float);
-    hipError_t e = set_lds(probe_f32_kernel<JT, NHWC, JOBS...>, lds);
+    hipError_t e = set_lds(probe_f32_kernel<DT, JT, NHWC, JOBS...>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_f32_kernel<JT, NHWC, JOBS...>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st, X, Z, zpack, Xt, C_in, HW, r,
-                       CS, j0, ngroups, ntiles, sm, dist, seed, jobs...);
+    hipLaunchKernelGGL((probe_f32_kernel<DT, JT, NHWC, JOBS...>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st,
+                       static_cast<const elem_of<DT> *>(X), Z, zpack, static_cast<elem_of<DT> *>(Xt), C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist,
+                       seed, jobs...);
     return hipGetLastError();
 }
 
-template <int JT, bool NHWC>
-static hipError_t launch_probe_f32_jt(const float *X, const float *Z, const float *zpack, float *Xt, int C_in, int HW, int r, int CS,
+template <int DT, int JT, bool NHWC>
+static hipError_t launch_probe_f32_jt(const void *X, const float *Z, const float *zpack, void *Xt, int C_in, int HW, int r, int CS,
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
-    if (nside) return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
-    return launch_probe_f32_side<JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+    if (nside) return launch_probe_f32_side<DT, JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
+    return launch_probe_f32_side<DT, JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
 }
 
 template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
@@ -862,6 +891,13 @@ bool probe_fast_path_ok(int dtype, int C_in, int HW, bool nhwc)
     return lds <= 128 * 1024;
 }
 
+// 16-bit planes of a ragged number of pixels whose Z need not be +-1 and 0: fp32 arithmetic.  As a sum of two 16-bit values Z has 16
+// (bf16) or 22 bits (f16), no value beyond 65504 or well below 1e-7 at f16, and an infinity of X against parts of opposite sign
+// gives a NaN; fp32 sums have none of that.  bf16, Gaussian: 64 channels 57x57, batch 32, r = 32 takes 13.6 us (65 on the vector
+// ALUs, 15.3 as two values), 200 channels 101x99, batch 24, r = 64 71 us (484, 36).  Aligned planes and channels-last rows keep the
+// sum of two values that they always had.
+bool probe_in_f32(int dtype, int HW, bool nhwc, bool pm1) { return dtype != XCONV_F32 && !nhwc && HW % 4 != 0 && !pm1; }
+
 // Bytes of Z in fragment order (pack_z_*_kernel) for all column blocks.
 size_t zpack_bytes(int dtype, int C_in, int r, bool z_exact16)
 {
@@ -893,9 +929,9 @@ hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, 
 }
 
 // zpack: Z in fragment order (launch_pack_z) or nullptr, in which case every workgroup gathers
-// its fragments from Z itself.
+// its fragments from Z itself.  arith32: 16-bit planes in fp32 arithmetic (probe_in_f32), Z in the order of fp32 fragments.
 hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zpack, void *Xt, int B, int C_in, int HW, int r,
-                        int CS, bool z_exact16, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
+                        int CS, bool z_exact16, bool arith32, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
                         const SideJobs *J)
 {
     const long long npix = (long long)B * HW;
@@ -905,18 +941,19 @@ hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zp
         const int jt = (ntj - t0) < 4 ? (ntj - t0) : 4;
         const int j0 = t0 * 16;
         const size_t bi = (size_t)(t0 / 4);
-        if (dtype == XCONV_F32) {
-            const float *x = static_cast<const float *>(X);
-            float *o = static_cast<float *>(Xt);
+        if (dtype == XCONV_F32 || arith32) {
             const float *zp = zpack ? static_cast<const float *>(zpack) + bi * ceil_div(C_in, 16) * 4 * 4 * 64 : nullptr;
-#define XC_P32(NH)                                                                                  \
+#define XC_P32(DT, NH)                                                                              \
     switch (jt) {                                                                                   \
-    case 1: e = launch_probe_f32_jt<1, NH>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
-    case 2: e = launch_probe_f32_jt<2, NH>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
-    case 3: e = launch_probe_f32_jt<3, NH>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
-    default: e = launch_probe_f32_jt<4, NH>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;     \
+    case 1: e = launch_probe_f32_jt<DT, 1, NH>(X, Z, zp, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
+    case 2: e = launch_probe_f32_jt<DT, 2, NH>(X, Z, zp, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
+    case 3: e = launch_probe_f32_jt<DT, 3, NH>(X, Z, zp, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;      \
+    default: e = launch_probe_f32_jt<DT, 4, NH>(X, Z, zp, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, t0 ? nullptr : J); break;     \
     }
-            if (nhwc) { XC_P32(true) } else { XC_P32(false) }
+            if (dtype == XCONV_BF16) { XC_P32(XCONV_BF16, false) }
+            else if (dtype == XCONV_F16) { XC_P32(XCONV_F16, false) }
+            else if (nhwc) { XC_P32(XCONV_F32, true) }
+            else { XC_P32(XCONV_F32, false) }
 #undef XC_P32
         } else {
             const uint16_t *x = static_cast<const uint16_t *>(X);

@@ -269,6 +269,10 @@ xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const
         // With scratch, Z goes to the kernels in fragment order (drawn from the seed when no Z
         // is given); without it, every workgroup gathers its fragments from Z_dev.
         void *zpack = ws_dev ? static_cast<char *>(ws_dev) + zb : nullptr;
+        const bool arith32 = probe_in_f32(d->dtype, HWv, nhwc, z_exact16 && !Z_dev);
+        const int zdtype = arith32 ? XCONV_F32 : d->dtype;     // type of the fragments
+        // (the scratch of a +-1 desc is sized for one 16-bit value per entry: a given Z is gathered by the workgroups)
+        if (zpack_bytes(zdtype, d->C_in, d->r, z_exact16) > fb) zpack = nullptr;
         // a small +-1 matrix defined by the seed is cheaper to draw in every workgroup than in a launch of its own
         {
             const char *v = getenv("XCONV_PROBE_DRAW");   // sweeps: largest Z drawn inside the probe kernel, Rademacher / Gaussian
@@ -277,8 +281,8 @@ xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const
             // 16-bit storage: a dense +-1 matrix of any size the kernel's word table holds
             if (!Z_dev && !v && d->dtype != XCONV_F32 && probe_draws_words(d->C_in, d->r, probe_code(d))) zpack = nullptr;
         }
-        if (zpack) XC_LAUNCH(K_PACK_Z, st, launch_pack_z(d->dtype, Z_dev, zpack, d->C_in, d->r, z_exact16, probe_code(d), d->seed, nhwc, st, zmul));
-        XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, nhwc, sm,
+        if (zpack) XC_LAUNCH(K_PACK_Z, st, launch_pack_z(zdtype, Z_dev, zpack, d->C_in, d->r, z_exact16, probe_code(d), d->seed, nhwc, st, zmul));
+        XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, arith32, nhwc, sm,
                                             probe_code(d), d->seed, st, J));
         taken(J);
     } else {
