@@ -214,8 +214,11 @@ __global__ __launch_bounds__(kThreads) void pack_z_16_kernel(const float *__rest
 // DT of 16 bits (NCHW): X is widened on its way into the matrix instructions and the sums are rounded once.  It serves the calls
 // that probe_in_f32 names: Z keeps the bits and the range of fp32, where probe_16_kernel would take it as a sum of two values of
 // the storage type.
+// RAGGED: the last group of 16 channels is not whole.  Its channels past the end re-read the last ones and are cleared on their way
+// into the matrix instructions (their entries of Z are zero, but zero times an infinity is not): a branch per group, which whole
+// channel groups (0.2-0.4 us of C2's and C4's probe) are spared.
 // JOBS: nothing, or the small jobs that the launch carries along
-template <int DT, int JT, bool NHWC, class... JOBS>
+template <int DT, int JT, bool NHWC, bool RAGGED, class... JOBS>
 __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const elem_of<DT> *__restrict__ X, const float *__restrict__ Z,
                                                              const float *__restrict__ zpack, elem_of<DT> *__restrict__ Xt, int C_in,
                                                              int HW, int r, int CS, int j0, long long ngroups, int ntiles,
@@ -275,7 +278,6 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
             tl.xb[0] = X + first;
         }
     };
-    // Channels past the end re-read the last channels against zero fragment entries.
     struct Staged {
         std::conditional_t<DT == XCONV_F32, float4, uint2> v[4];
     };
@@ -327,6 +329,13 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
                 if constexpr (DT == XCONV_F32) v[u] = sg.v[u];
                 else v[u] = float4{st16_to_f32<DT>((uint16_t)sg.v[u].x), st16_to_f32<DT>((uint16_t)(sg.v[u].x >> 16)),
                                    st16_to_f32<DT>((uint16_t)sg.v[u].y), st16_to_f32<DT>((uint16_t)(sg.v[u].y >> 16))};
+            }
+            if constexpr (RAGGED) {
+                if (kk == KK - 1) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (kk * 16 + (NHWC ? 4 * g : 4 * u + g) >= C_in) v[u] = float4{0.f, 0.f, 0.f, 0.f};
+                }
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -400,7 +409,8 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
 // ---------------------------------------------------------------------------
 // NHWC: X is [pixels, C_in]; the 8 channels a lane supplies are then one 16-byte load, no
 // transpose; the wave's tile is PT sub-tiles of 16 pixels and `ngroups` is the number of pixels.
-template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
+// RAGGED: as in probe_f32_kernel, for groups of 32 channels.
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, bool RAGGED, class... JOBS>
 __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *__restrict__ X, const float *__restrict__ Z,
                                                             const uint4 *__restrict__ zpack, uint16_t *__restrict__ Xt, int C_in,
                                                             int HW, int r, int CS, int j0, long long ngroups, int ntiles,
@@ -442,6 +452,18 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
                 zf[e] = uint4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
                 if constexpr (SPLIT) zf[nfrag + e] = uint4{0u, 0u, 0u, 0u};   // (+-1 is exact in 16 bits: no residue)
             }
+        } else if (!Z) {
+            // other entries that come from the seed (few of them: block-sparse +-1), drawn one after the other
+            uint16_t *zh = reinterpret_cast<uint16_t *>(zf);
+#pragma unroll 1
+            for (int e = tid; e < nfrag * 8; e += kThreads) {
+                const int l = (e >> 3) & 63, jt = (e >> 9) % JT, kk = (e >> 9) / JT;
+                const int j = j0 + jmap(jt, l & 15, JT), c = kk * 32 + 8 * (l >> 4) + (e & 7);
+                const float z = c < C_in && j < r ? probe_entry(probe_gen(dist, seed), (uint64_t)c * r + j) : 0.0f;
+                const uint16_t h = f32_to_st16<DT>(z);
+                zh[e] = h;
+                if constexpr (SPLIT) zh[nfrag * 8 + e] = f32_to_st16<DT>(z - st16_to_f32<DT>(h));
+            }
         } else {
             // Z fragments: four entries (32 scalar loads) per thread in flight at a time
             for (int base = 0; base < nfrag; base += 4 * kThreads) {
@@ -454,9 +476,7 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
 #pragma unroll
                     for (int q = 0; q < 8; ++q) {
                         const int c = kk * 32 + 8 * (l >> 4) + q;
-                        z[k][q] = (e < nfrag && c < C_in && j < r)
-                                      ? (Z ? Z[(size_t)c * r + j] : probe_entry(probe_gen(dist, seed), (uint64_t)c * r + j))
-                                      : 0.0f;
+                        z[k][q] = (e < nfrag && c < C_in && j < r) ? Z[(size_t)c * r + j] : 0.0f;
                     }
                 }
 #pragma unroll
@@ -514,7 +534,6 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
         }
     };
     // MFMA operands of one K-step: cols[t] = the 8 channels 32kk + 8g .. +7 of pixel t.
-    // Channels past the end re-read the last channels, whose Z fragment entries are zero.
     struct Staged {
         uint32_t rows[NHWC ? 1 : 8][NHWC ? 1 : NW];  // NCHW: 8 channel rows of PT pixels
         uint4 cols[NHWC ? PT : 1];                   // NHWC: ready-made operands
@@ -575,6 +594,21 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
             if constexpr (NHWC) {
 #pragma unroll
                 for (int t = 0; t < PT; ++t) cols[t] = sg.cols[t];
+                if constexpr (RAGGED) {
+                    if (kk == KK - 1 && kk * 32 + 8 * g >= C_in) {
+#pragma unroll
+                        for (int t = 0; t < PT; ++t) cols[t] = uint4{0u, 0u, 0u, 0u};
+                    }
+                }
+            } else if constexpr (RAGGED) {
+                Staged whole = sg;
+                if (kk == KK - 1) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+#pragma unroll
+                        for (int w = 0; w < NW; ++w) whole.rows[q][w] = kk * 32 + 8 * g + q < C_in ? sg.rows[q][w] : 0u;
+                }
+                transpose_rows8<NW>(whole.rows, cols);
             } else {
                 transpose_rows8<NW>(sg.rows, cols);
             }
@@ -804,7 +838,7 @@ static SideJobs with_groups(SideJobs J, int groups)
     return J;
 }
 
-template <int DT, int JT, bool NHWC, class... JOBS>
+template <int DT, int JT, bool NHWC, bool RAGGED, class... JOBS>
 static hipError_t launch_probe_f32_side(const void *X, const float *Z, const float *zpack, void *Xt, int C_in, int HW, int r, int CS,
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
@@ -812,9 +846,9 @@ static hipError_t launch_probe_f32_side(const void *X, const float *Z, const flo
     const long long ngroups = NHWC ? npix : PlaneGroups<4>::count(npix, HW, sm);
     const int ntiles = (int)(NHWC ? (npix + 63) / 64 : (ngroups + 15) / 16);
     const size_t lds = (size_t)ceil_div(C_in, 16) * 4 * JT * 64 * sizeof(float);
-    hipError_t e = set_lds(probe_f32_kernel<DT, JT, NHWC, JOBS...>, lds);
+    hipError_t e = set_lds(probe_f32_kernel<DT, JT, NHWC, RAGGED, JOBS...>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_f32_kernel<DT, JT, NHWC, JOBS...>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st,
+    hipLaunchKernelGGL((probe_f32_kernel<DT, JT, NHWC, RAGGED, JOBS...>), dim3(probe_grid(ntiles, JT == 1 ? 4 : 2) + nside), dim3(kThreads), lds, st,
                        static_cast<const elem_of<DT> *>(X), Z, zpack, static_cast<elem_of<DT> *>(Xt), C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist,
                        seed, jobs...);
     return hipGetLastError();
@@ -825,11 +859,15 @@ static hipError_t launch_probe_f32_jt(const void *X, const float *Z, const float
                                       int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
-    if (nside) return launch_probe_f32_side<DT, JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
-    return launch_probe_f32_side<DT, JT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+    auto launch = [&](auto ragged) {
+        constexpr bool R = decltype(ragged)::value;
+        if (nside) return launch_probe_f32_side<DT, JT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
+        return launch_probe_f32_side<DT, JT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+    };
+    return C_in % 16 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
-template <int DT, int JT, int PT, bool SPLIT, bool NHWC, class... JOBS>
+template <int DT, int JT, int PT, bool SPLIT, bool NHWC, bool RAGGED, class... JOBS>
 static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
                                       int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
 {
@@ -838,9 +876,9 @@ static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const 
     // a dense +-1 matrix that comes from the seed and has no fragments in scratch is drawn by the workgroups from its generator words
     const int nword = (!Z && !zpack && probe_draws_words(C_in, r, dist)) ? (int)(((long long)C_in * r + 63) / 64) : 0;
     const size_t lds = (size_t)(SPLIT ? 2 : 1) * ceil_div(C_in, 32) * JT * 64 * sizeof(uint4) + (size_t)round_up(nword, 2) * 8;
-    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, JOBS...>, lds);
+    hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, RAGGED, JOBS...>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, JOBS...>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
+    hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, RAGGED, JOBS...>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
                        Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), jobs...);
     return hipGetLastError();
 }
@@ -850,8 +888,12 @@ static hipError_t launch_probe_16_cfg(const uint16_t *X, const float *Z, const u
                                       int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
-    if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
-    return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+    auto launch = [&](auto ragged) {
+        constexpr bool R = decltype(ragged)::value;
+        if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
+        return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+    };
+    return C_in % 32 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 template <int DT, int JT>

@@ -114,3 +114,34 @@ def test_projections_beyond_half_precision(dims):
     torch.cuda.synchronize()
     got = dW.cpu().numpy().astype(np.float64)
     assert np.all(np.isfinite(got)) and np.max(np.abs(got - want)) <= 2e-2 * np.max(np.abs(want))
+
+
+# an infinity stays with its pixel and its channel's entries of Z: +-inf there, in the last channel (which the lanes of channels past the
+# end read again) and in a middle one; every other pixel as without it
+@pytest.mark.parametrize("hw", [(7, 7), (8, 8), (3, 37)])
+@pytest.mark.parametrize("dtype,probe,C,r,nhwc", [("f32", "gaussian", 24, 12, False), ("f32", "rademacher", 33, 40, False), ("f32", "gaussian", 20, 64, True),
+                                                  ("bf16", "rademacher", 40, 16, False), ("f16", "rademacher", 1, 36, False),
+                                                  ("f16", "rademacher", 65, 64, False), ("bf16", "rademacher", 40, 24, True),
+                                                  ("f16", "gaussian", 33, 12, False), ("bf16", "gaussian", 17, 64, False)])
+def test_infinities(hw, dtype, probe, C, r, nhwc):
+    if dtype != "f32" and probe == "gaussian" and hw[0] * hw[1] % 4 == 0:
+        pytest.skip("aligned 16-bit planes take such a Z as a sum of two values, which an infinity times their opposite signs is not")
+    (H, W), B = hw, 3
+    X = synth.draw((B, C, H, W), 81, "normal", 1.0, dtype)
+    dist, dt = (xo.GAUSSIAN if probe == "gaussian" else xo.RADEMACHER), {"f32": xo.F32, "bf16": xo.BF16, "f16": xo.F16}[dtype]
+    Z = np.asarray(xo.probe_matrix(dist, 77, C, r)).reshape(C, r)
+    want = xo.probe_fwd(X, Z, dt).copy()
+    for b, c, y, x, v in [(0, C - 1, 0, 0, np.inf), (1, C // 2, H - 1, W - 1, -np.inf), (2, C - 1, H - 1, 1, -np.inf)]:
+        X[b, c, y, x] = v
+        want[b, :, y, x] = v * Z[c]
+    d = xb.make_desc(B, C, 8, H, W, 1, 1, 0, r, dtype, probe, 77, xb.XCONV_NHWC if nhwc else xb.XCONV_NCHW)
+    Xt = xb.alloc_xt(d, DEV)
+    out = torch.empty((B, r, H, W), dtype=torch.float32, device=DEV)
+    Xd = xb.to_device(X.transpose(0, 2, 3, 1) if nhwc else X, dtype, DEV)
+    xb.xconv_probe_fwd(d, Xd, Xt, None, xb.alloc_ws(d, xb.XCONV_OP_PROBE, DEV))
+    xb.xconv_xt_unpack(d, Xt, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    inf = np.isinf(want)
+    assert inf.any() and np.array_equal(got[inf], want[inf])
+    assert np.all(np.abs(got[~inf] - want[~inf]) <= TOL[dtype] * np.max(np.abs(want[~inf])))
