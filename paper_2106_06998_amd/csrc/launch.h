@@ -22,7 +22,7 @@ hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, 
 // Z == nullptr and zpack == nullptr: every workgroup draws its fragments of Z from (dist, seed) itself
 // J: small jobs to carry along
 hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zpack, void *Xt, int B, int C_in, int HW, int r,
-                        int CS, bool z_exact16, bool arith32, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
+                        int CS, bool z_exact16, bool arith32, bool nhwc, bool x_next, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
                         const SideJobs *J = nullptr);
 hipError_t launch_probe_generic(int dtype, const void *X, const float *Z, void *Xt, int B, int C_in, int HW, int r, int CS,
                                 bool nhwc, SliceMap sm, hipStream_t st);

@@ -20,28 +20,27 @@
 
 namespace xc {
 
-// X is read once and never again: where a wave's piece of a channel plane is whole cache lines, its loads carry the
-// non-temporal hint, so that the lines do not displace what the caches could keep.  Measured event-timed per probe
-// launch: C4 34.2 -> 31.3 us, C3 20.8 -> 17.2, C2 13.4 -> 12.0.  Planes that are not whole lines (C5: 1568 bytes) share
-// lines between neighbouring tiles, and a hinted line is fetched again by the neighbour (113-120 MB read instead of 104):
-// there the hint made the kernel 1 us faster at first and, once the workgroups drew Z themselves and started less evenly,
-// 1.3 us slower, so the 16-bit kernel loads such planes without it (`nt` = 0; the fp32 kernel always hints: a run-time
-// choice cost it 0.5 us on C2 and C4).  The
+// X is read once by this kernel.  With the non-temporal hint on its loads the lines do not displace what the caches could keep, but X
+// itself is not kept for whoever reads it next, and an X that is still cached is read more slowly.  The fp32 kernel and channels-last
+// rows always take the hint (event-timed per probe launch of the fp32 layers: C4 34.2 -> 31.3 us, C2 13.4 -> 12.0; a run-time choice
+// cost the fp32 kernel 0.5 us), 16-bit planes by probe_nt's rule.  The
 // stores of Xt never carry it: the correlation reads them next (with the hint on the stores the correlation got slower);
 // nor do the correlation's loads of dY, whose rows share cache lines with the rows of the next row-step (with the hint
 // the C5 correlation took 69.7 instead of 62.9 us).
 // The loads assume no more than the alignment of an element (the memory system takes vectors at any address): planes of a ragged
-// number of pixels run here too (PlaneGroups).
+// number of pixels run here too (PlaneGroups).  The two kinds of load are of different types: of one type, the compiler makes one
+// load of the two arms of a choice between them, without the hint.
 typedef unsigned int u32x4e __attribute__((ext_vector_type(4), aligned(2)));
 typedef unsigned int u32x2e __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned short u16x8e __attribute__((ext_vector_type(8), aligned(2)));
+typedef unsigned short u16x4e __attribute__((ext_vector_type(4), aligned(2)));
 template <bool NT> __device__ inline uint4 load_x16(const void *p)
 {
     if constexpr (NT) {
         const u32x4e v = __builtin_nontemporal_load(static_cast<const u32x4e *>(p));
         return uint4{v.x, v.y, v.z, v.w};
     } else {
-        const u32x4e v = *static_cast<const u32x4e *>(p);
-        return uint4{v.x, v.y, v.z, v.w};
+        return __builtin_bit_cast(uint4, *static_cast<const u16x8e *>(p));
     }
 }
 template <bool NT> __device__ inline uint2 load_x8(const void *p)
@@ -50,8 +49,7 @@ template <bool NT> __device__ inline uint2 load_x8(const void *p)
         const u32x2e v = __builtin_nontemporal_load(static_cast<const u32x2e *>(p));
         return uint2{v.x, v.y};
     } else {
-        const u32x2e v = *static_cast<const u32x2e *>(p);
-        return uint2{v.x, v.y};
+        return __builtin_bit_cast(uint2, *static_cast<const u16x4e *>(p));
     }
 }
 // Groups of PT pixels, one for each lane, of NCHW planes (a volume's depth slices): each plane has as many as cover it, the last
@@ -82,8 +80,19 @@ template <int PT> struct PlaneGroups {
     }
 };
 
-// whether the planes of an NCHW tensor (pitch bytes apart) are whole cache lines; channels-last rows always take the hint
-static int probe_nt(bool nhwc, long long pitch_bytes) { return (nhwc || pitch_bytes % 128 == 0) ? 1 : 0; }
+// Whether the 16-bit kernel's loads of X take the non-temporal hint (`bytes` of X; planes pitch_bytes apart; x_next: the launch behind
+// the probe reads X out of the caches).  Planes that are not whole cache lines share lines between neighbouring tiles, and a hinted
+// line is fetched again by the neighbour (C5, 1568 bytes: 113-120 MB read instead of 104).  Among the others it is worth it from 64
+// MiB on, where X no longer comes from or stays in the last-level cache: estimates (probe and correlation) of inputs that change
+// from call to call are 4-12 % faster with it at 67-206 MB (128 channels 32x32, batch 256: 69.8 -> 64.2 us; 256 channels 56x56 1x1,
+// batch 64: 49.5 -> 45.1), those of an input still cached 2-4 % slower, and at 2-51 MB both are 0-7 % slower.  Layers whose forward
+// product keeps patches of X for several taps or all channels are slower with it at all sizes (2-8 % from 25 MB on: 64 channels
+// 64x64 3x3, batch 128: 204 -> 215 us; 128 channels 56x56 3x3 at stride 2, batch 64: 179 -> 184); 1x1 layers of more channels take
+// them from memory in chunks (256 -> 64 channels 56x56, batch 64: 139.8 -> 134.9, batch 80: 171 -> 163).
+static int probe_nt(bool nhwc, long long pitch_bytes, long long bytes, bool x_next)
+{
+    return nhwc || (pitch_bytes % 128 == 0 && bytes >= (64LL << 20) && !x_next) ? 1 : 0;
+}
 
 void host_probe_matrix(int dist, uint64_t seed, int n, float *Z)
 {
@@ -869,7 +878,7 @@ static hipError_t launch_probe_f32_jt(const void *X, const float *Z, const float
 
 template <int DT, int JT, int PT, bool SPLIT, bool NHWC, bool RAGGED, class... JOBS>
 static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
-                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, int nside, const JOBS &...jobs)
+                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, int nt, hipStream_t st, int nside, const JOBS &...jobs)
 {
     const long long ngroups = NHWC ? npix : PlaneGroups<PT>::count(npix, HW, sm);
     const int ntiles = (int)(NHWC ? (npix + 16 * PT - 1) / (16 * PT) : (ngroups + 15) / 16);
@@ -879,41 +888,41 @@ static hipError_t launch_probe_16_side(const uint16_t *X, const float *Z, const 
     hipError_t e = set_lds(probe_16_kernel<DT, JT, PT, SPLIT, NHWC, RAGGED, JOBS...>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((probe_16_kernel<DT, JT, PT, SPLIT, NHWC, RAGGED, JOBS...>), dim3(probe_grid(ntiles, 2) + nside), dim3(kThreads), lds, st, X, Z, zpack,
-                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, probe_nt(NHWC, 2LL * (sm.sd ? sm.HWs : HW)), jobs...);
+                       Xt, C_in, HW, r, CS, j0, ngroups, ntiles, sm, dist, seed, nword, nt, jobs...);
     return hipGetLastError();
 }
 
 template <int DT, int JT, int PT, bool SPLIT, bool NHWC>
 static hipError_t launch_probe_16_cfg(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
-                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
+                                      int CS, int j0, long long npix, SliceMap sm, int dist, uint64_t seed, int nt, hipStream_t st, const SideJobs *J)
 {
     const int nside = side_groups<kThreads>(J);
     auto launch = [&](auto ragged) {
         constexpr bool R = decltype(ragged)::value;
-        if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, nside, with_groups(*J, nside));
-        return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, 0);
+        if (nside) return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, nside, with_groups(*J, nside));
+        return launch_probe_16_side<DT, JT, PT, SPLIT, NHWC, R>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, 0);
     };
     return C_in % 32 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 template <int DT, int JT>
 static hipError_t launch_probe_16_jt(const uint16_t *X, const float *Z, const uint4 *zpack, uint16_t *Xt, int C_in, int HW, int r,
-                                     int CS, int j0, long long npix, bool split, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st, const SideJobs *J)
+                                     int CS, int j0, long long npix, bool split, bool nhwc, SliceMap sm, int dist, uint64_t seed, int nt, hipStream_t st, const SideJobs *J)
 {
     if (nhwc) {
-        if (split) return launch_probe_16_cfg<DT, JT, 4, true, true>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
-        return launch_probe_16_cfg<DT, JT, 4, false, true>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
+        if (split) return launch_probe_16_cfg<DT, JT, 4, true, true>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
+        return launch_probe_16_cfg<DT, JT, 4, false, true>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
     }
     // 8 pixels per lane when the accumulators stay small, 4 for wide probe blocks
     if constexpr (JT <= 2) {
         const int HWs = sm.sd ? sm.HWs : HW;
         if (HWs % 8 == 0 || (HWs % 4 != 0 && HWs > 8)) {
-            if (split) return launch_probe_16_cfg<DT, JT, 8, true, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
-            return launch_probe_16_cfg<DT, JT, 8, false, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
+            if (split) return launch_probe_16_cfg<DT, JT, 8, true, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
+            return launch_probe_16_cfg<DT, JT, 8, false, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
         }
     }
-    if (split) return launch_probe_16_cfg<DT, JT, 4, true, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
-    return launch_probe_16_cfg<DT, JT, 4, false, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, st, J);
+    if (split) return launch_probe_16_cfg<DT, JT, 4, true, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
+    return launch_probe_16_cfg<DT, JT, 4, false, false>(X, Z, zpack, Xt, C_in, HW, r, CS, j0, npix, sm, dist, seed, nt, st, J);
 }
 
 // Dense +-1 matrices whose generator words (one per 64 entries) fit 16 KB of LDS next to the fragments: the 16-bit probe
@@ -972,8 +981,9 @@ hipError_t launch_pack_z(int dtype, const float *Z, void *out, int C_in, int r, 
 
 // zpack: Z in fragment order (launch_pack_z) or nullptr, in which case every workgroup gathers
 // its fragments from Z itself.  arith32: 16-bit planes in fp32 arithmetic (probe_in_f32), Z in the order of fp32 fragments.
+// x_next: the launch behind the probe reads X too, out of the caches (probe_nt).
 hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zpack, void *Xt, int B, int C_in, int HW, int r,
-                        int CS, bool z_exact16, bool arith32, bool nhwc, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
+                        int CS, bool z_exact16, bool arith32, bool nhwc, bool x_next, SliceMap sm, int dist, uint64_t seed, hipStream_t st,
                         const SideJobs *J)
 {
     const long long npix = (long long)B * HW;
@@ -1001,13 +1011,14 @@ hipError_t launch_probe(int dtype, const void *X, const float *Z, const void *zp
             const uint16_t *x = static_cast<const uint16_t *>(X);
             uint16_t *o = static_cast<uint16_t *>(Xt);
             const bool split = !z_exact16;
+            const int nt = probe_nt(nhwc, 2LL * (sm.sd ? sm.HWs : HW), 2 * npix * C_in, x_next);
             const uint4 *zp = zpack ? static_cast<const uint4 *>(zpack) + bi * ceil_div(C_in, 32) * 4 * 64 * (split ? 2 : 1) : nullptr;
 #define XC_P16(DT)                                                                                            \
     switch (jt) {                                                                                             \
-    case 1: e = launch_probe_16_jt<DT, 1>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, st, t0 ? nullptr : J); break;          \
-    case 2: e = launch_probe_16_jt<DT, 2>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, st, t0 ? nullptr : J); break;          \
-    case 3: e = launch_probe_16_jt<DT, 3>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, st, t0 ? nullptr : J); break;          \
-    default: e = launch_probe_16_jt<DT, 4>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, st, t0 ? nullptr : J); break;         \
+    case 1: e = launch_probe_16_jt<DT, 1>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, nt, st, t0 ? nullptr : J); break;          \
+    case 2: e = launch_probe_16_jt<DT, 2>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, nt, st, t0 ? nullptr : J); break;          \
+    case 3: e = launch_probe_16_jt<DT, 3>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, nt, st, t0 ? nullptr : J); break;          \
+    default: e = launch_probe_16_jt<DT, 4>(x, Z, zp, o, C_in, HW, r, CS, j0, npix, split, nhwc, sm, dist, seed, nt, st, t0 ? nullptr : J); break;         \
     }
             if (dtype == XCONV_BF16) { XC_P16(XCONV_BF16) } else { XC_P16(XCONV_F16) }
 #undef XC_P16

@@ -281,8 +281,11 @@ xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const
             // 16-bit storage: a dense +-1 matrix of any size the kernel's word table holds
             if (!Z_dev && !v && d->dtype != XCONV_F32 && probe_draws_words(d->C_in, d->r, probe_code(d))) zpack = nullptr;
         }
+        // (only layers hand over jobs: their forward product is the next launch, and reads X from memory in chunks where a 1x1 kernel
+        // has more channels than a resident patch)
+        const bool x_next = J && (d->kH * d->kW > 1 || d->C_in <= kConvResident);
         if (zpack) XC_LAUNCH(K_PACK_Z, st, launch_pack_z(zdtype, Z_dev, zpack, d->C_in, d->r, z_exact16, probe_code(d), d->seed, nhwc, st, zmul));
-        XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, arith32, nhwc, sm,
+        XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, arith32, nhwc, x_next, sm,
                                             probe_code(d), d->seed, st, J));
         taken(J);
     } else {
