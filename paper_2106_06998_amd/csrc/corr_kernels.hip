@@ -1199,17 +1199,21 @@ static bool shape_corr(CorrParams &P, int dtype, int WM, int nsets)
     return true;
 }
 
-// Expected microseconds of the correlation and its second pass at 16-bit storage: partial tiles written and read again, steps in a row
-// per round of workgroups, matrix instructions and starts of workgroups per compute unit.  A fit to 260 launch shapes of 106
-// layers (1x1 to 5x5, strides 1 and 2, 4 to 64 probes), 18 % off on average.
+// Expected microseconds of the correlation and its second pass at 16-bit storage: partial tiles written and read again, cache lines of
+// dY and values of A staged, steps in a row and matrix instructions per compute unit, and the sum over the waves that split the k-steps
+// of a row.  Those take whole k-steps: of a row of 4 columns one wave has work, so that the split of narrow rows gives nothing and its
+// sum is still paid.  A fit to 2353 launches of 1006 layers (estimates with 16 to 80 columns, exact gradients and the shifted
+// products of pixel probes with 16 to 208, volumes with three offsets; 1x1 to 5x5, strides 1 and 2, 65 to 512 output channels, rows
+// of 3 to 254 columns): 14 % off on average (exact gradients 33 %), 9 % for the ratio of two shapes of a layer.
 static double corr_cost(const CorrParams &P, int dtype, int nsets)
 {
-    const int MT = corr_mt(dtype, P.C_out), per_cu = corr_per_cu(P, dtype);
-    const long long groups = (long long)P.S * P.NTM * P.NTJ * P.NOG * nsets;
-    const double steps = ceil_div(P.NS, P.S), q = (double)((groups + 255) / 256), rounds = (double)((groups + 256 * per_cu - 1) / (256 * per_cu));
+    const int MT = corr_mt(dtype, P.C_out);
+    const double tiles = (double)P.NTM * P.NTJ * P.NOG * nsets, groups = P.S * tiles, staged = 8.0 * P.NS * tiles;   // 8 images per step
     const double offs = P.K2 < kMaxOff ? P.K2 : kMaxOff;
-    return 9.2 + 0.25e-6 * (double)groups * P.M_WG * P.J_WG * offs * 4 + 2.6 * steps * rounds +
-           0.034 * steps * q * P.RB * P.CWp / 4 / P.WK * MT * offs + 6.5 * q;
+    const double rounds = (double)(((long long)groups + 255) / 256), steps = rounds * ceil_div(P.NS, P.S);
+    const double lines = P.NSTRIP > 1 ? P.RB * (P.CW / 64.0 + 1) : P.RB * P.Wo / 64.0 + 1;   // of 128 bytes, per image and channel of a step
+    return 13 + 0.25e-6 * groups * P.M_WG * P.J_WG * offs * 4 + 4.9e-6 * staged * P.M_WG * lines + 0.21e-6 * staged * P.NNEW * P.BWc * P.J_WG +
+           steps * (1.45 + 0.012 * P.RB * ceil_div(P.CWp / 4, P.WK) * MT * offs) + 0.052 * rounds * (P.WK - 1) * MT * offs;
 }
 
 bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
@@ -1247,10 +1251,13 @@ bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH,
     const bool widest = shape_corr(P, dtype, WM, nsets);
     if (f32 || forced || !widest) return widest;
     // Fewer waves along the output channels, so a smaller tile: more steps per workgroup, but as many times fewer bytes of partial
-    // tiles, wider strips and a split of the k-steps over the waves.  Where the estimate sees 15 % in it (on 106 layers none is
-    // slower for it and they are 5 % faster in the geometric mean): 256 channels 28x28 3x3 r = 16, batch 256, bf16 123 -> 60 us
-    // with second pass, 128 -> 256 channels 56x56 at stride 2 r = 16 55 -> 32 us, 219 -> 200 channels 144x98 1x1 r = 4 1176 -> 396.
-    const double limit = 0.85 * corr_cost(P, dtype, nsets);
+    // tiles, wider strips and a split of the k-steps over the waves.  Where the estimate sees 10 % in it (401 of the 1006 layers;
+    // estimates are 10 %, exact gradients 7 %, pixel probes 14 %, volumes 9 % faster for it in the geometric mean, 5 of the 1006 more
+    // than 3 % slower, 15 % at most; an estimate that priced idle waves as working, fitted to estimates alone, had 27, 23 % at most):
+    // 256 channels 28x28 3x3 r = 16, batch 256, bf16 124 -> 61 us with second pass, 128 -> 256 channels 56x56 at stride 2 r = 16
+    // 56 -> 30 us, 219 -> 200 channels 144x98 1x1 r = 4, batch 39 292 -> 99.
+    // fp32 keeps the widest: its tiles are half as high to begin with, and the best shape of each of 71 layers would be 3.5 % faster.
+    const double limit = 0.9 * corr_cost(P, dtype, nsets);
     double best = limit;
     for (int wm = WM >> 1; wm >= 1; wm >>= 1) {
         CorrParams C = given;
