@@ -224,8 +224,9 @@ __global__ __launch_bounds__(kThreads) void pack_z_16_kernel(const float *__rest
 // that probe_in_f32 names: Z keeps the bits and the range of fp32, where probe_16_kernel would take it as a sum of two values of
 // the storage type.
 // RAGGED: the last group of 16 channels is not whole.  Its channels past the end re-read the last ones and are cleared on their way
-// into the matrix instructions (their entries of Z are zero, but zero times an infinity is not): a branch per group, which whole
-// channel groups (0.2-0.4 us of C2's and C4's probe) are spared.
+// into the matrix instructions (their entries of Z are zero, but zero times an infinity is not), where the group can be the last one: a
+// branch per D groups (estimate of 120 -> 176 channels 48x48 1x1, batch 12, r = 8: 31.9 us, 32.3 with a branch per group, 31.7 without
+// any), which whole channel groups are spared.
 // JOBS: nothing, or the small jobs that the launch carries along
 template <int DT, int JT, bool NHWC, bool RAGGED, class... JOBS>
 __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(const elem_of<DT> *__restrict__ X, const float *__restrict__ Z,
@@ -331,7 +332,8 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
         for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[jt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto process = [&](const Staged &sg, int kk) {
+        // may_end (known when the loops below are unrolled): the group can be the last one
+        auto process = [&](const Staged &sg, int kk, bool may_end) {
             float4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -340,7 +342,7 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
                                    st16_to_f32<DT>((uint16_t)sg.v[u].y), st16_to_f32<DT>((uint16_t)(sg.v[u].y >> 16))};
             }
             if constexpr (RAGGED) {
-                if (kk == KK - 1) {
+                if (may_end && kk == KK - 1) {
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
                         if (kk * 16 + (NHWC ? 4 * g : 4 * u + g) >= C_in) v[u] = float4{0.f, 0.f, 0.f, 0.f};
@@ -375,13 +377,13 @@ __global__ __launch_bounds__(kThreads, (JT == 1 ? 4 : 2)) void probe_f32_kernel(
         for (; kk + D <= KK; kk += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                process(rg[d], kk + d);
+                process(rg[d], kk + d, d == D - 1);
                 if (kk + d + D < KK) load16(rg[d], cur, kk + d + D);
             }
         }
 #pragma unroll
         for (int d = 0; d < D - 1; ++d)
-            if (kk + d < KK) process(rg[d], kk + d);
+            if (kk + d < KK) process(rg[d], kk + d, true);
 
         // the next tile's first loads go out before this tile's stores
         const Tile done = cur;
@@ -598,20 +600,21 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
         for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
             for (int t = 0; t < PT; ++t) acc[jt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto process = [&](const Staged &sg, int kk) {
+        // may_end (known when the loops below are unrolled): the group can be the last one
+        auto process = [&](const Staged &sg, int kk, bool may_end) {
             uint4 cols[PT];
             if constexpr (NHWC) {
 #pragma unroll
                 for (int t = 0; t < PT; ++t) cols[t] = sg.cols[t];
                 if constexpr (RAGGED) {
-                    if (kk == KK - 1 && kk * 32 + 8 * g >= C_in) {
+                    if (may_end && kk == KK - 1 && kk * 32 + 8 * g >= C_in) {
 #pragma unroll
                         for (int t = 0; t < PT; ++t) cols[t] = uint4{0u, 0u, 0u, 0u};
                     }
                 }
             } else if constexpr (RAGGED) {
                 Staged whole = sg;
-                if (kk == KK - 1) {
+                if (may_end && kk == KK - 1) {
 #pragma unroll
                     for (int q = 0; q < 8; ++q)
 #pragma unroll
@@ -637,13 +640,13 @@ __global__ __launch_bounds__(kThreads, 2) void probe_16_kernel(const uint16_t *_
         for (; kk + D <= KK; kk += D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                process(rg[d], kk + d);
+                process(rg[d], kk + d, d == D - 1);
                 if (kk + d + D < KK) load_step(rg[d], cur, kk + d + D);
             }
         }
 #pragma unroll
         for (int d = 0; d < D - 1; ++d)
-            if (kk + d < KK) process(rg[d], kk + d);
+            if (kk + d < KK) process(rg[d], kk + d, true);
 
         // the next tile's first loads go out before this tile's stores
         const Tile done = cur;
