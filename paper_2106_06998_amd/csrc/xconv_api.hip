@@ -233,13 +233,19 @@ xconv_status xconv_probe_matrix_dev(const xconv_desc *d, float *Z_dev, void *str
 namespace {
 
 // Forward probe over B images of HW pixels each; `sm` says where the output goes in Xt
-// (SliceMap{} for 2-D layers: plain order).  `HWv`: extent whose divisibility decides the vector loads.
+// (SliceMap{} for 2-D layers: plain order).  `HWv`: pixels that lie together in X (a plane, a volume's depth slice), at least 4 of
+// them for the vector loads.
+// x_next: the caller reads X again, out of the caches.
 // zmul: factor on a given Z, applied where Z is brought into fragment order (callers that pass one check
 // probe_scales_z first)
 bool probe_scales_z(const xconv_desc *d, int HWv, const void *X_dev, const void *ws_dev)
 {
     return ws_dev && probe_fast_path_ok(d->dtype, d->C_in, HWv, d->layout == XCONV_NHWC) && aligned16(X_dev);
 }
+
+// Whether a layer's product over `channels` reads its input out of the caches, if a launch in front of it left it there: it reads it
+// from memory in chunks where a 1x1 kernel has more channels than a resident patch (probe_nt has the figures)
+bool product_reads_caches(const xconv_desc *d, int channels) { return d->kH * d->kW > 1 || channels <= kConvResident; }
 
 // J (here and below): small jobs for a launch to carry along; emptied where one takes them
 void taken(SideJobs *J)
@@ -248,7 +254,7 @@ void taken(SideJobs *J)
 }
 
 xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const void *X_dev, void *Xt_dev, const float *Z_dev,
-                        void *ws_dev, size_t ws_bytes, hipStream_t st, float zmul = 1.0f, SideJobs *J = nullptr)
+                        void *ws_dev, size_t ws_bytes, hipStream_t st, bool x_next = false, float zmul = 1.0f, SideJobs *J = nullptr)
 {
     if (!X_dev || !Xt_dev) return XCONV_EINVAL;
     if (!aligned16(Xt_dev) || (reinterpret_cast<uintptr_t>(X_dev) & (elem_bytes(d->dtype) - 1)) != 0) return XCONV_EINVAL;
@@ -281,9 +287,6 @@ xconv_status probe_impl(const xconv_desc *d, int HW, int HWv, SliceMap sm, const
             // 16-bit storage: a dense +-1 matrix of any size the kernel's word table holds
             if (!Z_dev && !v && d->dtype != XCONV_F32 && probe_draws_words(d->C_in, d->r, probe_code(d))) zpack = nullptr;
         }
-        // (only layers hand over jobs: their forward product is the next launch, and reads X from memory in chunks where a 1x1 kernel
-        // has more channels than a resident patch)
-        const bool x_next = J && (d->kH * d->kW > 1 || d->C_in <= kConvResident);
         if (zpack) XC_LAUNCH(K_PACK_Z, st, launch_pack_z(zdtype, Z_dev, zpack, d->C_in, d->r, z_exact16, probe_code(d), d->seed, nhwc, st, zmul));
         XC_LAUNCH(K_PROBE, st, launch_probe(d->dtype, X_dev, Z_dev, zpack, Xt_dev, d->B, d->C_in, HW, d->r, CS, z_exact16, arith32, nhwc, x_next, sm,
                                             probe_code(d), d->seed, st, J));
@@ -1158,13 +1161,15 @@ xconv_status pixel_dw_estimate(const xconv_desc *d, bool indep, const void *dY_d
     XC_LAUNCH(K_GEN_ZIMG, st, launch_gen_zimg(d->dtype, zimg, g.K, d->r, g.CS, probe_code(d), d->seed, d->C_in, round_up(d->C_in, 16),
                                               0, 0, d->C_in, st, J));
     taken(J);
+    // (a layer, which hands over jobs, reads dY again for its input gradient)
     // Lt[p, j] = sum_b dY[b, p] Xbar[b, j] / r, rounded to the storage type (Alg. 1 backward step 3); p runs over
     // an image of dY in its own order, so the images of L come out in dY's layout.  The factor 1/r goes on Xbar where
     // the product brings it into fragment order, or in a launch of its own for the shapes that do not pass there
     const float inv_r = 1.0f / (float)d->r;
     const bool zfused = probe_scales_z(&g.probe, (int)g.P, dY_dev, pws);
     if (!zfused) XC_LAUNCH(K_SCALE, st, launch_scale(Xbar_dev, xs, d->B * g.R, inv_r, st));
-    s = probe_impl(&g.probe, (int)g.P, (int)g.P, SliceMap{}, dY_dev, lt, zfused ? Xbar_dev : xs, pws, g.probe_ws, st, zfused ? inv_r : 1.0f);
+    s = probe_impl(&g.probe, (int)g.P, (int)g.P, SliceMap{}, dY_dev, lt, zfused ? Xbar_dev : xs, pws, g.probe_ws, st, J && product_reads_caches(d, d->C_out),
+                   zfused ? inv_r : 1.0f);
     if (s != XCONV_OK) return s;
     XC_LAUNCH(K_REPACK, st, launch_to_nchw(d->dtype, lt, l, 1, g.CS, (int)g.P, (int)g.P, st));
     // dw_i = tr(L T_{-k(i)} Z) (Alg. 1 backward step 4; the factor 1/r is already in L)
@@ -1242,7 +1247,7 @@ xconv_status xconv_layer_fwd(const xconv_desc *d, int mode, const void *X_dev, c
     SideJobs J{};
     const bool packed = conv_pack_job(*plan, W_dev, cws, J);
     s = mode == XCONV_LAYER_CHANNEL
-            ? probe_impl(d, d->H * d->W, d->H * d->W, SliceMap{}, X_dev, state_dev, nullptr, ws_dev, eb, st, 1.0f, &J)
+            ? probe_impl(d, d->H * d->W, d->H * d->W, SliceMap{}, X_dev, state_dev, nullptr, ws_dev, eb, st, product_reads_caches(d, d->C_in), 1.0f, &J)
             : pixel_probe_fwd(d, false, X_dev, static_cast<float *>(state_dev), ws_dev, eb, stream, &J);
     if (s != XCONV_OK) return s;
     if (J.total) XC_LAUNCH(K_CONV, st, launch_side_jobs(J, st));
