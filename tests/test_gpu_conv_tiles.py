@@ -61,18 +61,30 @@ def test_conv_tiles(case, packed, shape, monkeypatch):
     run_tiles(case, packed, shape, monkeypatch)
 
 
-# classes of unequal size take turns in the grid: a tile past the last of its class does nothing
+# classes of unequal size take turns in the grid: a tile past the last of its class does nothing.  Classes of one tile each, then rows
+# of 2 and 1 times 1501 and 1500 positions (151 and 150), which no tile holds: the smallest class has about half of the largest's tiles
 UNEQUAL = [
     (3, 16, 24, 1, 5, 3, 2, 1, "bf16", False),
     (2, 40, 16, 3, 301, 5, 2, 2, "f32", False),
     (1, 24, 40, 33, 2, 3, 2, 1, "f16", True),
     (4, 144, 24, 5, 3, 3, 2, 1, "f16", False),
+    (1, 24, 16, 3, 3001, 3, 2, 1, "bf16", False),
+    (1, 24, 40, 3, 3001, 3, 2, 1, "f16", True),
+    (1, 24, 144, 3, 3001, 3, 2, 1, "f16", False),    # the contraction over 144 channels in chunks
 ]
 
 
 @pytest.mark.parametrize("packed", [True, False], ids=["packed", "gathered"])
 @pytest.mark.parametrize("case", UNEQUAL, ids=["%s-%dx%d" % (c[8], c[3], c[4]) for c in UNEQUAL])
 def test_classes_of_unequal_size(case, packed, monkeypatch):
+    B, C_in, C_out, H, W, k, s, p, dtype, nhwc = case
+    if W >= 301:
+        d = xb.make_desc(B, C_in, C_out, H, W, k, s, p, 1, dtype, "rademacher", 1, layout=xb.XCONV_NHWC if nhwc else xb.XCONV_NCHW)
+        v = xb.xconv_conv_plan_info(d, 1, packed)
+        tile = 32 * (v["shape"] % 10) * (4 // v["WM"])
+        # 2 x 1501 positions have more tiles than 1 x 1500, also with one tile lost to the end of a strip
+        assert (v["launches"], v["classes"]) == (1, 4) and -(-2 * ((W + 1) // 2) // tile) > -(-(W // 2) // tile) + (W > 301)
+        assert C_out < 144 or not v["res"]
     run_tiles(case, packed, "0", monkeypatch)
 
 
