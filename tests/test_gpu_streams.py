@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 LAYERS = [
     ("f32", 6, 32, 48, 17, 15, 3, 1, 1, 16, "gaussian"),       # fp32 producer/consumer kernel
     ("f16", 9, 64, 64, 14, 14, 3, 1, 1, 64, "rademacher"),     # 16-bit producer/consumer kernel
-    ("bf16", 3, 20, 18, 7, 9, 3, 2, 1, 20, "rademacher"),      # generic kernels, repacked dY
+    ("bf16", 3, 20, 18, 7, 9, 3, 2, 1, 20, "rademacher"),      # ragged planes: probe on the matrix cores, repacked dY
+    ("bf16", 3, 20, 18, 7, 9, 3, 1, 1, 20, "gaussian"),        # ... in fp32 arithmetic, Z in fragment order from a launch in front
+    ("f16", 3, 528, 18, 7, 9, 3, 2, 1, 20, "rademacher"),      # generic probe, Z through the workspace between two launches
 ]
 
 
@@ -41,7 +43,7 @@ class Layer:
         self.dY.copy_(xb.to_device(synth.draw(tuple(self.dY.shape), 51 + salt, "normal", 1e-2, dtype), dtype, DEV))
 
 
-@pytest.mark.parametrize("e", LAYERS, ids=[e[0] for e in LAYERS])
+@pytest.mark.parametrize("e", LAYERS, ids=["%s-%d-%s" % (e[0], e[1], e[10]) for e in LAYERS])
 def test_side_stream_gives_the_default_stream_result(e):
     say("side stream %s" % (e,))
     L = Layer(e)
@@ -63,7 +65,7 @@ def test_side_stream_gives_the_default_stream_result(e):
     assert torch.equal(L.dW, want)
 
 
-@pytest.mark.parametrize("e", LAYERS, ids=[e[0] for e in LAYERS])
+@pytest.mark.parametrize("e", LAYERS, ids=["%s-%d-%s" % (e[0], e[1], e[10]) for e in LAYERS])
 def test_captured_graph_replays_give_the_eager_result(e):
     say("graph capture %s" % (e,))
     L = Layer(e)
@@ -83,6 +85,21 @@ def test_captured_graph_replays_give_the_eager_result(e):
         torch.cuda.synchronize()
         assert torch.equal(L.dW, want), salt
         assert bool(torch.isfinite(L.dW).all())
+
+
+def test_layers_reach_the_kernels_they_stand_for():
+    names = []
+    for e in LAYERS:
+        L = Layer(e)
+        xb.xconv_prof_enable(True)
+        xb.xconv_prof_collect()
+        L.step()
+        torch.cuda.synchronize()
+        names.append({xb.xconv_prof_kernel_name(k) for k, _ in xb.xconv_prof_collect()})
+        xb.xconv_prof_enable(False)
+    assert "probe_generic_kernel" not in set().union(*names[:4])
+    assert {"probe_generic_kernel", "gen_z_kernel", "repack_planes_kernel"} <= names[4], names[4]
+    assert {"pack_z_kernel"} <= names[3] and "repack_planes_kernel" in names[2], names
 
 
 def test_two_layers_on_two_streams_at_once():
