@@ -147,9 +147,10 @@ xconv_status xconv_bias_grad(const xconv_desc *desc, const void *dY_dev, void *d
  * The scratch is a device array inside the library, XCONV_STATIC_SCRATCH_BYTES per GPU the
  * library runs on, held until the process ends; its address is looked up once per device, on
  * the first call with that device current.  The call allocates and frees nothing.  Arguments,
- * result and status as xconv_dw_estimate; XCONV_EWORKSPACE when
- * xconv_workspace_bytes(desc, XCONV_OP_ESTIMATE) exceeds XCONV_STATIC_SCRATCH_BYTES (nothing is
- * launched then), XCONV_EHIP when the runtime does not give the array's address.  All calls on
+ * result and status as xconv_dw_estimate.  Where xconv_workspace_bytes(desc, XCONV_OP_ESTIMATE)
+ * exceeds XCONV_STATIC_SCRATCH_BYTES, the correlation takes the tile with the least scratch in
+ * place of the fastest (sums in another order); XCONV_EWORKSPACE when that does not fit either
+ * (nothing is launched then), XCONV_EHIP when the runtime does not give the array's address.  All calls on
  * one GPU share the one array: calls that overlap in time on a GPU (two streams, two threads)
  * race on it, so issue them on one stream or order them with events. */
 #define XCONV_STATIC_SCRATCH_BYTES (40u * 1024u * 1024u)

@@ -1217,7 +1217,7 @@ static double corr_cost(const CorrParams &P, int dtype, int nsets)
 }
 
 bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
-               int CS, bool dy_aligned, int nsets)
+               int CS, bool dy_aligned, int nsets, bool small)
 {
     const bool f32 = dtype == XCONV_F32;
     const int BI = f32 ? 1 : 8, EPV = f32 ? 4 : 8;
@@ -1263,7 +1263,7 @@ bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH,
         CorrParams C = given;
         if (!shape_corr(C, dtype, wm, nsets) || corr_partial_bytes(C) > corr_partial_bytes(P)) continue;
         const double t = corr_cost(C, dtype, nsets);
-        if (t >= best) continue;
+        if (!small && t >= best) continue;
         best = t;
         P = C;
     }

@@ -63,7 +63,8 @@ hipError_t launch_pad_channels(int dtype, const void *src, void *out, long long 
 // probe/activation columns that carry data (r, or C_in on the exact path), CS
 // their padded stride.  Returns false when no launch shape fits the device.
 bool plan_corr(CorrParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw,
-               int CS, bool dy_aligned, int nsets);   // nsets: kernel-depth offsets per launch (1: 2-D layers)
+               int CS, bool dy_aligned, int nsets,    // nsets: kernel-depth offsets per launch (1: 2-D layers)
+               bool small = false);                   // the tile of the least scratch, not that of the least expected time
 size_t corr_partial_bytes(const CorrParams &P);
 size_t corr_lds_bytes(int dtype, const CorrParams &P);
 hipError_t launch_corr(int dtype, const CorrParams &P, hipStream_t st);

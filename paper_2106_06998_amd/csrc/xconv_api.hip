@@ -97,9 +97,9 @@ int plan_override_hash()
 // nsets > 0: kernel-depth offsets per launch.  2-D layers (nsets == 1 with plane == true) may take the row-sweep kernel; the
 // volumetric entry points, which hand the kernels depth slices through an offset table, keep to the kernels that know that table
 bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS,
-              bool dy_aligned, int nsets = 1, bool plane = true)
+              bool dy_aligned, int nsets = 1, bool plane = true, bool small = false)
 {
-    PlanKey k{{dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, (dy_aligned ? 1 : 0) | (plane ? 2 : 0) | nsets << 2, plan_override_hash()}};
+    PlanKey k{{dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, (dy_aligned ? 1 : 0) | (plane ? 2 : 0) | (small ? 4 : 0) | nsets << 3, plan_override_hash()}};
     {
         std::lock_guard<std::mutex> lk(g_plan_mu);
         for (const PlanEntry &e : g_plans)
@@ -123,7 +123,7 @@ bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH,
         e.P.K2 = e.Wp.K2; e.P.JP = e.Wp.JP; e.P.MP = e.Wp.MP;
         e.P.Ho = e.Wp.Ho; e.P.Wo = e.Wp.Wo;
     } else {
-        e.ok = plan_corr(e.P, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, dy_aligned, nsets);
+        e.ok = plan_corr(e.P, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, dy_aligned, nsets, small);
     }
     out = e;
     std::lock_guard<std::mutex> lk(g_plan_mu);
@@ -162,6 +162,16 @@ size_t dy_repack_bytes(const xconv_desc *d)
     return align_up((size_t)d->B * d->C_out * dy_pitch(d) * elem_bytes(d->dtype), 256);
 }
 
+// scratch of the estimate; small: with the correlation's tile of the least scratch.  0: no plan
+size_t estimate_ws_bytes(const xconv_desc *d, bool small)
+{
+    PlanEntry E;
+    if (!get_plan(E, d->dtype, d->B, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w,
+                  round_up(d->r, 16), true, 1, true, small))
+        return 0;
+    return z_bytes(d) + align_up(corr_partial_bytes(E.P), 256) + dy_repack_bytes(d);
+}
+
 }  // namespace
 
 extern "C" {
@@ -193,13 +203,8 @@ size_t xconv_workspace_bytes(const xconv_desc *d, int op)
 {
     if (xconv_check_desc(d) != XCONV_OK) return 0;
     if (op == XCONV_OP_PROBE) return z_bytes(d) + zfrag_bytes(d);
+    if (op == XCONV_OP_ESTIMATE) return estimate_ws_bytes(d, false);
     PlanEntry E;
-    if (op == XCONV_OP_ESTIMATE) {
-        if (!get_plan(E, d->dtype, d->B, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w,
-                      round_up(d->r, 16), true))
-            return 0;
-        return z_bytes(d) + align_up(corr_partial_bytes(E.P), 256) + dy_repack_bytes(d);
-    }
     if (op == XCONV_OP_EXACT) {
         const int CSx = round_up(d->C_in, 16);
         if (!get_plan(E, d->dtype, d->B, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CSx, true))
@@ -448,7 +453,7 @@ xconv_status xconv_probe_fwd(const xconv_desc *d, const void *X_dev, void *Xt_de
 
 // dw_dtype: the type dW is rounded to
 static xconv_status estimate_impl(const xconv_desc *d, const void *dY_dev, const void *Xt_dev, const float *Z_dev, void *dW_dev, int dw_dtype,
-                                  void *ws_dev, size_t ws_bytes, void *stream, SideJobs *J = nullptr)
+                                  void *ws_dev, size_t ws_bytes, void *stream, SideJobs *J = nullptr, bool small = false)
 {
     xconv_status s = xconv_check_desc(d);
     if (s != XCONV_OK) return s;
@@ -461,7 +466,7 @@ static xconv_status estimate_impl(const xconv_desc *d, const void *dY_dev, const
     const int CS = round_up(d->r, 16);
     PlanEntry E;
     if (!get_plan(E, d->dtype, d->B, d->C_out, d->H, d->W, d->kH, d->kW, d->stride_h, d->stride_w, d->pad_h, d->pad_w, CS,
-                  aligned16(dY_dev)))
+                  aligned16(dY_dev), 1, true, small))
         return XCONV_EUNSUPPORTED;
     CorrParams &P = E.P;
     const size_t zb = z_bytes(d), pb = align_up(corr_partial_bytes(P), 256), rb = dy_repack_bytes(d);
@@ -585,11 +590,13 @@ xconv_status xconv_dw_estimate_static(const xconv_desc *d, const void *dY_dev, c
     if (s != XCONV_OK) return s;
     const size_t need = xconv_workspace_bytes(d, XCONV_OP_ESTIMATE);
     if (need == 0) return XCONV_EUNSUPPORTED;
-    if (need > (size_t)XCONV_STATIC_SCRATCH_BYTES) return XCONV_EWORKSPACE;
+    // a layer whose fastest tile wants more than there is takes the tile that wants the least
+    const bool small = need > (size_t)XCONV_STATIC_SCRATCH_BYTES;
+    if (small && estimate_ws_bytes(d, true) > (size_t)XCONV_STATIC_SCRATCH_BYTES) return XCONV_EWORKSPACE;
     void *ws = static_scratch();
     if (!ws) return XCONV_EHIP;
     // every partial sum the kernels read from the scratch is written earlier in the same call: nothing to clear
-    return xconv_dw_estimate(d, dY_dev, Xt_dev, Z_dev, dW_dev, ws, XCONV_STATIC_SCRATCH_BYTES, stream);
+    return estimate_impl(d, dY_dev, Xt_dev, Z_dev, dW_dev, XCONV_F32, ws, XCONV_STATIC_SCRATCH_BYTES, stream, nullptr, small);
 }
 
 }  // extern "C"

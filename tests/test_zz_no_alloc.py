@@ -1,7 +1,7 @@
 """xconv_dw_estimate_static, the entry point for callers that cannot allocate device memory: through the C ABI its
 output equals xconv_dw_estimate's bit for bit, on two calls in a row (the second on a smaller layer, so that what the
-first call left in the library's scratch array lies beyond what the second one writes), and a layer whose scratch
-exceeds the array is refused before anything is launched."""
+first call left in the library's scratch array lies beyond what the second one writes), a layer whose fastest tile wants more
+than the array holds runs with a smaller one, and a layer that no tile fits is refused before anything is launched."""
 import numpy as np
 import pytest
 import torch
@@ -43,6 +43,17 @@ def test_static_scratch_estimate_equals_the_workspace_one_twice_in_a_row(dtype):
         got, want = _both(*layer)
         assert np.all(np.isfinite(want))
         assert np.array_equal(got, want)
+
+
+# partial tiles of 44, 42 and 72 MB with the fastest tile, 11 to 16 with the smallest
+@pytest.mark.parametrize("dims,r,dtype", [((46, 16, 448, 25, 12), 16, "bf16"), ((26, 24, 256, 18, 29), 12, "f16"), ((47, 16, 232, 27, 36), 4, "f16")])
+def test_static_scratch_estimate_with_the_smallest_tile(dims, r, dtype):
+    print("[gpu-case] xconv_dw_estimate_static %s r=%d %s" % (dims, r, dtype), flush=True)
+    layer = _layer(*dims, r, dtype, 701)
+    assert xb.xconv_workspace_bytes(layer[0], xb.XCONV_OP_ESTIMATE) > xb.xconv_static_scratch_bytes()
+    got, want = _both(*layer)
+    # equal products, fp32 sums in another order
+    assert np.all(np.isfinite(got)) and np.max(np.abs(got - want)) <= 1e-5 * np.max(np.abs(want))
 
 
 def test_static_scratch_estimate_refuses_what_does_not_fit():
