@@ -113,7 +113,11 @@ xconv_status xconv_probe_matrix_dev(const xconv_desc *desc, float *Z_dev, void *
  * Xt_dev: xconv_xt_bytes() bytes, written once.  Z_dev: [C_in,r] fp32 or NULL;
  * NULL draws Z from (probe, seed) into the workspace (XCONV_USER_Z then is
  * XCONV_EINVAL).  Sums are fp32; Xt is rounded once (nearest even) to
- * desc->dtype.  ws_dev may be NULL when Z_dev is given; with a workspace Z is
+ * desc->dtype.  At 16 bits, a Z that is not +-1 counts as the sum of two values
+ * of desc->dtype (16 bits of it for bf16; 22 for f16, entries up to 65504) on
+ * planes of a multiple of 4 pixels and on channels-last rows of a multiple of 8
+ * channels, and with all its bits elsewhere; for a desc with XCONV_RADEMACHER
+ * those take a given Z to be +-1 and 0.  ws_dev may be NULL when Z_dev is given; with a workspace Z is
  * first laid out once in the matrix-core operand order, without one every
  * workgroup gathers its operands from Z_dev (same result, slower).  A non-NULL
  * ws_dev smaller than xconv_workspace_bytes(XCONV_OP_PROBE) is
