@@ -110,6 +110,59 @@ template <int DT> __device__ inline f32x4 mfma16(const uint4 &a, const uint4 &b,
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
+// A float as the sum of three bf16 numbers (8 + 8 + 8 bits of the 24), each rounded to nearest: h + m + l = x exactly, down to bf16's smallest
+// number, 2^-133.  A product of two such sums, less its terms below 2^-25 (m*l, l*m, l*l), is six products on the 16-bit matrix
+// cores in place of one on the fp32 ones, which take 16 times as long (kSplitA, kSplitB).
+// An infinity becomes (+-1, 0, +-inf): l meets nothing but the other factor's h, which is zero only if that factor is, so that the
+// product is the infinity (or NaN) that fp32 gives; (inf, 0, 0) would meet zeros of m and l.  Finite values that bf16 would round to
+// an infinity take its largest number for h.
+constexpr int kSplit = 3;
+constexpr int kSplitProducts = 6;
+constexpr int kSplitA[kSplitProducts] = {2, 0, 1, 1, 0, 0}, kSplitB[kSplitProducts] = {0, 2, 1, 0, 1, 0};   // small terms first
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t bf16_pair(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
+__device__ inline void split8(const float (&x)[8], uint4 (&out)[kSplit])
+{
+    constexpr float kLimit = 0x1.ffp127f;      // from here on bf16 rounds to infinity
+    uint32_t p[kSplit][4];
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
+#pragma unroll
+        for (int q = 0; q < kSplit; ++q) {
+            const uint32_t w = bf16_pair(a, b);
+            p[q][i] = w;
+            if (q + 1 < kSplit) {
+                a -= __uint_as_float(w << 16);
+                b -= __uint_as_float(w & 0xffff0000u);
+            }
+        }
+    }
+    if (top >= kLimit) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (!(fabsf(x[e]) >= kLimit)) continue;
+            const uint32_t sign = __float_as_uint(x[e]) >> 16 & 0x8000u;
+            uint32_t h = sign | 0x3f80u, m = 0u, l = sign | 0x7f80u;
+            if (fabsf(x[e]) < __builtin_inff()) {
+                h = sign | 0x7f7fu;
+                const float r = x[e] - __uint_as_float(h << 16);
+                m = bf16_pair(r, 0.f) & 0xffffu;
+                l = bf16_pair(r - __uint_as_float(m << 16), 0.f) & 0xffffu;
+            }
+            const uint32_t v[kSplit] = {h, m, l};
+#pragma unroll
+            for (int q = 0; q < kSplit; ++q)
+                p[q][e / 2] = e & 1 ? (p[q][e / 2] & 0xffffu) | (v[q] << 16) : (p[q][e / 2] & 0xffff0000u) | v[q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kSplit; ++q) out[q] = uint4{p[q][0], p[q][1], p[q][2], p[q][3]};
+}
+
 // In-register transpose of an 8 (rows q) x 2*NW (16-bit columns) block held as
 // rows[q][w] (two columns per 32-bit word) into per-column vectors: column t
 // gets the eight row values packed in q order.
@@ -337,10 +390,11 @@ __device__ inline int xcd_block(int b, int grid)
 }
 
 // ---- forward convolution / exact input gradient as implicit GEMMs (conv_core.h, conv_kernels.hip) ----
-constexpr int kConvUnits = 8;   // 16-byte units of channels per staged chunk
+constexpr int kConvUnits = 8;   // 16-byte units of channels per staged chunk ...
+constexpr int kConvUnitsSplit = 4;   // ... of products whose floats are split (three times 16 bytes each)
 constexpr int kConvGatherM = 64;   // output channels that a group of kConvUnits / 2 k-steps of gathered weights covers (no workspace)
 constexpr int kConvResident = 128;   // most contraction channels whose whole patch is kept in LDS
-constexpr int kConvOverread = 4096; // bytes behind the packed weights that the last requests may touch
+constexpr int kConvOverread = 3 * kSplit * 1024; // bytes behind the packed weights that the last requests may touch (three k-steps ahead)
 constexpr int kConvSubs = 4;    // classes of output positions per launch ...
 constexpr int kConvSubsMany = 16;   // ... of the kernels that take many (conv_many)
 
@@ -427,6 +481,14 @@ typedef ConvArgs<kConvSubsMany> ConvParams;
 // tiles and weights of which there are kernels for many classes: the classes of a large stride have few taps each
 constexpr bool conv_many(int MT, int NT, bool packed, bool big, bool res) { return MT == NT && !big && (res || !packed); }
 
+// packed floats are multiplied as sums of three bf16 numbers
+constexpr bool conv_split(int dtype, bool packed) { return dtype == XCONV_F32 && packed; }
+// waves per SIMD that the registers of a kernel leave room for
+constexpr int conv_occupancy(int MT, int NT, bool split, bool packed)
+{
+    return split ? (MT * NT >= 2 ? 3 : 4) : MT * NT >= 8 || !packed ? 2 : MT * NT >= 4 ? 3 : 4;
+}
+
 // Small jobs that a launch carries along in workgroups of its own, in place of a launch each (4-6 us on the stream for work
 // of 1 us): the weights of a convolution in fragment order, and the sum of the pieces of a bias gradient.  The probe (forward)
 // and the second pass of the weight gradient (backward) carry them; the convolution that reads the weights follows.
@@ -439,7 +501,7 @@ template <int N> struct PackJobs {
     int total;                        // fragments and channels: one wave each
     int groups;                       // workgroups of the carrying launch that do them, in front of its own
     int nsub, NMB, Cin, Cout, w_sco, w_sci, kWfull;
-    int res, il, es;                  // resident patches, even and odd channels apart (conv_unit_channel), bytes per element
+    int res, es;                      // resident patches, bytes per element
     int C, S, dtype;                  // bias gradient: channels, pieces, storage type
     const void *w;
     void *packed;

@@ -20,6 +20,11 @@
 //         products of an output are summed tap by tap and, within a tap, by ascending channel.
 //   !RES  chunks of kConvUnits units: the next chunk's patch is on its way through registers while the current one is multiplied
 //         (two LDS buffers, one barrier per chunk).
+// Floats with packed weights (conv_split) are multiplied on the 16-bit matrix cores, as sums of three bf16 numbers (split8, common.h): a
+// patch holds three units for the one of the 16-bit types, split once as they are staged, the packed weights three fragments.  Six
+// products of 32 cycles then do the work of eight fp32 ones of 64; they take 12 registers a fragment and twice the accumulators, which leaves
+// room for one block of 32 channels a wave.  128 x 64 -> 64 channels 3x3 32x32: 98 -> 58 us (fp32 matrix instructions -> here), 64 x
+// 256 -> 256 channels 28x28 521 -> 327, 8 x 64 -> 64 channels 256x256 321 -> 204, and the sums are three times closer to 64 bits.
 // Strided layers keep the patch columns split by their remainder modulo the stride, so that the lanes' reads stay consecutive.
 // Weights come packed in fragment order (pack_fragment, one coalesced kilobyte per fragment, read through the L1 by
 // every wave) or, without a workspace, are gathered from [C_out, C_in, kH, kW] through LDS, a group of k-steps at a time; patches are
@@ -79,15 +84,17 @@ constexpr uint32_t kConvOob = 0x80000000u;   // byte offset past every buffer de
 //      argument where it is used: a launch of one class does without).
 // PACKED: weights in fragment order; else GW waves along the output channels (P.WM).  BIG: 64-bit addresses (tensors beyond a 2 GiB buffer descriptor).
 template <int DT, int VEC, bool SWAP, int MT, int NT, bool PACKED, bool BIG, bool RES, int NC, int GW>
-__global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 4 ? 3 : 4) void conv_kernel(const ConvArgs<NC> P)
+__global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PACKED), PACKED)) void conv_kernel(const ConvArgs<NC> P)
 {
     typedef typename ConvElem<DT>::t elem_t;
-    constexpr int UE = ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
-    constexpr int KS = kConvUnits / 2, CK = kConvUnits * UE;     // k-steps and channels of a chunk (!RES)
-    constexpr bool IL = DT == XCONV_F32 && VEC != 2;             // units of a pair hold the even and the odd channels (conv_unit_channel)
+    constexpr bool SPL = conv_split(DT, PACKED);                 // floats as three bf16 numbers each
+    constexpr int NP = SPL ? kSplit : 1, CU = SPL ? kConvUnitsSplit : kConvUnits;   // pieces of a unit, units of a chunk
+    constexpr int UE = SPL ? 8 : ConvElem<DT>::UE, ES = ConvElem<DT>::ES;
+    constexpr int KS = CU / 2, CK = CU * UE;                     // k-steps and channels of a chunk (!RES)
+    constexpr bool IL = DT == XCONV_F32 && !SPL && VEC != 2;     // units of a pair hold the even and the odd channels (conv_unit_channel)
     constexpr int VW = VEC == 1 ? 2 : 1;                         // columns per staging task
-    constexpr int RW = VEC == 2 ? 4 : UE;                        // registers per staging task
-    constexpr int G = (RES ? 64 : 32) / RW;                      // staging tasks of a thread in flight
+    constexpr int RW = VEC == 2 && !SPL ? 4 : UE;                // registers per staging task
+    constexpr int G = (!RES ? (SPL ? 16 : 32) : SPL && MT * NT == 1 ? 32 : 64) / RW;           // staging tasks of a thread in flight
 
     extern __shared__ uint4 conv_lds[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
@@ -112,9 +119,9 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     const int TN = 32 * NT * WN;
     const int npp_max = S.NPPmax;
     const int nks = (P.Cin + 2 * UE - 1) / (2 * UE);                            // k-steps of all channels
-    const int NU = RES ? 2 * nks : PACKED ? kConvUnits : std::min(2 * nks, kConvUnits);   // units of a staged patch
-    uint4 *patch = conv_lds;                                                    // [1 or 2][NU][NPOS]
-    const int patch_units = (RES || (!PACKED && nks <= KS) ? 1 : 2) * NU * S.NPOS;
+    const int NU = RES ? 2 * nks : PACKED ? CU : std::min(2 * nks, kConvUnits);   // units of a staged patch
+    uint4 *patch = conv_lds;                                                    // [1 or 2][NU][NP][NPOS]
+    const int patch_units = (RES || (!PACKED && nks <= KS) ? 1 : 2) * NU * NP * S.NPOS;
     uint2 *ptab = reinterpret_cast<uint2 *>(conv_lds + patch_units);             // [NPPmax] {source byte offset, LDS positions}
     uint2 *otab = ptab + npp_max;                                               // [TN] {output offset, LDS position of tap (0, 0)}
     uint4 *stab = conv_lds + patch_units + (npp_max + TN + 1) / 2;           // PACKED: LDS offsets of the k-steps' fragments, two lists
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             int tap, ks, ky, kx;
             (list ? P.dksl : P.dks).divmod(k, tap, ks);
             S.dkW.divmod(tap, ky, kx);
-            t[i] = tap < taps ? (tap_offset(ky, kx) + 2 * ks * S.NPOS) * 16 : 0;
+            t[i] = tap < taps ? (tap_offset(ky, kx) + 2 * ks * NP * S.NPOS) * 16 : 0;
         }
     }
     __syncthreads();
@@ -225,6 +232,14 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                         if (off != 0xffffffffu && c < P.Cin) v = src[(size_t)c * (size_t)P.in_sc];
                         sr[i][e] = ES == 4 ? __builtin_bit_cast(uint32_t, (float)v) : (uint32_t)v;
                     }
+                } else if constexpr (VEC == 2 && SPL) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const uint32_t vo = c0 + u * UE + 4 * q < P.Cin ? off + (uint32_t)u * 32u + 16u * q : kConvOob;
+                        const u32x4c v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)vo, c0 * ES, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sr[i][4 * q + e] = v[e];
+                    }
                 } else if constexpr (VEC == 2) {
                     const uint32_t vo = c0 + u * UE < P.Cin ? off + (uint32_t)u * 16u : kConvOob;
                     const u32x4c v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)vo, c0 * ES, 0);
@@ -250,7 +265,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         }
     };
     auto stage_write = [&](int buf, int phase) {
-        uint4 *dst = patch + (size_t)buf * NU * S.NPOS;
+        uint4 *dst = patch + (size_t)buf * NU * NP * S.NPOS;
 #pragma unroll
         for (int i = 0; i < G; ++i) {
             const int t = tid + kThreads * (phase * G + i);
@@ -258,8 +273,16 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                 int u, pp;
                 split(t, u, pp);
                 const uint32_t pos = ptab[pp].y;
-                uint4 *d = dst + (size_t)u * S.NPOS;
-                if constexpr (VEC == 1) {
+                uint4 *d = dst + (size_t)u * NP * S.NPOS;
+                if constexpr (SPL) {
+                    float v[8];
+                    uint4 piece[kSplit];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(sr[i][e]);
+                    split8(v, piece);
+#pragma unroll
+                    for (int q = 0; q < kSplit; ++q) d[q * S.NPOS + (pos & 0xffffu)] = piece[q];
+                } else if constexpr (VEC == 1) {
                     uint32_t rows[8][1];
                     uint4 cols[2];
 #pragma unroll
@@ -278,18 +301,24 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     };
     const int nphase = (ntask + kThreads * G - 1) / (kThreads * G);
 
-    f32x16c acc[MT][NT];
+    // split floats: the products h*h in a sum of their own, so that the five smaller ones do not round it (sums of 576 terms are off
+    // by 2.3e-7 of their norm; 3.6e-7 in one sum, 4.2e-7 on the fp32 matrix instructions)
+    constexpr int NS = SPL ? 2 : 1;
+    f32x16c accs[NS][MT][NT];
+    auto &acc = accs[0];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int q = 0; q < NS; ++q)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[mt][nt][e] = 0.f;
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) accs[q][mt][nt][e] = 0.f;
 
     const int co_w = (mtile * P.WM + wm) * (32 * MT);    // first output channel of this wave
     int pos[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) pos[nt] = ((int)otab[(wn * NT + nt) * 32 + l32].y + h * S.NPOS) * 16;   // bytes
+    for (int nt = 0; nt < NT; ++nt) pos[nt] = ((int)otab[(wn * NT + nt) * 32 + l32].y + h * NP * S.NPOS) * 16;   // bytes
 
     // ---- packed weight fragments: one kilobyte per k-step and 32 output channels, in the order of the k-steps
     const int nk = taps * nks;
@@ -299,7 +328,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         for (int mt = 0; mt < MT; ++mt) {
             int mb = co_w / 32 + mt;
             mb = mb < P.NMB ? mb : P.NMB - 1;
-            apk[mt] = static_cast<const char *>(P.wp) + ((size_t)S.w0 + (size_t)mb * nk * 64) * 16;
+            apk[mt] = static_cast<const char *>(P.wp) + ((size_t)S.w0 + (size_t)mb * nk * (64 * NP)) * 16;
         }
     }
     const uint32_t lane16 = (uint32_t)lane * 16u;
@@ -362,30 +391,39 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
     };
     // ---- k-steps.  Weights are requested kAhead k-steps ahead (they come from the L2), patch fragments one step ahead, both in
     // front of the step's matrix instructions (sched_barrier: left alone, the compiler reads each fragment right before its
-    // use and waits).  Four steps make a block, so that the rings are indexed by constants.
-    constexpr int kRing = 4, kAhead = kRing - 1;
-    static_assert(KS == kRing, "a full chunk is whole blocks");
-    u32x4c a[kRing][MT], b[2][NT];
+    // use and waits).  Four steps make a block (two of split floats, six products of each tile and three times the registers a step,
+    // but for the smallest tile), so that the rings are indexed by constants.
+    constexpr int kRing = SPL && !(RES && MT * NT == 1) ? 2 : 4, kAhead = kRing - 1;
+    static_assert(KS % kRing == 0 || RES, "a full chunk is whole blocks");
+    u32x4c a[kRing][MT][NP], b[2][NT][NP];
     auto load_a = [&](auto slot) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            a[decltype(slot)::value][mt] = *reinterpret_cast<const u32x4c *>(apk[mt] + lane16);
-            apk[mt] += 1024;
+#pragma unroll
+            for (int q = 0; q < NP; ++q) a[decltype(slot)::value][mt][q] = *reinterpret_cast<const u32x4c *>(apk[mt] + lane16 + 1024 * q);
+            apk[mt] += 1024 * NP;
         }
     };
     const char *patch_b = reinterpret_cast<const char *>(patch);
+    const int piece = S.NPOS * 16;
     auto load_b = [&](auto slot, int off) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) b[decltype(slot)::value][nt] = *reinterpret_cast<const u32x4c *>(patch_b + (pos[nt] + off));
-    };
-    auto multiply = [&](auto as, auto bs) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const u32x4c &av = a[decltype(as)::value][mt], &bv = b[decltype(bs)::value][nt];
-                acc[mt][nt] = SWAP ? conv_mma<DT>(bv, av, acc[mt][nt]) : conv_mma<DT>(av, bv, acc[mt][nt]);
-            }
+            for (int q = 0; q < NP; ++q) b[decltype(slot)::value][nt][q] = *reinterpret_cast<const u32x4c *>(patch_b + (pos[nt] + off + q * piece));
+    };
+    auto multiply = [&](auto as, auto bs) {
+#pragma unroll
+        for (int p = 0; p < (SPL ? kSplitProducts : 1); ++p)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const u32x4c &av = a[decltype(as)::value][mt][SPL ? kSplitA[p] : 0], &bv = b[decltype(bs)::value][nt][SPL ? kSplitB[p] : 0];
+                    constexpr int T = SPL ? XCONV_BF16 : DT;
+                    f32x16c &c = accs[SPL && kSplitA[p] + kSplitB[p] > 0 ? 1 : 0][mt][nt];
+                    c = SWAP ? conv_mma<T>(bv, av, c) : conv_mma<T>(av, bv, c);
+                }
     };
     auto step = [&](auto jc, int next_off) {
         constexpr int j = decltype(jc)::value;
@@ -396,25 +434,30 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         __builtin_amdgcn_sched_barrier(0);
     };
     // blocks b0 .. b1-1 of a list, and the rest of n steps behind the last whole block when `tail`
-    int4 so;
+    typedef std::conditional_t<kRing == 4, int4, int2> offsets_t;
+    offsets_t so;
     auto first_block = [&](const uint4 *list, int base) {
-        so = reinterpret_cast<const int4 *>(list)[0];
+        so = reinterpret_cast<const offsets_t *>(list)[0];
         load_b(std::integral_constant<int, 0>{}, base + so.x);
     };
     auto run_blocks = [&](const uint4 *list, int base, int blk0, int blk1) {
         for (int i = blk0; i < blk1; ++i) {
-            const int4 sn = reinterpret_cast<const int4 *>(list)[i + 1];
+            const offsets_t sn = reinterpret_cast<const offsets_t *>(list)[i + 1];
             step(std::integral_constant<int, 0>{}, base + so.y);
-            step(std::integral_constant<int, 1>{}, base + so.z);
-            step(std::integral_constant<int, 2>{}, base + so.w);
-            step(std::integral_constant<int, 3>{}, base + sn.x);
+            if constexpr (kRing == 4) {
+                step(std::integral_constant<int, 1>{}, base + so.z);
+                step(std::integral_constant<int, 2>{}, base + so.w);
+            }
+            step(std::integral_constant<int, kRing - 1>{}, base + sn.x);
             so = sn;
         }
     };
     auto run_tail = [&](int base, int left) {
         if (left > 0) step(std::integral_constant<int, 0>{}, base + so.y);
-        if (left > 1) step(std::integral_constant<int, 1>{}, base + so.z);
-        if (left > 2) step(std::integral_constant<int, 2>{}, base + so.w);
+        if constexpr (kRing == 4) {
+            if (left > 1) step(std::integral_constant<int, 1>{}, base + so.z);
+            if (left > 2) step(std::integral_constant<int, 2>{}, base + so.w);
+        }
     };
 
     if (nck > 0) {
@@ -424,10 +467,12 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             // gradient of 256 -> 64 channels 1x1 56x56, batch 64, bf16 took 44 us with the order kept, 42 without.)
             load_a(std::integral_constant<int, 0>{});
             if constexpr (!RES) __builtin_amdgcn_sched_barrier(0);
-            load_a(std::integral_constant<int, 1>{});
-            if constexpr (!RES) __builtin_amdgcn_sched_barrier(0);
-            load_a(std::integral_constant<int, 2>{});
-            if constexpr (!RES) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (kAhead > 1) {
+                load_a(std::integral_constant<int, 1>{});
+                if constexpr (!RES) __builtin_amdgcn_sched_barrier(0);
+                load_a(std::integral_constant<int, 2>{});
+                if constexpr (!RES) __builtin_amdgcn_sched_barrier(0);
+            }
         } else {
             gather_load(nck > 1 ? gtab : gtab + cap0, 0, 0);
             gather_write(0);
@@ -439,14 +484,14 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
         __syncthreads();
         if constexpr (RES) {
             first_block(stab, 0);
-            run_blocks(stab, 0, 0, n_full / 4);
-            run_tail(0, n_full & 3);
+            run_blocks(stab, 0, 0, n_full / kRing);
+            run_tail(0, n_full % kRing);
         } else if constexpr (PACKED) {
             const uint4 *list1 = stab + conv_step_list(taps, KS);
             for (int ck = 0; ck < nck; ++ck) {
                 const bool more = ck + 1 < nck;
                 const uint4 *list = more ? stab : list1;
-                const int nblk = (more ? n_full : n_last) / 4, base = (ck & 1) * NU * S.NPOS * 16;
+                const int nblk = (more ? n_full : n_last) / kRing, base = (ck & 1) * NU * NP * S.NPOS * 16;
                 first_block(list, base);
                 for (int ph = 0; ph < nphase; ++ph) {
                     if (more) stage_load((ck + 1) * CK, ph);
@@ -457,7 +502,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
             }
             // behind the loop: with a path from the tail back into the blocks (a ring that is one or two steps further), the
             // compiler would have every block wait for all but the last step's weights
-            run_tail(((nck - 1) & 1) * NU * S.NPOS * 16, n_last & 3);
+            run_tail(((nck - 1) & 1) * NU * NP * S.NPOS * 16, n_last % kRing);
         } else {
             int abuf = 0;
             for (int ck = 0; ck < nck; ++ck) {
@@ -479,7 +524,7 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
 #pragma unroll
                             for (int j = 0; j < SG; ++j)
 #pragma unroll
-                                for (int mt = 0; mt < MT; ++mt) a[j][mt] = af[(j * GW * MT + mt) * 64];
+                                for (int mt = 0; mt < MT; ++mt) a[j][mt][0] = af[(j * GW * MT + mt) * 64];
                             auto off = [&](int j) { return base + (int)(l[j].x & ~15u); };
                             load_b(std::integral_constant<int, 0>{}, off(0));
                             load_b(std::integral_constant<int, 1>{}, off(1));
@@ -501,6 +546,15 @@ __global__ __launch_bounds__(kThreads, MT * NT >= 8 || !PACKED ? 2 : MT * NT >= 
                 __syncthreads();
             }
         }
+    }
+
+    if constexpr (SPL) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[mt][nt][e] += accs[NS - 1][mt][nt][e];
     }
 
     // ---- accumulator tile: lane l holds column l % 32 and rows 8*(i/4) + 4*(l/32) + i%4, rounded once to the storage type.
@@ -634,14 +688,18 @@ template <int DT, int VEC, bool SWAP> static hipError_t launch_conv_shape(const 
     }
     const int shape = P.MT * 10 + P.NT;
     if (P.res) {
-        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false, true>(P, sub, st);
-        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false, true>(P, sub, st);
+        if constexpr (!conv_split(DT, true)) {
+            if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false, true>(P, sub, st);
+            if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false, true>(P, sub, st);
+        }
         if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false, true>(P, sub, st);
         return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false, true>(P, sub, st);
     }
     if (P.wp) {
-        if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false>(P, sub, st);
-        if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false>(P, sub, st);
+        if constexpr (!conv_split(DT, true)) {
+            if (shape == 24) return launch_conv_one<DT, VEC, SWAP, 2, 4, true, false>(P, sub, st);
+            if (shape == 22) return launch_conv_one<DT, VEC, SWAP, 2, 2, true, false>(P, sub, st);
+        }
         if (shape == 12) return launch_conv_one<DT, VEC, SWAP, 1, 2, true, false>(P, sub, st);
         return launch_conv_one<DT, VEC, SWAP, 1, 1, true, false>(P, sub, st);
     }

@@ -28,23 +28,28 @@ constexpr long long kMaxReach = 0x7f000000;    // bytes a tile reads or writes f
 constexpr long long kMaxReachBig = 0xfffffffe; // elements of the same with 64-bit addresses (32-bit tables, all ones marks the outside)
 
 // see expected_cycles
-constexpr struct {
+struct ConvModel {
     double e24, e22, e12, e11;   // share of the 16-bit matrix rate of the wave tiles (MT, NT)
     double ef32;                 // ... of the fp32 rate
     double task;                 // cycles per staging task
     double in_bpc, out_bpc;      // bytes per cycle and compute unit
     double chunk, overlap;       // k-steps per overlapping step, how completely steps overlap
-    double start;                // cycles per round
+    double start, per_chunk;     // cycles per round, and per chunk of one
     double alone, pair;          // surcharges for one and two workgroups per unit
     double gather;               // cycles per gathered group of k-steps
-} kConvModel = {0.58, 0.465, 0.55, 0.575, 1.0, 367, 30.7, 15.1, 16, 0.634, 13900, 1.5, 0.145, 600};
+};
+constexpr ConvModel kConvModel = {0.58, 0.465, 0.55, 0.575, 1.0, 367, 30.7, 15.1, 16, 0.634, 13900, 0, 1.5, 0.145, 600};
+constexpr ConvModel kConvModelSplit = {0, 0, 0.656, 0.635, 0, 594, 15.7, 33.6, 1e9, 0.352, 6490, 1870, 0.911, 0, 0};
 
 int env_value(const char *name)
 {
     const char *e = getenv(name);
     return e ? atoi(e) : 0;
 }
-int units_elems(int dtype) { return dtype == XCONV_F32 ? 4 : 8; }
+// channels of a staged unit and units of a chunk; packed: with weights in fragment order, so that floats are split
+int units_elems(int dtype, bool packed) { return dtype == XCONV_F32 && !conv_split(dtype, packed) ? 4 : 8; }
+int chunk_units(int dtype, bool packed) { return conv_split(dtype, packed) ? kConvUnitsSplit : kConvUnits; }
+int pieces(int dtype, bool packed) { return conv_split(dtype, packed) ? kSplit : 1; }
 int elem_size(int dtype) { return dtype == XCONV_F32 ? 4 : 2; }
 
 void image_strides(int layout, int C, int H, int W, long long &sb, int &sc, int &sy, int &sx)
@@ -89,20 +94,20 @@ std::vector<ConvSub> make_subs(const xconv_desc *d, int transposed, int Ho, int 
     return v;
 }
 
-int ksteps(int dtype, int C) { return ceil_div(C, 2 * units_elems(dtype)); }
+int ksteps(int dtype, bool packed, int C) { return ceil_div(C, 2 * units_elems(dtype, packed)); }
 long long packed_units(const ConvSub &s, int dtype, int Cin, int Cout)
 {
-    return (long long)ceil_div(Cout, 32) * ksteps(dtype, Cin) * s.kH * s.kW * 64;
+    return (long long)ceil_div(Cout, 32) * ksteps(dtype, true, Cin) * s.kH * s.kW * 64 * pieces(dtype, true);
 }
 
 // LDS of a workgroup: patch, tables, lists of the k-steps, gathered weights (conv_kernel's layout)
-long long conv_lds(const ConvParams &P, const ConvSub &c, int TN, int nks)
+long long conv_lds(const ConvParams &P, const ConvSub &c, int dtype, int TN, int nks)
 {
-    constexpr int KS = kConvUnits / 2;
+    const int units = chunk_units(dtype, P.wp != nullptr), KS = units / 2, np = pieces(dtype, P.wp != nullptr);
     const int taps = c.kH * c.kW;
     const long long tables = (c.NPPmax + TN + 1) / 2 * 16;
-    if (P.res) return 2LL * nks * c.NPOS * 16 + tables + conv_step_list(taps, nks) * 16;
-    if (P.wp) return 2LL * kConvUnits * c.NPOS * 16 + tables + 2 * conv_step_list(taps, KS) * 16;
+    if (P.res) return 2LL * nks * np * c.NPOS * 16 + tables + conv_step_list(taps, nks) * 16;
+    if (P.wp) return 2LL * units * np * c.NPOS * 16 + tables + 2 * conv_step_list(taps, KS) * 16;
     const int last = nks - (nks - 1) / KS * KS;
     return (nks > KS ? 2LL * kConvUnits : 2LL * nks) * c.NPOS * 16 + tables +
            ((nks > KS ? round_up(taps * KS, 8) : 0) + round_up(taps * last, 8)) * 8 + 2 * KS * kConvGatherM / 32 * 1024;
@@ -122,7 +127,7 @@ struct Work {
 // or a tile's offsets from its first image would not.
 bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN, Work &w)
 {
-    const int es = elem_size(dtype), nks = ksteps(dtype, P.Cin), VW = P.vec == 1 ? 2 : 1;
+    const int es = elem_size(dtype), nks = ksteps(dtype, P.wp != nullptr, P.Cin), VW = P.vec == 1 ? 2 : 1;
     const int taps = s.kH * s.kW, SW = ceil_div(s.Wo, std::min(nst, s.Wo));
     s.SW = SW;
     s.TU = TU;
@@ -144,7 +149,7 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
     s.NPOS = round_up(NPR * s.PWs, 16);
     s.NPPmax = NPR * s.PWv;
     s.TPS = (int)((NR * SW + TU - 1) / TU);
-    const long long lds = conv_lds(P, s, TN, nks);
+    const long long lds = conv_lds(P, s, dtype, TN, nks);
     if (lds > kLdsMax || s.NPOS > 65535) return false;
     const double n = (double)ceil_div(s.Wo, SW) * s.TPS * P.NMT;
     const int TM = std::min(32 * P.MT * P.WM, P.Cout);
@@ -167,41 +172,49 @@ bool lay_out(ConvSub &s, const ConvParams &P, int dtype, int nst, int TU, int TN
 // and 16-bit, both layouts, 1x1 to 5x5, strides 1 and 2); picking by them costs 1 % against the best configuration of each.
 // Gathered weights add a share for each group (453 products of strides 1 to 4, 1x1 to 7x7, in up to five configurations: 1.8 %;
 // 2.0 to 3.3 % with a third of that share up to seven times as much, 5 % without).
+// Split floats have constants of their own, a fit to 3087 configurations of 60 layers' two products, resident and in chunks: picking
+// by them costs 1.4 % (4.6 % with those of the others and a guess at the rate).
 double expected_cycles(const ConvParams &P, int dtype, const Work &w, int ncu)
 {
-    const int shape = P.MT * 10 + P.NT, nks = ksteps(dtype, P.Cin);
-    const double eff = shape == 24 ? kConvModel.e24 : shape == 22 ? kConvModel.e22 : shape == 12 ? kConvModel.e12 : kConvModel.e11;
-    const double clk = dtype == XCONV_F32 ? 256.0 / kConvModel.ef32 : 32.0 / eff;
-    const int occ = std::max(1, std::min(kLdsMax / w.lds, P.MT * P.NT >= 8 ? 2 : P.MT * P.NT >= 4 ? (P.wp ? 3 : 2) : P.wp ? 4 : 3));
+    const bool packed = P.wp != nullptr, split = conv_split(dtype, packed);
+    const int shape = P.MT * 10 + P.NT, nks = ksteps(dtype, packed, P.Cin);
+    const ConvModel &m = split ? kConvModelSplit : kConvModel;
+    const double eff = shape == 24 ? m.e24 : shape == 22 ? m.e22 : shape == 12 ? m.e12 : m.e11;
+    const double clk = split ? 32.0 * kSplitProducts / eff : dtype == XCONV_F32 ? 256.0 / m.ef32 : 32.0 / eff;
+    const int occ = std::max(1, std::min(kLdsMax / w.lds, packed ? conv_occupancy(P.MT, P.NT, split, true) : P.MT * P.NT >= 4 ? 2 : 3));
     const double q = (double)((w.wgs + ncu - 1) / ncu), rounds = (double)((w.wgs + (long long)ncu * occ - 1) / ((long long)ncu * occ));
     const double tm = w.mma / w.wgs * clk * q;
-    const double ts = std::max(w.tasks / w.wgs * kConvModel.task * q, w.in / ncu / kConvModel.in_bpc) + w.out / ncu / kConvModel.out_bpc;
-    const double steps = rounds * (P.res ? 1.0 : std::max(1.0, nks / kConvModel.chunk));
-    double t = kConvModel.start * rounds + std::max(tm, ts) + std::min(tm, ts) / std::pow(steps, kConvModel.overlap);
-    if (!P.wp) t += kConvModel.gather * w.groups / w.wgs * q;
-    if (occ == 1) t += kConvModel.alone * ts;
-    if (occ == 2) t += kConvModel.pair * tm;
+    const double ts = std::max(w.tasks / w.wgs * m.task * q, w.in / ncu / m.in_bpc) + w.out / ncu / m.out_bpc;
+    const double steps = rounds * (P.res ? 1.0 : std::max(1.0, nks / m.chunk));
+    double t = m.start * rounds + std::max(tm, ts) + std::min(tm, ts) / std::pow(steps, m.overlap);
+    if (split && !P.res) t += m.per_chunk * rounds * ((nks + kConvUnitsSplit / 2 - 1) / (kConvUnitsSplit / 2));
+    if (!P.wp) t += m.gather * w.groups / w.wgs * q;
+    if (occ == 1) t += m.alone * ts;
+    if (occ == 2) t += m.pair * tm;
     return t;
 }
 
-bool plan(ConvParams &P, int dtype, int ncu)
+// the tiles of the least expected time, which is returned; -1 where none fits
+double plan(ConvParams &P, int dtype, int ncu)
 {
     const int force = env_value("XCONV_CONV_SHAPE"), force_wm = env_value("XCONV_CONV_WM");
     const int force_strips = env_value("XCONV_CONV_STRIPS"), force_rows = env_value("XCONV_CONV_ROWS");
-    const int nks = ksteps(dtype, P.Cin);
+    const bool packed = P.wp != nullptr, split = conv_split(dtype, packed);
+    const int units = chunk_units(dtype, packed), nks = ksteps(dtype, packed, P.Cin);
     int wide = 1;
     for (int i = 0; i < P.nsub; ++i) wide = std::max(wide, P.sub[i].Wo);
     double best = -1;
     ConvParams bp = P;
     // tiles of TN positions or of whole rows only (fewer positions, but no partly used row and halo); only where no patch fits
     // (large strides or kernels on narrow images), less
-    for (int part = 1; part <= 512 && best < 0; part *= 2)
+    for (int part = 1; part <= 512 && (best < 0 || (split && part <= 2)); part *= 2)
         for (const int shape : {24, 22, 12, 11})
             for (int WM = 1; WM <= 4; WM *= 2) {
                 ConvParams C = P;
                 C.MT = shape / 10; C.NT = shape % 10; C.WM = WM;
                 const int TM = 32 * C.MT * WM, TN = 32 * C.NT * (4 / WM);
-                if (force && !P.big && (P.wp || force != 24) && P.nsub <= kConvSubs && shape != force) continue;
+                if (split && shape > 12) continue;
+                if (force && !P.big && (packed || force != 24) && !(split && force > 12) && P.nsub <= kConvSubs && shape != force) continue;
                 if (force_wm && WM != force_wm) continue;
                 if (!P.wp && (C.NT > 2 || (WM > 1 && shape != 11))) continue;   // (the gathers there are)
                 if (P.big && shape != 22) continue;
@@ -243,17 +256,17 @@ bool plan(ConvParams &P, int dtype, int ncu)
                     }
                 }
             }
-    if (best < 0) return false;
+    if (best < 0) return best;
     P = bp;
     P.dNMT = fast_div(P.NMT);
-    P.dks = fast_div(P.res ? nks : kConvUnits / 2);
-    P.dksl = fast_div(P.res ? nks : nks - (nks - 1) / (kConvUnits / 2) * (kConvUnits / 2));
+    P.dks = fast_div(P.res ? nks : units / 2);
+    P.dksl = fast_div(P.res ? nks : nks - (nks - 1) / (units / 2) * (units / 2));
     for (int i = 0; i < P.nsub; ++i) {
         ConvSub &s = P.sub[i];
         s.dSW = fast_div(s.SW); s.dHo = fast_div(s.Ho); s.dHV = fast_div((s.Ho - 1) * s.sth + s.kH);
         s.dPWv = fast_div(s.PWv); s.dTPS = fast_div(s.TPS); s.dkW = fast_div(s.kW);
     }
-    return true;
+    return best;
 }
 
 }  // namespace
@@ -262,7 +275,7 @@ bool plan(ConvParams &P, int dtype, int ncu)
 size_t conv_ws_bytes(const xconv_desc *d, int transposed)
 {
     const int Cin = transposed ? d->C_out : d->C_in, Cout = transposed ? d->C_in : d->C_out;
-    return (size_t)ceil_div(Cout, 32) * ksteps(d->dtype, Cin) * d->kH * d->kW * 64 * 16 + kConvOverread;
+    return (size_t)ceil_div(Cout, 32) * ksteps(d->dtype, true, Cin) * d->kH * d->kW * 64 * 16 * pieces(d->dtype, true) + kConvOverread;
 }
 
 // One launch of a product: a class group of a run of images.  The pointers of P are filled in per call.
@@ -304,7 +317,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
         d = &flat;
     }
     const int Ho = (d->H + 2 * d->pad_h - d->kH) / d->stride_h + 1, Wo = (d->W + 2 * d->pad_w - d->kW) / d->stride_w + 1;
-    const int es = elem_size(d->dtype), ue = units_elems(d->dtype);
+    const int es = elem_size(d->dtype), ue = units_elems(d->dtype, packed), units = chunk_units(d->dtype, packed);
     ConvParams P{};
     P.Cin = transposed ? d->C_out : d->C_in;
     P.Cout = transposed ? d->C_in : d->C_out;
@@ -338,7 +351,7 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
     // masked by an offset past the descriptor, but the scalar offset of their channel, up to a whole unit or block, counts as
     // well, and the hardware's bounds check subtracts it from the size.  (Stopping it at the last channel in the kernel cost the 1x1
     // layers 2-4 %.)
-    const int in_ch = round_up(P.Cin, P.Cin > kConvUnits * ue ? kConvUnits * ue : 2 * ue);
+    const int in_ch = round_up(P.Cin, P.Cin > units * ue ? units * ue : 2 * ue);
     const bool huge = std::max(P.in_sb, P.out_sb) * es > kMaxReach || (long long)in_ch * P.in_sc * es > kMaxReach ||
                       (long long)round_up(P.Cout, 32) * P.out_sc * es > kMaxReach;
     // (an image that fits 32-bit offsets never needs 64-bit addresses, and patches of so few channels are resident: a tile of one
@@ -358,15 +371,21 @@ bool make_plan(ConvPlan &out, const xconv_desc *d, int transposed, bool packed, 
             for (int big = first ? first->P.big : huge; big <= (first ? first->P.big : 1) && !found; ++big) {
                 P.big = big;
                 P.vec = 0;
-                if (!P.big && nhwc && P.Cin % ue == 0 && align % 16 == 0) P.vec = 2;
+                if (!P.big && nhwc && P.Cin % (16 / es) == 0 && align % 16 == 0) P.vec = 2;
                 bool pairs = !P.big && !nhwc && es == 2 && P.Wi % 2 == 0 && align % 4 == 0;
                 for (int i = 0; i < P.nsub; ++i) pairs = pairs && P.sub[i].kW >= P.sw;
                 if (pairs) P.vec = 1;
-                for (int res = first ? first->P.res : packed && !big && P.Cin <= kConvResident; res >= (first ? first->P.res : 0) && !found; --res) {
-                    L.P = P;
-                    L.P.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
-                    L.P.res = res;
-                    found = plan(L.P, d->dtype, ncu);
+                double best = -1;
+                for (int res = first ? first->P.res : packed && !big && P.Cin <= kConvResident; res >= (first ? first->P.res : 0); --res) {
+                    ConvParams C = P;
+                    C.wp = packed && !P.big ? &out : nullptr;   // only whether it is set counts here
+                    C.res = res;
+                    const double t = plan(C, d->dtype, ncu);
+                    if (t < 0 || (found && t >= best)) continue;
+                    best = t;
+                    L.P = C;
+                    found = true;
+                    if (!conv_split(d->dtype, C.wp != nullptr)) break;   // (a resident patch that fits is the better one)
                 }
             }
             if (!found) return false;
@@ -456,10 +475,9 @@ template <int N> static void add_pack_job(PackJobs<N> &J, const ConvLaunch &L, i
     J.nsub = P.nsub;
     J.NMB = P.NMB; J.Cin = P.Cin; J.Cout = P.Cout; J.w_sco = P.w_sco; J.w_sci = P.w_sci; J.kWfull = P.kWfull; J.res = P.res;
     J.es = elem_size(dtype);
-    J.il = dtype == XCONV_F32 && P.vec != 2;
     J.w = w;
     J.packed = ws;
-    const int nks = ceil_div(P.Cin, 2 * units_elems(dtype));
+    const int nks = ksteps(dtype, true, P.Cin);
     for (int i = 0; i < P.nsub; ++i) {
         const ConvSub &s = P.sub[i];
         J.sub[i] = PackClass{s.kH, s.kW, s.ky0, s.kx0, s.kys, s.kxs, P.NMB * nks * s.kH * s.kW, s.w0};

@@ -8,30 +8,33 @@
 namespace xc {
 
 // Fragment i of a class: weights in the order [block of 32 output channels][chunk][tap][k-step][lane] of 16 bytes (a chunk =
-// kConvUnits / 2 k-steps of channels, or all of them for resident patches); zero beyond the channels.
+// kConvUnits / 2 k-steps of channels, or all of them for resident patches); zero beyond the channels.  Floats are split: three
+// times 64 lanes of 16 bytes a fragment, chunks of kConvUnitsSplit / 2 k-steps.
 template <int ES, class SJ> __device__ inline void pack_fragment(const SJ &J, const PackClass &S, int i, int lane)
 {
-    constexpr int UE = 16 / ES;
+    constexpr int UE = 8, KS = (ES == 4 ? kConvUnitsSplit : kConvUnits) / 2;
     const int taps = S.kH * S.kW, nks = (J.Cin + 2 * UE - 1) / (2 * UE), nk = taps * nks;
-    const int cks = J.res ? nks : kConvUnits / 2;             // k-steps of a full chunk
+    const int cks = J.res ? nks : KS;                         // k-steps of a full chunk
     const int mb = i / nk, k = i - mb * nk;
     const int ck = k / (taps * cks), r = k - ck * taps * cks;
     const int per = min(cks, nks - ck * cks), tap = r / per, s = r - tap * per;
     const int ky = tap / S.kW, kx = tap - ky * S.kW;
     const int co = mb * 32 + (lane & 31), u = 2 * (ck * cks + s) + (lane >> 5);
-    // channel of element e of unit u: c0 + e * step (conv_unit_channel)
-    const int c0 = J.il ? (u >> 1) * 2 * UE + (u & 1) : u * UE, step = J.il ? 2 : 1;
-    typedef typename std::conditional<ES == 4, uint32_t, uint16_t>::type elem_t;
+    const int c0 = u * UE;
+    typedef typename std::conditional<ES == 4, float, uint16_t>::type elem_t;
     const elem_t *src = static_cast<const elem_t *>(J.w) + (size_t)co * J.w_sco + (S.ky0 + ky * S.kys) * J.kWfull + S.kx0 + kx * S.kxs;
-    uint32_t v[UE];
+    elem_t v[UE];
 #pragma unroll
-    for (int e = 0; e < UE; ++e) {
-        const int c = c0 + e * step;
-        v[e] = co < J.Cout && c < J.Cin ? (uint32_t)src[(size_t)c * J.w_sci] : 0u;
+    for (int e = 0; e < UE; ++e) v[e] = co < J.Cout && c0 + e < J.Cin ? src[(size_t)(c0 + e) * J.w_sci] : elem_t(0);
+    uint4 *out = static_cast<uint4 *>(J.packed) + S.w0 + (size_t)i * (ES == 4 ? kSplit * 64 : 64) + lane;
+    if constexpr (ES == 4) {
+        uint4 p[kSplit];
+        split8(v, p);
+#pragma unroll
+        for (int q = 0; q < kSplit; ++q) out[q * 64] = p[q];
+    } else {
+        *out = uint4{v[0] | ((uint32_t)v[1] << 16), v[2] | ((uint32_t)v[3] << 16), v[4] | ((uint32_t)v[5] << 16), v[6] | ((uint32_t)v[7] << 16)};
     }
-    uint4 *out = static_cast<uint4 *>(J.packed) + S.w0 + (size_t)i * 64 + lane;
-    if constexpr (ES == 4) *out = uint4{v[0], v[1], v[2], v[3]};
-    else *out = uint4{v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16)};
 }
 
 // one wave adds the S pieces of channel c in a fixed order: lanes take the pieces lane, lane + 64, ...
