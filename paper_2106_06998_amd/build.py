@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libxconv.so")
 GLUE = os.path.join(HERE, "_torch_glue.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["xconv_api.hip", "probe_kernels.hip", "corr_kernels.hip", "corr_ws_kernels.hip", "corr_row_kernels.hip", "corr_ws32_kernels.hip", "pixel_kernels.hip", "relu_kernels.hip", "bias_kernels.hip", "conv_kernels.hip", "conv_f32.hip", "conv_bf16.hip", "conv_f16.hip", "diag_kernels.hip"]
+SOURCES = ["xconv_api.hip", "probe_kernels.hip", "corr_kernels.hip", "corr_ws_kernels.hip", "corr_row_kernels.hip", "corr_ws32_kernels.hip", "corr_split_kernels.hip", "pixel_kernels.hip", "relu_kernels.hip", "bias_kernels.hip", "conv_kernels.hip", "conv_f32.hip", "conv_bf16.hip", "conv_f16.hip", "diag_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # XCONV_SANITIZE_HOST=1: a second library whose host code (descriptor checks, plans, size arithmetic) is built under

@@ -113,24 +113,26 @@ template <int DT> __device__ inline f32x4 mfma16(const uint4 &a, const uint4 &b,
 // A float as the sum of three bf16 numbers (8 + 8 + 8 bits of the 24), each rounded to nearest: h + m + l = x exactly, down to bf16's smallest
 // number, 2^-133.  A product of two such sums, less its terms below 2^-25 (m*l, l*m, l*l), is six products on the 16-bit matrix
 // cores in place of one on the fp32 ones, which take 16 times as long (kSplitA, kSplitB).
-// An infinity becomes (+-1, 0, +-inf): l meets nothing but the other factor's h, which is zero only if that factor is, so that the
-// product is the infinity (or NaN) that fp32 gives; (inf, 0, 0) would meet zeros of m and l.  Finite values that bf16 would round to
-// an infinity take its largest number for h.
+// Values from kSplitLimit on, which bf16 rounds to infinity, are rare and take code of their own (split_value; what split8 makes of them
+// is thrown away): an infinity becomes (+-1, 0, +-inf): l meets nothing but the other factor's h, which is zero only if that factor is, so
+// that the product is the infinity (or NaN) that fp32 gives; (inf, 0, 0) would meet zeros of m and l.  Finite ones take bf16's
+// largest number for h.  A NaN is one in all three.
 constexpr int kSplit = 3;
 constexpr int kSplitProducts = 6;
 constexpr int kSplitA[kSplitProducts] = {2, 0, 1, 1, 0, 0}, kSplitB[kSplitProducts] = {0, 2, 1, 0, 1, 0};   // small terms first
+constexpr float kSplitLimit = 0x1.ffp127f;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t bf16_pair(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
-__device__ inline void split8(const float (&x)[8], uint4 (&out)[kSplit])
+// eight floats in pieces; the largest magnitude among them
+__device__ __forceinline__ float split8(const float (&x)[8], uint4 (&out)[kSplit])
 {
-    constexpr float kLimit = 0x1.ffp127f;      // from here on bf16 rounds to infinity
     uint32_t p[kSplit][4];
     float top = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float a = x[2 * i], b = x[2 * i + 1];
-        top = fmaxf(top, fmaxf(fabsf(a), fabsf(b)));
+        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(a), "v"(b));
 #pragma unroll
         for (int q = 0; q < kSplit; ++q) {
             const uint32_t w = bf16_pair(a, b);
@@ -141,23 +143,46 @@ __device__ inline void split8(const float (&x)[8], uint4 (&out)[kSplit])
             }
         }
     }
-    if (top >= kLimit) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (!(fabsf(x[e]) >= kLimit)) continue;
-            const uint32_t sign = __float_as_uint(x[e]) >> 16 & 0x8000u;
-            uint32_t h = sign | 0x3f80u, m = 0u, l = sign | 0x7f80u;
-            if (fabsf(x[e]) < __builtin_inff()) {
-                h = sign | 0x7f7fu;
-                const float r = x[e] - __uint_as_float(h << 16);
-                m = bf16_pair(r, 0.f) & 0xffffu;
-                l = bf16_pair(r - __uint_as_float(m << 16), 0.f) & 0xffffu;
-            }
-            const uint32_t v[kSplit] = {h, m, l};
+    for (int q = 0; q < kSplit; ++q) out[q] = uint4{p[q][0], p[q][1], p[q][2], p[q][3]};
+    return top;
+}
+// one float from kSplitLimit on
+__device__ inline void split_value(float x, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    const uint32_t sign = __float_as_uint(x) >> 16 & 0x8000u;
+    h = sign | 0x3f80u, m = 0u, l = sign | 0x7f80u;
+    if (fabsf(x) < __builtin_inff()) {
+        h = sign | 0x7f7fu;
+        const float r = x - __uint_as_float(h << 16);
+        m = bf16_pair(r, 0.f) & 0xffffu;
+        l = bf16_pair(r - __uint_as_float(m << 16), 0.f) & 0xffffu;
+    }
+}
+// ... to element 0 of three rows of 16-bit numbers `pitch` apart
+__device__ inline void split_value(float x, uint16_t *out, int pitch)
+{
+    uint32_t h, m, l;
+    split_value(x, h, m, l);
+    out[0] = (uint16_t)h;
+    out[pitch] = (uint16_t)m;
+    out[2 * pitch] = (uint16_t)l;
+}
+// split8 for any values
+__device__ __forceinline__ void split8_any(const float (&x)[8], uint4 (&out)[kSplit])
+{
+    if (split8(x, out) < kSplitLimit) return;
+    uint32_t p[kSplit][4];
 #pragma unroll
-            for (int q = 0; q < kSplit; ++q)
-                p[q][e / 2] = e & 1 ? (p[q][e / 2] & 0xffffu) | (v[q] << 16) : (p[q][e / 2] & 0xffff0000u) | v[q];
-        }
+    for (int q = 0; q < kSplit; ++q) p[q][0] = out[q].x, p[q][1] = out[q].y, p[q][2] = out[q].z, p[q][3] = out[q].w;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        if (!(fabsf(x[e]) >= kSplitLimit)) continue;
+        uint32_t v[kSplit];
+        split_value(x[e], v[0], v[1], v[2]);
+#pragma unroll
+        for (int q = 0; q < kSplit; ++q)
+            p[q][e / 2] = e & 1 ? (p[q][e / 2] & 0xffffu) | (v[q] << 16) : (p[q][e / 2] & 0xffff0000u) | v[q];
     }
 #pragma unroll
     for (int q = 0; q < kSplit; ++q) out[q] = uint4{p[q][0], p[q][1], p[q][2], p[q][3]};

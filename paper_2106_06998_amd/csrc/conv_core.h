@@ -279,7 +279,7 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
                     uint4 piece[kSplit];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(sr[i][e]);
-                    split8(v, piece);
+                    split8_any(v, piece);
 #pragma unroll
                     for (int q = 0; q < kSplit; ++q) d[q * S.NPOS + (pos & 0xffffu)] = piece[q];
                 } else if constexpr (VEC == 1) {

@@ -427,6 +427,7 @@ static const size_t kWs32LdsLimit = 160 * 1024;
 
 size_t corr_ws32_lds_bytes(const WsParams &P)
 {
+    if (P.MT == 2) return corr_split_lds_bytes(P);
     return ((size_t)2 * P.a_units + (size_t)P.NRING * P.b_row_units) * 16;
 }
 
@@ -434,6 +435,10 @@ bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int 
 {
     if (dtype != XCONV_F32) return false;
     if (ws32_env_int("XCONV_CORR_WS32", 1) == 0) return false;
+    // the overrides below are those of the kernel on fp32 instructions
+    if (!getenv("XCONV_WS32_OCC") && !getenv("XCONV_WS32_WJ") && !getenv("XCONV_WS32_CW") &&
+        plan_corr_split(P, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets, ws32_env_int("XCONV_WS32_SPLITS", 0)))
+        return true;
     P.B = B; P.C_out = C_out; P.H = H; P.W = W;
     P.kH = kH; P.kW = kW; P.sh = sh; P.sw = sw; P.ph = ph; P.pw = pw;
     P.Ho = (H + 2 * ph - kH) / sh + 1;
@@ -542,6 +547,7 @@ template <int NTASK, int D, int OCC> static hipError_t launch_ws32_cfg(const WsP
 
 hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st)
 {
+    if (P.MT == 2) return launch_corr_split(P, st);
     // two workgroups per compute unit when LDS and the staging registers (two stages of at most
     // two tasks) allow it
     if (P.NTASK <= 2 && 2 * corr_ws32_lds_bytes(P) <= kWs32LdsLimit) {

@@ -106,6 +106,11 @@ hipError_t launch_corr_row(int dtype, const WsParams &P, hipStream_t st);
 bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets);
 size_t corr_ws32_lds_bytes(const WsParams &P);
 hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st);
+// corr_split_kernels.hip: the same layers on the 16-bit matrix cores, floats as three bf16 numbers; plan_corr_ws32 takes it first (its plans have MT == 2).
+// splits: K-splits, 0: as many as fill the chip
+bool plan_corr_split(WsParams &P, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets, int splits);
+size_t corr_split_lds_bytes(const WsParams &P);
+hipError_t launch_corr_split(const WsParams &P, hipStream_t st);
 
 // conv_kernels.hip: forward convolution (transposed = 0) and exact input gradient (1) of a layer.  `ws` (conv_ws_bytes)
 // holds the weights in fragment order; null: the kernel gathers them from w.

@@ -752,7 +752,7 @@ xconv_status xconv_plan_info(const xconv_desc *d, int op, int32_t *out)
         return XCONV_EUNSUPPORTED;
     if (E.ws) {
         const WsParams &Q = E.Wp;
-        const int32_t v[16] = {Q.S, Q.NS, 1, Q.CW, Q.WM, Q.WJ, 1, Q.M_WG, Q.J_WG, (int32_t)(E.ws == 3 ? corr_row_lds_bytes(Q) : E.ws == 2 ? corr_ws32_lds_bytes(Q) : corr_ws_lds_bytes(Q)),
+        const int32_t v[16] = {Q.S, Q.NS, 1, Q.CW, Q.WM, Q.WJ, 4 / (Q.WM * Q.WJ), Q.M_WG, Q.J_WG, (int32_t)(E.ws == 3 ? corr_row_lds_bytes(Q) : E.ws == 2 ? corr_ws32_lds_bytes(Q) : corr_ws_lds_bytes(Q)),
                                Q.NTM, Q.NTJ, Q.NOG, Q.CS, Q.NSUB, E.ws};
         for (int i = 0; i < 16; ++i) out[i] = v[i];
         return XCONV_OK;
