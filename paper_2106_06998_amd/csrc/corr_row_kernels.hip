@@ -370,6 +370,7 @@ __global__ __launch_bounds__(kWsThreads) void corr_row_kernel(const WsArgs P)
             r.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
             r.z = __builtin_amdgcn_readfirstlane((int)((uint32_t)left * img_bytes));
             r.w = 0x00020000;
+            settle_resource(r);
             return r;
         };
         // loads are opaque to the compiler and waited for by hand (see corr_ws_kernel)

@@ -382,9 +382,6 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
             }
         }
 
-        // The loads below are opaque to the compiler, which therefore does not know that a scalar register a vector instruction has written
-        // (v_readfirstlane) must not be read by a memory instruction within five wait states.
-        auto settle = [](i32x4s &r) __attribute__((always_inline)) { asm volatile("s_nop 4" : "+s"(r)); };
         // Buffer resources built by hand: a group with fewer than 8 images, or a step that does not exist, gets a smaller (or empty)
         // resource: reads past it return zero.
         auto rsrc_of = [&](const float *base, int bg, uint32_t img_bytes, bool live) __attribute__((always_inline)) {
@@ -398,7 +395,7 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
             r.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
             r.z = __builtin_amdgcn_readfirstlane((int)((uint32_t)left * img_bytes));
             r.w = 0x00020000;
-            settle(r);
+            settle_resource(r);
             return r;
         };
         // Loads of the software pipeline: opaque instructions, waited for by hand (stage_wait); nothing reads a stage between its
@@ -453,7 +450,7 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                 rsA.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
                 rsA.z = __builtin_amdgcn_readfirstlane((int)(live ? P.vol_bytes : 0u));
                 rsA.w = 0x00020000;
-                settle(rsA);
+                settle_resource(rsA);
                 const uint32_t vol_stride = (uint32_t)P.C_out * dy_plane_bytes;
 #pragma unroll
                 for (int img = 0; img < 8; ++img) {

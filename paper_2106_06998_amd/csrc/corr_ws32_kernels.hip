@@ -249,12 +249,15 @@ __global__ __launch_bounds__(kWsThreads, 2 * OCC) void corr_ws32_kernel(const st
             r.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
             r.z = __builtin_amdgcn_readfirstlane((int)((uint32_t)left * img_bytes));
             r.w = 0x00020000;
+            settle_resource(r);
             return r;
         };
         // Loads of the software pipeline: opaque instructions, waited for by hand (stage_wait);
         // nothing reads a stage between its loads and its wait.
         auto buf16_async = [](u32x4 &dst, i32x4 r, uint32_t voff) {
-            asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voff), "s"(r) : "memory");
+            // (volumes: the resources may be brought back from vector registers right in front of a load)
+            if constexpr (VOL) asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voff), "s"(r) : "memory");
+            else asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voff), "s"(r) : "memory");
         };
         // the 4 images x 4 values of a task as 4 units (value e of every image)
         auto store_units = [&](uint4 *dst, int stride, const u32x4 (&r)[4], bool (&keep)[4]) {

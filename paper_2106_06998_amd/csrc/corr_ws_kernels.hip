@@ -481,6 +481,7 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const std::conditio
             r.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
             r.z = __builtin_amdgcn_readfirstlane((int)((uint32_t)left * img_bytes));
             r.w = 0x00020000;
+            settle_resource(r);
             return r;
         };
         // Loads of the software pipeline.  They are issued as opaque instructions: the compiler
@@ -609,6 +610,7 @@ __global__ __launch_bounds__(kWsThreads) void corr_ws_kernel(const std::conditio
                 rsA.y = __builtin_amdgcn_readfirstlane((int)(uint32_t)((addr >> 32) & 0xffffu));
                 rsA.z = __builtin_amdgcn_readfirstlane((int)(live ? P.vol_bytes : 0u));
                 rsA.w = 0x00020000;
+                settle_resource(rsA);
                 const uint32_t vol_stride = (uint32_t)P.C_out * dy_plane_bytes;
 #pragma unroll
                 for (int img = 0; img < 8; ++img) {

@@ -17,6 +17,10 @@ __device__ inline void ws_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// A buffer resource built by hand, for loads that are opaque to the compiler: it does not know that they read scalar registers, which a
+// memory instruction must not within five wait states of the vector instruction (v_readfirstlane) that wrote them.
+template <class R> __device__ inline void settle_resource(R &r) { asm volatile("s_nop 4" : "+s"(r)); }
+
 // Position of a sub-step; every field is wave-uniform.
 struct WsPos {
     int u;       // sub-step inside the row-step

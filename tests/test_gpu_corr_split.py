@@ -156,7 +156,7 @@ def test_opaque_loads_are_waited_for_and_read_settled_registers(tmp_path):
                         "--cuda-device-only", "-S", os.path.join(waits.CSRC, src), "-o", out], check=True, stderr=subprocess.DEVNULL)
         return open(out).read()
 
-    sources = ["corr_split_kernels.hip"]
+    sources = ["corr_split_kernels.hip", "corr_ws32_kernels.hip", "corr_ws_kernels.hip", "corr_row_kernels.hip"]
     with ThreadPoolExecutor(4) as ex:
         for src, text in zip(sources, ex.map(assembly, sources)):
             assert "buffer_load_dwordx4" in text
