@@ -429,8 +429,20 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
         constexpr int j = decltype(jc)::value;
         load_b(std::integral_constant<int, (j + 1) & 1>{}, next_off);
         load_a(std::integral_constant<int, (j + kAhead) % kRing>{});
-        __builtin_amdgcn_sched_barrier(0);
+        // 16-bit chunks of the larger tiles: behind each matrix instruction a read of a fragment, a request for weights and two vector
+        // instructions (addresses), which it hides (products of C5, rocprofv3: 260 -> 249 us); elsewhere they all go in front
+        constexpr bool spread = !SPL && !RES && PACKED && DT != XCONV_F32 && MT * NT >= 4;
+        if constexpr (!spread) __builtin_amdgcn_sched_barrier(0);
         multiply(std::integral_constant<int, j>{}, std::integral_constant<int, j & 1>{});
+        if constexpr (spread) {
+#pragma unroll
+            for (int m = 0; m < MT * NT; ++m) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, 2, 0);
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
     // blocks b0 .. b1-1 of a list, and the rest of n steps behind the last whole block when `tail`
