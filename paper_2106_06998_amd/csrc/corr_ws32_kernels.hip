@@ -434,12 +434,12 @@ size_t corr_ws32_lds_bytes(const WsParams &P)
     return ((size_t)2 * P.a_units + (size_t)P.NRING * P.b_row_units) * 16;
 }
 
-bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets)
+bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets, bool split)
 {
     if (dtype != XCONV_F32) return false;
     if (ws32_env_int("XCONV_CORR_WS32", 1) == 0) return false;
     // the overrides below are those of the kernel on fp32 instructions
-    if (!getenv("XCONV_WS32_OCC") && !getenv("XCONV_WS32_WJ") && !getenv("XCONV_WS32_CW") &&
+    if (split && !getenv("XCONV_WS32_OCC") && !getenv("XCONV_WS32_WJ") && !getenv("XCONV_WS32_CW") &&
         plan_corr_split(P, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets, ws32_env_int("XCONV_WS32_SPLITS", 0)))
         return true;
     P.B = B; P.C_out = C_out; P.H = H; P.W = W;

@@ -103,7 +103,8 @@ size_t corr_row_lds_bytes(const WsParams &P);
 hipError_t launch_corr_row(int dtype, const WsParams &P, hipStream_t st);
 
 // corr_ws32_kernels.hip: the producer/consumer kernel for fp32 storage (same plan structure)
-bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets);
+bool plan_corr_ws32(WsParams &P, int dtype, int B, int C_out, int H, int W, int kH, int kW, int sh, int sw, int ph, int pw, int CS, int nsets,
+                    bool split = true);      // false: not corr_split_kernel, whose partial tiles can be more
 size_t corr_ws32_lds_bytes(const WsParams &P);
 hipError_t launch_corr_ws32(const WsParams &P, hipStream_t st);
 // corr_split_kernels.hip: the same layers on the 16-bit matrix cores, floats as three bf16 numbers; plan_corr_ws32 takes it first (its plans have MT == 2).

@@ -115,7 +115,7 @@ bool get_plan(PlanEntry &out, int dtype, int B, int C_out, int H, int W, int kH,
     // the producer/consumer kernel reads dY in place, so the caller's planes must be usable as they are
     e.ws = (dy_aligned && plane && plan_corr_row(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS)) ? 3 : 0;
     if (!e.ws && dy_aligned && plan_corr_ws(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets)) e.ws = 1;
-    if (!e.ws && dy_aligned && plan_corr_ws32(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets)) e.ws = 2;
+    if (!e.ws && dy_aligned && plan_corr_ws32(e.Wp, dtype, B, C_out, H, W, kH, kW, sh, sw, ph, pw, CS, nsets, !small)) e.ws = 2;
     if (e.ws) {
         e.ok = true;
         e.P.C_out = C_out;

@@ -162,3 +162,17 @@ def test_opaque_loads_are_waited_for_and_read_settled_registers(tmp_path):
             assert "buffer_load_dwordx4" in text
             assert not waits.early_copies(text), src
             assert not scalar_hazards(text), (src, scalar_hazards(text)[:5])
+
+
+def test_the_call_without_a_workspace_keeps_the_smaller_scratch():
+    # 5 groups of 10 kernel offsets instead of 6 of 9: more splits, and more partial tiles, than the kernel on fp32 instructions has
+    L, limit = xb.lib(), xb.lib().xconv_static_scratch_bytes()
+    for C_out in range(32, 160, 8):
+        d = xb.make_desc(16, 128, C_out, 64, 64, 7, 1, 3, 64, "f32", "rademacher", 7)
+        assert split_taken(d, xb.XCONV_OP_ESTIMATE)
+        one = xb.ctypes.c_void_p(16)
+        # (null dW: refused behind the check of the scratch, on any machine)
+        status = L.xconv_dw_estimate_static(xb.ctypes.byref(d), one, one, None, None, None)
+        tile, splits = 49 * 64 * -(-C_out // 64) * 64 * 4, 256 // (6 * -(-C_out // 64))
+        if tile * splits + 128 * 64 * 4 + 4096 < limit:
+            assert status != xb.XCONV_EWORKSPACE, (C_out, status)
