@@ -110,29 +110,26 @@ template <int DT> __device__ inline f32x4 mfma16(const uint4 &a, const uint4 &b,
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 
-// A float as the sum of three bf16 numbers (8 + 8 + 8 bits of the 24), each rounded to nearest: h + m + l = x exactly, down to bf16's smallest
-// number, 2^-133.  A product of two such sums, less its terms below 2^-25 (m*l, l*m, l*l), is six products on the 16-bit matrix
-// cores in place of one on the fp32 ones, which take 16 times as long (kSplitA, kSplitB).
-// Values from kSplitLimit on, which bf16 rounds to infinity, are rare and take code of their own (split_value; what split8 makes of them
-// is thrown away): an infinity becomes (+-1, 0, +-inf): l meets nothing but the other factor's h, which is zero only if that factor is, so
-// that the product is the infinity (or NaN) that fp32 gives; (inf, 0, 0) would meet zeros of m and l.  Finite ones take bf16's
-// largest number for h.  A NaN is one in all three.
+// A float x as three bf16 numbers (8 + 8 + 8 bits of the 24), each rounded to nearest: h + m + l = x * kSplitScale exactly, for every
+// float below kSplitTop, subnormal ones too (the last bit of the smallest is 2^-149; scaled, it is a normal bf16 number).  A product of two
+// such sums, less its terms below 2^-25 (m*l, l*m, l*l), is six products on the 16-bit matrix cores in place of one on the fp32
+// ones, which take 16 times as long (kSplitA, kSplitB); sums of them are scaled back by kSplitUnscale.
+// From kSplitTop on (2.0e31, infinities) and for NaN the pieces are infinities and NaN, and a sum of products beyond 1.2e24 overflows too: then
+// the sum is no finite number, whatever the other factors are, and the kernel computes it again on the fp32 matrix instructions.
 constexpr int kSplit = 3;
 constexpr int kSplitProducts = 6;
 constexpr int kSplitA[kSplitProducts] = {2, 0, 1, 1, 0, 0}, kSplitB[kSplitProducts] = {0, 2, 1, 0, 1, 0};   // small terms first
-constexpr float kSplitLimit = 0x1.ffp127f;
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f, kSplitTop = 0x1p104f;
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t bf16_pair(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
-// eight floats in pieces; the largest magnitude among them
-__device__ __forceinline__ float split8(const float (&x)[8], uint4 (&out)[kSplit])
+// eight floats in pieces
+__device__ __forceinline__ void split8(const float (&x)[8], uint4 (&out)[kSplit])
 {
     uint32_t p[kSplit][4];
-    float top = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float a = x[2 * i], b = x[2 * i + 1];
-        asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(a), "v"(b));
+        float a = x[2 * i] * kSplitScale, b = x[2 * i + 1] * kSplitScale;
 #pragma unroll
         for (int q = 0; q < kSplit; ++q) {
             const uint32_t w = bf16_pair(a, b);
@@ -145,41 +142,20 @@ __device__ __forceinline__ float split8(const float (&x)[8], uint4 (&out)[kSplit
     }
 #pragma unroll
     for (int q = 0; q < kSplit; ++q) out[q] = uint4{p[q][0], p[q][1], p[q][2], p[q][3]};
-    return top;
 }
-// one float from kSplitLimit on
-__device__ inline void split_value(float x, uint32_t &h, uint32_t &m, uint32_t &l)
+// Packed weights keep every float: one that the pieces do not hold is a NaN, so that no sum with it is finite, and its own bits in the
+// other two places.
+constexpr uint32_t kSplitRaw = 0x7fc0u;
+__device__ inline void split8_packed(const float (&x)[8], uint4 (&out)[kSplit])
 {
-    const uint32_t sign = __float_as_uint(x) >> 16 & 0x8000u;
-    h = sign | 0x3f80u, m = 0u, l = sign | 0x7f80u;
-    if (fabsf(x) < __builtin_inff()) {
-        h = sign | 0x7f7fu;
-        const float r = x - __uint_as_float(h << 16);
-        m = bf16_pair(r, 0.f) & 0xffffu;
-        l = bf16_pair(r - __uint_as_float(m << 16), 0.f) & 0xffffu;
-    }
-}
-// ... to element 0 of three rows of 16-bit numbers `pitch` apart
-__device__ inline void split_value(float x, uint16_t *out, int pitch)
-{
-    uint32_t h, m, l;
-    split_value(x, h, m, l);
-    out[0] = (uint16_t)h;
-    out[pitch] = (uint16_t)m;
-    out[2 * pitch] = (uint16_t)l;
-}
-// split8 for any values
-__device__ __forceinline__ void split8_any(const float (&x)[8], uint4 (&out)[kSplit])
-{
-    if (split8(x, out) < kSplitLimit) return;
+    split8(x, out);
     uint32_t p[kSplit][4];
 #pragma unroll
     for (int q = 0; q < kSplit; ++q) p[q][0] = out[q].x, p[q][1] = out[q].y, p[q][2] = out[q].z, p[q][3] = out[q].w;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        if (!(fabsf(x[e]) >= kSplitLimit)) continue;
-        uint32_t v[kSplit];
-        split_value(x[e], v[0], v[1], v[2]);
+        if (fabsf(x[e]) < 0.5f * kSplitTop) continue;
+        const uint32_t bits = __float_as_uint(x[e]), v[kSplit] = {kSplitRaw, bits >> 16, bits & 0xffffu};
 #pragma unroll
         for (int q = 0; q < kSplit; ++q)
             p[q][e / 2] = e & 1 ? (p[q][e / 2] & 0xffffu) | (v[q] << 16) : (p[q][e / 2] & 0xffff0000u) | v[q];
@@ -187,6 +163,14 @@ __device__ __forceinline__ void split8_any(const float (&x)[8], uint4 (&out)[kSp
 #pragma unroll
     for (int q = 0; q < kSplit; ++q) out[q] = uint4{p[q][0], p[q][1], p[q][2], p[q][3]};
 }
+// the float of the pieces in the upper halves of h, m and l
+__device__ inline float joined(uint32_t h, uint32_t m, uint32_t l)
+{
+    if (h == kSplitRaw << 16) return __uint_as_float(m | (l >> 16));
+    return (__uint_as_float(h) + __uint_as_float(m) + __uint_as_float(l)) * (1.f / kSplitScale);
+}
+__device__ inline float joined_low(uint32_t h, uint32_t m, uint32_t l) { return joined(h << 16, m << 16, l << 16); }
+__device__ inline float joined_high(uint32_t h, uint32_t m, uint32_t l) { return joined(h & 0xffff0000u, m & 0xffff0000u, l & 0xffff0000u); }
 
 // In-register transpose of an 8 (rows q) x 2*NW (16-bit columns) block held as
 // rows[q][w] (two columns per 32-bit word) into per-column vectors: column t

@@ -1,8 +1,8 @@
 // Offset-wise correlation G[m,j,ky,kx] = sum_{b,oy,ox} dY[b,m,oy,ox] * A[b, oy*sh+ky-ph, ox*sw+kx-pw, j]
 // (Algorithm 1, backward step 3 with the shift of step 4; Eq. (2)/(5) when A = X) for fp32 storage on the 16-bit matrix cores:
 // every float is the sum of three bf16 numbers, and six products of 32x32x16 matrix instructions (192 cycles) do the work of 512
-// cycles of fp32 ones (split8, common.h; the products h*h are summed apart from the smaller ones).  Same division of labour as the
-// other producer/consumer kernels:
+// cycles of fp32 ones (split8, common.h; the products h*h are summed apart from the smaller ones).  A workgroup with sums that the pieces do
+// not hold walks through its steps a second time, on fp32 matrix instructions.  Same division of labour as the other producer/consumer kernels:
 //
 //   waves 0-3 (consumers)  read fragments from LDS and issue matrix instructions.  Each owns 32 output channels x kSplitTiles
 //                          tiles of 32 columns: one kernel offset x 32 columns of A, or (WJ = 1, few probing vectors) two kernel
@@ -36,6 +36,7 @@ typedef int i32x4s __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitTiles = 5;       // accumulator tiles of a consumer wave
 constexpr int kSplitOffsets = 10;    // kernel offsets a workgroup accumulates
+__host__ __device__ inline int split_sum_units(const WsArgs &P) { return (4 - P.WM * P.WJ) * kSplitTiles * 4 * 64; }   // LDS of the sums along the reduction; the votes are behind them
 
 // Cycles of a step of w columns: its k-steps (those of the wave with the most) or the staging, which takes as long for a narrow
 // strip.  Steps are shared out by them, so that workgroups with steps of a narrow last strip take more of them (28 columns in
@@ -93,6 +94,15 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
     const int t_begin = split_step(P, bx), NI = split_step(P, bx + 1) - t_begin;  // steps of this workgroup
     const int a_slot = kSplit * P.M_WG, b_col = kSplit * kJ;    // units of a slot of dY and of a staged column of A
     const int wk_shift = 2 - (P.WM >> 1) - (WJ >> 1), WK = 1 << wk_shift;     // WM and WJ are 1 or 2
+    // Votes of the consumers, once all have read their last fragments: sums that are no finite numbers, with a factor or a sum beyond what the
+    // pieces hold (split8), are computed once more on the fp32 matrix instructions, from floats in the places of the first two pieces.
+    int *votes = reinterpret_cast<int *>(split_lds + split_sum_units(P));
+    auto again = [&]() __attribute__((always_inline)) {
+        ws_barrier();
+        const int any = votes[0] | votes[1] | votes[2] | votes[3];
+        ws_barrier();
+        return __builtin_amdgcn_readfirstlane(any) != 0;
+    };
 
     if (wave < 4) {
         // =========================== consumers ===========================
@@ -113,7 +123,8 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
             const int i = WJ == 2 ? t : 2 * t + (l32 >> 4);
             return i < per && wj * per + i < noff ? o_first + wj * per + i : -1;
         };
-        if (NI > 0) {
+        // through the steps of this workgroup: products of the pieces (0) or of floats, into `rest` (1; rare, and not scheduled by hand)
+        auto walk = [&](auto pass) __attribute__((always_inline)) {
             WsPos pc = ws_pos_of(P, t_begin);
             const int ring_bytes = P.NRING * P.b_row_units * 16, row_bytes = P.b_row_units * 16;
             const int a_lane = ring_bytes + ((2 * wk + h) * a_slot + wm * 32 + l32) * 16;         // k-step wk
@@ -257,34 +268,54 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                     for (int y = pc.y + 1; y < P.Ho; ++y, ++i) ws_barrier();
                     next_run();
                 }
-                load_a(a);
-                load_b(bp, 0);
-                load_b(b, 1);
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (decltype(pass)::value == 1) {
+                    for (int n = total; n > 0; --n) {
+                        const int addr = pa ^ ((q >> 1 & 3) << 6);
+                        a[0] = read(addr);
+                        a[1] = read(addr + a_piece);
+                        ws_static_for<0, kSplitTiles>([&](auto tc) __attribute__((always_inline)) {
+                            constexpr int t = decltype(tc)::value;
+                            b[0] = read(pb[t]);
+                            b[1] = read(pb[t] + kJ * 16);
 #pragma unroll
-                for (int p = 0; p < 3; ++p) mma(0, p, a, bp);
-                // the fragments of tile t + 2 are on their way beside tiles t and t + 1 (behind the last tile those of the next k-step)
-                u32x4s an[kSplit], bn[kSplit];
-                for (int n = total; n > 1; --n) {
-                    ws_static_for<0, kSplitTiles>([&](auto tc) __attribute__((always_inline)) {
+                            for (int e = 0; e < 8; ++e)
+                                rest[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e / 4][e & 3]), __uint_as_float(b[e / 4][e & 3]), rest[t], 0, 0, 0);
+                        });
+                        if (n == 1) break;
+                        look_ahead();
+                        ws_static_for<0, kSplitTiles>([&](auto tc) __attribute__((always_inline)) { next_b(decltype(tc)::value); });
+                        advance();
+                    }
+                } else {
+                    load_a(a);
+                    load_b(bp, 0);
+                    load_b(b, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) mma(0, p, a, bp);
+                    // the fragments of tile t + 2 are on their way beside tiles t and t + 1 (behind the last tile those of the next k-step)
+                    u32x4s an[kSplit], bn[kSplit];
+                    for (int n = total; n > 1; --n) {
+                        ws_static_for<0, kSplitTiles>([&](auto tc) __attribute__((always_inline)) {
+                            constexpr int t = decltype(tc)::value;
+                            if constexpr (t + 3 == kSplitTiles) look_ahead();
+                            if constexpr (t + 2 == kSplitTiles) advance();
+                            round(t, an, bn, [&]() __attribute__((always_inline)) {
+                                load_b(bn, (t + 2) % kSplitTiles);
+                                if constexpr (t + 2 == kSplitTiles) load_a(an);
+                            }, [&]() __attribute__((always_inline)) { next_b((t + 3) % kSplitTiles); });
+                        });
+                        copy(a, an);
+                    }
+                    ws_static_for<0, kSplitTiles - 1>([&](auto tc) __attribute__((always_inline)) {
                         constexpr int t = decltype(tc)::value;
-                        if constexpr (t + 3 == kSplitTiles) look_ahead();
-                        if constexpr (t + 2 == kSplitTiles) advance();
-                        round(t, an, bn, [&]() __attribute__((always_inline)) {
-                            load_b(bn, (t + 2) % kSplitTiles);
-                            if constexpr (t + 2 == kSplitTiles) load_a(an);
-                        }, [&]() __attribute__((always_inline)) { next_b((t + 3) % kSplitTiles); });
+                        round(t, a, bn, [&]() __attribute__((always_inline)) { if constexpr (t + 2 < kSplitTiles) load_b(bn, t + 2); },
+                              [&]() __attribute__((always_inline)) { if constexpr (t + 3 < kSplitTiles) next_b(t + 3); });
                     });
-                    copy(a, an);
+                    mma(kSplitTiles - 1, 5, a, bp);
+                    mma(kSplitTiles - 1, 3, a, bp);
+                    mma(kSplitTiles - 1, 4, a, bp);
                 }
-                ws_static_for<0, kSplitTiles - 1>([&](auto tc) __attribute__((always_inline)) {
-                    constexpr int t = decltype(tc)::value;
-                    round(t, a, bn, [&]() __attribute__((always_inline)) { if constexpr (t + 2 < kSplitTiles) load_b(bn, t + 2); },
-                          [&]() __attribute__((always_inline)) { if constexpr (t + 3 < kSplitTiles) next_b(t + 3); });
-                });
-                mma(kSplitTiles - 1, 5, a, bp);
-                mma(kSplitTiles - 1, 3, a, bp);
-                mma(kSplitTiles - 1, 4, a, bp);
             }
             // steps behind the last one with k-steps of this wave
             for (WsPos p = ws_pos_of(P, t_begin + i); i + 1 < NI; ++i) {
@@ -292,11 +323,34 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                 if (p.y == 0) ws_barrier();
                 ws_barrier();
             }
+        };
+        // (nothing but the sums is kept from one walk to the other)
+        if (NI > 0) {
+            walk(std::integral_constant<int, 0>{});
+            float odd_sum = 0.f;       // NaN as soon as a sum is not finite
+#pragma unroll
+            for (int t = 0; t < kSplitTiles; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    big[t][e] = (big[t][e] + rest[t][e]) * kSplitUnscale;
+                    odd_sum = fmaf(big[t][e], 0.f, odd_sum);
+                }
+            const int vote = __ballot(odd_sum != 0.f) != 0;
+            ws_barrier();
+            if (lane == 0) votes[wave] = vote;
+            if (again()) {
+#pragma unroll
+                for (int t = 0; t < kSplitTiles; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) rest[t][e] = 0.f;
+                walk(std::integral_constant<int, 1>{});
+#pragma unroll
+                for (int t = 0; t < kSplitTiles; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (!(fabsf(big[t][e]) < __builtin_inff())) big[t][e] = rest[t][e];
+            }
         }
-#pragma unroll
-        for (int t = 0; t < kSplitTiles; ++t)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) big[t][e] += rest[t][e];
 
         // the waves along the reduction meet in LDS: [wave][tile][quad of rows][lane]
         if (WK > 1) {
@@ -403,33 +457,27 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
         auto buf16_async = [](u32x4s &dst, i32x4s r, uint32_t voff) {
             asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(dst) : "v"(voff), "s"(r) : "memory");
         };
-        // The 4 x 8 values of a task, split: value e of the 8 images is unit e * step (dY: the next slot) or e ^ flip (A: the next
-        // column), then `piece` and 2 * `piece` further on.  source(img) is where the values are,
-        // null for zeros: those that need code of their own are read once more (one rolled loop: the code of a step is executed
-        // a few times by each wave, and what it fetches of it counts).
-        auto put = [&](uint4 *dst, int step, int flip, int piece, const u32x4s (&r)[8], auto &&source) __attribute__((always_inline)) {
-            float top = 0.f;
+        // The 4 x 8 values of a task: value e of the 8 images is unit e * step (dY: the next slot) or e ^ flip (A: the next column), its
+        // pieces `piece` units apart; as floats, images 0-3 are in the place of the first piece and 4-7 in that of the second.
+        bool floats = false;
+        auto put = [&](uint4 *dst, int step, int flip, int piece, const u32x4s (&r)[8]) __attribute__((always_inline)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float v[8];
-                uint4 w[kSplit];
-#pragma unroll
-                for (int img = 0; img < 8; ++img) {
-                    const unsigned int u = r[img][e];
-                    v[img] = __uint_as_float(u);
-                }
-                top = fmaxf(top, split8(v, w));
                 uint4 *unit = dst + (step ? e * step : e ^ flip);
+                if (floats) {
+                    unit[0] = uint4{r[0][e], r[1][e], r[2][e], r[3][e]};
+                    unit[piece] = uint4{r[4][e], r[5][e], r[6][e], r[7][e]};
+                } else {
+                    float v[8];
+                    uint4 w[kSplit];
 #pragma unroll
-                for (int x = 0; x < kSplit; ++x) unit[x * piece] = w[x];
-            }
-            if (top >= kSplitLimit) {
-#pragma nounroll
-                for (int img = 0; img < 8; ++img) {
-                    const float *src = source(img);
-#pragma nounroll
-                    for (int e = 0; src && e < 4; ++e)
-                        if (fabsf(src[e]) >= kSplitLimit) split_value(src[e], reinterpret_cast<uint16_t *>(dst + (step ? e * step : e ^ flip)) + img, piece * 8);
+                    for (int img = 0; img < 8; ++img) {
+                        const unsigned int u = r[img][e];
+                        v[img] = __uint_as_float(u);
+                    }
+                    split8(v, w);
+#pragma unroll
+                    for (int x = 0; x < kSplit; ++x) unit[x * piece] = w[x];
                 }
             }
         };
@@ -495,8 +543,6 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
         };
         // ---- registers -> LDS
         auto write = [&](const WsPos &ps, int buf, const u32x4s (&r)[NTASK][8]) __attribute__((always_inline)) {
-            const uint32_t fs = (uint32_t)(ps.y * P.Wo + ps.strip * P.CW) * 4u;
-            const uint32_t origin = (uint32_t)((ps.y * P.sh + rows_old - P.ph) * P.W + ps.strip * P.CW * P.sw - P.pw) * ((uint32_t)P.CS * 4u);
             int slot0 = ps.rowmod + rows_old;   // ring slot of the first added row
             slot0 = slot0 >= P.NRING ? slot0 - P.NRING : slot0;
 #pragma unroll
@@ -506,18 +552,7 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                 uint4 *dst = is_a[k] ? lds_a + buf * P.a_units + t_lds[k] : lds_b + slot * P.b_row_units + t_lds[k];
                 // (rows of channels beyond the last are written too: zeros)
                 if (is_a[k] ? p + kProducers * k < P.NA : t_goff[k] != kOOR)
-                    put(dst, is_a[k] ? a_slot : 0, t_aux[k] & 3, is_a[k] ? P.M_WG : kJ, r[k], [&](int img) -> const float * {
-                        const int i = ps.bg * 8 + img;
-                        if (i >= P.B || t_goff[k] == kOOR) return nullptr;
-                        if (!is_a[k])
-                            return reinterpret_cast<const float *>(reinterpret_cast<const char *>(Ag) + (size_t)i * a_img_bytes + (uint32_t)(origin + t_goff[k]));
-                        size_t at = (size_t)i * dy_img_bytes;
-                        if constexpr (VOL) {
-                            if (i % P.vol_period >= P.vol_Do) return nullptr;
-                            at = (size_t)(i / P.vol_period) * P.C_out * dy_plane_bytes + (size_t)(i % P.vol_period) * dy_img_bytes;
-                        }
-                        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(dY) + at + t_goff[k] + fs);
-                    });
+                    put(dst, is_a[k] ? a_slot : 0, t_aux[k] & 3, is_a[k] ? P.M_WG : kJ, r[k]);
             }
         };
         // ---- the rows a step inherits, loaded and written at once (start of a run)
@@ -542,15 +577,11 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                              : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7])
                              :
                              : "memory");
-                if (idx < total)
-                    put(lds_b + slot * P.b_row_units + c * b_col + 4 * jc, 0, c & 3, kJ, r, [&](int img) -> const float * {
-                        const int i = ps.bg * 8 + img;
-                        return i < P.B && in ? reinterpret_cast<const float *>(reinterpret_cast<const char *>(Ag) + (size_t)i * a_img_bytes + voff) : nullptr;
-                    });
+                if (idx < total) put(lds_b + slot * P.b_row_units + c * b_col + 4 * jc, 0, c & 3, kJ, r);
             }
         };
 
-        if (NI > 0) {
+        while (NI > 0) {
             WsPos pw = ws_pos_of(P, t_begin);  // step whose data is written next
             WsPos pi = pw;                     // step whose loads are issued next
             u32x4s st[D][NTASK][8];
@@ -591,6 +622,10 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
                                    "+v"(st[d][k][6]), "+v"(st[d][k][7])
                                  :
                                  : "memory");
+            if (floats) break;
+            ws_barrier();
+            floats = again();
+            if (!floats) break;
         }
         if (WK > 1) {      // the consumers' sums
             ws_barrier();
@@ -607,7 +642,7 @@ static const size_t kSplitLdsLimit = 160 * 1024;
 size_t corr_split_lds_bytes(const WsParams &P)
 {
     const size_t stage = ((size_t)2 * P.a_units + (size_t)P.NRING * P.b_row_units) * 16;
-    const size_t sums = (size_t)(4 - P.WM * P.WJ) * kSplitTiles * 4 * 64 * 16;
+    const size_t sums = ((size_t)split_sum_units(P) + 1) * 16;
     return stage > sums ? stage : sums;
 }
 

@@ -29,7 +29,7 @@ template <int ES, class SJ> __device__ inline void pack_fragment(const SJ &J, co
     uint4 *out = static_cast<uint4 *>(J.packed) + S.w0 + (size_t)i * (ES == 4 ? kSplit * 64 : 64) + lane;
     if constexpr (ES == 4) {
         uint4 p[kSplit];
-        split8_any(v, p);
+        split8_packed(v, p);
 #pragma unroll
         for (int q = 0; q < kSplit; ++q) out[q * 64] = p[q];
     } else {
