@@ -250,7 +250,8 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
                     const uint32_t cs = (uint32_t)P.in_sc * ES;             // bytes from a channel to the next
                     const int cu = conv_unit_channel<UE, IL>(u, 0), left = P.Cin - c0 - cu;
                     uint32_t first = (uint32_t)cu * cs;
-                    // (a multiply-add has 64 bits and reads a neighbour of `off`, which may be on its way from memory: waits between the loads)
+                    // (a multiply-add has 64 bits and reads a neighbour of `off`, which may be on its way from memory: waits between the loads,
+                    // C2's products 64.1 us for 62.9)
                     if constexpr (SPL) asm("" : "+v"(first));
                     const uint32_t vo = off + first;
                     constexpr int step = IL ? 2 : 1;
@@ -282,10 +283,7 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
                     float v[8];
                     uint4 piece[kSplit];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        asm volatile("" : "+v"(sr[i][e]));      // the compiler would scale each float where it is loaded, and wait for it there (C2's products: 59 -> 64 us)
-                        v[e] = __uint_as_float(sr[i][e]);
-                    }
+                    for (int e = 0; e < 8; ++e) v[e] = __uint_as_float(sr[i][e]);
                     split8(v, piece);
 #pragma unroll
                     for (int q = 0; q < kSplit; ++q) d[q * S.NPOS + (pos & 0xffffu)] = piece[q];
@@ -500,7 +498,7 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
             stage_load(0, ph);
             stage_write(0, ph);
             // vmcnt(0): for the compiler, a branch of stage_write that is not taken leaves loads in flight, whose registers it waits for
-            // between the loads of the next phase
+            // between the loads of the next phase (C2's products 66.4 us without this wait, 62.9 with it)
             if constexpr (SPL) __builtin_amdgcn_s_waitcnt(0x0f70);
         }
         __syncthreads();
@@ -570,6 +568,35 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
         }
     }
 
+    uint32_t again = 0;          // split floats: a bit for each sum that has to be computed again
+    if constexpr (SPL) {
+        // The sums, scaled back.  One that is no finite number, with a factor or a sum beyond what the pieces hold (split8), is computed
+        // once more on the fp32 matrix instructions: the tile's patch again, as floats, and the packed weights put together again.  So are sums
+        // of one or two products, which round so seldom that what a product leaves out shows (largest error, in terms of the products: 1.4 times that
+        // of fp32; with three 0.93, with 64 0.33).  The waves vote behind their stores, where they have nothing else to wait for; what
+        // they stored is then stored again.
+        static_assert(MT * NT <= 2, "one bit for each sum");
+        float odd_sum = 0.f;       // NaN as soon as one of them is not finite
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                acc[0][nt][e] = (acc[0][nt][e] + accs[NS - 1][0][nt][e]) * kSplitUnscale;
+                odd_sum = fmaf(acc[0][nt][e], 0.f, odd_sum);
+            }
+        again = taps * P.Cin <= 2 ? 0xffffffffu : 0u;
+        if (odd_sum != 0.f) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    // (positions that are not stored may have read what was never staged)
+                    const int n = (wn * NT + nt) * 32 + (SWAP ? 8 * (e / 4) + 4 * h + e % 4 : l32);
+                    if (otab[n].x != kConvOob && !(fabsf(acc[0][nt][e]) < __builtin_inff())) again |= 1u << (nt * 16 + e);
+                }
+        }
+    }
+
     // ---- accumulator tile: lane l holds column l % 32 and rows 8*(i/4) + 4*(l/32) + i%4, rounded once to the storage type.
     // The bias is added to the rounded product, in fp32, and the sum rounded again: what a separate addition gives, bit for
     // bit (a sum rounded once falls on the other side of zero now and then, which a ReLU behind the layer would show).
@@ -592,106 +619,76 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
     const auto orsrc = __builtin_amdgcn_make_buffer_rsrc(out_b, 0, (int)kConvOob, 0x00020000);
     const uint32_t cs = (uint32_t)P.out_sc * ES;
     const uint32_t odd = (uint32_t)lane & 1u;
-    auto store_tile = [&](auto &acc, uint32_t skip) __attribute__((always_inline)) {      // split floats: without the sums of the bits set in `skip`
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int cb = co_w + mt * 32;          // channels cb .. cb + 31
-            if (cb >= P.Cout) break;
-            const bool full = cb + 32 <= P.Cout;
-            if (bias) {
-                float bv[16];
+    for (int mt = 0; mt < MT; ++mt) {
+        const int cb = co_w + mt * 32;          // channels cb .. cb + 31
+        if (cb >= P.Cout) break;
+        const bool full = cb + 32 <= P.Cout;
+        if (bias) {
+            float bv[16];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) bv[i] = bias_of(SWAP ? cb + l32 : cb + 8 * (i / 4) + 4 * h + i % 4);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[mt][nt][i] = add_bias(acc[mt][nt][i], bv[i]);
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                if constexpr (BIG) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int r = 8 * (i / 4) + 4 * h + i % 4, co = cb + (SWAP ? l32 : r);
-                        const uint32_t off = otab[(wn * NT + nt) * 32 + (SWAP ? r : l32)].x;
-                        if (off != 0xffffffffu && co < P.Cout) out_b[(size_t)off + (size_t)co * (size_t)P.out_sc] = stored(acc[mt][nt][i]);
-                    }
-                } else if (ES == 2 && P.pair) {
-                    // neighbouring lanes exchange halves: the even one stores two neighbours of register i, the odd one of register i + 1
-                    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
-                    auto both = [&](int i) {
-                        const uint32_t p = (uint32_t)stored(acc[mt][nt][i]) | ((uint32_t)stored(acc[mt][nt][i + 1]) << 16);
-                        const uint32_t q = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xB1, 0xF, 0xF, true);    // lane ^ 1
-                        return __builtin_amdgcn_perm(q, p, sel);
-                    };
-                    if constexpr (SWAP) {
-                        const uint32_t lo = (uint32_t)(l32 & ~1) * 2u;
-                        const bool on = cb + l32 < P.Cout;
-#pragma unroll
-                        for (int i = 0; i < 16; i += 2) {
-                            const uint2 *e = otab + (wn * NT + nt) * 32 + 8 * (i / 4) + 4 * h + i % 4;
-                            const uint32_t off = e[odd].x;
-                            __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)(on ? off + lo : kConvOob), cb * 2, 0);
-                        }
-                    } else {
-                        const uint32_t off = otab[(wn * NT + nt) * 32 + l32].x;
-                        const uint32_t vo = off == kConvOob ? off : off + (4u * h + odd) * cs - odd * 2u;
-#pragma unroll
-                        for (int i = 0; i < 16; i += 2) {
-                            const int r = 8 * (i / 4) + i % 4;      // + 4 * h + odd
-                            const uint32_t v = full || cb + r + 4 * h + (int)odd < P.Cout ? vo : kConvOob;
-                            __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)v, (int)((uint32_t)(cb + r) * cs), 0);
-                        }
-                    }
-                } else {
-                    const uint32_t lo = SWAP ? (uint32_t)l32 * cs : (uint32_t)(4 * h) * cs;
-                    const uint32_t offl = otab[(wn * NT + nt) * 32 + l32].x;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int r = 8 * (i / 4) + i % 4;          // + 4 * h
-                        const uint32_t off = SWAP ? otab[(wn * NT + nt) * 32 + r + 4 * h].x : offl;
-                        bool on = full || cb + (SWAP ? l32 : r + 4 * h) < P.Cout;
-                        if constexpr (SPL) on = on && !(skip >> (nt * 16 + i) & 1);
-                        const int vo = (int)(on && off != kConvOob ? off + lo : kConvOob), so = (int)((uint32_t)(SWAP ? cb : cb + r) * cs);
-                        const elem_t v = stored(acc[mt][nt][i]);
-                        if constexpr (ES == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, vo, so, 0);
-                        else __builtin_amdgcn_raw_buffer_store_b16((short)v, orsrc, vo, so, 0);
-                    }
-                }
-            }
-        }
-    };
-    if constexpr (!SPL) {
-        store_tile(acc, 0);
-    } else {
-        // The sums, scaled back.  One that is no finite number, with a factor or a sum beyond what the pieces hold (split8), is computed
-        // once more on the fp32 matrix instructions: the tile's patch again, as floats, and the packed weights put together again.  So are sums
-        // of one or two products, which round so seldom that what a product leaves out shows (largest error, in terms of the products: 1.4 times that
-        // of fp32; with three 0.93, with 64 0.33).  The waves vote behind their stores, where they have nothing else to wait for; what
-        // they stored is then stored again.
-        static_assert(MT * NT <= 2, "one bit for each sum");
-        auto &exact = accs[NS - 1];
-        float odd_sum = 0.f;       // NaN as soon as one of them is not finite
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                acc[0][nt][e] = (acc[0][nt][e] + exact[0][nt][e]) * kSplitUnscale;
-                odd_sum = fmaf(acc[0][nt][e], 0.f, odd_sum);
-            }
-        uint32_t again = taps * P.Cin <= 2 ? 0xffffffffu : 0u;
-        if (odd_sum != 0.f) {
+            for (int i = 0; i < 16; ++i) bv[i] = bias_of(SWAP ? cb + l32 : cb + 8 * (i / 4) + 4 * h + i % 4);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    // (positions that are not stored may have read what was never staged)
-                    const int n = (wn * NT + nt) * 32 + (SWAP ? 8 * (e / 4) + 4 * h + e % 4 : l32);
-                    if (otab[n].x != kConvOob && !(fabsf(acc[0][nt][e]) < __builtin_inff())) again |= 1u << (nt * 16 + e);
-                }
+                for (int i = 0; i < 16; ++i) acc[mt][nt][i] = add_bias(acc[mt][nt][i], bv[i]);
         }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            if constexpr (BIG) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int r = 8 * (i / 4) + 4 * h + i % 4, co = cb + (SWAP ? l32 : r);
+                    const uint32_t off = otab[(wn * NT + nt) * 32 + (SWAP ? r : l32)].x;
+                    if (off != 0xffffffffu && co < P.Cout) out_b[(size_t)off + (size_t)co * (size_t)P.out_sc] = stored(acc[mt][nt][i]);
+                }
+            } else if (ES == 2 && P.pair) {
+                // neighbouring lanes exchange halves: the even one stores two neighbours of register i, the odd one of register i + 1
+                const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+                auto both = [&](int i) {
+                    const uint32_t p = (uint32_t)stored(acc[mt][nt][i]) | ((uint32_t)stored(acc[mt][nt][i + 1]) << 16);
+                    const uint32_t q = (uint32_t)__builtin_amdgcn_mov_dpp((int)p, 0xB1, 0xF, 0xF, true);    // lane ^ 1
+                    return __builtin_amdgcn_perm(q, p, sel);
+                };
+                if constexpr (SWAP) {
+                    const uint32_t lo = (uint32_t)(l32 & ~1) * 2u;
+                    const bool on = cb + l32 < P.Cout;
+#pragma unroll
+                    for (int i = 0; i < 16; i += 2) {
+                        const uint2 *e = otab + (wn * NT + nt) * 32 + 8 * (i / 4) + 4 * h + i % 4;
+                        const uint32_t off = e[odd].x;
+                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)(on ? off + lo : kConvOob), cb * 2, 0);
+                    }
+                } else {
+                    const uint32_t off = otab[(wn * NT + nt) * 32 + l32].x;
+                    const uint32_t vo = off == kConvOob ? off : off + (4u * h + odd) * cs - odd * 2u;
+#pragma unroll
+                    for (int i = 0; i < 16; i += 2) {
+                        const int r = 8 * (i / 4) + i % 4;      // + 4 * h + odd
+                        const uint32_t v = full || cb + r + 4 * h + (int)odd < P.Cout ? vo : kConvOob;
+                        __builtin_amdgcn_raw_buffer_store_b32(both(i), orsrc, (int)v, (int)((uint32_t)(cb + r) * cs), 0);
+                    }
+                }
+            } else {
+                const uint32_t lo = SWAP ? (uint32_t)l32 * cs : (uint32_t)(4 * h) * cs;
+                const uint32_t offl = otab[(wn * NT + nt) * 32 + l32].x;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int r = 8 * (i / 4) + i % 4;          // + 4 * h
+                    const uint32_t off = SWAP ? otab[(wn * NT + nt) * 32 + r + 4 * h].x : offl;
+                    const bool on = full || cb + (SWAP ? l32 : r + 4 * h) < P.Cout;
+                    const int vo = (int)(on && off != kConvOob ? off + lo : kConvOob), so = (int)((uint32_t)(SWAP ? cb : cb + r) * cs);
+                    const elem_t v = stored(acc[mt][nt][i]);
+                    if constexpr (ES == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, vo, so, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b16((short)v, orsrc, vo, so, 0);
+                }
+            }
+        }
+    }
+
+    if constexpr (SPL) {
+        auto &exact = accs[NS - 1];
         const int vote = __ballot(again != 0) != 0;
-        store_tile(acc, 0);
         auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };      // (__syncthreads waits for the stores)
         int *votes = reinterpret_cast<int *>(conv_lds);
         barrier();                 // all have read their last patch
@@ -751,7 +748,16 @@ __global__ __launch_bounds__(kThreads, conv_occupancy(MT, NT, conv_split(DT, PAC
                 }
             }
         }
-        store_tile(exact, ~again);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = 8 * (e / 4) + 4 * h + e % 4, co = co_w + (SWAP ? l32 : r);
+                const uint32_t off = otab[(wn * NT + nt) * 32 + (SWAP ? r : l32)].x;
+                const bool on = (again >> (nt * 16 + e) & 1) != 0 && off != kConvOob && co < P.Cout;
+                const float v = bias && on ? add_bias(exact[0][nt][e], bias_of(co)) : exact[0][nt][e];
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), orsrc, (int)(on ? off + (uint32_t)co * cs : kConvOob), 0, 0);
+            }
     }
 }
 

@@ -80,6 +80,27 @@ def test_an_infinity_times_the_smallest_numbers(tiny):
         assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a.nan_to_num(1.0), b.float().nan_to_num(1.0))
 
 
+@pytest.mark.parametrize("nhwc", [False, True])
+def test_the_bias_is_added_to_sums_that_are_computed_again(nhwc):
+    # one product a sum, and sums on either side that the pieces hold
+    g = torch.Generator().manual_seed(5)
+    X, Wt, bias = torch.zeros((2, 16, 6, 10)), torch.zeros((40, 16, 1, 1)), torch.randn(40, generator=g) * 2.0 ** 84
+    Wt[torch.arange(40), torch.arange(40) % 16] = torch.randn(40, generator=g).view(40, 1, 1)
+    X[:, 3], X[1, 7, 2, 4], X[0, 9, 5, 9] = 1.5 * 2.0 ** 105, float("inf"), float("nan")
+    X[:, 10] = torch.randn((2, 6, 10), generator=g)
+    d = xb.make_desc(2, 16, 40, 6, 10, 1, 1, 0, 1, "f32", "rademacher", 1, layout=xb.XCONV_NHWC if nhwc else xb.XCONV_NCHW)
+    Xd = (X.permute(0, 2, 3, 1) if nhwc else X).contiguous().to(DEV)
+    Y = torch.full((2, 6, 10, 40) if nhwc else (2, 40, 6, 10), float("nan"), device=DEV)
+    xb.xconv_conv_fwd_ws(d, Xd, Wt.to(DEV), bias.to(DEV), Y, xb.alloc_bytes(xb.xconv_conv_workspace_bytes(d, 0), DEV))
+    torch.cuda.synchronize()
+    got = (Y.permute(0, 3, 1, 2) if nhwc else Y).cpu()
+    want = torch.nn.functional.conv2d(X.double(), Wt.double()).float() + bias.view(1, 40, 1, 1)
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    finite = torch.isfinite(want)
+    assert torch.equal(got[~finite].nan_to_num(0.0), want[~finite].nan_to_num(0.0))
+    assert bool(((got - want)[finite].abs() <= 2.0 ** -23 * (want - bias.view(1, 40, 1, 1))[finite].abs() + 2.0 ** -23 * want[finite].abs()).all())
+
+
 # B, C_in, C_out, H, W, k, stride, splits: 16 columns side by side and 32, four, two and one waves along the reduction, a narrow last
 # strip, several runs, strides beside and beyond the kernel's rows
 CORRELATIONS = [(9, 48, 72, 10, 28, 3, 1, 3), (8, 40, 30, 24, 20, 5, 1, 1), (6, 64, 24, 11, 36, 3, 1, 2), (16, 96, 64, 12, 24, 3, 2, 3), (9, 32, 40, 23, 23, 3, 3, 1)]
