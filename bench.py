@@ -29,15 +29,26 @@ PEAK_MFMA_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f16": 2500.0}
 MEASURED_TRAFFIC = {
     # (FETCH_SIZE * 2 + WRITE_SIZE) KiB per launch, profiles/xconv_kernels_<config>.txt
     ("C1", "corr_ws32_kernel"): 3.8e6, ("C1", "probe_kernel"): 0.7e6,
-    ("C2", "corr_ws32_kernel"): 53.1e6, ("C2", "probe_kernel"): 42.1e6,
+    ("C2", "corr_split_kernel"): 52.0e6, ("C2", "probe_kernel"): 42.1e6,
     ("C3", "corr_kernel"): 73.1e6, ("C3", "probe_kernel"): 64.5e6,
-    ("C4", "corr_ws32_kernel"): 218.0e6, ("C4", "probe_kernel"): 168.0e6,
+    ("C4", "corr_split_kernel"): 193.0e6, ("C4", "probe_kernel"): 168.0e6,
     ("C5", "corr_row_kernel"): 218.2e6, ("C5", "probe_kernel"): 129.5e6,
 }
 
 
 def elem_bytes(dtype):
     return 4 if dtype == "f32" else 2
+
+
+CORR_KERNEL_NAMES = {0: "corr_kernel", 1: "corr_ws_kernel", 2: "corr_ws32_kernel", 3: "corr_row_kernel"}
+
+
+def corr_kernel_of(plan, dtype):
+    """Name of the correlation kernel of a plan and the peak of the matrix instructions it runs on."""
+    if plan["ws"] == 2 and plan["M_WG"] == 32 * plan["WM"]:
+        # floats as three bf16 numbers: six products on the 16-bit matrix cores for each
+        return "corr_split_kernel", PEAK_MFMA_TFLOPS["bf16"] / 6
+    return CORR_KERNEL_NAMES[plan["ws"]], PEAK_MFMA_TFLOPS[dtype]
 
 
 def algorithmic(cfg):
@@ -184,13 +195,14 @@ def measure_config(cfg, steps, warmup, dev, with_exact=False, nhwc=False):
                act_bytes_saved=alg["act_bytes_saved"], buffer_sets=len(L.sets))
     tp = kt.get("probe_kernel", kt.get("probe_generic_kernel"))
     tc = kt.get("corr_kernel")
+    peak = corr_kernel_of(out["plan"], cfg.dtype)[1]
     if tp:
         out["probe"] = dict(ms=tp, gbps=alg["probe_bytes"] / tp / 1e6, gflops=alg["probe_flops"] / tp / 1e6,
                             hbm_frac=alg["probe_bytes"] / tp / 1e6 / PEAK_HBM_GBS)
     if tc:
         out["corr"] = dict(ms=tc, gbps=alg["corr_bytes"] / tc / 1e6, gflops=alg["corr_flops"] / tc / 1e6,
                            hbm_frac=alg["corr_bytes"] / tc / 1e6 / PEAK_HBM_GBS,
-                           mfma_frac=alg["corr_flops"] / tc / 1e9 / PEAK_MFMA_TFLOPS[cfg.dtype])
+                           mfma_frac=alg["corr_flops"] / tc / 1e9 / peak)
     if with_exact:
         ms_x = time_region(L.exact, max(steps // 4, 5), max(warmup // 4, 2))
         out["exact_ms"] = ms_x
@@ -316,10 +328,13 @@ def measure_volume(name, steps, warmup, dev, with_cpu, with_exact=True):
     corr_flops = 2.0 * vox * C_out * r * k * k * k      # one launch: all offsets of the kernel
     corr_bytes = vox * C_out * es + vox * r * es + C_out * r * k * k * k * 4
     tp, tc = kt.get("probe_kernel", kt.get("probe_generic_kernel")), kt["corr_kernel"]
+    # (the kernel is that of one kernel-depth offset: a 2-D layer whose images are the depth slices)
+    kernel, peak = corr_kernel_of(xb.xconv_plan_info(xb.make_desc(B * (D + c["pad"]), C_in, C_out, H, W, k, 1, c["pad"], r, dtype, c["probe"], 1),
+                                                     xb.XCONV_OP_ESTIMATE), dtype)
     out = dict(name=name, dtype=dtype, ms_per_layer=ms_step, kernels_ms=kt,
                probe=dict(ms=tp, gbps=probe_bytes / tp / 1e6, hbm_frac=probe_bytes / tp / 1e6 / PEAK_HBM_GBS),
                corr=dict(ms=tc, launches_per_layer=1, gflops=corr_flops / tc / 1e6, gbps=corr_bytes / tc / 1e6,
-                         mfma_frac=corr_flops / tc / 1e9 / PEAK_MFMA_TFLOPS[dtype]),
+                         mfma_frac=corr_flops / tc / 1e9 / peak, kernel=kernel, peak=peak),
                act_bytes_saved=(C_in - r) * vox * es, exact_ms=ms_exact, estimate_vs_exact_speedup=(ms_exact / ms_step if ms_exact else None),
                workload="%s: B=%d C_in=%d C_out=%d D=H=W=%d k=%dx%dx%d pad=%d r=%d %s probes, %s storage, NCDHW" % (
                    name, B, C_in, C_out, D, k, k, k, c["pad"], r, c["probe"], dtype))
@@ -533,7 +548,6 @@ def workload_string(cfg, nhwc):
         "NHWC" if nhwc else "NCHW")
 
 
-CORR_KERNEL_NAMES = {0: "corr_kernel", 1: "corr_ws_kernel", 2: "corr_ws32_kernel", 3: "corr_row_kernel"}
 
 
 def roofline_of(cfg, res):
@@ -542,11 +556,7 @@ def roofline_of(cfg, res):
     that peak.  `achieved` = algorithmic flops (bytes) of the one launch / its event-timed duration."""
     alg = algorithmic(cfg)
     c = res["corr"]
-    plan, peak = res["plan"], PEAK_MFMA_TFLOPS[cfg.dtype]
-    kname = CORR_KERNEL_NAMES[plan.get("ws", 0)]
-    if plan.get("ws") == 2 and plan["M_WG"] == 32 * plan["WM"]:
-        # floats as three bf16 numbers: six products on the 16-bit matrix cores for each
-        kname, peak = "corr_split_kernel", PEAK_MFMA_TFLOPS["bf16"] / 6
+    kname, peak = corr_kernel_of(res["plan"], cfg.dtype)
     mfma_bound = (alg["corr_flops"] / (peak * 1e12)) >= (alg["corr_bytes"] / (PEAK_HBM_GBS * 1e9))
     if mfma_bound:
         ach = c["gflops"] / 1e3
@@ -621,9 +631,8 @@ def main():
             "value": res["ms_per_layer"], "unit": "ms", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": res["ms_per_layer"], "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
             "dtype": res["dtype"], "data": "synthetic", "config": {"workload": res["workload"]},
-            "roofline": dict(bound="mfma", achieved=ach, peak=PEAK_MFMA_TFLOPS["bf16"] / 6, unit="TFLOP/s",
-                             frac=ach / (PEAK_MFMA_TFLOPS["bf16"] / 6), kernel="corr_split_kernel", kernel_ms=res["corr"]["ms"],
-                             traffic=None),
+            "roofline": dict(bound="mfma", achieved=ach, peak=res["corr"]["peak"], unit="TFLOP/s", frac=res["corr"]["mfma_frac"],
+                             kernel=res["corr"]["kernel"], kernel_ms=res["corr"]["ms"], traffic=None),
             "detail": res,
         }
         if "cpu_baseline" in res:
