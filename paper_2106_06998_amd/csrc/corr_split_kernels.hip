@@ -17,7 +17,7 @@
 //
 // Bound by the matrix instructions: one wave a SIMD issues them (160 registers of accumulators leave room for one consumer and one
 // producer each), 41 cycles apart for 32 each takes, since neighbours add to the same two sums, and 5 tiles hold 9 offsets.  In C4 (8 x 64 x
-// 256x256, 16 columns; 62 us) a workgroup's 16 steps take 50 us of 3.1 us each, 2.7 without the producers; its first step arrives after
+// 256x256, 16 columns; 67 us in the trace) a workgroup's 16 steps take 50 us of 3.1 us each, 2.7 without the producers; its first step arrives after
 // 7 us.  Against the kernel on fp32 instructions (corr_ws32_kernels.hip) the backward call of C4 takes 105 -> 74 us, of C2 (128 x 64 x 32x32,
 // four steps a workgroup) 36.6 -> 31, exact gradients of both 401 -> 355 and 106 -> 79.
 #include <type_traits>
@@ -461,24 +461,29 @@ __global__ __launch_bounds__(kWsThreads, 2) void corr_split_kernel(const std::co
         // pieces `piece` units apart; as floats, images 0-3 are in the place of the first piece and 4-7 in that of the second.
         bool floats = false;
         auto put = [&](uint4 *dst, int step, int flip, int piece, const u32x4s (&r)[8]) __attribute__((always_inline)) {
+            // (one branch for the task: with one for each value the exact gradient of C4 takes 376 us for 361)
+            if (floats) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    uint4 *unit = dst + (step ? e * step : e ^ flip);
+                    unit[0] = uint4{r[0][e], r[1][e], r[2][e], r[3][e]};
+                    unit[piece] = uint4{r[4][e], r[5][e], r[6][e], r[7][e]};
+                }
+                return;
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 uint4 *unit = dst + (step ? e * step : e ^ flip);
-                if (floats) {
-                    unit[0] = uint4{r[0][e], r[1][e], r[2][e], r[3][e]};
-                    unit[piece] = uint4{r[4][e], r[5][e], r[6][e], r[7][e]};
-                } else {
-                    float v[8];
-                    uint4 w[kSplit];
+                float v[8];
+                uint4 w[kSplit];
 #pragma unroll
-                    for (int img = 0; img < 8; ++img) {
-                        const unsigned int u = r[img][e];
-                        v[img] = __uint_as_float(u);
-                    }
-                    split8(v, w);
-#pragma unroll
-                    for (int x = 0; x < kSplit; ++x) unit[x * piece] = w[x];
+                for (int img = 0; img < 8; ++img) {
+                    const unsigned int u = r[img][e];
+                    v[img] = __uint_as_float(u);
                 }
+                split8(v, w);
+#pragma unroll
+                for (int x = 0; x < kSplit; ++x) unit[x * piece] = w[x];
             }
         };
 
