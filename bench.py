@@ -31,7 +31,7 @@ MEASURED_TRAFFIC = {
     ("C1", "corr_ws32_kernel"): 3.8e6, ("C1", "probe_kernel"): 0.7e6,
     ("C2", "corr_split_kernel"): 52.0e6, ("C2", "probe_kernel"): 42.1e6,
     ("C3", "corr_kernel"): 73.1e6, ("C3", "probe_kernel"): 64.5e6,
-    ("C4", "corr_split_kernel"): 193.0e6, ("C4", "probe_kernel"): 168.0e6,
+    ("C4", "corr_split_kernel"): 194.9e6, ("C4", "probe_kernel"): 168.0e6,
     ("C5", "corr_row_kernel"): 218.2e6, ("C5", "probe_kernel"): 129.5e6,
 }
 

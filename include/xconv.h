@@ -49,7 +49,9 @@ typedef enum {
     XCONV_EHIP = 4          /* the HIP runtime reported an error while enqueuing, or no host memory for a plan */
 } xconv_status;
 
-typedef enum { XCONV_F32 = 0, XCONV_BF16 = 1, XCONV_F16 = 2 } xconv_dtype;   /* storage of X, dY, Xt; sums and dW are fp32 */
+typedef enum { XCONV_F32 = 0, XCONV_BF16 = 1, XCONV_F16 = 2 } xconv_dtype;   /* storage of X, dY, Xt; sums and dW are fp32 (fp32 products
+   may run on the 16-bit matrix cores, every float as three bf16 numbers: over the whole range of a float, subnormal numbers, infinities and NaN
+   included, no further from 64 bits than sums on the fp32 instructions) */
 typedef enum { XCONV_NCHW = 0, XCONV_NHWC = 1 } xconv_layout;                /* of X and dY ([B,C,H,W] or [B,H,W,C]); dW is always [C_out,C_in,kH,kW] */
 typedef enum { XCONV_RADEMACHER = 0, XCONV_GAUSSIAN = 1, XCONV_USER_Z = 2 } xconv_probe;
 typedef enum { XCONV_OP_PROBE = 0, XCONV_OP_ESTIMATE = 1, XCONV_OP_EXACT = 2 } xconv_op;
